@@ -139,9 +139,10 @@ pmc_status pmc_nn_mfma_probe(int32_t iters, void* hip_stream, double* ms_out, do
  * ref and eval: [nz][ny][nx] float64 device arrays; d_gamma (float32, may be
  * NULL) receives gamma (or -1 below the cutoff).  *pass_rate (host) = the
  * fraction of evaluated voxels with gamma <= 1; *n_eval their count.
- * Synchronous.  The reduction counters (32 bytes per device) are allocated
- * on a device's first call of this function or pmc_denoise_disagreement and
- * kept; calls of the two are serialised within the process. */
+ * Synchronous.  The reduction buffers (4 KiB of device and 32 KiB of pinned
+ * host memory per device) are allocated on a device's first call of this
+ * function or pmc_denoise_disagreement and kept; calls of the two are
+ * serialised within the process. */
 pmc_status pmc_gamma_index(const double* d_ref, const double* d_eval, int nx, int ny, int nz,
                            float dx_cm, float dy_cm, float dz_cm, float dose_frac, float dta_cm,
                            float cutoff_frac, float search_cm, float step_cm, float* d_gamma,

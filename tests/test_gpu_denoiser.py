@@ -431,6 +431,45 @@ def test_gamma_full_size_sampled():
     _say("full-size gamma pass rate %.4f over %d voxels" % (rate, n))
 
 
+@pytest.mark.parametrize("shape,search,step", [
+    ((1, 1, 1), 0.3, 0.05),      # one voxel: the zero offset only is inside the grid
+    ((1, 73, 7), 0.25, 0.05),    # 511 and 513 voxels: a workgroup's run is 512
+    ((1, 19, 27), 0.25, 0.05),
+    ((5, 9, 7), 0.0, 0.05),      # the zero offset alone
+    ((5, 9, 7), 0.33, 0.05),     # a radius between steps
+    ((7, 5, 6), 0.4, 0.05),      # exactly the eight steps of the sorted offsets
+    ((7, 5, 6), 0.445, 0.05),    # shells past the sorted offsets, eight steps a side
+    ((6, 5, 4), 0.55, 0.05),     # eleven steps a side
+])
+def test_gamma_search_radii_match_oracle(shape, search, step):
+    """Where the search changes its course: the workgroups' runs of voxels,
+    the offsets kept in order of distance (eight steps) and the ones beyond
+    them.  Tolerance: a search point is an FP32 voxel coordinate, at most
+    delta = 2^-23 n from the oracle's on an axis of n voxels, and the
+    interpolated dose changes by at most 2 max(ev) per voxel and axis, so
+    gamma moves by at most 6 max(ev) delta / (dose criterion), beside the
+    header's 1e-5 (voxel sizes no multiple of the step: no point on a face)."""
+    import torch
+    _say("case: gamma radii %s search=%g step=%g" % (shape, search, step))
+    U = _unet()
+    rng = np.random.default_rng(63)
+    ref = rng.gamma(2.0, 1.0, size=shape) * (rng.random(shape) < 0.6)
+    ref[0, 0, 0] = 3.0
+    ev = ref * (1 + 0.4 * rng.normal(size=shape))     # far off: the whole sphere is searched
+    vox = (0.23, 0.27, 0.31)
+    kw = dict(dose_frac=0.02, dta_cm=0.3, cutoff_frac=0.1, search_cm=search, step_cm=step)
+    g_o, rate_o, n_o = D.gamma_index(ref, ev, vox, **kw)
+    gam = torch.zeros(shape, dtype=torch.float32, device="cuda")
+    rate, n = U.pmc_gamma_index(torch.from_numpy(ref).cuda(), torch.from_numpy(ev).cuda(), vox, gamma=gam, **kw)
+    g = gam.cpu().numpy().astype(np.float64)
+    assert n == n_o
+    assert np.array_equal(g == -1.0, g_o < 0)
+    bound = 1e-5 * np.maximum(1.0, g_o) + 6 * ev.max() / (0.02 * ref.max()) * 2.0 ** -23 * max(shape)
+    assert np.all((np.abs(g - g_o) <= bound)[g_o >= 0])
+    amb = int(((g_o >= 0) & (np.abs(g_o - 1.0) <= bound)).sum())
+    assert abs(rate - rate_o) <= amb / max(n_o, 1) + 1e-12
+
+
 @pytest.mark.parametrize("shape,k", [((160, 128, 128), 4.0), ((7, 9, 11), 2.5), ((1, 1, 1), 4.0)])
 def test_disagreement_rule_matches_oracle(shape, k):
     """The fallback rule's fraction and count equal the oracle's exactly
