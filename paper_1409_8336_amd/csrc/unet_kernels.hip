@@ -17,6 +17,8 @@ namespace pmc {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// an 8-byte store that may sit at any 2-byte boundary (a caller's tensor)
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 #define GLOBAL __attribute__((address_space(1)))
 #define LOCAL __attribute__((address_space(3)))
 
@@ -37,186 +39,207 @@ DEV uint16_t f2bf(float f)
 
 // ------------------------------------------------------------ convolution
 
-// Forward convolution, pipelined through LDS.  A workgroup computes a
-// 64 (x) x TY (y) x TZ (z) block of output voxels (TY x TZ = 4R rows; wave w
-// owns rows wR .. wR+R-1, each as four 16-voxel M tiles) for 16*NB output
-// channels.  The input is consumed 8 channels (one 16-byte voxel entry) at a
-// time: the block's halo (66 x (TY+2) x (TZ+2) entries) and the chunk's
-// weights (28 taps x 16*NB output channels, tap 27 the zero padding of K to
-// 7 x 32) are copied straight from global memory into LDS
-// (global_load_lds_dwordx4, out-of-range voxels from a zero page), into one of
-// two buffers while the MFMAs read the other, so every operand comes from
-// LDS and the copies of chunk c+1 overlap the arithmetic of chunk c (kPipe;
-// a one-chunk input uses a single buffer).  K order inside a chunk: 4 taps x
-// 8 channels per MFMA K-step (lane group g takes tap 4*s + g), i.e. weight
-// column tap*Cin + 8*c + e.  With a coarse source (Cc > 0) the input is the
-// decoder's concatenation [nearest upsampling of coarse (Cc channels, half
-// resolution), in (Cin - Cc channels)], read from both without forming it.
-__device__ const u32x4 kZero16[4] = {};
-
-// TX: tile width in x (64, 32 or 16; a 64-voxel row of a wave covers TX
-// voxels in x and 64 / TX in y, so narrow levels waste no lanes)
-template <int NB, int R, int TX>
+// Forward convolution through LDS.  A workgroup of eight waves computes a 16
+// (x) x 8 (y) x 4 (z) block of output voxels (each wave 16 x 4 x 1, as four
+// 16-voxel tiles) for 16*NB output channels.  The input is consumed in stages
+// of QC chunks of 8 channels (one 16-byte voxel entry each): the block's halo
+// (18 x 10 x 6 voxels) and the stage's weights (28 taps x 16*NB output
+// channels, tap 27 the zero padding of K to 7 x 32) are copied straight from
+// global memory into LDS (buffer loads to LDS; a lane past the tensor's end,
+// which is where voxels outside the grid are sent, reads zero), and every
+// operand is an LDS read.  K order inside a chunk: 4 taps x 8 channels per
+// MFMA K-step (lane group g takes tap 4*s + g), i.e. weight column tap*Cin +
+// 8*c + e.  The weights are the MFMA's A operand, so that a lane ends up with
+// four consecutive output channels of one voxel and a wave stores whole rows.
+// With a coarse source (Cc > 0) the input is the decoder's concatenation
+// [nearest upsampling of coarse (Cc channels, half resolution), in (Cin - Cc
+// channels)], read from both without forming it.
+// What bounds it: the rate of L2 requests and L1 lookups, one for every piece
+// of a voxel's channels a stage copies.  With one chunk a stage and 64 x 2 x 2
+// blocks (4.1 halo voxels per output voxel, against 2.1 here) 96 -> 32
+// channels on 80 x 64 x 64 voxels made 2.9e7 L2 requests in 115 us, 82% of one
+// per channel and cycle, with the LDS 14% and the matrix cores 20% busy, and
+// took 134 us; this block shape alone 89 us (1.5e7 requests), with two chunks
+// a stage (32-byte pieces) 70 us.  48 -> 16 on 160 x 128 x 128: 328, 201 and
+// 153 us.
+// kPipe: two buffers, the copies of stage c+1 overlap the arithmetic of stage
+// c; else one, and the workgroups on a CU (three with NB = 1, two with NB = 2)
+// overlap each other.
+template <int NB, int QC>
 struct FwdTile {
-    static constexpr int XT = TX / 16, YR = 4 / XT;          // M tiles per row in x; y values per row
-    static constexpr int RY = R >= 2 ? 4 : 2, RZ = R >= 4 ? 4 : 2;   // rows in y, in z
-    static constexpr int TY = RY * YR, TZ = RZ;
+    static constexpr int TX = 16, TY = 8, TZ = 4, WAVES = 8;
     static constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
-    static constexpr int NHALO = HX * HY * HZ;
-    static constexpr int NWT = 28 * 16 * NB;
-    static constexpr int NENT = (NHALO + NWT + 63) / 64 * 64;   // whole 64-entry blocks
+    static constexpr int NHALO = HX * HY * HZ;                  // voxels
+    static constexpr int HBLK = (NHALO * QC + 63) / 64;         // 64-entry copies of the halo
+    static constexpr int WBLK = 28 * NB * QC / 4;               // and of the weights
+    static constexpr int NENT = 64 * (HBLK + WBLK);
 };
 
-template <int NB, int R, int TX, bool kPipe>
-__global__ void __launch_bounds__(256) conv3d_fwd_kernel(const uint16_t* __restrict__ in,
-                                                         const uint16_t* __restrict__ coarse, int Cc,
-                                                         const uint16_t* __restrict__ wt,
-                                                         const float* __restrict__ bias,
-                                                         uint16_t* __restrict__ out, int D, int H,
-                                                         int W, int Cin, int Cout, int Kp, int relu)
+template <int NB, int QC, bool kPipe, int kMinWaves>
+__global__ void __launch_bounds__(512, kMinWaves)
+    conv3d_fwd_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ coarse, int Cc,
+                      const uint16_t* __restrict__ wt, const float* __restrict__ bias, uint16_t* __restrict__ out,
+                      int N, int D, int H, int W, int Cin, int Cout, int Kp, int relu)
 {
-    using T = FwdTile<NB, R, TX>;
+    using T = FwdTile<NB, QC>;
+    constexpr int WAVES = T::WAVES;
     // two distinct LDS objects, so that the compiler's wait for the copies
     // into one is not placed before reads of the other
     __shared__ __attribute__((aligned(16))) u32x4 buf0[T::NENT];
     __shared__ __attribute__((aligned(16))) u32x4 buf1[kPipe ? T::NENT : 4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g = lane >> 4;
     const int n_yb = (H + T::TY - 1) / T::TY;
     const int yb = blockIdx.y % n_yb, cg = blockIdx.y / n_yb;
     const int n_zb = (D + T::TZ - 1) / T::TZ;
     const int zb = blockIdx.z % n_zb, n = blockIdx.z / n_zb;
-    const int x0 = blockIdx.x * TX, y0 = T::TY * yb, z0 = T::TZ * zb;
+    const int x0 = blockIdx.x * T::TX, y0 = T::TY * yb, z0 = T::TZ * zb;
     const int co0 = cg * 16 * NB;
-    const size_t plane = (size_t)H * W;
-    const size_t nbase = (size_t)n * D * plane;
     const int n_chunks = Cin / 8;
     const int Cs = Cin - Cc;   // channels of `in`
     const int Hc = H >> 1, Wc = W >> 1;
-    const size_t nbase_c = (size_t)n * (D >> 1) * Hc * Wc;
-    // copy chunk c (halo, then weights) into dst: 64-entry blocks dealt to
-    // the waves in turn, lane l of a block writing entry 64 * blk + l.  The
-    // element offsets of a lane's entries do not depend on the chunk (which
-    // only adds 8 c): computed once, -1 for the zero page.
-    constexpr int kBlk = T::NENT / 64, kPer = (kBlk + 3) / 4;
-    int off_in[kPer], off_co[kPer];
+    // buffer descriptors: byte offsets up to the tensors' sizes; kOutside is
+    // past every tensor (all are below 2^32 - 16 bytes, checked by the host)
+    constexpr uint32_t kOutside = 0xFFFFFFF0u;
+    constexpr int kRaw = 0x00020000;
+    const uint32_t nv = (uint32_t)((size_t)N * D * H * W);
+    const auto rs_in = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(in), 0, (int)(nv * (uint32_t)Cs * 2u), kRaw);
+    const auto rs_co = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(coarse), 0,
+                                                         (int)((nv >> 3) * (uint32_t)Cc * 2u), kRaw);
+    const auto rs_wt = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(wt), 0,
+                                                         (int)((uint32_t)Cout * (uint32_t)Kp * 2u), kRaw);
+    // copy the stage from chunk c on (halo, then weights) into dst: 64-entry
+    // blocks dealt to the waves in turn, lane l of a block writing entry
+    // 64 * blk + l.  The byte offsets of a lane's entries do not depend on the
+    // chunk, which only moves the (scalar) base by 16 bytes: computed once.
+    // With two chunks a stage an entry's chunk is its parity, exchanged every
+    // eight voxels of a row (output channels of a tap), so that 16 neighbours
+    // of one chunk lie in 16 different bank groups.
+    constexpr int kBlk = T::HBLK + T::WBLK, kPer = (kBlk + WAVES - 1) / WAVES;
+    uint32_t off_in[kPer], off_co[kPer];
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-        const int e = (wave + 4 * q) * 64 + lane;
-        off_in[q] = -1;
-        off_co[q] = -1;
-        if (e < T::NHALO) {
+        const int blk = wave + WAVES * q;
+        off_in[q] = kOutside;
+        off_co[q] = kOutside;
+        if (blk < T::HBLK) {
+            const int e = (blk * 64 + lane) / QC;
             const int hx = e % T::HX, r2 = e / T::HX;
             const int hy = r2 % T::HY, hz = r2 / T::HY;
             const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
-            if (x >= 0 && x < W && y >= 0 && y < H && z >= 0 && z < D) {
-                off_in[q] = (int)((nbase + (size_t)z * plane + (size_t)y * W + x) * Cs);
-                if (Cc) off_co[q] = (int)((nbase_c + ((size_t)(z >> 1) * Hc + (y >> 1)) * Wc + (x >> 1)) * Cc);
+            const uint32_t part = QC == 2 ? 16u * ((lane & 1) ^ ((hx >> 3) & 1)) : 0u;
+            if (e < T::NHALO && x >= 0 && x < W && y >= 0 && y < H && z >= 0 && z < D) {
+                off_in[q] = (uint32_t)(((n * D + z) * H + y) * W + x) * (uint32_t)Cs * 2u + part;
+                if (Cc)
+                    off_co[q] = (uint32_t)(((n * (D >> 1) + (z >> 1)) * Hc + (y >> 1)) * Wc + (x >> 1)) * (uint32_t)Cc * 2u + part;
             }
-        } else if (e < T::NHALO + T::NWT) {
-            const int qq = e - T::NHALO, tap = qq / (16 * NB), co = co0 + qq % (16 * NB);
-            if (tap < 27 && co < Cout) off_in[q] = co * Kp + tap * Cin;
+        } else {
+            const int qq = ((blk - T::HBLK) * 64 + lane) / QC, tap = qq / (16 * NB), co = co0 + qq % (16 * NB);
+            const uint32_t part = QC == 2 ? 16u * ((lane & 1) ^ ((qq >> 3) & 1)) : 0u;
+            if (tap < 27 && co < Cout) off_in[q] = (uint32_t)(co * Kp + tap * Cin) * 2u + part;
         }
     }
-    auto issue = [&](int c, u32x4* dst) {
+    auto issue = [&](int c, u32x4* dst) __attribute__((always_inline)) {
         const bool from_coarse = 8 * c < Cc;
+        const int s_in = from_coarse ? 16 * c : 16 * c - 2 * Cc;
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
-            const int blk = wave + 4 * q;
-            if (kBlk % 4 != 0 && blk >= kBlk) break;
-            const int e = blk * 64 + lane;
-            const GLOBAL void* src = (const GLOBAL void*)&kZero16[0];
-            if (e < T::NHALO) {
-                if (from_coarse) {
-                    if (off_co[q] >= 0) src = (const GLOBAL void*)(coarse + off_co[q] + 8 * c);
-                } else if (off_in[q] >= 0) {
-                    src = (const GLOBAL void*)(in + off_in[q] + (8 * c - Cc));
-                }
-            } else if (off_in[q] >= 0) {
-                src = (const GLOBAL void*)(wt + off_in[q] + 8 * c);
+            const int blk = wave + WAVES * q;
+            LOCAL void* to = (LOCAL void*)(dst + blk * 64);
+            if (blk < T::HBLK) {
+                if (from_coarse)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_co, to, 16, (int)off_co[q], s_in, 0, 0);
+                else
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_in, to, 16, (int)off_in[q], s_in, 0, 0);
+            } else if (kBlk % WAVES == 0 || blk < kBlk) {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_wt, to, 16, (int)off_in[q], 16 * c, 0, 0);
             }
-            __builtin_amdgcn_global_load_lds(src, (LOCAL void*)(dst + blk * 64), 16, 0, 0);
         }
     };
-    f32x4 acc[R][4][NB];
+    f32x4 acc[4][NB];
 #pragma unroll
-    for (int i = 0; i < R; ++i)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) acc[i][t][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    auto compute = [&](const u32x4* bf) {
+        for (int j = 0; j < NB; ++j) acc[t][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // this wave's voxels: y0 + yw + t, z0 + zw; its lane's first halo entry
+    // and first weight entry
+    const int yw = 4 * (wave & 1), zw = wave >> 1;
+    const int vox0 = (zw * T::HY + yw) * T::HX + m;
+    const int wt0 = g * 16 * NB + m;
+    auto compute = [&](const u32x4* bf, int q) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < 7; ++s) {
             const int tap = 4 * s + g;
-            const bool real = tap < 27;
             const int kz = tap / 9, ky = (tap / 3) % 3, kx = tap % 3;
-            bf16x8 b[NB];
+            // (for the padding tap the index stays inside the buffer; the
+            // entry read is discarded)
+            const int v = QC * (vox0 + (kz * T::HY + ky) * T::HX + kx) + (QC == 2 ? q ^ (((m + kx) >> 3) & 1) : 0);
+            const int w0 = 64 * T::HBLK + QC * wt0 + (QC == 2 ? q ^ ((m >> 3) & 1) : 0);
+            bf16x8 a[NB];
 #pragma unroll
-            for (int j = 0; j < NB; ++j) b[j] = __builtin_bit_cast(bf16x8, bf[T::NHALO + tap * 16 * NB + 16 * j + m]);
+            for (int j = 0; j < NB; ++j) a[j] = __builtin_bit_cast(bf16x8, bf[w0 + QC * (64 * NB * s + 16 * j)]);
 #pragma unroll
-            for (int i = 0; i < R; ++i) {
-                const int r = wave * R + i, ry = r % T::RY, rz = r / T::RY;
+            for (int t = 0; t < 4; ++t) {
+                const u32x4 e = bf[v + QC * T::HX * t];
+                const bf16x8 b = s < 6 || tap < 27 ? __builtin_bit_cast(bf16x8, e) : (bf16x8){};
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int xl = 16 * (t % T::XT), yl = ry * T::YR + t / T::XT;
-                    // (for the padding tap the index stays inside the buffer;
-                    // the entry read is discarded)
-                    const u32x4 q = bf[((rz + kz) * T::HY + (yl + ky)) * T::HX + xl + m + kx];
-                    const bf16x8 a = real ? __builtin_bit_cast(bf16x8, q) : (bf16x8){};
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        acc[i][t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[j], acc[i][t][j], 0, 0, 0);
-                }
+                for (int j = 0; j < NB; ++j)
+                    acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], b, acc[t][j], 0, 0, 0);
             }
         }
+    };
+    auto stage = [&](const u32x4* bf, int c) __attribute__((always_inline)) {
+        compute(bf, 0);
+        if (QC == 2 && c + 1 < n_chunks) compute(bf, 1);
     };
     // vmcnt(0), other counters untouched: this wave's copies have landed
     constexpr int kWaitCopies = 0x0F70;
     if constexpr (kPipe) {
         issue(0, buf0);
-        for (int c = 0; c < n_chunks; c += 2) {
+        for (int c = 0; c < n_chunks; c += 2 * QC) {
             __builtin_amdgcn_s_waitcnt(kWaitCopies);
-            __syncthreads();   // chunk c in buf0 complete; buf1 no longer read
-            if (c + 1 < n_chunks) issue(c + 1, buf1);
-            compute(buf0);
-            if (c + 1 >= n_chunks) break;
+            __syncthreads();   // the stage in buf0 complete; buf1 no longer read
+            if (c + QC < n_chunks) issue(c + QC, buf1);
+            stage(buf0, c);
+            if (c + QC >= n_chunks) break;
             __builtin_amdgcn_s_waitcnt(kWaitCopies);
-            __syncthreads();   // chunk c+1 in buf1 complete; buf0 no longer read
-            if (c + 2 < n_chunks) issue(c + 2, buf0);
-            compute(buf1);
+            __syncthreads();   // the stage in buf1 complete; buf0 no longer read
+            if (c + 2 * QC < n_chunks) issue(c + 2 * QC, buf0);
+            stage(buf1, c + QC);
         }
     } else {
-        for (int c = 0; c < n_chunks; ++c) {
+        for (int c = 0; c < n_chunks; c += QC) {
             if (c) __syncthreads();   // buf0 no longer read
             issue(c, buf0);
             __builtin_amdgcn_s_waitcnt(kWaitCopies);
             __syncthreads();
-            compute(buf0);
+            stage(buf0, c);
         }
     }
+    // lane (m, g) holds output channels co0 + 16 j + 4 g .. + 3 of voxel m
+    const int x = x0 + m, z = z0 + zw;
+    if (x >= W || z >= D) return;
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        const int r = wave * R + i, ry = r % T::RY, z = z0 + r / T::RY;
-        if (z >= D) continue;
+    for (int j = 0; j < NB; ++j) {
+        const int co = co0 + 16 * j + 4 * g;
+        if (co >= Cout) continue;   // (Cout is a multiple of 8)
+        float bv[4] = {0.f, 0.f, 0.f, 0.f};
+        if (bias)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int co = co0 + 16 * j + m;
-            if (co >= Cout) continue;
-            const float bv = bias ? bias[co] : 0.f;
+            for (int i = 0; i < 4; ++i) bv[i] = bias[co + i];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int y = y0 + ry * T::YR + t / T::XT;
-                if (y >= H) continue;
+        for (int t = 0; t < 4; ++t) {
+            const int y = y0 + yw + t;
+            if (y >= H) continue;
+            uint32_t o[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int x = x0 + 16 * (t % T::XT) + 4 * g + q;
-                    if (x >= W) continue;
-                    float v = acc[i][t][j][q] + bv;
-                    if (relu) v = v > 0.f ? v : kLeak * v;
-                    out[(nbase + (size_t)z * plane + (size_t)y * W + x) * Cout + co] = f2bf(v);
-                }
+            for (int i = 0; i < 4; ++i) {
+                float v = acc[t][j][i] + bv[i];
+                if (relu) v = v > 0.f ? v : kLeak * v;
+                o[i] = f2bf(v);
             }
+            const size_t at = ((((size_t)n * D + z) * H + y) * W + x) * Cout + co;
+            *reinterpret_cast<u32x2_any*>(out + at) = (u32x2_any){o[0] | (o[1] << 16), o[2] | (o[3] << 16)};
         }
     }
 }
@@ -841,16 +864,16 @@ static unsigned grid_for(size_t n, unsigned block = 256, unsigned cap = 65536)
     return (unsigned)g;
 }
 
-template <int NB, int TX, bool kPipe>
+template <int NB, int QC, bool kPipe, int kMinWaves>
 static hipError_t launch_fwd(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* wt, const float* bias,
                              uint16_t* out, int N, int D, int H, int W, int Cin, int Cout, int Kp, int relu,
                              hipStream_t s)
 {
-    using T = FwdTile<NB, 1, TX>;
+    using T = FwdTile<NB, QC>;
     const int cgroups = (Cout + 16 * NB - 1) / (16 * NB);
-    dim3 grid((W + TX - 1) / TX, ((H + T::TY - 1) / T::TY) * cgroups, N * ((D + T::TZ - 1) / T::TZ));
-    hipLaunchKernelGGL((conv3d_fwd_kernel<NB, 1, TX, kPipe>), grid, dim3(256), 0, s, in, coarse, Cc, wt, bias, out, D,
-                       H, W, Cin, Cout, Kp, relu);
+    dim3 grid((W + T::TX - 1) / T::TX, ((H + T::TY - 1) / T::TY) * cgroups, N * ((D + T::TZ - 1) / T::TZ));
+    hipLaunchKernelGGL((conv3d_fwd_kernel<NB, QC, kPipe, kMinWaves>), grid, dim3(64 * T::WAVES), 0, s, in, coarse, Cc,
+                       wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu);
     return hipGetLastError();
 }
 
@@ -858,31 +881,33 @@ hipError_t nn_conv3d_fwd_cat(const uint16_t* in, const uint16_t* coarse, int Cc,
                              const float* bias, uint16_t* out, int N, int D, int H, int W, int Cin, int Cout,
                              int Kp, int relu, hipStream_t s)
 {
-    // Tiles of 4 rows of 64 voxels (TX in x by 64 / TX in y; two rows in y,
-    // two in z); 16 output channels per workgroup (three workgroups per CU)
-    // or 32 (two per CU).  The copies in flight per CU set the pace (a
-    // 64 x 4 x 2 tile, fewer halo bytes per voxel but two workgroups per CU,
-    // was 4% slower at 160 x 128 x 128; 64 x 4 x 4, one workgroup per CU, 19%
-    // slower).  A one-chunk input (Cin = 8) is single-buffered.
     if (Cin % 8 || Cin < 8 || Kp < 27 * Cin || Cc % 8 || Cc < 0 || Cc >= Cin || (Cc && !coarse) ||
         (Cc && (D % 2 || H % 2 || W % 2)))
         return hipErrorInvalidValue;
     // the kernel keeps element offsets in 32 bits
     if ((size_t)N * D * H * W * (size_t)Cin >= (size_t)0x7FFFFFFF || (size_t)Cout * Kp >= (size_t)0x7FFFFFFF)
         return hipErrorInvalidValue;
-    // tile width: the grid's x extent up to 64
-    const int tx = W >= 64 ? 64 : (W >= 32 ? 32 : 16);
-#define PMC_FWD(NB, TX, PIPE) \
-    launch_fwd<NB, TX, PIPE>(in, coarse, Cc, wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu, s)
-    if (Cout <= 16) {
-        if (Cin == 8 && tx == 64) return PMC_FWD(1, 64, false);
-        if (tx == 64) return PMC_FWD(1, 64, true);
-        if (tx == 32) return PMC_FWD(1, 32, true);
-        return PMC_FWD(1, 16, true);
-    }
-    if (tx == 64) return PMC_FWD(2, 64, true);
-    if (tx == 32) return PMC_FWD(2, 32, true);
-    return PMC_FWD(2, 16, true);
+    // Which tile, by what each was measured at (us; 160 x 128 x 128 voxels and
+    // its halves; "1, 2" = the stage's chunks of 8 channels, "pipe" = two
+    // buffers, one workgroup per CU):
+    // - Up to 24 input channels there is little to gain from whole 32-byte
+    //   pieces and the smaller buffers keep more workgroups resident:
+    //   8 -> 16: 39 with 1, 59 with 2; 16 -> 48: 176 and 188.
+    // - Grids of at most one workgroup per CU pipeline their stages:
+    //   128 -> 64 at 20 x 16 x 16: 18.6 with pipe, 21.3 without; 64 -> 32 at
+    //   40 x 32 x 32 (160 workgroups): 13.5 and 15.4; 32 -> 64 there (320
+    //   workgroups): 15.4 and 11.3.
+    // - Else two chunks and the resident workgroups overlap each other's
+    //   copies: 48 -> 16: 153 with 2, 201 with 1 and pipe, 214 with 2 and pipe.
+    //   32 output channels a workgroup where there are that many (32 -> 96:
+    //   63 against 72 with 16; 48 -> 32 on 2 x 41 x 53 x 75: 45 and 53).
+    const size_t tiles = (size_t)N * ((D + 3) / 4) * ((H + 7) / 8) * ((W + 15) / 16);
+    const int n16 = (Cout + 15) / 16;
+#define PMC_FWD(...) launch_fwd<__VA_ARGS__>(in, coarse, Cc, wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu, s)
+    if (Cin <= 24 || Cc % 16) return PMC_FWD(1, 1, false, 8);   // (a stage of two chunks has one source)
+    if (tiles * n16 <= 256) return PMC_FWD(1, 2, true, 2);
+    if (Cout <= 16) return PMC_FWD(1, 2, false, 6);
+    return PMC_FWD(2, 2, false, 4);
 #undef PMC_FWD
 }
 

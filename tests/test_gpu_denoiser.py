@@ -125,6 +125,43 @@ def test_conv_backward_weight(cin, cout, shape):
     assert np.all(r[:, 27 * cin:] == 0.0)
 
 
+# grids of more than 256 workgroup tiles of 16 x 8 x 4 voxels (the small ones
+# above take the pipelined variant), sides one past and one short of a tile,
+# an odd number of 8-channel chunks, output channels that do not fill the last
+# 16 or 32
+BIG_CONV_CASES = [
+    (40, 16, (1, 33, 41, 97)),
+    (40, 24, (1, 31, 39, 95)),
+    (32, 48, (2, 29, 33, 65)),
+    (24, 40, (1, 17, 25, 33)),
+]
+
+
+@pytest.mark.parametrize("cin,cout,shape", BIG_CONV_CASES)
+def test_conv_forward_and_data_gradient_many_tiles(cin, cout, shape):
+    """The convolution's variants for grids of many tiles, forward and as the
+    data gradient, at the same bound as the small cases."""
+    import torch
+    _say("case: conv many tiles cin=%d cout=%d shape=%s" % (cin, cout, shape))
+    U = _unet()
+    rng = np.random.default_rng(cin * 1000 + cout + 5)
+    xb, x = synth.bf16_normal(rng, shape + (cin,))
+    gb, g = synth.bf16_normal(rng, shape + (cout,))
+    wb, w = synth.conv_weights(rng, cin, cout)
+    b = rng.normal(0, 0.1, cout).astype(np.float32)
+    y = torch.zeros(shape + (cout,), dtype=torch.int16, device="cuda")
+    U.pmc_nn_conv3d_forward(_dev(xb), _dev(wb), torch.from_numpy(b).cuda(), y, relu=False)
+    dx = torch.zeros(shape + (cin,), dtype=torch.int16, device="cuda")
+    U.pmc_nn_conv3d_backward_data(_dev(gb), _dev(wb), dx)
+    torch.cuda.synchronize()
+    for r, o, s, k in ((y, D.conv3d(x, w, b), D.conv3d(np.abs(x), np.abs(w), np.abs(b)), 27 * cin),
+                       (dx, D.conv3d_backward_data(g, w, cin), D.conv3d_backward_data(np.abs(g), np.abs(w), cin),
+                        27 * cout)):
+        r = _host_bf16(r)
+        bad = np.abs(r - o) > _conv_bound(o, s, k)
+        assert not bad.any(), (int(bad.sum()), float(np.abs(r - o).max()))
+
+
 @pytest.mark.parametrize("cin,cout,level", [(8, 16, 0), (48, 16, 0), (192, 64, 2)])
 def test_conv_forward_full_size_sampled(cin, cout, level):
     """At the full 160x128x128 input (level 0) or its level-2 grid, 300
