@@ -188,9 +188,9 @@ __global__ void __launch_bounds__(512, kMinWaves)
             }
         }
     };
-    auto stage = [&](const u32x4* bf, int c) __attribute__((always_inline)) {
+    auto stage = [&](const u32x4* bf) __attribute__((always_inline)) {
         compute(bf, 0);
-        if (QC == 2 && c + 1 < n_chunks) compute(bf, 1);
+        if constexpr (QC == 2) compute(bf, 1);
     };
     // vmcnt(0), other counters untouched: this wave's copies have landed
     constexpr int kWaitCopies = 0x0F70;
@@ -200,12 +200,12 @@ __global__ void __launch_bounds__(512, kMinWaves)
             __builtin_amdgcn_s_waitcnt(kWaitCopies);
             __syncthreads();   // the stage in buf0 complete; buf1 no longer read
             if (c + QC < n_chunks) issue(c + QC, buf1);
-            stage(buf0, c);
+            stage(buf0);
             if (c + QC >= n_chunks) break;
             __builtin_amdgcn_s_waitcnt(kWaitCopies);
             __syncthreads();   // the stage in buf1 complete; buf0 no longer read
             if (c + 2 * QC < n_chunks) issue(c + 2 * QC, buf0);
-            stage(buf1, c + QC);
+            stage(buf1);
         }
     } else {
         for (int c = 0; c < n_chunks; c += QC) {
@@ -213,7 +213,7 @@ __global__ void __launch_bounds__(512, kMinWaves)
             issue(c, buf0);
             __builtin_amdgcn_s_waitcnt(kWaitCopies);
             __syncthreads();
-            stage(buf0, c);
+            stage(buf0);
         }
     }
     // lane (m, g) holds output channels co0 + 16 j + 4 g .. + 3 of voxel m
@@ -904,7 +904,8 @@ hipError_t nn_conv3d_fwd_cat(const uint16_t* in, const uint16_t* coarse, int Cc,
     const size_t tiles = (size_t)N * ((D + 3) / 4) * ((H + 7) / 8) * ((W + 15) / 16);
     const int n16 = (Cout + 15) / 16;
 #define PMC_FWD(...) launch_fwd<__VA_ARGS__>(in, coarse, Cc, wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu, s)
-    if (Cin <= 24 || Cc % 16) return PMC_FWD(1, 1, false, 8);   // (a stage of two chunks has one source)
+    // (a stage of two chunks has one source and never runs past the last channel)
+    if (Cin <= 24 || Cin % 16 || Cc % 16) return PMC_FWD(1, 1, false, 8);
     if (tiles * n16 <= 256) return PMC_FWD(1, 2, true, 2);
     if (Cout <= 16) return PMC_FWD(1, 2, false, 6);
     return PMC_FWD(2, 2, false, 4);

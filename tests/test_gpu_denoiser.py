@@ -130,7 +130,7 @@ def test_conv_backward_weight(cin, cout, shape):
 # an odd number of 8-channel chunks, output channels that do not fill the last
 # 16 or 32
 BIG_CONV_CASES = [
-    (40, 16, (1, 33, 41, 97)),
+    (48, 16, (1, 33, 41, 97)),
     (40, 24, (1, 31, 39, 95)),
     (32, 48, (2, 29, 33, 65)),
     (24, 40, (1, 17, 25, 33)),
