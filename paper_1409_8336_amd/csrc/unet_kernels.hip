@@ -10,6 +10,7 @@
 // A[l%16][8(l/16)..+7], B[8(l/16)..+7][l%16]; the result D[4(l/16)+i][l%16].
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 namespace pmc {
@@ -18,6 +19,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // an 8-byte store that may sit at any 2-byte boundary (a caller's tensor)
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 #define GLOBAL __attribute__((address_space(1)))
 #define LOCAL __attribute__((address_space(3)))
@@ -260,183 +263,210 @@ __global__ void flip_weights_kernel(const uint16_t* __restrict__ w, uint16_t* __
     }
 }
 
-// Weight gradient.  Workgroup = (a run of rows) x kz x (32-channel input
-// block) x (64-channel output block).  For tap (kz, ky, kx):
-//   dW[co][ci] += sum_x dout[x][co] in[x + kx - 1][ci]
-//               = sum_x' dout[x' - kx + 1][co] in[x'][ci],
-// so per 64-voxel segment of a row the input rows are staged once (aligned,
-// no halo) and the output gradient three times, shifted by kx, both
-// transposed in LDS (voxel index fastest): every MFMA operand is one aligned
-// 16-byte LDS read, A = output-gradient rows (16 channels x 32 voxels), B =
-// input columns (32 voxels x 16 channels).  The waves split the 16-channel
-// output tiles of the block; where the block has fewer than four of them,
-// they also split the two 32-voxel K-steps and the two input tiles.
-// Staging: a thread takes an 8-voxel x 8-channel block (one 16-byte load per
-// voxel), transposes it in registers and writes eight 16-byte rows (8 voxels
-// of one channel) to LDS; the three x-shifted output-gradient copies come
-// from one load of 10 voxels, and the block walks its rows with the input
-// rows in a three-slot ring (one new row per row where the plane continues).
-constexpr int kWgSeg = 64;              // voxels per staged segment (two MFMA K-steps)
-constexpr int kWgPitch = kWgSeg + 8;    // LDS row pitch in elements (16-byte multiple)
-// kOneCt (Cout <= 16): every wave owns one input tile and one K-step half,
-// so it accumulates 9 tiles (the taps) instead of 18: half the accumulator
-// registers, three workgroups per CU instead of two
-template <bool kOneCt>
-__global__ void __launch_bounds__(256) conv3d_wgrad_kernel(const uint16_t* __restrict__ in,
-                                                           const uint16_t* __restrict__ dout,
-                                                           float* __restrict__ dw, int N, int D,
-                                                           int H, int W, int Cin, int Cout, int Kp,
-                                                           int rows_per_block)
+// Weight gradient: dW[co][tap][ci] += sum over input voxels v' of in[v'][ci]
+// dout[v' - off(tap)][co], off(tap) = (kz, ky, kx) - 1.  The voxels are the K
+// dimension of the product, so both operands have voxels along K while the
+// tensors are channels-last: they are copied to LDS as they are and read with
+// the transposing LDS load (ds_read_b64_tr_b16: four voxels of one channel per
+// lane), no shifted or transposed copies.
+// A workgroup of 12 waves owns a column of 32 (x) x TY (y) input voxels, 16 NCI
+// input and 16 NCO output channels, and walks a run of z planes.  Per plane it
+// holds the input plane (x halo of one, two buffers) and the output gradient of
+// planes z-1, z, z+1 (y halo of one, a ring of four), the next plane's copies
+// in flight.  A wave has one 16-channel input tile, one 16-channel output tile
+// and two of the rows, and all 27 taps in 108 accumulator registers: per plane
+// 6 input and 12 output-gradient fragments (each 32 voxels of a row) feed 54
+// MFMAs.  Planes and rows are split by the input's, x by the output's, so that
+// the smaller tensor carries the y and z halo; what lies outside the grid is
+// copied as zeros.  At the end the waves' row slices are added in LDS and the
+// workgroup adds its sums to dw, one atomic per weight.
+// What bounds it: with 16 output channels the MFMA rate (48 -> 16 channels on
+// 160 x 128 x 128: 113 us, 0.96 PFLOP/s; a kernel that transposed both operands
+// through registers into shifted LDS copies, 2,048 workgroups in flight, was
+// latency-bound at 701 us); the deeper, smaller layers the 16-20 us of the
+// first copies and the final sums, which every workgroup pays once (192 -> 64
+// on 40 x 32 x 32: 59 us, before 243; 64 -> 128 on 20 x 16 x 16: 31, before
+// 124).
+constexpr int kWgWaves = 12;
+
+// 64 lanes x 16 bytes at the lanes' byte offsets of a buffer to LDS address
+// `to` + 16 * lane; lanes past the buffer's end write zeros.  As an
+// instruction the compiler does not see as a load, so that it does not wait
+// for the copy before unrelated LDS reads: the caller waits for vmcnt(0)
+// before the barrier that hands the data over.
+DEV void copy_to_lds(i32x4 rsrc, uint32_t off, uint32_t to)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t sdo[3][64][kWgPitch];
-    __shared__ __attribute__((aligned(16))) uint16_t sin[3][32][kWgPitch];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(to), "v"(off), "s"(rsrc)
+                 : "memory");
+}
+template <int NCI, int NCO>
+struct WgTile {
+    static constexpr int KS = kWgWaves / (NCI * NCO), TY = 2 * KS;
+    static constexpr int IBLK = (TY * 68 + 63) / 64;            // 64-entry copies of one input tile's plane
+    static constexpr int NIN = NCI * IBLK, NDO = NCO * (TY + 2);
+    static constexpr int PER = (NIN + NDO + kWgWaves - 1) / kWgWaves;
+};
+
+template <int NCI, int NCO>
+__global__ void __launch_bounds__(64 * kWgWaves, 3)
+    conv3d_wgrad_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ dout, float* __restrict__ dw,
+                        int D, int H, int W, int Cin, int Cout, int Kp, int n_xt, int n_yt, unsigned long long n_planes,
+                        int per_block)
+{
+    using T = WgTile<NCI, NCO>;
+    constexpr int KS = T::KS, TY = T::TY;
+    // two input planes, then a ring of four output-gradient planes
+    constexpr int kInBytes = 1024 * T::NIN, kDoBytes = 1024 * T::NDO;
+    __shared__ __attribute__((aligned(16))) char lds[2 * kInBytes + 4 * kDoBytes];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g = lane >> 4;
-    const int n_ci_blk = (Cin + 31) / 32;
-    const int kz = blockIdx.y % 3;
-    const int cib = (blockIdx.y / 3) % n_ci_blk;
-    const int cob = blockIdx.y / (3 * n_ci_blk);
-    const int ci0 = cib * 32, co0 = cob * 64;
-    // this wave's share: output tile ct, K-steps and input tiles (an input
-    // block with 16 channels or fewer has one input tile: the second is
-    // neither staged nor multiplied)
-    const int n_cot = min(4, (Cout - co0 + 15) / 16);
-    const int n_cit = min(2, (Cin - ci0 + 15) / 16);
-    int ct, ks_sel = -1, cit_sel = -1;
-    if (n_cot >= 3) {
-        ct = wave;
-    } else if (n_cot == 2) {
-        ct = wave & 1;
-        ks_sel = wave >> 1;
-    } else {
-        ct = 0;
-        ks_sel = wave & 1;
-        cit_sel = wave >> 1;
-    }
-    const bool active = ct < n_cot && (cit_sel < 0 || cit_sel < n_cit);
-    const int total_rows = N * D * H;
-    const int row0 = blockIdx.x * rows_per_block;
-    const int r_end = min(row0 + rows_per_block, total_rows);
+    // workgroup -> channel blocks and its run of the block's planes: plane
+    // index = ((volume * n_yt + y tile) * n_xt + x tile) * D + z
+    const int n_cib = (Cin + 16 * NCI - 1) / (16 * NCI);
+    const int blk2 = blockIdx.x / per_block, part = blockIdx.x % per_block;
+    const int ci0 = 16 * NCI * (blk2 % n_cib), co0 = 16 * NCO * (blk2 / n_cib);
+    unsigned long long p = n_planes * part / per_block;
+    const unsigned long long p_end = n_planes * (part + 1) / per_block;
     const size_t plane = (size_t)H * W;
-    constexpr int kTiles = kOneCt ? 9 : 18;
-    f32x4 acc[kTiles];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(LOCAL char*)lds;
+    // this wave's tiles and rows
+    const int tj = wave % NCI, tc = (wave / NCI) % NCO, ks = wave / (NCI * NCO);
+    // fragment reads: lane (g, m) addresses voxel 4 g + m / 4 of a row, four
+    // channels from 4 (m % 4); the second half of a fragment lies 16 voxels on
+    // (both operands alike, so the order along K does not matter)
+    const int lane_at = (4 * g + (m >> 2)) * 32 + 8 * (m & 3);
+    const int in_at = tj * T::IBLK * 1024 + 2 * ks * 34 * 32 + lane_at;
+    const int do_at = tc * (TY + 2) * 1024 + 2 * ks * 32 * 32 + lane_at;
+    auto frag = [&](const char* p) __attribute__((always_inline)) {
+        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LOCAL i16x4*)p);
+        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LOCAL i16x4*)(p + 512));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    f32x4 acc[27];
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    // 8 voxels of one channel group -> 8 LDS rows (channel c = 2 q + h of
-    // voxel j is half h of word q of v[j]; a row packs the voxels in pairs)
-    auto put = [](uint16_t* dst, const uint4* v) {
+    for (int t = 0; t < 27; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    while (p < p_end) {
+    // the planes of one column: z_begin .. z_end - 1 of volume n
+    const unsigned long long col = p / (unsigned)D;
+    const int z_begin = (int)(p - col * (unsigned)D);
+    const int z_end = (int)min((unsigned long long)D, z_begin + (p_end - p));
+    p += z_end - z_begin;
+    const int xt = (int)(col % (unsigned)n_xt), yt = (int)(col / (unsigned)n_xt % (unsigned)n_yt);
+    const size_t n = (size_t)(col / (unsigned)n_xt / (unsigned)n_yt);
+    const int x0 = 32 * xt, y0 = TY * yt;
+    // byte offsets, within a z plane, of the entries this lane copies: blocks
+    // of 64 dealt to the waves in turn, the input's tiles first
+    constexpr uint32_t kOutside = 0xFFFFFFF0u;
+    uint32_t off[T::PER];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t w[8];
+    for (int q = 0; q < T::PER; ++q) {
+        const int blk = wave + kWgWaves * q;
+        off[q] = kOutside;
+        if (blk < T::NIN) {
+            const int e = (blk % T::IBLK) * 64 + lane;
+            const int row = e / 68, r2 = e % 68;
+            const int x = x0 + (r2 >> 1) - 1, y = y0 + row, c = ci0 + 16 * (blk / T::IBLK) + 8 * (r2 & 1);
+            if (row < TY && x >= 0 && x < W && y < H && c < Cin) off[q] = (((uint32_t)y * W + x) * Cin + c) * 2u;
+        } else if (blk < T::NIN + T::NDO) {
+            const int d = blk - T::NIN;
+            const int x = x0 + (lane >> 1), y = y0 + d % (TY + 2) - 1, c = co0 + 16 * (d / (TY + 2)) + 8 * (lane & 1);
+            if (x < W && y >= 0 && y < H && c < Cout) off[q] = (((uint32_t)y * W + x) * Cout + c) * 2u;
+        }
+    }
+    // z plane -> buffer descriptor (empty outside the grid: every lane reads zero)
+    auto plane_rsrc = [&](const uint16_t* t, int z, int C) {
+        const bool ok = z >= 0 && z < D;
+        const uint64_t at = (uint64_t)(uintptr_t)(t + (n * D + (ok ? z : 0)) * plane * C);
+        return (i32x4){(int)(uint32_t)at, (int)(uint32_t)(at >> 32), ok ? (int)(uint32_t)(plane * C * 2) : 0, 0x00020000};
+    };
+    // input plane z (its own buffer) and output-gradient plane zd to LDS
+    auto load = [&](int z, bool with_in, int zd) __attribute__((always_inline)) {
+        const i32x4 ri = plane_rsrc(in, z, Cin), rd = plane_rsrc(dout, zd, Cout);
+        const uint32_t ti = lds0 + (z & 1) * kInBytes, td = lds0 + 2 * kInBytes + (zd & 3) * kDoBytes;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) w[j] = q == 0 ? v[j].x : (q == 1 ? v[j].y : (q == 2 ? v[j].z : v[j].w));
-            uint4 lo, hi;
-            lo.x = (w[0] & 0xFFFFu) | (w[1] << 16);
-            lo.y = (w[2] & 0xFFFFu) | (w[3] << 16);
-            lo.z = (w[4] & 0xFFFFu) | (w[5] << 16);
-            lo.w = (w[6] & 0xFFFFu) | (w[7] << 16);
-            hi.x = (w[0] >> 16) | (w[1] & 0xFFFF0000u);
-            hi.y = (w[2] >> 16) | (w[3] & 0xFFFF0000u);
-            hi.z = (w[4] >> 16) | (w[5] & 0xFFFF0000u);
-            hi.w = (w[6] >> 16) | (w[7] & 0xFFFF0000u);
-            *reinterpret_cast<uint4*>(dst + (2 * q) * kWgPitch) = lo;
-            *reinterpret_cast<uint4*>(dst + (2 * q + 1) * kWgPitch) = hi;
+        for (int q = 0; q < T::PER; ++q) {
+            const int blk = wave + kWgWaves * q;
+            if (blk < T::NIN) {
+                if (with_in) copy_to_lds(ri, off[q], ti + 1024 * blk);
+            } else if (blk < T::NIN + T::NDO) {
+                copy_to_lds(rd, off[q], td + 1024 * (blk - T::NIN));
+            }
         }
     };
-    // x segments outside, the block's rows inside: the input rows of row r
-    // (y + ky - 1, ky < 3) sit in the ring slot (y + ky - 1 + 3) % 3, and the
-    // next row of the same plane stages only its new row y + 2
-    for (int xb = 0; xb < W; xb += kWgSeg) {
-        int prev_nz = -1, prev_y = -2;
-        for (int r = row0; r < r_end; ++r) {
-            const int y = r % H, nz = r / H, z = nz % D;
-            const size_t nbase = (size_t)(nz - z) * plane;
-            const int zz = z + kz - 1;
-            const bool zin = zz >= 0 && zz < D;
-            const bool slide = nz == prev_nz && y == prev_y + 1;
-            prev_nz = nz;
-            prev_y = y;
-            const int n_new = slide ? 1 : 3;            // input rows to stage
-            __syncthreads();
-            const int i = threadIdx.x;
-            if (i < 64) {
-                // output gradient of row r, channels co0 + 8 cg .., voxels
-                // x = xb + 8 vg - 1 .. + 8 loaded once; copy kx holds slot
-                // xp = x - xb + kx - 1 (the voxel x = xb + xp + 1 - kx)
-                const int cg = i & 7, vg = i >> 3;
-                const int c0 = co0 + 8 * cg;
-                if (c0 < Cout) {
-                    const uint16_t* src = dout + (nbase + (size_t)z * plane + (size_t)y * W) * Cout + c0;
-                    uint4 u[10];
+    // input plane z against the output gradient's planes z+1, z, z-1 (kz = 0,
+    // 1, 2); at the grid's faces the products with the rows and planes outside
+    // are left out (an infinite input times their zeros would not vanish)
+    auto step = [&](int z) __attribute__((always_inline)) {
+        const char* pin = lds + (z & 1) * kInBytes + in_at;
+        const char* pd[3];
 #pragma unroll
-                    for (int k = 0; k < 10; ++k) {
-                        const int x = xb + 8 * vg - 1 + k;
-                        u[k] = make_uint4(0u, 0u, 0u, 0u);
-                        if (x >= 0 && x < W) u[k] = *reinterpret_cast<const uint4*>(src + (size_t)x * Cout);
-                    }
+        for (int kz = 0; kz < 3; ++kz) pd[kz] = lds + 2 * kInBytes + ((z + 1 - kz) & 3) * kDoBytes + do_at;
+        bf16x8 bv[2][3];
 #pragma unroll
-                    for (int kx = 0; kx < 3; ++kx) put(&sdo[kx][8 * cg][8 * vg], u + 2 - kx);
-                }
-            } else if (i < 64 + 32 * n_new) {
-                // input row yy = y + 1 (slide) or y - 1 + k, channels
-                // ci0 + 8 cg .., x = xb + 8 vg ..; input rows past Cin
-                // inside a used tile are staged as zeros
-                const int t = i - 64;
-                const int cg = t & 3, vg = (t >> 2) & 7, k = t >> 5;
-                if (cg < 2 * n_cit) {
-                    const int yy = slide ? y + 1 : y - 1 + k;
-                    const int c0 = ci0 + 8 * cg;
-                    const bool ok = zin && yy >= 0 && yy < H && c0 < Cin;
-                    const uint16_t* src = in + (nbase + (size_t)zz * plane + (size_t)yy * W) * Cin + c0;
-                    uint4 v[8];
+        for (int r = 0; r < 2; ++r)
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int x = xb + 8 * vg + j;
-                        v[j] = make_uint4(0u, 0u, 0u, 0u);
-                        if (ok && x < W) v[j] = *reinterpret_cast<const uint4*>(src + (size_t)x * Cin);
-                    }
-                    put(&sin[(yy + 3) % 3][8 * cg][8 * vg], v);
-                }
-            }
-            __syncthreads();
-            if (!active) continue;
+            for (int kx = 0; kx < 3; ++kx) bv[r][kx] = frag(pin + (r * 34 + kx) * 32);
+        // row 2 ks + a - 1 of the output gradient: tap ky = r + 2 - a of input row r
 #pragma unroll
-            for (int kh = 0; kh < kWgSeg / 32; ++kh) {
-                if (ks_sel >= 0 && kh != ks_sel) continue;
-                const int ks = 32 * kh;
-                bf16x8 av[3];
+        for (int a = 0; a < 4; ++a) {
+            const bf16x8 av[3] = {frag(pd[0] + a * 1024), frag(pd[1] + a * 1024), frag(pd[2] + a * 1024)};
+            const int y = y0 + 2 * ks + a - 1;
+            if (y < 0 || y >= H) continue;
 #pragma unroll
-                for (int kx = 0; kx < 3; ++kx)
-                    av[kx] = *reinterpret_cast<const bf16x8*>(&sdo[kx][ct * 16 + m][ks + 8 * g]);
+            for (int kz = 0; kz < 3; ++kz) {
+                if (kz != 1 && (z + 1 - kz < 0 || z + 1 - kz >= D)) continue;
 #pragma unroll
-                for (int cit = 0; cit < 2; ++cit) {
-                    if ((cit_sel >= 0 && cit != cit_sel) || cit >= n_cit) continue;
+                for (int r = 0; r < 2; ++r) {
+                    const int ky = r + 2 - a;
+                    if (ky < 0 || ky > 2) continue;
 #pragma unroll
-                    for (int ky = 0; ky < 3; ++ky) {
-                        const int sl = (y + ky - 1 + 3) % 3;
-                        const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&sin[sl][cit * 16 + m][ks + 8 * g]);
-#pragma unroll
-                        for (int kx = 0; kx < 3; ++kx) {
-                            const int t = kOneCt ? ky * 3 + kx : (ky * 3 + kx) * 2 + cit;
-                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[kx], bv, acc[t], 0, 0, 0);
-                        }
+                    for (int kx = 0; kx < 3; ++kx) {
+                        f32x4& t = acc[(kz * 3 + ky) * 3 + kx];
+                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[kz], bv[r][kx], t, 0, 0, 0);
                     }
                 }
             }
         }
+    };
+    constexpr int kWaitCopies = 0x0F70;   // vmcnt(0), other counters untouched
+    load(z_begin, true, z_begin - 1);
+    load(z_begin, false, z_begin);
+    load(z_begin, false, z_begin + 1);
+    __builtin_amdgcn_s_waitcnt(kWaitCopies);
+    __syncthreads();
+    for (int z = z_begin; z < z_end; ++z) {
+        // the next plane's copies go where nothing is read during this one
+        if (z + 1 < z_end) load(z + 1, true, z + 2);
+        step(z);
+        __builtin_amdgcn_s_waitcnt(kWaitCopies);
+        __syncthreads();
     }
-    if (!active) return;
+    }   // columns
+    // add up the row slices, three taps at a time: every wave leaves its tiles
+    // in the copies' LDS (no longer read; lane (g, m) holds output channels
+    // 4 g .. + 3 of input channel m), then each weight's KS values are summed
+    constexpr int kTiles = 3 * NCI * NCO;
+    static_assert(KS * kTiles * 1024 <= (int)sizeof(lds), "the waves' tiles fit the copies' LDS");
+    float* const red = reinterpret_cast<float*>(lds);
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t) {
-        const int kyx = kOneCt ? t : t >> 1, cit = kOneCt ? cit_sel : t & 1;
-        const int tap = kz * 9 + kyx;
-        const int ci = ci0 + cit * 16 + m;
-        if (ci >= Cin) continue;
+    for (int k3 = 0; k3 < 9; ++k3) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int co = co0 + ct * 16 + 4 * g + i;
-            if (co < Cout && acc[t][i] != 0.f) atomicAdd(&dw[(size_t)co * Kp + tap * Cin + ci], acc[t][i]);
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                red[((ks * 3 + kx) * NCO * NCI + tc * NCI + tj) * 256 + (4 * g + i) * 16 + m] = acc[3 * k3 + kx][i];
+        __syncthreads();
+        for (int e = threadIdx.x; e < kTiles * 256; e += 64 * kWgWaves) {
+            const int t = e >> 8, j = t % NCI, c = (t / NCI) % NCO, kx = t / (NCI * NCO);
+            const int co = co0 + 16 * c + ((e >> 4) & 15), ci = ci0 + 16 * j + (e & 15);
+            float v = 0.f;
+#pragma unroll
+            for (int q = 0; q < KS; ++q) v += red[q * kTiles * 256 + e];
+            if (co < Cout && ci < Cin && v != 0.f) atomicAdd(&dw[(size_t)co * Kp + (3 * k3 + kx) * Cin + ci], v);
         }
+        __syncthreads();
     }
 }
 
@@ -924,27 +954,35 @@ hipError_t nn_flip_weights(const uint16_t* w, uint16_t* wf, int Cin, int Cout, i
     return hipGetLastError();
 }
 
-hipError_t nn_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W,
-                           int Cin, int Cout, int Kp, hipStream_t s)
+template <int NCI, int NCO>
+static hipError_t launch_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W, int Cin,
+                               int Cout, int Kp, hipStream_t s)
 {
-    const int total_rows = N * D * H;
-    const int n_ci = (Cin + 31) / 32, n_co = (Cout + 63) / 64;
-    const int others = 3 * n_ci * n_co;
-    // enough workgroups to fill the chip, each with a run of rows
-    int blocks_x = (2048 + others - 1) / others;
-    if (blocks_x > total_rows) blocks_x = total_rows;
-    if (blocks_x < 1) blocks_x = 1;
-    const int rows = (total_rows + blocks_x - 1) / blocks_x;
-    blocks_x = (total_rows + rows - 1) / rows;
-    if (Cout <= 16)
-        hipLaunchKernelGGL(conv3d_wgrad_kernel<true>, dim3(blocks_x, others), dim3(256), 0, s, in, dout, dw, N, D, H,
-                           W, Cin, Cout, Kp, rows);
-    else
-        hipLaunchKernelGGL(conv3d_wgrad_kernel<false>, dim3(blocks_x, others), dim3(256), 0, s, in, dout, dw, N, D,
-                           H, W, Cin, Cout, Kp, rows);
+    using T = WgTile<NCI, NCO>;
+    const int n_xt = (W + 31) / 32, n_yt = (H + T::TY - 1) / T::TY;
+    const int blocks = ((Cin + 16 * NCI - 1) / (16 * NCI)) * ((Cout + 16 * NCO - 1) / (16 * NCO));
+    // one workgroup per CU (its waves fill it), the planes of a channel block
+    // dealt to its workgroups in equal runs
+    const unsigned long long n_planes = (unsigned long long)N * n_yt * n_xt * D;
+    const int per_block = (int)std::min<unsigned long long>(n_planes, (unsigned long long)std::max(1, 256 / blocks));
+    hipLaunchKernelGGL((conv3d_wgrad_kernel<NCI, NCO>), dim3((unsigned)(blocks * per_block)), dim3(64 * kWgWaves), 0, s, in,
+                       dout, dw, D, H, W, Cin, Cout, Kp, n_xt, n_yt, n_planes, per_block);
     return hipGetLastError();
 }
 
+hipError_t nn_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W,
+                           int Cin, int Cout, int Kp, hipStream_t s)
+{
+    // (the kernel keeps byte offsets within a z plane in 32 bits)
+    if ((size_t)H * W * (size_t)std::max(Cin, Cout) >= (size_t)0x7FFFFFFF) return hipErrorInvalidValue;
+#define PMC_WG(NCI, NCO) launch_wgrad<NCI, NCO>(in, dout, dw, N, D, H, W, Cin, Cout, Kp, s)
+    // input tiles: three of 16 channels where they divide the channels, else two, or one
+    const int ti = (Cin + 15) / 16, to = (Cout + 15) / 16;
+    const int nci = ti % 3 == 0 ? 3 : (ti == 1 ? 1 : 2);
+    if (to == 1) return nci == 3 ? PMC_WG(3, 1) : (nci == 2 ? PMC_WG(2, 1) : PMC_WG(1, 1));
+    return nci == 3 ? PMC_WG(3, 2) : (nci == 2 ? PMC_WG(2, 2) : PMC_WG(1, 2));
+#undef PMC_WG
+}
 
 hipError_t nn_relu_bias_bwd(uint16_t* dy, const uint16_t* y, float* db, size_t nvox, int C, hipStream_t s)
 {

@@ -162,6 +162,61 @@ def test_conv_forward_and_data_gradient_many_tiles(cin, cout, shape):
         assert not bad.any(), (int(bad.sum()), float(np.abs(r - o).max()))
 
 
+@pytest.mark.parametrize("cin,cout,shape", [
+    # each split of a workgroup's 12 waves over input tiles, output tiles and
+    # rows, with sides one past and one short of its 32 x TY tile
+    (8, 8, (2, 3, 25, 33)),
+    (32, 16, (1, 4, 13, 31)),
+    (48, 16, (1, 5, 9, 65)),
+    (16, 32, (1, 1, 11, 32)),
+    (56, 24, (1, 3, 7, 17)),
+    (96, 48, (1, 2, 5, 30)),
+    # more z planes of a channel block than workgroups: a run crosses columns
+    (16, 16, (2, 130, 26, 34)),
+])
+def test_conv_backward_weight_tiles(cin, cout, shape):
+    import torch
+    _say("case: weight gradient tiles cin=%d cout=%d shape=%s" % (cin, cout, shape))
+    U = _unet()
+    rng = np.random.default_rng(cin * 1000 + cout + 9)
+    xb, x = synth.bf16_normal(rng, shape + (cin,))
+    gb, g = synth.bf16_normal(rng, shape + (cout,))
+    k = D.kp(cin)
+    dw = torch.zeros(cout, k, dtype=torch.float32, device="cuda")
+    U.pmc_nn_conv3d_backward_weight(_dev(xb), _dev(gb), dw)
+    torch.cuda.synchronize()
+    o = D.conv3d_backward_weight(x, g, k)
+    s = D.conv3d_backward_weight(np.abs(x), np.abs(g), k)
+    r = dw.cpu().numpy().astype(np.float64)
+    bad = np.abs(r - o) > 2.0 * (int(np.prod(shape)) + 1) * 2.0 ** -24 * s + 1e-30
+    assert not bad.any(), (int(bad.sum()), float(np.abs(r - o).max()))
+    assert np.all(r[:, 27 * cin:] == 0.0)
+
+
+def test_conv_backward_weight_infinite_input_at_a_face():
+    """An infinite input in the first plane and row meets no tap that would
+    reach it from outside the grid: those weights' gradients stay finite and
+    are those of a zero in its place."""
+    import torch
+    U = _unet()
+    rng = np.random.default_rng(5)
+    shape, cin, cout = (1, 4, 10, 33), 16, 16
+    xb, x = synth.bf16_normal(rng, shape + (cin,))
+    gb, g = synth.bf16_normal(rng, shape + (cout,))
+    x[0, 0, 0, 7, 3] = 0.0
+    xi = xb.copy()
+    xi[0, 0, 0, 7, 3] = 0x7F80
+    dw = torch.zeros(cout, D.kp(cin), dtype=torch.float32, device="cuda")
+    U.pmc_nn_conv3d_backward_weight(_dev(xi), _dev(gb), dw)
+    r = dw.cpu().numpy()[:, :27 * cin].reshape(cout, 3, 3, 3, cin).astype(np.float64)
+    o = D.conv3d_backward_weight(x, g, D.kp(cin))[:, :27 * cin].reshape(cout, 3, 3, 3, cin)
+    s = D.conv3d_backward_weight(np.abs(x), np.abs(g), D.kp(cin))[:, :27 * cin].reshape(cout, 3, 3, 3, cin)
+    bound = 2.0 * (int(np.prod(shape)) + 1) * 2.0 ** -24 * s
+    assert np.all(np.abs(r - o)[:, 2] <= bound[:, 2])          # kz = 2: from below the first plane
+    assert np.all(np.abs(r - o)[:, :, 2] <= bound[:, :, 2])    # ky = 2: from before the first row
+    assert not np.isfinite(r[:, :2, :2, :2, 3]).any()
+
+
 @pytest.mark.parametrize("cin,cout,level", [(8, 16, 0), (48, 16, 0), (192, 64, 2)])
 def test_conv_forward_full_size_sampled(cin, cout, level):
     """At the full 160x128x128 input (level 0) or its level-2 grid, 300
