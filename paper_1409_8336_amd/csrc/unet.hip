@@ -22,14 +22,14 @@ hipError_t nn_conv3d_fwd_cat(const uint16_t* in, const uint16_t* coarse, int Cc,
                              const float* bias, uint16_t* out, int N, int D, int H, int W, int Cin, int Cout,
                              int Kp, int relu, hipStream_t s);
 hipError_t nn_flip_weights(const uint16_t* w, uint16_t* wf, int Cin, int Cout, int Kp, int Kpf, hipStream_t s);
+hipError_t nn_conv3d_wgrad_cat(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* dout, float* dw, int N,
+                               int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s);
 hipError_t nn_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W,
                            int Cin, int Cout, int Kp, hipStream_t s);
 hipError_t nn_relu_bias_bwd(uint16_t* dy, const uint16_t* y, float* db, size_t nvox, int C, hipStream_t s);
 hipError_t nn_pool_fwd(const uint16_t* in, uint16_t* out, int N, int D, int H, int W, int C, hipStream_t s);
 hipError_t nn_pool_bwd(const uint16_t* dout, const uint16_t* add, uint16_t* din, int N, int D, int H, int W, int C,
                        hipStream_t s);
-hipError_t nn_up_concat(const uint16_t* coarse, const uint16_t* skip, uint16_t* cat, int N, int D, int H, int W,
-                        int Cc, int Cs, hipStream_t s);
 hipError_t nn_up_concat_bwd(const uint16_t* dcat, uint16_t* dcoarse, uint16_t* dskip, int N, int D, int H, int W,
                             int Cc, int Cs, hipStream_t s);
 hipError_t nn_make_input(const float* dose, const float* rho, float* scale, uint16_t* x, size_t nvox, int N, int D,
@@ -111,7 +111,7 @@ struct pmc_unet {
     uint16_t *wbf = nullptr, *wf = nullptr;
     int step = 0;
     // activations
-    Act x, e1, p1, e2, p2, e3, p3, e4, c3, d3, c2, d2, c1, d1;
+    Act x, e1, p1, e2, p2, e3, p3, e4, d3, d2, d1;
     // gradients
     Act g_d1, g_c1, g_d2, g_e1s, g_c2, g_d3, g_e2s, g_c3, g_e4, g_e3s, g_p3, g_e3, g_p2, g_e2, g_p1, g_e1;
     float* out = nullptr;     // FP32 network output (denoised dose)
@@ -164,42 +164,39 @@ hipError_t conv_fwd(pmc_unet* u, const Conv& c, const Act& in, Act& out, int lev
                          u->W >> level, c.cin, c.cout, c.kp, 1, s);
 }
 
-// a decoder convolution whose input is [upsampled coarse, skip]: either from
-// the concatenation, formed first (training keeps it for the weight
-// gradient), or read from both sources by the convolution itself
-hipError_t dec_fwd(pmc_unet* u, const Conv& c, const Act& coarse, const Act& skip, Act& cat, Act& out, int level,
-                   bool keep_cat, hipStream_t s)
+// a decoder convolution whose input is [upsampled coarse, skip], read from
+// both (here and by the weight gradient) without forming it: forming the three
+// concatenations took 112 us of a training step at 160 x 128 x 128 and the
+// convolutions that read them 74 us more (the coarse tensor is an eighth as
+// large; step 2,046 -> 1,842 us)
+hipError_t dec_fwd(pmc_unet* u, const Conv& c, const Act& coarse, const Act& skip, Act& out, int level, hipStream_t s)
 {
-    const int d = u->D >> level, h = u->H >> level, w = u->W >> level;
-    if (keep_cat) {
-        hipError_t e = nn_up_concat(coarse.p, skip.p, cat.p, u->N, d, h, w, coarse.c, skip.c, s);
-        if (e != hipSuccess) return e;
-        return conv_fwd(u, c, cat, out, level, s);
-    }
-    return nn_conv3d_fwd_cat(skip.p, coarse.p, coarse.c, u->wbf + c.off_wbf, u->p + c.off_b, out.p, u->N, d, h, w,
-                             c.cin, c.cout, c.kp, 1, s);
+    return nn_conv3d_fwd_cat(skip.p, coarse.p, coarse.c, u->wbf + c.off_wbf, u->p + c.off_b, out.p, u->N, u->D >> level,
+                             u->H >> level, u->W >> level, c.cin, c.cout, c.kp, 1, s);
 }
 
 // backward of one conv + ReLU layer: dy (gradient at the ReLU output, made
-// the pre-activation gradient in place), its input x and output y; writes
-// the input gradient dx unless dx is NULL
-hipError_t conv_bwd(pmc_unet* u, const Conv& c, const Act& x, const Act& y, Act& dy, Act* dx, int level,
-                    hipStream_t s)
+// the pre-activation gradient in place), its input [upsampled coarse, x]
+// (coarse NULL: x alone) and output y; writes the input gradient dx unless dx
+// is NULL
+hipError_t conv_bwd(pmc_unet* u, const Conv& c, const Act& x, const Act* coarse, const Act& y, Act& dy, Act* dx,
+                    int level, hipStream_t s)
 {
     const int d = u->D >> level, h = u->H >> level, w = u->W >> level;
     hipError_t e;
     if ((e = nn_relu_bias_bwd(dy.p, y.p, u->g + c.off_b, dy.nvox, c.cout, s)) != hipSuccess) return e;
-    if ((e = nn_conv3d_wgrad(x.p, dy.p, u->g + c.off_w, u->N, d, h, w, c.cin, c.cout, c.kp, s)) != hipSuccess) return e;
+    if ((e = nn_conv3d_wgrad_cat(x.p, coarse ? coarse->p : nullptr, coarse ? coarse->c : 0, dy.p, u->g + c.off_w, u->N, d,
+                                 h, w, c.cin, c.cout, c.kp, s)) != hipSuccess)
+        return e;
     if (!dx) return hipSuccess;
     if ((e = nn_flip_weights(u->wbf + c.off_wbf, u->wf + c.off_wf, c.cin, c.cout, c.kp, c.kpf, s)) != hipSuccess)
         return e;
     return nn_conv3d_fwd(dy.p, u->wf + c.off_wf, nullptr, dx->p, u->N, d, h, w, c.cout, c.cin, c.kpf, 0, s);
 }
 
-// train: keep what the backward pass reads; out: the head's output; the
-// caller's grid is d x h x w inside the network's (the whole of it in
-// training)
-hipError_t forward(pmc_unet* u, const float* dose, const float* rho, bool train, float* out, int d, int h, int w,
+// out: the head's output; the caller's grid is d x h x w inside the
+// network's (the whole of it in training)
+hipError_t forward(pmc_unet* u, const float* dose, const float* rho, float* out, int d, int h, int w,
                    hipStream_t s)
 {
     hipError_t e;
@@ -215,9 +212,9 @@ hipError_t forward(pmc_unet* u, const float* dose, const float* rho, bool train,
     if ((e = conv_fwd(u, u->conv[2], u->p2, u->e3, 2, s)) != hipSuccess) return e;
     if ((e = nn_pool_fwd(u->e3.p, u->p3.p, N, D >> 2, H >> 2, W >> 2, 64, s)) != hipSuccess) return e;
     if ((e = conv_fwd(u, u->conv[3], u->p3, u->e4, 3, s)) != hipSuccess) return e;
-    if ((e = dec_fwd(u, u->conv[4], u->e4, u->e3, u->c3, u->d3, 2, train, s)) != hipSuccess) return e;
-    if ((e = dec_fwd(u, u->conv[5], u->d3, u->e2, u->c2, u->d2, 1, train, s)) != hipSuccess) return e;
-    if ((e = dec_fwd(u, u->conv[6], u->d2, u->e1, u->c1, u->d1, 0, train, s)) != hipSuccess) return e;
+    if ((e = dec_fwd(u, u->conv[4], u->e4, u->e3, u->d3, 2, s)) != hipSuccess) return e;
+    if ((e = dec_fwd(u, u->conv[5], u->d3, u->e2, u->d2, 1, s)) != hipSuccess) return e;
+    if ((e = dec_fwd(u, u->conv[6], u->d2, u->e1, u->d1, 0, s)) != hipSuccess) return e;
     return nn_head_fwd(u->d1.p, u->p + u->off_hw, u->p + u->off_hb, dose, u->scale, out, nv, 16, D, H, W, d, h, w, s);
 }
 
@@ -231,28 +228,28 @@ hipError_t backward(pmc_unet* u, const float* dose, const float* target, hipStre
     if ((e = nn_loss_head_bwd(u->out, target, dose, u->scale, u->region, u->d1.p, u->p + u->off_hw, u->g_d1.p,
                               u->g + u->off_hw, u->g + u->off_hb, u->loss, nv, 16, s)) != hipSuccess)
         return e;
-    // dec1: c1 (48) -> d1 (16)
-    if ((e = conv_bwd(u, u->conv[6], u->c1, u->d1, u->g_d1, &u->g_c1, 0, s)) != hipSuccess) return e;
+    // dec1: [d2, e1] (48) -> d1 (16)
+    if ((e = conv_bwd(u, u->conv[6], u->e1, &u->d2, u->d1, u->g_d1, &u->g_c1, 0, s)) != hipSuccess) return e;
     if ((e = nn_up_concat_bwd(u->g_c1.p, u->g_d2.p, u->g_e1s.p, N, D, H, W, 32, 16, s)) != hipSuccess) return e;
-    // dec2: c2 (96) -> d2 (32)
-    if ((e = conv_bwd(u, u->conv[5], u->c2, u->d2, u->g_d2, &u->g_c2, 1, s)) != hipSuccess) return e;
+    // dec2: [d3, e2] (96) -> d2 (32)
+    if ((e = conv_bwd(u, u->conv[5], u->e2, &u->d3, u->d2, u->g_d2, &u->g_c2, 1, s)) != hipSuccess) return e;
     if ((e = nn_up_concat_bwd(u->g_c2.p, u->g_d3.p, u->g_e2s.p, N, D >> 1, H >> 1, W >> 1, 64, 32, s)) != hipSuccess)
         return e;
-    // dec3: c3 (192) -> d3 (64)
-    if ((e = conv_bwd(u, u->conv[4], u->c3, u->d3, u->g_d3, &u->g_c3, 2, s)) != hipSuccess) return e;
+    // dec3: [e4, e3] (192) -> d3 (64)
+    if ((e = conv_bwd(u, u->conv[4], u->e3, &u->e4, u->d3, u->g_d3, &u->g_c3, 2, s)) != hipSuccess) return e;
     if ((e = nn_up_concat_bwd(u->g_c3.p, u->g_e4.p, u->g_e3s.p, N, D >> 2, H >> 2, W >> 2, 128, 64, s)) != hipSuccess)
         return e;
     // enc4: p3 (64) -> e4 (128)
-    if ((e = conv_bwd(u, u->conv[3], u->p3, u->e4, u->g_e4, &u->g_p3, 3, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, u->conv[3], u->p3, nullptr, u->e4, u->g_e4, &u->g_p3, 3, s)) != hipSuccess) return e;
     if ((e = nn_pool_bwd(u->g_p3.p, u->g_e3s.p, u->g_e3.p, N, D >> 2, H >> 2, W >> 2, 64, s)) != hipSuccess) return e;
     // enc3: p2 (32) -> e3 (64)
-    if ((e = conv_bwd(u, u->conv[2], u->p2, u->e3, u->g_e3, &u->g_p2, 2, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, u->conv[2], u->p2, nullptr, u->e3, u->g_e3, &u->g_p2, 2, s)) != hipSuccess) return e;
     if ((e = nn_pool_bwd(u->g_p2.p, u->g_e2s.p, u->g_e2.p, N, D >> 1, H >> 1, W >> 1, 32, s)) != hipSuccess) return e;
     // enc2: p1 (16) -> e2 (32)
-    if ((e = conv_bwd(u, u->conv[1], u->p1, u->e2, u->g_e2, &u->g_p1, 1, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, u->conv[1], u->p1, nullptr, u->e2, u->g_e2, &u->g_p1, 1, s)) != hipSuccess) return e;
     if ((e = nn_pool_bwd(u->g_p1.p, u->g_e1s.p, u->g_e1.p, N, D, H, W, 16, s)) != hipSuccess) return e;
     // enc1: x (8) -> e1 (16), no input gradient
-    return conv_bwd(u, u->conv[0], u->x, u->e1, u->g_e1, nullptr, 0, s);
+    return conv_bwd(u, u->conv[0], u->x, nullptr, u->e1, u->g_e1, nullptr, 0, s);
 }
 
 hipError_t refresh_bf16(pmc_unet* u, hipStream_t s)
@@ -326,11 +323,8 @@ pmc_status pmc_unet_create(pmc_unet** out, int device, int n, int d, int h, int 
     A(act(u, u->e3, 2, 64));
     A(act(u, u->p3, 3, 64));
     A(act(u, u->e4, 3, 128));
-    A(act(u, u->c3, 2, 192));
     A(act(u, u->d3, 2, 64));
-    A(act(u, u->c2, 1, 96));
     A(act(u, u->d2, 1, 32));
-    A(act(u, u->c1, 0, 48));
     A(act(u, u->d1, 0, 16));
     A(act(u, u->g_d1, 0, 16));
     A(act(u, u->g_c1, 0, 48));
@@ -447,7 +441,7 @@ pmc_status pmc_unet_forward_region(pmc_unet* u, const float* dose, const float* 
         return ufail(u, PMC_ERR_ARG, "the grid must fit inside the network's shape");
     UCHK(hipSetDevice(u->device), "set device");
     hipStream_t s = (hipStream_t)stream;
-    UCHK(forward(u, dose, rho, false, d_out, d, h, w, s), "forward");
+    UCHK(forward(u, dose, rho, d_out, d, h, w, s), "forward");
     return PMC_OK;
 }
 
@@ -458,7 +452,7 @@ pmc_status pmc_unet_backward(pmc_unet* u, const float* dose, const float* rho, c
     if (!dose || !rho || !target) return ufail(u, PMC_ERR_ARG, "NULL tensor");
     UCHK(hipSetDevice(u->device), "set device");
     hipStream_t s = (hipStream_t)stream;
-    UCHK(forward(u, dose, rho, true, u->out, u->D, u->H, u->W, s), "forward");
+    UCHK(forward(u, dose, rho, u->out, u->D, u->H, u->W, s), "forward");
     UCHK(backward(u, dose, target, s), "backward");
     if (loss_out) {
         UCHK(hipMemcpyAsync(loss_out, u->loss, 8, hipMemcpyDeviceToHost, s), "read loss");

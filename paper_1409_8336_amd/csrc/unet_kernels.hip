@@ -278,7 +278,9 @@ __global__ void flip_weights_kernel(const uint16_t* __restrict__ w, uint16_t* __
 // 6 input and 12 output-gradient fragments (each 32 voxels of a row) feed 54
 // MFMAs.  Planes and rows are split by the input's, x by the output's, so that
 // the smaller tensor carries the y and z halo; what lies outside the grid is
-// copied as zeros.  At the end the waves' row slices are added in LDS and the
+// copied as zeros.  With a coarse source (Cc > 0, a multiple of 16) the input
+// is the decoder's concatenation [nearest upsampling of coarse, in], read from
+// both.  At the end the waves' row slices are added in LDS and the
 // workgroup adds its sums to dw, one atomic per weight.
 // What bounds it: with 16 output channels the MFMA rate (48 -> 16 channels on
 // 160 x 128 x 128: 113 us, 0.96 PFLOP/s; a kernel that transposed both operands
@@ -311,8 +313,8 @@ struct WgTile {
 
 template <int NCI, int NCO>
 __global__ void __launch_bounds__(64 * kWgWaves, 3)
-    conv3d_wgrad_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ dout, float* __restrict__ dw,
-                        int D, int H, int W, int Cin, int Cout, int Kp, int n_xt, int n_yt, unsigned long long n_planes,
+    conv3d_wgrad_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ coarse, int Cc,
+                        const uint16_t* __restrict__ dout, float* __restrict__ dw, int D, int H, int W, int Cin, int Cout, int Kp, int n_xt, int n_yt, unsigned long long n_planes,
                         int per_block)
 {
     using T = WgTile<NCI, NCO>;
@@ -368,7 +370,9 @@ __global__ void __launch_bounds__(64 * kWgWaves, 3)
             const int e = (blk % T::IBLK) * 64 + lane;
             const int row = e / 68, r2 = e % 68;
             const int x = x0 + (r2 >> 1) - 1, y = y0 + row, c = ci0 + 16 * (blk / T::IBLK) + 8 * (r2 & 1);
-            if (row < TY && x >= 0 && x < W && y < H && c < Cin) off[q] = (((uint32_t)y * W + x) * Cin + c) * 2u;
+            if (row < TY && x >= 0 && x < W && y < H && c < Cin)
+                off[q] = c < Cc ? (((uint32_t)(y >> 1) * (W >> 1) + (x >> 1)) * Cc + c) * 2u
+                                : (((uint32_t)y * W + x) * (Cin - Cc) + (c - Cc)) * 2u;
         } else if (blk < T::NIN + T::NDO) {
             const int d = blk - T::NIN;
             const int x = x0 + (lane >> 1), y = y0 + d % (TY + 2) - 1, c = co0 + 16 * (d / (TY + 2)) + 8 * (lane & 1);
@@ -376,20 +380,21 @@ __global__ void __launch_bounds__(64 * kWgWaves, 3)
         }
     }
     // z plane -> buffer descriptor (empty outside the grid: every lane reads zero)
-    auto plane_rsrc = [&](const uint16_t* t, int z, int C) {
-        const bool ok = z >= 0 && z < D;
-        const uint64_t at = (uint64_t)(uintptr_t)(t + (n * D + (ok ? z : 0)) * plane * C);
-        return (i32x4){(int)(uint32_t)at, (int)(uint32_t)(at >> 32), ok ? (int)(uint32_t)(plane * C * 2) : 0, 0x00020000};
+    auto plane_rsrc = [&](const uint16_t* t, int z, int planes, size_t bytes) {
+        const bool ok = z >= 0 && z < planes;
+        const uint64_t at = (uint64_t)(uintptr_t)t + (n * planes + (ok ? z : 0)) * bytes;
+        return (i32x4){(int)(uint32_t)at, (int)(uint32_t)(at >> 32), ok ? (int)(uint32_t)bytes : 0, 0x00020000};
     };
     // input plane z (its own buffer) and output-gradient plane zd to LDS
     auto load = [&](int z, bool with_in, int zd) __attribute__((always_inline)) {
-        const i32x4 ri = plane_rsrc(in, z, Cin), rd = plane_rsrc(dout, zd, Cout);
+        const i32x4 ri = plane_rsrc(in, z, D, plane * (Cin - Cc) * 2), rd = plane_rsrc(dout, zd, D, plane * Cout * 2);
+        const i32x4 rc = plane_rsrc(coarse, z >> 1, D >> 1, (plane >> 2) * Cc * 2);
         const uint32_t ti = lds0 + (z & 1) * kInBytes, td = lds0 + 2 * kInBytes + (zd & 3) * kDoBytes;
 #pragma unroll
         for (int q = 0; q < T::PER; ++q) {
             const int blk = wave + kWgWaves * q;
             if (blk < T::NIN) {
-                if (with_in) copy_to_lds(ri, off[q], ti + 1024 * blk);
+                if (with_in) copy_to_lds(ci0 + 16 * (blk / T::IBLK) < Cc ? rc : ri, off[q], ti + 1024 * blk);
             } else if (blk < T::NIN + T::NDO) {
                 copy_to_lds(rd, off[q], td + 1024 * (blk - T::NIN));
             }
@@ -588,36 +593,7 @@ __global__ void pool_bwd_kernel(const uint16_t* __restrict__ dout, const uint16_
     }
 }
 
-// cat[v] = (coarse[parent(v)][0..Cc), skip[v][0..Cs))  -- nearest 2x upsampling + concat;
-// 8 channels (16 bytes) per lane, Cc and Cs multiples of 8
-__global__ void up_concat_kernel(const uint16_t* __restrict__ coarse, const uint16_t* __restrict__ skip,
-                                 uint16_t* __restrict__ cat, int N, int D, int H, int W, int Cc, int Cs)
-{
-    const int C8 = (Cc + Cs) >> 3, Cc8 = Cc >> 3, Cs8 = Cs >> 3;
-    const size_t total = (size_t)N * D * H * W * C8;
-    const int Ho = H / 2, Wo = W / 2, Do = D / 2;
-    const uint4* cs = reinterpret_cast<const uint4*>(coarse);
-    const uint4* ss = reinterpret_cast<const uint4*>(skip);
-    uint4* dst = reinterpret_cast<uint4*>(cat);
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int c = (int)(i % C8);
-        const size_t v = i / C8;
-        uint4 val;
-        if (c < Cc8) {
-            size_t r = v;
-            const int x = (int)(r % W); r /= W;
-            const int y = (int)(r % H); r /= H;
-            const int z = (int)(r % D);
-            const int n = (int)(r / D);
-            val = cs[((((size_t)n * Do + z / 2) * Ho + y / 2) * Wo + x / 2) * Cc8 + c];
-        } else {
-            val = ss[v * Cs8 + (c - Cc8)];
-        }
-        dst[i] = val;
-    }
-}
-
-// backward of up_concat: d_coarse[p][c] = sum over the 8 children of dcat[v][c];
+// backward of the nearest 2x upsampling and concatenation: d_coarse[p][c] = sum over the 8 children of dcat[v][c];
 // d_skip[v][c] = dcat[v][Cc + c]
 __global__ void up_concat_bwd_coarse_kernel(const uint16_t* __restrict__ dcat, uint16_t* __restrict__ dcoarse,
                                             int N, int D, int H, int W, int Cc, int Cs)
@@ -955,8 +931,8 @@ hipError_t nn_flip_weights(const uint16_t* w, uint16_t* wf, int Cin, int Cout, i
 }
 
 template <int NCI, int NCO>
-static hipError_t launch_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W, int Cin,
-                               int Cout, int Kp, hipStream_t s)
+static hipError_t launch_wgrad(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* dout, float* dw, int N,
+                               int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s)
 {
     using T = WgTile<NCI, NCO>;
     const int n_xt = (W + 31) / 32, n_yt = (H + T::TY - 1) / T::TY;
@@ -966,22 +942,29 @@ static hipError_t launch_wgrad(const uint16_t* in, const uint16_t* dout, float* 
     const unsigned long long n_planes = (unsigned long long)N * n_yt * n_xt * D;
     const int per_block = (int)std::min<unsigned long long>(n_planes, (unsigned long long)std::max(1, 256 / blocks));
     hipLaunchKernelGGL((conv3d_wgrad_kernel<NCI, NCO>), dim3((unsigned)(blocks * per_block)), dim3(64 * kWgWaves), 0, s, in,
-                       dout, dw, D, H, W, Cin, Cout, Kp, n_xt, n_yt, n_planes, per_block);
+                       coarse, Cc, dout, dw, D, H, W, Cin, Cout, Kp, n_xt, n_yt, n_planes, per_block);
     return hipGetLastError();
 }
 
-hipError_t nn_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W,
-                           int Cin, int Cout, int Kp, hipStream_t s)
+hipError_t nn_conv3d_wgrad_cat(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* dout, float* dw, int N,
+                               int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s)
 {
+    if (Cc < 0 || Cc % 16 || Cc >= Cin || (Cc && !coarse) || (Cc && (D % 2 || H % 2 || W % 2))) return hipErrorInvalidValue;
     // (the kernel keeps byte offsets within a z plane in 32 bits)
     if ((size_t)H * W * (size_t)std::max(Cin, Cout) >= (size_t)0x7FFFFFFF) return hipErrorInvalidValue;
-#define PMC_WG(NCI, NCO) launch_wgrad<NCI, NCO>(in, dout, dw, N, D, H, W, Cin, Cout, Kp, s)
+#define PMC_WG(NCI, NCO) launch_wgrad<NCI, NCO>(in, coarse, Cc, dout, dw, N, D, H, W, Cin, Cout, Kp, s)
     // input tiles: three of 16 channels where they divide the channels, else two, or one
     const int ti = (Cin + 15) / 16, to = (Cout + 15) / 16;
     const int nci = ti % 3 == 0 ? 3 : (ti == 1 ? 1 : 2);
     if (to == 1) return nci == 3 ? PMC_WG(3, 1) : (nci == 2 ? PMC_WG(2, 1) : PMC_WG(1, 1));
     return nci == 3 ? PMC_WG(3, 2) : (nci == 2 ? PMC_WG(2, 2) : PMC_WG(1, 2));
 #undef PMC_WG
+}
+
+hipError_t nn_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W,
+                           int Cin, int Cout, int Kp, hipStream_t s)
+{
+    return nn_conv3d_wgrad_cat(in, nullptr, 0, dout, dw, N, D, H, W, Cin, Cout, Kp, s);
 }
 
 hipError_t nn_relu_bias_bwd(uint16_t* dy, const uint16_t* y, float* db, size_t nvox, int C, hipStream_t s)
@@ -1007,15 +990,6 @@ hipError_t nn_pool_bwd(const uint16_t* dout, const uint16_t* add, uint16_t* din,
     if (C % 8) return hipErrorInvalidValue;
     hipLaunchKernelGGL(pool_bwd_kernel, dim3(grid_for((size_t)N * D * H * W * (C / 8))), dim3(256), 0, s, dout, add,
                        din, N, D, H, W, C);
-    return hipGetLastError();
-}
-
-hipError_t nn_up_concat(const uint16_t* coarse, const uint16_t* skip, uint16_t* cat, int N, int D, int H, int W,
-                        int Cc, int Cs, hipStream_t s)
-{
-    if ((Cc | Cs) & 7) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(up_concat_kernel, dim3(grid_for((size_t)N * D * H * W * (Cc + Cs) / 8)), dim3(256), 0, s, coarse,
-                       skip, cat, N, D, H, W, Cc, Cs);
     return hipGetLastError();
 }
 
