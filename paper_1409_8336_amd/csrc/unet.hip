@@ -21,21 +21,25 @@ hipError_t nn_conv3d_fwd(const uint16_t* in, const uint16_t* wt, const float* bi
 hipError_t nn_conv3d_fwd_cat(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* wt,
                              const float* bias, uint16_t* out, int N, int D, int H, int W, int Cin, int Cout,
                              int Kp, int relu, hipStream_t s);
+hipError_t nn_conv3d_fwd_pool(const uint16_t* in, const uint16_t* wt, const float* bias, uint16_t* out,
+                              uint16_t* pooled, int N, int D, int H, int W, int Cin, int Cout, int Kp, int relu,
+                              hipStream_t s);
+hipError_t nn_conv3d_fwd_split(const uint16_t* in, const uint16_t* wt, uint16_t* dcoarse, int Cc, uint16_t* dskip, int N,
+                               int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s);
+hipError_t nn_conv3d_fwd_cat_head(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* wt,
+                                  const float* bias, uint16_t* out, const float* w, const float* b, const float* dose,
+                                  const float* scale, float* res, int N, int D, int H, int W, int Cin, int Kp, int d,
+                                  int h, int wd, hipStream_t s);
 hipError_t nn_flip_weights(const uint16_t* w, uint16_t* wf, int Cin, int Cout, int Kp, int Kpf, hipStream_t s);
 hipError_t nn_conv3d_wgrad_cat(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* dout, float* dw, int N,
                                int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s);
 hipError_t nn_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W,
                            int Cin, int Cout, int Kp, hipStream_t s);
 hipError_t nn_relu_bias_bwd(uint16_t* dy, const uint16_t* y, float* db, size_t nvox, int C, hipStream_t s);
-hipError_t nn_pool_fwd(const uint16_t* in, uint16_t* out, int N, int D, int H, int W, int C, hipStream_t s);
 hipError_t nn_pool_bwd(const uint16_t* dout, const uint16_t* add, uint16_t* din, int N, int D, int H, int W, int C,
                        hipStream_t s);
-hipError_t nn_up_concat_bwd(const uint16_t* dcat, uint16_t* dcoarse, uint16_t* dskip, int N, int D, int H, int W,
-                            int Cc, int Cs, hipStream_t s);
 hipError_t nn_make_input(const float* dose, const float* rho, float* scale, uint16_t* x, size_t nvox, int N, int D,
                          int H, int W, int d, int h, int w, hipStream_t s);
-hipError_t nn_head_fwd(const uint16_t* d1, const float* w, const float* b, const float* dose, const float* scale,
-                       float* out, size_t nvox, int C, int D, int H, int W, int d, int h, int wd, hipStream_t s);
 hipError_t nn_loss_head_bwd(const float* out, const float* target, const float* dose, const float* scale,
                             unsigned int* region, const uint16_t* d1, const float* w, uint16_t* dd1, float* dw,
                             float* db, double* loss, size_t nvox, int C, hipStream_t s);
@@ -113,7 +117,7 @@ struct pmc_unet {
     // activations
     Act x, e1, p1, e2, p2, e3, p3, e4, d3, d2, d1;
     // gradients
-    Act g_d1, g_c1, g_d2, g_e1s, g_c2, g_d3, g_e2s, g_c3, g_e4, g_e3s, g_p3, g_e3, g_p2, g_e2, g_p1, g_e1;
+    Act g_d1, g_d2, g_e1s, g_d3, g_e2s, g_e4, g_e3s, g_p3, g_e3, g_p2, g_e2, g_p1, g_e1;
     float* out = nullptr;     // FP32 network output (denoised dose)
     float* scale = nullptr;
     unsigned int* region = nullptr;   // voxels in the dose region (loss normalisation)
@@ -157,11 +161,15 @@ hipError_t act(pmc_unet* u, Act& a, int level, int c)
     return ualloc(u, &a.p, a.nvox * c);
 }
 
-// runs one convolution of the network: forward
-hipError_t conv_fwd(pmc_unet* u, const Conv& c, const Act& in, Act& out, int level, hipStream_t s)
+// an encoder convolution with, unless pooled is NULL, the 2x2x2 average of its
+// output for the next level
+hipError_t enc_fwd(pmc_unet* u, const Conv& c, const Act& in, Act& out, Act* pooled, int level, hipStream_t s)
 {
-    return nn_conv3d_fwd(in.p, u->wbf + c.off_wbf, u->p + c.off_b, out.p, u->N, u->D >> level, u->H >> level,
-                         u->W >> level, c.cin, c.cout, c.kp, 1, s);
+    const int d = u->D >> level, h = u->H >> level, w = u->W >> level;
+    if (!pooled)
+        return nn_conv3d_fwd(in.p, u->wbf + c.off_wbf, u->p + c.off_b, out.p, u->N, d, h, w, c.cin, c.cout, c.kp, 1, s);
+    return nn_conv3d_fwd_pool(in.p, u->wbf + c.off_wbf, u->p + c.off_b, out.p, pooled->p, u->N, d, h, w, c.cin, c.cout,
+                              c.kp, 1, s);
 }
 
 // a decoder convolution whose input is [upsampled coarse, skip], read from
@@ -177,10 +185,10 @@ hipError_t dec_fwd(pmc_unet* u, const Conv& c, const Act& coarse, const Act& ski
 
 // backward of one conv + ReLU layer: dy (gradient at the ReLU output, made
 // the pre-activation gradient in place), its input [upsampled coarse, x]
-// (coarse NULL: x alone) and output y; writes the input gradient dx unless dx
-// is NULL
+// (coarse NULL: x alone) and output y; writes the input's gradients dx and,
+// with a coarse input, dcoarse unless dx is NULL
 hipError_t conv_bwd(pmc_unet* u, const Conv& c, const Act& x, const Act* coarse, const Act& y, Act& dy, Act* dx,
-                    int level, hipStream_t s)
+                    Act* dcoarse, int level, hipStream_t s)
 {
     const int d = u->D >> level, h = u->H >> level, w = u->W >> level;
     hipError_t e;
@@ -191,12 +199,15 @@ hipError_t conv_bwd(pmc_unet* u, const Conv& c, const Act& x, const Act* coarse,
     if (!dx) return hipSuccess;
     if ((e = nn_flip_weights(u->wbf + c.off_wbf, u->wf + c.off_wf, c.cin, c.cout, c.kp, c.kpf, s)) != hipSuccess)
         return e;
+    if (coarse)
+        return nn_conv3d_fwd_split(dy.p, u->wf + c.off_wf, dcoarse->p, coarse->c, dx->p, u->N, d, h, w, c.cout, c.cin,
+                                   c.kpf, s);
     return nn_conv3d_fwd(dy.p, u->wf + c.off_wf, nullptr, dx->p, u->N, d, h, w, c.cout, c.cin, c.kpf, 0, s);
 }
 
-// out: the head's output; the caller's grid is d x h x w inside the
-// network's (the whole of it in training)
-hipError_t forward(pmc_unet* u, const float* dose, const float* rho, float* out, int d, int h, int w,
+// out: the head's output; the caller's grid is d x h x w inside the network's
+// (the whole of it in training); keep_d1: the backward pass follows
+hipError_t forward(pmc_unet* u, const float* dose, const float* rho, float* out, int d, int h, int w, bool keep_d1,
                    hipStream_t s)
 {
     hipError_t e;
@@ -204,18 +215,16 @@ hipError_t forward(pmc_unet* u, const float* dose, const float* rho, float* out,
     if ((e = hipMemsetAsync(u->scale, 0, sizeof(float), s)) != hipSuccess) return e;
     if ((e = nn_make_input(dose, rho, u->scale, u->x.p, nv, u->N, u->D, u->H, u->W, d, h, w, s)) != hipSuccess)
         return e;
-    const int N = u->N, D = u->D, H = u->H, W = u->W;
-    if ((e = conv_fwd(u, u->conv[0], u->x, u->e1, 0, s)) != hipSuccess) return e;
-    if ((e = nn_pool_fwd(u->e1.p, u->p1.p, N, D, H, W, 16, s)) != hipSuccess) return e;
-    if ((e = conv_fwd(u, u->conv[1], u->p1, u->e2, 1, s)) != hipSuccess) return e;
-    if ((e = nn_pool_fwd(u->e2.p, u->p2.p, N, D >> 1, H >> 1, W >> 1, 32, s)) != hipSuccess) return e;
-    if ((e = conv_fwd(u, u->conv[2], u->p2, u->e3, 2, s)) != hipSuccess) return e;
-    if ((e = nn_pool_fwd(u->e3.p, u->p3.p, N, D >> 2, H >> 2, W >> 2, 64, s)) != hipSuccess) return e;
-    if ((e = conv_fwd(u, u->conv[3], u->p3, u->e4, 3, s)) != hipSuccess) return e;
+    if ((e = enc_fwd(u, u->conv[0], u->x, u->e1, &u->p1, 0, s)) != hipSuccess) return e;
+    if ((e = enc_fwd(u, u->conv[1], u->p1, u->e2, &u->p2, 1, s)) != hipSuccess) return e;
+    if ((e = enc_fwd(u, u->conv[2], u->p2, u->e3, &u->p3, 2, s)) != hipSuccess) return e;
+    if ((e = enc_fwd(u, u->conv[3], u->p3, u->e4, nullptr, 3, s)) != hipSuccess) return e;
     if ((e = dec_fwd(u, u->conv[4], u->e4, u->e3, u->d3, 2, s)) != hipSuccess) return e;
     if ((e = dec_fwd(u, u->conv[5], u->d3, u->e2, u->d2, 1, s)) != hipSuccess) return e;
-    if ((e = dec_fwd(u, u->conv[6], u->d2, u->e1, u->d1, 0, s)) != hipSuccess) return e;
-    return nn_head_fwd(u->d1.p, u->p + u->off_hw, u->p + u->off_hb, dose, u->scale, out, nv, 16, D, H, W, d, h, w, s);
+    const Conv& c = u->conv[6];
+    return nn_conv3d_fwd_cat_head(u->e1.p, u->d2.p, u->d2.c, u->wbf + c.off_wbf, u->p + c.off_b, keep_d1 ? u->d1.p : nullptr,
+                                  u->p + u->off_hw, u->p + u->off_hb, dose, u->scale, out, u->N, u->D, u->H, u->W, c.cin,
+                                  c.kp, d, h, w, s);
 }
 
 hipError_t backward(pmc_unet* u, const float* dose, const float* target, hipStream_t s)
@@ -228,28 +237,23 @@ hipError_t backward(pmc_unet* u, const float* dose, const float* target, hipStre
     if ((e = nn_loss_head_bwd(u->out, target, dose, u->scale, u->region, u->d1.p, u->p + u->off_hw, u->g_d1.p,
                               u->g + u->off_hw, u->g + u->off_hb, u->loss, nv, 16, s)) != hipSuccess)
         return e;
-    // dec1: [d2, e1] (48) -> d1 (16)
-    if ((e = conv_bwd(u, u->conv[6], u->e1, &u->d2, u->d1, u->g_d1, &u->g_c1, 0, s)) != hipSuccess) return e;
-    if ((e = nn_up_concat_bwd(u->g_c1.p, u->g_d2.p, u->g_e1s.p, N, D, H, W, 32, 16, s)) != hipSuccess) return e;
-    // dec2: [d3, e2] (96) -> d2 (32)
-    if ((e = conv_bwd(u, u->conv[5], u->e2, &u->d3, u->d2, u->g_d2, &u->g_c2, 1, s)) != hipSuccess) return e;
-    if ((e = nn_up_concat_bwd(u->g_c2.p, u->g_d3.p, u->g_e2s.p, N, D >> 1, H >> 1, W >> 1, 64, 32, s)) != hipSuccess)
-        return e;
-    // dec3: [e4, e3] (192) -> d3 (64)
-    if ((e = conv_bwd(u, u->conv[4], u->e3, &u->e4, u->d3, u->g_d3, &u->g_c3, 2, s)) != hipSuccess) return e;
-    if ((e = nn_up_concat_bwd(u->g_c3.p, u->g_e4.p, u->g_e3s.p, N, D >> 2, H >> 2, W >> 2, 128, 64, s)) != hipSuccess)
-        return e;
+    // dec1: [d2 (32), e1 (16)] -> d1 (16)
+    if ((e = conv_bwd(u, u->conv[6], u->e1, &u->d2, u->d1, u->g_d1, &u->g_e1s, &u->g_d2, 0, s)) != hipSuccess) return e;
+    // dec2: [d3 (64), e2 (32)] -> d2 (32)
+    if ((e = conv_bwd(u, u->conv[5], u->e2, &u->d3, u->d2, u->g_d2, &u->g_e2s, &u->g_d3, 1, s)) != hipSuccess) return e;
+    // dec3: [e4 (128), e3 (64)] -> d3 (64)
+    if ((e = conv_bwd(u, u->conv[4], u->e3, &u->e4, u->d3, u->g_d3, &u->g_e3s, &u->g_e4, 2, s)) != hipSuccess) return e;
     // enc4: p3 (64) -> e4 (128)
-    if ((e = conv_bwd(u, u->conv[3], u->p3, nullptr, u->e4, u->g_e4, &u->g_p3, 3, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, u->conv[3], u->p3, nullptr, u->e4, u->g_e4, &u->g_p3, nullptr, 3, s)) != hipSuccess) return e;
     if ((e = nn_pool_bwd(u->g_p3.p, u->g_e3s.p, u->g_e3.p, N, D >> 2, H >> 2, W >> 2, 64, s)) != hipSuccess) return e;
     // enc3: p2 (32) -> e3 (64)
-    if ((e = conv_bwd(u, u->conv[2], u->p2, nullptr, u->e3, u->g_e3, &u->g_p2, 2, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, u->conv[2], u->p2, nullptr, u->e3, u->g_e3, &u->g_p2, nullptr, 2, s)) != hipSuccess) return e;
     if ((e = nn_pool_bwd(u->g_p2.p, u->g_e2s.p, u->g_e2.p, N, D >> 1, H >> 1, W >> 1, 32, s)) != hipSuccess) return e;
     // enc2: p1 (16) -> e2 (32)
-    if ((e = conv_bwd(u, u->conv[1], u->p1, nullptr, u->e2, u->g_e2, &u->g_p1, 1, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, u->conv[1], u->p1, nullptr, u->e2, u->g_e2, &u->g_p1, nullptr, 1, s)) != hipSuccess) return e;
     if ((e = nn_pool_bwd(u->g_p1.p, u->g_e1s.p, u->g_e1.p, N, D, H, W, 16, s)) != hipSuccess) return e;
     // enc1: x (8) -> e1 (16), no input gradient
-    return conv_bwd(u, u->conv[0], u->x, nullptr, u->e1, u->g_e1, nullptr, 0, s);
+    return conv_bwd(u, u->conv[0], u->x, nullptr, u->e1, u->g_e1, nullptr, nullptr, 0, s);
 }
 
 hipError_t refresh_bf16(pmc_unet* u, hipStream_t s)
@@ -327,13 +331,10 @@ pmc_status pmc_unet_create(pmc_unet** out, int device, int n, int d, int h, int 
     A(act(u, u->d2, 1, 32));
     A(act(u, u->d1, 0, 16));
     A(act(u, u->g_d1, 0, 16));
-    A(act(u, u->g_c1, 0, 48));
     A(act(u, u->g_d2, 1, 32));
     A(act(u, u->g_e1s, 0, 16));
-    A(act(u, u->g_c2, 1, 96));
     A(act(u, u->g_d3, 2, 64));
     A(act(u, u->g_e2s, 1, 32));
-    A(act(u, u->g_c3, 2, 192));
     A(act(u, u->g_e4, 3, 128));
     A(act(u, u->g_e3s, 2, 64));
     A(act(u, u->g_p3, 3, 64));
@@ -441,7 +442,7 @@ pmc_status pmc_unet_forward_region(pmc_unet* u, const float* dose, const float* 
         return ufail(u, PMC_ERR_ARG, "the grid must fit inside the network's shape");
     UCHK(hipSetDevice(u->device), "set device");
     hipStream_t s = (hipStream_t)stream;
-    UCHK(forward(u, dose, rho, d_out, d, h, w, s), "forward");
+    UCHK(forward(u, dose, rho, d_out, d, h, w, false, s), "forward");
     return PMC_OK;
 }
 
@@ -452,7 +453,7 @@ pmc_status pmc_unet_backward(pmc_unet* u, const float* dose, const float* rho, c
     if (!dose || !rho || !target) return ufail(u, PMC_ERR_ARG, "NULL tensor");
     UCHK(hipSetDevice(u->device), "set device");
     hipStream_t s = (hipStream_t)stream;
-    UCHK(forward(u, dose, rho, u->out, u->D, u->H, u->W, s), "forward");
+    UCHK(forward(u, dose, rho, u->out, u->D, u->H, u->W, true, s), "forward");
     UCHK(backward(u, dose, target, s), "backward");
     if (loss_out) {
         UCHK(hipMemcpyAsync(loss_out, u->loss, 8, hipMemcpyDeviceToHost, s), "read loss");

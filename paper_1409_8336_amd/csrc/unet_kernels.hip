@@ -18,9 +18,10 @@ namespace pmc {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-// an 8-byte store that may sit at any 2-byte boundary (a caller's tensor)
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// an 8-byte store that may sit at any 2-byte boundary (a caller's tensor)
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 #define GLOBAL __attribute__((address_space(1)))
 #define LOCAL __attribute__((address_space(3)))
@@ -39,6 +40,25 @@ DEV uint16_t f2bf(float f)
     const uint32_t r = u + 0x7FFFu + ((u >> 16) & 1u);
     return (uint16_t)(r >> 16);
 }
+
+// Grids: the network's [n][D][H][W] and the caller's compact [n][d][h][w]
+// (d <= D, h <= H, w <= W) placed at its origin; outside it the input is
+// zero (no dose, density 0) and no output is written.
+struct Region {
+    int D, H, W, d, h, w;
+    // compact index of network voxel v, or -1 outside the caller's grid
+    DEV long long compact(size_t v) const
+    {
+        const int x = (int)(v % W);
+        size_t r = v / W;
+        const int y = (int)(r % H);
+        r /= H;
+        const int z = (int)(r % D);
+        const size_t n = r / D;
+        if (x >= w || y >= h || z >= d) return -1;
+        return (long long)(((n * d + z) * h + y) * w + x);
+    }
+};
 
 // ------------------------------------------------------------ convolution
 
@@ -78,11 +98,34 @@ struct FwdTile {
     static constexpr int NENT = 64 * (HBLK + WBLK);
 };
 
-template <int NB, int QC, bool kPipe, int kMinWaves>
+// What a convolution's epilogue does beside or instead of storing its output:
+// what would otherwise read the whole output back.
+//   kPool: also stores the 2x2x2 average of the stored (BF16) output;
+//   kSplit: the output is the gradient of a concatenation [upsampled coarse
+//     (Cc channels), skip]: channels below Cc are summed over the 2x2x2
+//     children and stored as the coarse gradient, the others go to the skip's;
+//   kHead (16 output channels): the network's head, out = dose + scale *
+//     (w . d1 + b) on the caller's grid, d1 being the rounded output, which is
+//     stored only if asked for.
+// The sums run in the order in which a kernel of its own would take them.  At
+// 160 x 128 x 128 (us, convolutions and kernels of their own against this): the
+// three encoder layers with their pooling 96 and 78, the last decoder layer
+// with the head 142 and 128, the three decoder gradients 386 and 248.
+constexpr int kPlain = 0, kPool = 1, kSplit = 2, kHead = 3;
+struct FwdAfter {
+    uint16_t* half;   // kPool: pooled output; kSplit: coarse gradient
+    uint16_t* rest;   // kSplit: skip gradient
+    int Cc;           // kSplit: channels of the coarse gradient (a multiple of a workgroup's)
+    const float *w, *b, *dose, *scale;   // kHead
+    float* res;
+    Region rg;
+};
+
+template <int NB, int QC, bool kPipe, int kMinWaves, int kAfter>
 __global__ void __launch_bounds__(512, kMinWaves)
     conv3d_fwd_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ coarse, int Cc,
                       const uint16_t* __restrict__ wt, const float* __restrict__ bias, uint16_t* __restrict__ out,
-                      int N, int D, int H, int W, int Cin, int Cout, int Kp, int relu)
+                      int N, int D, int H, int W, int Cin, int Cout, int Kp, int relu, FwdAfter after)
 {
     using T = FwdTile<NB, QC>;
     constexpr int WAVES = T::WAVES;
@@ -221,28 +264,109 @@ __global__ void __launch_bounds__(512, kMinWaves)
     }
     // lane (m, g) holds output channels co0 + 16 j + 4 g .. + 3 of voxel m
     const int x = x0 + m, z = z0 + zw;
-    if (x >= W || z >= D) return;
+    const bool in_xz = x < W && z < D;
+    // the block's channels go to a coarse gradient (kSplit): nothing to store per voxel
+    const bool to_half = kAfter == kSplit && co0 < after.Cc;
+    u32x2 o[4][NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int co = co0 + 16 * j + 4 * g;
-        if (co >= Cout) continue;   // (Cout is a multiple of 8)
         float bv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (bias)
+        if (bias && co < Cout)   // (Cout is a multiple of 8)
 #pragma unroll
             for (int i = 0; i < 4; ++i) bv[i] = bias[co + i];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int y = y0 + yw + t;
-            if (y >= H) continue;
-            uint32_t o[4];
+            uint32_t q[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float v = acc[t][j][i] + bv[i];
                 if (relu) v = v > 0.f ? v : kLeak * v;
-                o[i] = f2bf(v);
+                q[i] = f2bf(v);
             }
-            const size_t at = ((((size_t)n * D + z) * H + y) * W + x) * Cout + co;
-            *reinterpret_cast<u32x2_any*>(out + at) = (u32x2_any){o[0] | (o[1] << 16), o[2] | (o[3] << 16)};
+            o[t][j] = (u32x2){q[0] | (q[1] << 16), q[2] | (q[3] << 16)};
+            if (!in_xz || y >= H || co >= Cout) continue;
+            const size_t vox = (((size_t)n * D + z) * H + y) * W + x;
+            if constexpr (kAfter == kSplit) {
+                if (!to_half)
+                    *reinterpret_cast<u32x2_any*>(after.rest + vox * (Cout - after.Cc) + (co - after.Cc)) = o[t][j];
+            } else if (kAfter != kHead || out) {
+                *reinterpret_cast<u32x2_any*>(out + vox * Cout + co) = o[t][j];
+            }
+        }
+    }
+    if constexpr (kAfter == kPool || kAfter == kSplit) {
+        if (kAfter == kSplit && !to_half) return;   // (the whole workgroup)
+        // sums over 2x2x2 voxels in the order z, y, x: the wave of the even
+        // plane leaves its four-voxel sums in LDS, that of the odd plane adds
+        // its own; even lanes hold the x pairs
+        f32x4* const xch = reinterpret_cast<f32x4*>(buf0);
+        static_assert(8 * NB * 64 <= T::NENT, "the four-voxel sums fit a stage's buffer");
+        auto quad = [&](int tp, int j, f32x4 s) {
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy) {
+                const u32x2 own = o[2 * tp + dy][j];
+                const u32x2 next = {(uint32_t)__shfl_xor((int)own.x, 1), (uint32_t)__shfl_xor((int)own.y, 1)};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    s[i] += __uint_as_float(i & 1 ? own[i >> 1] & 0xFFFF0000u : own[i >> 1] << 16);
+                    s[i] += __uint_as_float(i & 1 ? next[i >> 1] & 0xFFFF0000u : next[i >> 1] << 16);
+                }
+            }
+            return s;
+        };
+        auto slot = [&](int tp, int j) { return ((((wave >> 2) * 2 + (wave & 1)) * 2 + tp) * NB + j) * 64 + lane; };
+        __syncthreads();   // the stage's buffer is no longer read
+        if (!(zw & 1)) {
+#pragma unroll
+            for (int tp = 0; tp < 2; ++tp)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) xch[slot(tp, j)] = quad(tp, j, (f32x4){0.f, 0.f, 0.f, 0.f});
+        }
+        __syncthreads();
+        if (zw & 1) {
+            const int Ch = kAfter == kSplit ? after.Cc : Cout;
+#pragma unroll
+            for (int tp = 0; tp < 2; ++tp)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const f32x4 s = quad(tp, j, xch[slot(tp, j)]);
+                    const float k = kAfter == kPool ? 0.125f : 1.f;
+                    const int co = co0 + 16 * j + 4 * g, y = y0 + yw + 2 * tp;
+                    if (!in_xz || (m & 1) || y >= H || co >= Ch) continue;
+                    const size_t vox = (((size_t)n * (D >> 1) + (z >> 1)) * Hc + (y >> 1)) * Wc + (x >> 1);
+                    *reinterpret_cast<u32x2*>(after.half + vox * Ch + co) =
+                        (u32x2){(uint32_t)f2bf(k * s[0]) | ((uint32_t)f2bf(k * s[1]) << 16),
+                                (uint32_t)f2bf(k * s[2]) | ((uint32_t)f2bf(k * s[3]) << 16)};
+                }
+        }
+    }
+    if constexpr (kAfter == kHead) {
+        // the sum over the 16 channels passes through the four lane groups in
+        // turn; group g then writes row g
+        float hw[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hw[i] = after.w[4 * g + i];
+        const float sc = fmaxf(after.scale[0], 1e-30f);
+        float s[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            s[t] = after.b[0];
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg) {
+                float v = s[t];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    v += hw[i] * __uint_as_float(i & 1 ? o[t][0][i >> 1] & 0xFFFF0000u : o[t][0][i >> 1] << 16);
+                s[t] = __shfl(v, 16 * gg + m);
+            }
+        }
+        const float sg = g == 0 ? s[0] : (g == 1 ? s[1] : (g == 2 ? s[2] : s[3]));
+        const int y = y0 + yw + g;
+        if (x < after.rg.w && y < after.rg.h && z < after.rg.d) {
+            const size_t vc = (((size_t)n * after.rg.d + z) * after.rg.h + y) * after.rg.w + x;
+            after.res[vc] = after.dose[vc] + sc * sg;
         }
     }
 }
@@ -525,39 +649,6 @@ __global__ void __launch_bounds__(256) relu_bias_bwd_kernel(uint16_t* __restrict
     }
 }
 
-// 2x2x2 average pooling, channels-last
-__global__ void pool_fwd_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out, int N, int D,
-                                int H, int W, int C)
-{
-    // 8 channels (16 bytes) per lane; C a multiple of 8; the eight children
-    // summed in the same order as element by element
-    const int Do = D / 2, Ho = H / 2, Wo = W / 2, C8 = C >> 3;
-    const size_t total = (size_t)N * Do * Ho * Wo * C8;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int c8 = (int)(i % C8);
-        size_t r = i / C8;
-        const int x = (int)(r % Wo); r /= Wo;
-        const int y = (int)(r % Ho); r /= Ho;
-        const int z = (int)(r % Do);
-        const int n = (int)(r / Do);
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int dz = 0; dz < 2; ++dz)
-            for (int dy = 0; dy < 2; ++dy)
-                for (int dx = 0; dx < 2; ++dx) {
-                    const uint4 v = *reinterpret_cast<const uint4*>(
-                        in + ((((size_t)n * D + 2 * z + dz) * H + 2 * y + dy) * W + 2 * x + dx) * C + 8 * c8);
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) acc[k] += bf2f((uint16_t)(w[k >> 1] >> (16 * (k & 1))));
-                }
-        uint32_t o[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            o[q] = (uint32_t)f2bf(0.125f * acc[2 * q]) | ((uint32_t)f2bf(0.125f * acc[2 * q + 1]) << 16);
-        *reinterpret_cast<uint4*>(out + 8 * i) = make_uint4(o[0], o[1], o[2], o[3]);
-    }
-}
-
 // d_in[v][c] = add[v][c] + d_out[parent(v)][c] / 8   (add may be NULL)
 __global__ void pool_bwd_kernel(const uint16_t* __restrict__ dout, const uint16_t* __restrict__ add,
                                 uint16_t* __restrict__ din, int N, int D, int H, int W, int C)
@@ -593,73 +684,8 @@ __global__ void pool_bwd_kernel(const uint16_t* __restrict__ dout, const uint16_
     }
 }
 
-// backward of the nearest 2x upsampling and concatenation: d_coarse[p][c] = sum over the 8 children of dcat[v][c];
-// d_skip[v][c] = dcat[v][Cc + c]
-__global__ void up_concat_bwd_coarse_kernel(const uint16_t* __restrict__ dcat, uint16_t* __restrict__ dcoarse,
-                                            int N, int D, int H, int W, int Cc, int Cs)
-{
-    // 8 channels (16 bytes) per lane; Cc and Cs multiples of 8
-    const int C = Cc + Cs, Cc8 = Cc >> 3;
-    const int Do = D / 2, Ho = H / 2, Wo = W / 2;
-    const size_t total = (size_t)N * Do * Ho * Wo * Cc8;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int c8 = (int)(i % Cc8);
-        size_t r = i / Cc8;
-        const int x = (int)(r % Wo); r /= Wo;
-        const int y = (int)(r % Ho); r /= Ho;
-        const int z = (int)(r % Do);
-        const int n = (int)(r / Do);
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int dz = 0; dz < 2; ++dz)
-            for (int dy = 0; dy < 2; ++dy)
-                for (int dx = 0; dx < 2; ++dx) {
-                    const uint4 v = *reinterpret_cast<const uint4*>(
-                        dcat + ((((size_t)n * D + 2 * z + dz) * H + 2 * y + dy) * W + 2 * x + dx) * C + 8 * c8);
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) acc[k] += bf2f((uint16_t)(w[k >> 1] >> (16 * (k & 1))));
-                }
-        uint32_t o[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = (uint32_t)f2bf(acc[2 * q]) | ((uint32_t)f2bf(acc[2 * q + 1]) << 16);
-        *reinterpret_cast<uint4*>(dcoarse + 8 * i) = make_uint4(o[0], o[1], o[2], o[3]);
-    }
-}
-
-__global__ void up_concat_bwd_skip_kernel(const uint16_t* __restrict__ dcat, uint16_t* __restrict__ dskip,
-                                          size_t nvox, int Cc, int Cs)
-{
-    const int C8 = (Cc + Cs) >> 3, Cc8 = Cc >> 3, Cs8 = Cs >> 3;
-    const size_t total = nvox * Cs8;
-    const uint4* src = reinterpret_cast<const uint4*>(dcat);
-    uint4* dst = reinterpret_cast<uint4*>(dskip);
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const size_t v = i / Cs8;
-        const int c = (int)(i % Cs8);
-        dst[i] = src[v * C8 + Cc8 + c];
-    }
-}
-
-// network input: x[v] = (dose[v] * inv_scale, density[v] * 0.5, 0 x 6)
-// Grids: the network's [n][D][H][W] and the caller's compact [n][d][h][w]
-// (d <= D, h <= H, w <= W) placed at its origin; outside it the input is
-// zero (no dose, density 0) and no output is written.
-struct Region {
-    int D, H, W, d, h, w;
-    // compact index of network voxel v, or -1 outside the caller's grid
-    DEV long long compact(size_t v) const
-    {
-        const int x = (int)(v % W);
-        size_t r = v / W;
-        const int y = (int)(r % H);
-        r /= H;
-        const int z = (int)(r % D);
-        const size_t n = r / D;
-        if (x >= w || y >= h || z >= d) return -1;
-        return (long long)(((n * d + z) * h + y) * w + x);
-    }
-};
-
+// network input: x[v] = (dose[v] * inv_scale, density[v] * 0.5, 0 x 6), zero
+// outside the caller's grid
 __global__ void make_input_kernel(const float* __restrict__ dose, const float* __restrict__ rho,
                                   const float* __restrict__ scale, uint16_t* __restrict__ x, size_t nvox, Region rg)
 {
@@ -706,34 +732,6 @@ __global__ void __launch_bounds__(256) region_count_kernel(const float* __restri
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
     if (threadIdx.x == 0) atomicAdd(region, part[0] + part[1] + part[2] + part[3]);
-}
-
-// head: out[v] = scale * (dose[v]/scale + sum_c w[c] d1[v][c] + b)  (1x1x1, 16 -> 1, residual)
-__global__ void head_fwd_kernel(const uint16_t* __restrict__ d1, const float* __restrict__ w,
-                                const float* __restrict__ b, const float* __restrict__ dose,
-                                const float* __restrict__ scale, float* __restrict__ out, size_t nvox, int C,
-                                Region rg)
-{
-    const float sc = fmaxf(scale[0], 1e-30f);
-    for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < nvox; v += (size_t)gridDim.x * blockDim.x) {
-        const long long vc = rg.compact(v);
-        if (vc < 0) continue;
-        float s = b[0];
-        if (C == 16) {
-            // the voxel's 32-byte row in two 16-byte loads (same sum order)
-            const uint4* r = reinterpret_cast<const uint4*>(d1 + v * 16);
-            const uint4 q0 = r[0], q1 = r[1];
-            const uint32_t u[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                s += w[2 * k] * __uint_as_float(u[k] << 16);
-                s += w[2 * k + 1] * __uint_as_float(u[k] & 0xFFFF0000u);
-            }
-        } else {
-            for (int c = 0; c < C; ++c) s += w[c] * bf2f(d1[v * C + c]);
-        }
-        out[vc] = dose[vc] + sc * s;
-    }
 }
 
 // Squared error in normalised units over the dose region,
@@ -870,25 +868,33 @@ static unsigned grid_for(size_t n, unsigned block = 256, unsigned cap = 65536)
     return (unsigned)g;
 }
 
-template <int NB, int QC, bool kPipe, int kMinWaves>
-static hipError_t launch_fwd(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* wt, const float* bias,
-                             uint16_t* out, int N, int D, int H, int W, int Cin, int Cout, int Kp, int relu,
-                             hipStream_t s)
+struct FwdArgs {
+    const uint16_t *in, *coarse;
+    int Cc;
+    const uint16_t* wt;
+    const float* bias;
+    uint16_t* out;
+    int N, D, H, W, Cin, Cout, Kp, relu;
+};
+
+template <int NB, int QC, bool kPipe, int kMinWaves, int kAfter>
+static hipError_t launch_fwd(const FwdArgs& a, const FwdAfter& after, hipStream_t s)
 {
     using T = FwdTile<NB, QC>;
-    const int cgroups = (Cout + 16 * NB - 1) / (16 * NB);
-    dim3 grid((W + T::TX - 1) / T::TX, ((H + T::TY - 1) / T::TY) * cgroups, N * ((D + T::TZ - 1) / T::TZ));
-    hipLaunchKernelGGL((conv3d_fwd_kernel<NB, QC, kPipe, kMinWaves>), grid, dim3(64 * T::WAVES), 0, s, in, coarse, Cc,
-                       wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu);
+    const int cgroups = (a.Cout + 16 * NB - 1) / (16 * NB);
+    dim3 grid((a.W + T::TX - 1) / T::TX, ((a.H + T::TY - 1) / T::TY) * cgroups, a.N * ((a.D + T::TZ - 1) / T::TZ));
+    hipLaunchKernelGGL((conv3d_fwd_kernel<NB, QC, kPipe, kMinWaves, kAfter>), grid, dim3(64 * T::WAVES), 0, s, a.in,
+                       a.coarse, a.Cc, a.wt, a.bias, a.out, a.N, a.D, a.H, a.W, a.Cin, a.Cout, a.Kp, a.relu, after);
     return hipGetLastError();
 }
 
-hipError_t nn_conv3d_fwd_cat(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* wt,
-                             const float* bias, uint16_t* out, int N, int D, int H, int W, int Cin, int Cout,
-                             int Kp, int relu, hipStream_t s)
+template <int kAfter>
+static hipError_t conv3d_fwd(const FwdArgs& a, const FwdAfter& after, hipStream_t s)
 {
-    if (Cin % 8 || Cin < 8 || Kp < 27 * Cin || Cc % 8 || Cc < 0 || Cc >= Cin || (Cc && !coarse) ||
-        (Cc && (D % 2 || H % 2 || W % 2)))
+    const int N = a.N, D = a.D, H = a.H, W = a.W, Cin = a.Cin, Cout = a.Cout, Kp = a.Kp, Cc = a.Cc;
+    if (Cin % 8 || Cin < 8 || Kp < 27 * Cin || Cc % 8 || Cc < 0 || Cc >= Cin || (Cc && !a.coarse) ||
+        ((Cc || kAfter == kPool || kAfter == kSplit) && (D % 2 || H % 2 || W % 2)) || (kAfter == kHead && Cout != 16) ||
+        (kAfter == kSplit && (after.Cc % 32 || after.Cc >= Cout)))
         return hipErrorInvalidValue;
     // the kernel keeps element offsets in 32 bits
     if ((size_t)N * D * H * W * (size_t)Cin >= (size_t)0x7FFFFFFF || (size_t)Cout * Kp >= (size_t)0x7FFFFFFF)
@@ -909,19 +915,69 @@ hipError_t nn_conv3d_fwd_cat(const uint16_t* in, const uint16_t* coarse, int Cc,
     //   63 against 72 with 16; 48 -> 32 on 2 x 41 x 53 x 75: 45 and 53).
     const size_t tiles = (size_t)N * ((D + 3) / 4) * ((H + 7) / 8) * ((W + 15) / 16);
     const int n16 = (Cout + 15) / 16;
-#define PMC_FWD(...) launch_fwd<__VA_ARGS__>(in, coarse, Cc, wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu, s)
-    // (a stage of two chunks has one source and never runs past the last channel)
-    if (Cin <= 24 || Cin % 16 || Cc % 16) return PMC_FWD(1, 1, false, 8);
-    if (tiles * n16 <= 256) return PMC_FWD(1, 2, true, 2);
-    if (Cout <= 16) return PMC_FWD(1, 2, false, 6);
-    return PMC_FWD(2, 2, false, 4);
-#undef PMC_FWD
+    // (a stage of two chunks has one source and never runs past the last
+    // channel; the network's head has 48 input channels, its other epilogues
+    // 32 or more output channels where there are more than 24 input channels)
+    if (Cin <= 24 || Cin % 16 || Cc % 16) {
+        if constexpr (kAfter == kHead) return hipErrorInvalidValue;
+        else return launch_fwd<1, 1, false, 8, kAfter>(a, after, s);
+    }
+    if (tiles * n16 <= 256) return launch_fwd<1, 2, true, 2, kAfter>(a, after, s);
+    if constexpr (kAfter == kHead) {
+        return launch_fwd<1, 2, false, 6, kAfter>(a, after, s);
+    } else {
+        if (kAfter == kPlain && Cout <= 16) return launch_fwd<1, 2, false, 6, kPlain>(a, after, s);
+        return launch_fwd<2, 2, false, 4, kAfter>(a, after, s);
+    }
 }
 
 hipError_t nn_conv3d_fwd(const uint16_t* in, const uint16_t* wt, const float* bias, uint16_t* out, int N,
                          int D, int H, int W, int Cin, int Cout, int Kp, int relu, hipStream_t s)
 {
-    return nn_conv3d_fwd_cat(in, nullptr, 0, wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu, s);
+    return conv3d_fwd<kPlain>({in, nullptr, 0, wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu}, {}, s);
+}
+
+hipError_t nn_conv3d_fwd_cat(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* wt,
+                             const float* bias, uint16_t* out, int N, int D, int H, int W, int Cin, int Cout,
+                             int Kp, int relu, hipStream_t s)
+{
+    return conv3d_fwd<kPlain>({in, coarse, Cc, wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu}, {}, s);
+}
+
+hipError_t nn_conv3d_fwd_pool(const uint16_t* in, const uint16_t* wt, const float* bias, uint16_t* out,
+                              uint16_t* pooled, int N, int D, int H, int W, int Cin, int Cout, int Kp, int relu,
+                              hipStream_t s)
+{
+    FwdAfter after{};
+    after.half = pooled;
+    return conv3d_fwd<kPool>({in, nullptr, 0, wt, bias, out, N, D, H, W, Cin, Cout, Kp, relu}, after, s);
+}
+
+hipError_t nn_conv3d_fwd_split(const uint16_t* in, const uint16_t* wt, uint16_t* dcoarse, int Cc, uint16_t* dskip, int N,
+                               int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s)
+{
+    FwdAfter after{};
+    after.half = dcoarse;
+    after.rest = dskip;
+    after.Cc = Cc;
+    return conv3d_fwd<kSplit>({in, nullptr, 0, wt, nullptr, nullptr, N, D, H, W, Cin, Cout, Kp, 0}, after, s);
+}
+
+// out (the rounded activations the head reads) may be NULL; d x h x wd: the
+// caller's grid inside the network's
+hipError_t nn_conv3d_fwd_cat_head(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* wt,
+                                  const float* bias, uint16_t* out, const float* w, const float* b, const float* dose,
+                                  const float* scale, float* res, int N, int D, int H, int W, int Cin, int Kp, int d,
+                                  int h, int wd, hipStream_t s)
+{
+    FwdAfter after{};
+    after.w = w;
+    after.b = b;
+    after.dose = dose;
+    after.scale = scale;
+    after.res = res;
+    after.rg = Region{D, H, W, d, h, wd};
+    return conv3d_fwd<kHead>({in, coarse, Cc, wt, bias, out, N, D, H, W, Cin, 16, Kp, 1}, after, s);
 }
 
 hipError_t nn_flip_weights(const uint16_t* w, uint16_t* wf, int Cin, int Cout, int Kp, int Kpf, hipStream_t s)
@@ -976,31 +1032,12 @@ hipError_t nn_relu_bias_bwd(uint16_t* dy, const uint16_t* y, float* db, size_t n
     return hipGetLastError();
 }
 
-hipError_t nn_pool_fwd(const uint16_t* in, uint16_t* out, int N, int D, int H, int W, int C, hipStream_t s)
-{
-    if (C % 8) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pool_fwd_kernel, dim3(grid_for((size_t)N * (D / 2) * (H / 2) * (W / 2) * (C / 8))), dim3(256), 0,
-                       s, in, out, N, D, H, W, C);
-    return hipGetLastError();
-}
-
 hipError_t nn_pool_bwd(const uint16_t* dout, const uint16_t* add, uint16_t* din, int N, int D, int H, int W, int C,
                        hipStream_t s)
 {
     if (C % 8) return hipErrorInvalidValue;
     hipLaunchKernelGGL(pool_bwd_kernel, dim3(grid_for((size_t)N * D * H * W * (C / 8))), dim3(256), 0, s, dout, add,
                        din, N, D, H, W, C);
-    return hipGetLastError();
-}
-
-hipError_t nn_up_concat_bwd(const uint16_t* dcat, uint16_t* dcoarse, uint16_t* dskip, int N, int D, int H, int W,
-                            int Cc, int Cs, hipStream_t s)
-{
-    if ((Cc | Cs) & 7) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(up_concat_bwd_coarse_kernel, dim3(grid_for((size_t)N * (D / 2) * (H / 2) * (W / 2) * (Cc / 8))),
-                       dim3(256), 0, s, dcat, dcoarse, N, D, H, W, Cc, Cs);
-    hipLaunchKernelGGL(up_concat_bwd_skip_kernel, dim3(grid_for((size_t)N * D * H * W * Cs / 8)), dim3(256), 0, s, dcat,
-                       dskip, (size_t)N * D * H * W, Cc, Cs);
     return hipGetLastError();
 }
 
@@ -1013,14 +1050,6 @@ hipError_t nn_make_input(const float* dose, const float* rho, float* scale, uint
     const size_t ncomp = (size_t)N * d * h * w;
     hipLaunchKernelGGL(max_kernel, dim3(grid_for(ncomp, 256, 1024)), dim3(256), 0, s, dose, ncomp, scale);
     hipLaunchKernelGGL(make_input_kernel, dim3(grid_for(nvox)), dim3(256), 0, s, dose, rho, scale, x, nvox, rg);
-    return hipGetLastError();
-}
-
-hipError_t nn_head_fwd(const uint16_t* d1, const float* w, const float* b, const float* dose, const float* scale,
-                       float* out, size_t nvox, int C, int D, int H, int W, int d, int h, int wd, hipStream_t s)
-{
-    const Region rg{D, H, W, d, h, wd};
-    hipLaunchKernelGGL(head_fwd_kernel, dim3(grid_for(nvox)), dim3(256), 0, s, d1, w, b, dose, scale, out, nvox, C, rg);
     return hipGetLastError();
 }
 
