@@ -30,22 +30,26 @@ hipError_t nn_conv3d_fwd_cat_head(const uint16_t* in, const uint16_t* coarse, in
                                   const float* bias, uint16_t* out, const float* w, const float* b, const float* dose,
                                   const float* scale, float* res, int N, int D, int H, int W, int Cin, int Kp, int d,
                                   int h, int wd, hipStream_t s);
-hipError_t nn_flip_weights(const uint16_t* w, uint16_t* wf, int Cin, int Cout, int Kp, int Kpf, hipStream_t s);
+struct FlipLayer {
+    const uint16_t* w;
+    uint16_t* wf;
+    int Cin, Cout, Kp, Kpf;
+};
+hipError_t nn_flip_weights(const FlipLayer* layers, int n, hipStream_t s);
 hipError_t nn_conv3d_wgrad_cat(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* dout, float* dw, int N,
                                int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s);
 hipError_t nn_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, int N, int D, int H, int W,
                            int Cin, int Cout, int Kp, hipStream_t s);
-hipError_t nn_relu_bias_bwd(uint16_t* dy, const uint16_t* y, float* db, size_t nvox, int C, hipStream_t s);
-hipError_t nn_pool_bwd(const uint16_t* dout, const uint16_t* add, uint16_t* din, int N, int D, int H, int W, int C,
-                       hipStream_t s);
+hipError_t nn_grad_relu(const uint16_t* src, const uint16_t* dpool, const uint16_t* y, uint16_t* dy, float* db, int N,
+                        int D, int H, int W, int C, hipStream_t s);
 hipError_t nn_make_input(const float* dose, const float* rho, float* scale, uint16_t* x, size_t nvox, int N, int D,
                          int H, int W, int d, int h, int w, hipStream_t s);
 hipError_t nn_loss_head_bwd(const float* out, const float* target, const float* dose, const float* scale,
-                            unsigned int* region, const uint16_t* d1, const float* w, uint16_t* dd1, float* dw,
-                            float* db, double* loss, size_t nvox, int C, hipStream_t s);
+                            unsigned int* region_part, const uint16_t* d1, const float* w, uint16_t* dd1, float* dw,
+                            float* db, float* dbias, double* loss_part, int* n_loss, size_t nvox, hipStream_t s);
 hipError_t nn_adam(float* p, float* g, float* m1, float* m2, uint16_t* p_bf, size_t n, float lr, float b1, float b2,
                    float eps, float c1, float c2, float gs, hipStream_t s);
-hipError_t nn_sqnorm(const float* g, size_t n, double* out, hipStream_t s);
+hipError_t nn_sqnorm(const float* g, size_t n, double* parts, int* n_parts, hipStream_t s);
 hipError_t nn_f32_to_bf16(const float* a, uint16_t* b, size_t n, hipStream_t s);
 hipError_t nn_mfma_probe(int grid, int iters, float* sink, hipStream_t s);
 }  // namespace pmc
@@ -58,6 +62,8 @@ constexpr size_t kFlipScratchElems = size_t(1) << 20;
 static __device__ __align__(256) uint16_t scratch[kFlipScratchElems];
 
 namespace {
+
+constexpr int kParts = 256;   // workgroups of a reduction whose shares are added up later
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
@@ -117,12 +123,14 @@ struct pmc_unet {
     // activations
     Act x, e1, p1, e2, p2, e3, p3, e4, d3, d2, d1;
     // gradients
-    Act g_d1, g_d2, g_e1s, g_d3, g_e2s, g_e4, g_e3s, g_p3, g_e3, g_p2, g_e2, g_p1, g_e1;
+    Act g_d1, g_d2, g_e1s, g_d3, g_e2s, g_e4, g_e3s, g_p3, g_p2, g_p1;
     float* out = nullptr;     // FP32 network output (denoised dose)
     float* scale = nullptr;
-    unsigned int* region = nullptr;   // voxels in the dose region (loss normalisation)
-    double* loss = nullptr;
-    double* gnorm2 = nullptr;   // squared gradient norm (pmc_unet_grad_norm)
+    unsigned int* region = nullptr;   // kParts counts of voxels in the dose region (loss normalisation)
+    // pinned host memory the kernels write to: the workgroups' shares of the
+    // loss (2 kParts) and of the squared gradient norm (kParts)
+    double *loss = nullptr, *gnorm2 = nullptr;
+    int n_loss = 0;                   // shares of the loss the last backward wrote
     std::vector<void*> allocs;
 };
 
@@ -183,26 +191,31 @@ hipError_t dec_fwd(pmc_unet* u, const Conv& c, const Act& coarse, const Act& ski
                              u->H >> level, u->W >> level, c.cin, c.cout, c.kp, 1, s);
 }
 
-// backward of one conv + ReLU layer: dy (gradient at the ReLU output, made
-// the pre-activation gradient in place), its input [upsampled coarse, x]
-// (coarse NULL: x alone) and output y; writes the input's gradients dx and,
-// with a coarse input, dcoarse unless dx is NULL
-hipError_t conv_bwd(pmc_unet* u, const Conv& c, const Act& x, const Act* coarse, const Act& y, Act& dy, Act* dx,
-                    Act* dcoarse, int level, hipStream_t s)
+// backward of one convolution: dy (gradient at its pre-activation), its input
+// [upsampled coarse, x] (coarse NULL: x alone); writes the input's gradients dx
+// and, with a coarse input, dcoarse unless dx is NULL (the weights are flipped)
+hipError_t conv_bwd(pmc_unet* u, const Conv& c, const Act& x, const Act* coarse, const Act& dy, Act* dx, Act* dcoarse,
+                    int level, hipStream_t s)
 {
     const int d = u->D >> level, h = u->H >> level, w = u->W >> level;
     hipError_t e;
-    if ((e = nn_relu_bias_bwd(dy.p, y.p, u->g + c.off_b, dy.nvox, c.cout, s)) != hipSuccess) return e;
     if ((e = nn_conv3d_wgrad_cat(x.p, coarse ? coarse->p : nullptr, coarse ? coarse->c : 0, dy.p, u->g + c.off_w, u->N, d,
                                  h, w, c.cin, c.cout, c.kp, s)) != hipSuccess)
         return e;
     if (!dx) return hipSuccess;
-    if ((e = nn_flip_weights(u->wbf + c.off_wbf, u->wf + c.off_wf, c.cin, c.cout, c.kp, c.kpf, s)) != hipSuccess)
-        return e;
     if (coarse)
         return nn_conv3d_fwd_split(dy.p, u->wf + c.off_wf, dcoarse->p, coarse->c, dx->p, u->N, d, h, w, c.cout, c.cin,
                                    c.kpf, s);
     return nn_conv3d_fwd(dy.p, u->wf + c.off_wf, nullptr, dx->p, u->N, d, h, w, c.cout, c.cin, c.kpf, 0, s);
+}
+
+// gradient at a layer's pre-activation (in place of g, the gradient at its
+// output y, plus that of the pooled output if any) and its bias gradient
+hipError_t relu_bwd(pmc_unet* u, const Conv& c, const Act& src, const Act* dpool, const Act& y, Act& dy, int level,
+                    hipStream_t s)
+{
+    return nn_grad_relu(src.p, dpool ? dpool->p : nullptr, y.p, dy.p, u->g + c.off_b, u->N, u->D >> level, u->H >> level,
+                        u->W >> level, c.cout, s);
 }
 
 // out: the head's output; the caller's grid is d x h x w inside the network's
@@ -230,30 +243,39 @@ hipError_t forward(pmc_unet* u, const float* dose, const float* rho, float* out,
 hipError_t backward(pmc_unet* u, const float* dose, const float* target, hipStream_t s)
 {
     hipError_t e;
-    const int N = u->N, D = u->D, H = u->H, W = u->W;
-    const size_t nv = u->x.nvox;
-    if ((e = hipMemsetAsync(u->loss, 0, sizeof(double), s)) != hipSuccess) return e;
-    if ((e = hipMemsetAsync(u->region, 0, sizeof(unsigned int), s)) != hipSuccess) return e;
+    // every layer but enc1 (whose input needs no gradient)
+    FlipLayer fl[6];
+    for (int i = 1; i < 7; ++i) {
+        const Conv& c = u->conv[i];
+        fl[i - 1] = {u->wbf + c.off_wbf, u->wf + c.off_wf, c.cin, c.cout, c.kp, c.kpf};
+    }
+    if ((e = nn_flip_weights(fl, 6, s)) != hipSuccess) return e;
+    const Conv* cv = u->conv;
+    // loss, head and dec1's ReLU
     if ((e = nn_loss_head_bwd(u->out, target, dose, u->scale, u->region, u->d1.p, u->p + u->off_hw, u->g_d1.p,
-                              u->g + u->off_hw, u->g + u->off_hb, u->loss, nv, 16, s)) != hipSuccess)
+                              u->g + u->off_hw, u->g + u->off_hb, u->g + cv[6].off_b, u->loss, &u->n_loss, u->x.nvox, s)) !=
+        hipSuccess)
         return e;
     // dec1: [d2 (32), e1 (16)] -> d1 (16)
-    if ((e = conv_bwd(u, u->conv[6], u->e1, &u->d2, u->d1, u->g_d1, &u->g_e1s, &u->g_d2, 0, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, cv[6], u->e1, &u->d2, u->g_d1, &u->g_e1s, &u->g_d2, 0, s)) != hipSuccess) return e;
     // dec2: [d3 (64), e2 (32)] -> d2 (32)
-    if ((e = conv_bwd(u, u->conv[5], u->e2, &u->d3, u->d2, u->g_d2, &u->g_e2s, &u->g_d3, 1, s)) != hipSuccess) return e;
+    if ((e = relu_bwd(u, cv[5], u->g_d2, nullptr, u->d2, u->g_d2, 1, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, cv[5], u->e2, &u->d3, u->g_d2, &u->g_e2s, &u->g_d3, 1, s)) != hipSuccess) return e;
     // dec3: [e4 (128), e3 (64)] -> d3 (64)
-    if ((e = conv_bwd(u, u->conv[4], u->e3, &u->e4, u->d3, u->g_d3, &u->g_e3s, &u->g_e4, 2, s)) != hipSuccess) return e;
+    if ((e = relu_bwd(u, cv[4], u->g_d3, nullptr, u->d3, u->g_d3, 2, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, cv[4], u->e3, &u->e4, u->g_d3, &u->g_e3s, &u->g_e4, 2, s)) != hipSuccess) return e;
     // enc4: p3 (64) -> e4 (128)
-    if ((e = conv_bwd(u, u->conv[3], u->p3, nullptr, u->e4, u->g_e4, &u->g_p3, nullptr, 3, s)) != hipSuccess) return e;
-    if ((e = nn_pool_bwd(u->g_p3.p, u->g_e3s.p, u->g_e3.p, N, D >> 2, H >> 2, W >> 2, 64, s)) != hipSuccess) return e;
+    if ((e = relu_bwd(u, cv[3], u->g_e4, nullptr, u->e4, u->g_e4, 3, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, cv[3], u->p3, nullptr, u->g_e4, &u->g_p3, nullptr, 3, s)) != hipSuccess) return e;
     // enc3: p2 (32) -> e3 (64)
-    if ((e = conv_bwd(u, u->conv[2], u->p2, nullptr, u->e3, u->g_e3, &u->g_p2, nullptr, 2, s)) != hipSuccess) return e;
-    if ((e = nn_pool_bwd(u->g_p2.p, u->g_e2s.p, u->g_e2.p, N, D >> 1, H >> 1, W >> 1, 32, s)) != hipSuccess) return e;
+    if ((e = relu_bwd(u, cv[2], u->g_e3s, &u->g_p3, u->e3, u->g_e3s, 2, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, cv[2], u->p2, nullptr, u->g_e3s, &u->g_p2, nullptr, 2, s)) != hipSuccess) return e;
     // enc2: p1 (16) -> e2 (32)
-    if ((e = conv_bwd(u, u->conv[1], u->p1, nullptr, u->e2, u->g_e2, &u->g_p1, nullptr, 1, s)) != hipSuccess) return e;
-    if ((e = nn_pool_bwd(u->g_p1.p, u->g_e1s.p, u->g_e1.p, N, D, H, W, 16, s)) != hipSuccess) return e;
+    if ((e = relu_bwd(u, cv[1], u->g_e2s, &u->g_p2, u->e2, u->g_e2s, 1, s)) != hipSuccess) return e;
+    if ((e = conv_bwd(u, cv[1], u->p1, nullptr, u->g_e2s, &u->g_p1, nullptr, 1, s)) != hipSuccess) return e;
     // enc1: x (8) -> e1 (16), no input gradient
-    return conv_bwd(u, u->conv[0], u->x, nullptr, u->e1, u->g_e1, nullptr, nullptr, 0, s);
+    if ((e = relu_bwd(u, cv[0], u->g_e1s, &u->g_p1, u->e1, u->g_e1s, 0, s)) != hipSuccess) return e;
+    return conv_bwd(u, cv[0], u->x, nullptr, u->g_e1s, nullptr, nullptr, 0, s);
 }
 
 hipError_t refresh_bf16(pmc_unet* u, hipStream_t s)
@@ -338,16 +360,13 @@ pmc_status pmc_unet_create(pmc_unet** out, int device, int n, int d, int h, int 
     A(act(u, u->g_e4, 3, 128));
     A(act(u, u->g_e3s, 2, 64));
     A(act(u, u->g_p3, 3, 64));
-    A(act(u, u->g_e3, 2, 64));
     A(act(u, u->g_p2, 2, 32));
-    A(act(u, u->g_e2, 1, 32));
     A(act(u, u->g_p1, 1, 16));
-    A(act(u, u->g_e1, 0, 16));
     A(ualloc(u, &u->out, u->x.nvox));
     A(ualloc(u, &u->scale, 1));
-    A(ualloc(u, &u->region, 1));
-    A(ualloc(u, &u->loss, 1));
-    A(ualloc(u, &u->gnorm2, 1));
+    A(ualloc(u, &u->region, kParts));
+    A(hipHostMalloc((void**)&u->loss, 3 * kParts * sizeof(double), hipHostMallocDefault));
+    u->gnorm2 = u->loss + 2 * kParts;
     // initial parameters
     std::vector<float> hp(u->n_params, 0.f);
     std::mt19937_64 rng(seed);
@@ -380,6 +399,7 @@ pmc_status pmc_unet_destroy(pmc_unet* u)
     if (!u) return PMC_OK;
     (void)hipSetDevice(u->device);
     for (void* q : u->allocs) (void)hipFree(q);
+    if (u->loss) (void)hipHostFree(u->loss);
     delete u;
     return PMC_OK;
 }
@@ -456,8 +476,10 @@ pmc_status pmc_unet_backward(pmc_unet* u, const float* dose, const float* rho, c
     UCHK(forward(u, dose, rho, u->out, u->D, u->H, u->W, true, s), "forward");
     UCHK(backward(u, dose, target, s), "backward");
     if (loss_out) {
-        UCHK(hipMemcpyAsync(loss_out, u->loss, 8, hipMemcpyDeviceToHost, s), "read loss");
         UCHK(hipStreamSynchronize(s), "backward");
+        double loss = 0.0;
+        for (int i = 0; i < u->n_loss; ++i) loss += u->loss[i];
+        *loss_out = loss;
     }
     return PMC_OK;
 }
@@ -468,11 +490,11 @@ pmc_status pmc_unet_grad_norm(pmc_unet* u, double* norm_out, void* stream)
     if (!norm_out) return ufail(u, PMC_ERR_ARG, "NULL output");
     UCHK(hipSetDevice(u->device), "set device");
     hipStream_t s = (hipStream_t)stream;
-    UCHK(hipMemsetAsync(u->gnorm2, 0, sizeof(double), s), "zero norm");
-    UCHK(nn_sqnorm(u->g, u->n_params, u->gnorm2, s), "gradient norm");
-    double n2 = 0.0;
-    UCHK(hipMemcpyAsync(&n2, u->gnorm2, sizeof(double), hipMemcpyDeviceToHost, s), "read norm");
+    int n_parts = 0;
+    UCHK(nn_sqnorm(u->g, u->n_params, u->gnorm2, &n_parts, s), "gradient norm");
     UCHK(hipStreamSynchronize(s), "gradient norm");
+    double n2 = 0.0;
+    for (int i = 0; i < n_parts; ++i) n2 += u->gnorm2[i];
     *norm_out = std::sqrt(n2);
     return PMC_OK;
 }
@@ -519,7 +541,8 @@ pmc_status pmc_nn_conv3d_backward_data(const uint16_t* dy, const uint16_t* w, ui
     uint16_t* wf = nullptr;
     hipStream_t s = (hipStream_t)stream;
     if (hipMalloc((void**)&wf, (size_t)cin * kpf * 2) != hipSuccess) return PMC_ERR_NOMEM;
-    hipError_t e = nn_flip_weights(w, wf, cin, cout, kp, kpf, s);
+    const FlipLayer fl{w, wf, cin, cout, kp, kpf};
+    hipError_t e = nn_flip_weights(&fl, 1, s);
     if (e == hipSuccess) e = nn_conv3d_fwd(dy, wf, nullptr, dx, n, d, h, wd, cout, cin, kpf, 0, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(wf);
@@ -537,7 +560,8 @@ pmc_status pmc_nn_conv3d_backward_data_noalloc(const uint16_t* dy, const uint16_
     uint16_t* wf = nullptr;
     if (flip_scratch(&wf) != hipSuccess) return PMC_ERR_DEVICE;
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = nn_flip_weights(w, wf, cin, cout, kp, kpf, s);
+    const FlipLayer fl{w, wf, cin, cout, kp, kpf};
+    hipError_t e = nn_flip_weights(&fl, 1, s);
     if (e == hipSuccess) e = nn_conv3d_fwd(dy, wf, nullptr, dx, n, d, h, wd, cout, cin, kpf, 0, s);
     return e == hipSuccess ? PMC_OK : PMC_ERR_DEVICE;
 }

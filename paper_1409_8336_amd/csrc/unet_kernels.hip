@@ -371,19 +371,29 @@ __global__ void __launch_bounds__(512, kMinWaves)
     }
 }
 
-// W'[ci][tap'*Cout + co] = W[co][(26 - tap')*Cin + ci]  (row length Kp')
-__global__ void flip_weights_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict__ wf, int Cin,
-                                    int Cout, int Kp, int Kpf)
+// W'[ci][tap'*Cout + co] = W[co][(26 - tap')*Cin + ci]  (row length Kp'); one
+// launch flips the layers of a whole backward pass (grid y: layer), where a
+// launch of its own took 4.7 us for each of six
+struct FlipLayer {
+    const uint16_t* w;
+    uint16_t* wf;
+    int Cin, Cout, Kp, Kpf;
+};
+struct FlipLayers {
+    FlipLayer l[7];
+};
+__global__ void flip_weights_kernel(FlipLayers f)
 {
-    const int total = Cin * Kpf;
+    const FlipLayer& a = f.l[blockIdx.y];
+    const int total = a.Cin * a.Kpf;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-        const int ci = i / Kpf, kk = i - ci * Kpf;
+        const int ci = i / a.Kpf, kk = i - ci * a.Kpf;
         uint16_t v = 0;
-        if (kk < 27 * Cout) {
-            const int tp = kk / Cout, co = kk - tp * Cout;
-            v = w[(size_t)co * Kp + (26 - tp) * Cin + ci];
+        if (kk < 27 * a.Cout) {
+            const int tp = kk / a.Cout, co = kk - tp * a.Cout;
+            v = a.w[(size_t)co * a.Kp + (26 - tp) * a.Cin + ci];
         }
-        wf[i] = v;
+        a.wf[i] = v;
     }
 }
 
@@ -602,86 +612,89 @@ __global__ void __launch_bounds__(64 * kWgWaves, 3)
 // ------------------------------------------------------------ elementwise
 
 // Leaky-ReLU backward through the stored output (which has the sign of the
-// pre-activation) and the bias gradient in one pass: dy *= (y > 0 ? 1 :
-// kLeak), rounded to BF16 in place, and db[c] += sum_v dy[v][c] of the
-// rounded values.  A lane takes 8 channels (16 bytes) of a voxel; the
-// block's partial sums meet in LDS, one atomic per (block, channel).
-// C is a multiple of 8 with C / 8 dividing 256.
-__global__ void __launch_bounds__(256) relu_bias_bwd_kernel(uint16_t* __restrict__ dy,
-                                                            const uint16_t* __restrict__ y,
-                                                            float* __restrict__ db, size_t nvox, int C)
+// pre-activation): the gradient of one BF16 value, rounded to BF16
+DEV uint32_t relu_grad(uint32_t d, bool positive) { return positive ? d : (uint32_t)f2bf(kLeak * bf2f((uint16_t)d)); }
+
+// the block's per-lane sums of 8 channels (channel group threadIdx.x % G) to
+// the bias gradient, one atomic per block and channel
+DEV void add_bias_grad(const float* acc, int G, int C, float* __restrict__ db)
 {
     __shared__ float part[256 * 8];
-    const int G = C / 8;                       // channel groups per voxel
-    const int g = threadIdx.x % G;
-    const int lanes_per_g = blockDim.x / G;
-    const int sub = threadIdx.x / G;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (size_t v = (size_t)blockIdx.x * lanes_per_g + sub; v < nvox; v += (size_t)gridDim.x * lanes_per_g) {
-        uint4* pd = reinterpret_cast<uint4*>(dy + v * C + 8 * g);
-        const uint4 yv = *reinterpret_cast<const uint4*>(y + v * C + 8 * g);
-        uint4 dv = *pd;
-        uint32_t dw[4] = {dv.x, dv.y, dv.z, dv.w};
-        const uint32_t yw[4] = {yv.x, yv.y, yv.z, yv.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t out = 0;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint16_t d = (uint16_t)(dw[q] >> (16 * h));
-                const uint16_t yy = (uint16_t)(yw[q] >> (16 * h));
-                if (!(bf2f(yy) > 0.f)) d = f2bf(kLeak * bf2f(d));
-                acc[2 * q + h] += bf2f(d);
-                out |= (uint32_t)d << (16 * h);
-            }
-            dw[q] = out;
-        }
-        *pd = make_uint4(dw[0], dw[1], dw[2], dw[3]);
-    }
 #pragma unroll
     for (int k = 0; k < 8; ++k) part[threadIdx.x * 8 + k] = acc[k];
     __syncthreads();
-    if ((int)threadIdx.x < C) {
-        const int cg = threadIdx.x / 8, k = threadIdx.x % 8;
+    const int lanes_per_g = 256 / G;
+    for (int c = threadIdx.x; c < C; c += 256) {
         float t = 0.f;
-        for (int j = 0; j < lanes_per_g; ++j) t += part[(j * G + cg) * 8 + k];
-        atomicAdd(&db[threadIdx.x], t);
+        for (int s = 0; s < lanes_per_g; ++s) t += part[(s * G + c / 8) * 8 + c % 8];
+        atomicAdd(&db[c], t);
     }
 }
 
-// d_in[v][c] = add[v][c] + d_out[parent(v)][c] / 8   (add may be NULL)
-__global__ void pool_bwd_kernel(const uint16_t* __restrict__ dout, const uint16_t* __restrict__ add,
-                                uint16_t* __restrict__ din, int N, int D, int H, int W, int C)
+// Gradient at a layer's pre-activation and its bias gradient in one pass over
+// rows of voxels: dy[v][c] = relu'(y[v][c]) * g with g = src[v][c], or with
+// kPool (the gradient of a pooled output beside that of a skip connection) g =
+// src[v][c] + dpool[parent(v)][c] / 8; both roundings of g and of the product
+// to BF16, db[c] += sum_v dy[v][c] of the rounded values.  src may be dy
+// itself.  A lane takes 8 channels (16 bytes) of a voxel, C / 8 a power of two
+// up to 32.  HBM-bound (160 x 128 x 128 x 16, with pooling: 262 MB, two
+// kernels 78 us, one 47); few workgroups where the tensor is small, as
+// each adds to the same C addresses.
+template <bool kPool>
+__global__ void __launch_bounds__(256) grad_relu_kernel(const uint16_t* src, const uint16_t* __restrict__ dpool,
+                                                        const uint16_t* __restrict__ y, uint16_t* dy,
+                                                        float* __restrict__ db, unsigned rows, int D, int H, int W, int C)
 {
-    // 8 channels (16 bytes) per lane; C a multiple of 8
-    const int C8 = C >> 3;
-    const size_t total = (size_t)N * D * H * W * C8;
-    const int Ho = H / 2, Wo = W / 2, Do = D / 2;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int c8 = (int)(i % C8);
-        size_t r = i / C8;
-        const int x = (int)(r % W); r /= W;
-        const int y = (int)(r % H); r /= H;
-        const int z = (int)(r % D);
-        const int n = (int)(r / D);
-        const size_t p = ((((size_t)n * Do + z / 2) * Ho + y / 2) * Wo + x / 2) * C + 8 * c8;
-        const uint4 dv = *reinterpret_cast<const uint4*>(dout + p);
-        const uint4 av = add ? *reinterpret_cast<const uint4*>(add + 8 * i) : make_uint4(0u, 0u, 0u, 0u);
-        const uint32_t dw[4] = {dv.x, dv.y, dv.z, dv.w}, aw[4] = {av.x, av.y, av.z, av.w};
-        uint32_t ow[4];
+    const int G = C / 8, lg = __builtin_ctz(G);
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // two rows at a time: six (four) 16-byte loads in flight per lane
+    for (unsigned r0 = blockIdx.x; r0 < rows; r0 += 2 * gridDim.x) {
+        const bool two = r0 + gridDim.x < rows;
+        size_t base[2];
+        const uint16_t* prow[2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t o = 0;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                float v = 0.125f * bf2f((uint16_t)(dw[q] >> (16 * h)));
-                if (add) v += bf2f((uint16_t)(aw[q] >> (16 * h)));
-                o |= (uint32_t)f2bf(v) << (16 * h);
-            }
-            ow[q] = o;
+        for (int k = 0; k < 2; ++k) {
+            const unsigned r = k && two ? r0 + gridDim.x : r0;
+            base[k] = (size_t)r * W * C;
+            const unsigned t = r / (unsigned)H, yy = r - t * (unsigned)H, n = t / (unsigned)D, z = t - n * (unsigned)D;
+            prow[k] = dpool + (((size_t)n * (D >> 1) + (z >> 1)) * (H >> 1) + (yy >> 1)) * (W >> 1) * C;
         }
-        *reinterpret_cast<uint4*>(din + 8 * i) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
+        for (int i = threadIdx.x; i < W * G; i += 256) {
+            uint4 sv[2], yv[2], pv[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                sv[k] = *reinterpret_cast<const uint4*>(src + base[k] + 8 * (size_t)i);
+                yv[k] = *reinterpret_cast<const uint4*>(y + base[k] + 8 * (size_t)i);
+                if (kPool)
+                    pv[k] = *reinterpret_cast<const uint4*>(prow[k] + 8 * ((size_t)(i >> (lg + 1)) * G + (i & (G - 1))));
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                if (k && !two) break;
+                const uint32_t sw[4] = {sv[k].x, sv[k].y, sv[k].z, sv[k].w}, yw[4] = {yv[k].x, yv[k].y, yv[k].z, yv[k].w},
+                               pw[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w};
+                uint32_t o[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    o[q] = 0;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        uint32_t d = (sw[q] >> (16 * h)) & 0xFFFFu;
+                        if (kPool) {
+                            float v = 0.125f * bf2f((uint16_t)(pw[q] >> (16 * h)));
+                            v += bf2f((uint16_t)d);
+                            d = f2bf(v);
+                        }
+                        d = relu_grad(d, bf2f((uint16_t)(yw[q] >> (16 * h))) > 0.f);
+                        acc[2 * q + h] += bf2f((uint16_t)d);
+                        o[q] |= d << (16 * h);
+                    }
+                }
+                *reinterpret_cast<uint4*>(dy + base[k] + 8 * (size_t)i) = make_uint4(o[0], o[1], o[2], o[3]);
+            }
+        }
     }
+    add_bias_grad(acc, G, C, db);
 }
 
 // network input: x[v] = (dose[v] * inv_scale, density[v] * 0.5, 0 x 6), zero
@@ -717,115 +730,157 @@ __global__ void __launch_bounds__(256) max_kernel(const float* __restrict__ a, s
     }
 }
 
-// region[0] += number of voxels with dose >= frac * scale (the dose region
-// that normalises the loss); one atomic per block
+// Workgroups of the reductions below; each leaves its value in an array that
+// the next kernel (or the host) adds up, since atomics of all workgroups on
+// one address serialise at about 12 ns each (counting the dose region with
+// 1,024 of them took 15.7 us, the gradient norm's 16.5 us).
+constexpr int kParts = 256;
+
+// f(a[i]) over the grid's share of a, eight loads in flight per lane
+template <class F>
+DEV void each_of(size_t n, const float* __restrict__ a, F f)
+{
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    for (; i + 7 * stride < n; i += 8 * stride) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = a[i + k * stride];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) f(v[k]);
+    }
+    for (; i < n; i += stride) f(a[i]);
+}
+
+// part[b] = workgroup b's number of voxels with dose >= frac * scale (the dose
+// region that normalises the loss)
 __global__ void __launch_bounds__(256) region_count_kernel(const float* __restrict__ dose, size_t n,
                                                            const float* __restrict__ scale, float frac,
-                                                           unsigned int* __restrict__ region)
+                                                           unsigned int* __restrict__ parts)
 {
     __shared__ unsigned int part[4];
     const float thr = frac * scale[0];
     unsigned int c = 0;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        c += dose[i] >= thr;
+    each_of(n, dose, [&](float a) { c += a >= thr; });
     for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(region, part[0] + part[1] + part[2] + part[3]);
+    if (threadIdx.x == 0) parts[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
 // Squared error in normalised units over the dose region,
 // L = sum_v ((out_v - t_v) / scale)^2 / n_region (every voxel contributes;
 // n_region, the count of voxels with dose >= 1% of scale, sets the scale of
-// the gradients), and the head backward: g_v = dL/d(head pre-activation) =
-// 2 (out_v - t_v) / scale / n_region; dd1[v][c] = g_v w[c];
-// dw[c] += sum_v g_v d1[v][c]; db += sum_v g_v; loss += L.  C = 16
+// the gradients), the head backward: g_v = dL/d(head pre-activation) =
+// 2 (out_v - t_v) / scale / n_region, dw[c] += sum_v g_v d1[v][c], db += sum_v
+// g_v; and the backward of the last layer's leaky ReLU, whose output d1 is at
+// hand: dd1[v][c] = relu'(d1[v][c]) * bf16(g_v w[c]), dbias[c] += sum_v
+// dd1[v][c].  loss_part[b] = workgroup b's share of L (host memory).  C = 16
 // channels: one 32-byte row per voxel.  Block partial sums meet in LDS; one
-// atomic per block and quantity.
+// atomic per block and quantity.  HBM-bound (160 x 128 x 128: 190 MB, 42
+// us; 83 us as two kernels).
 __global__ void __launch_bounds__(256) loss_head_bwd_kernel(const float* __restrict__ out,
                                                             const float* __restrict__ target,
                                                             const float* __restrict__ scale,
                                                             const uint16_t* __restrict__ d1,
                                                             const float* __restrict__ w,
                                                             uint16_t* __restrict__ dd1, float* __restrict__ dw,
-                                                            float* __restrict__ db, double* __restrict__ loss,
-                                                            size_t nvox, const unsigned int* __restrict__ region)
+                                                            float* __restrict__ db, float* __restrict__ dbias,
+                                                            double* __restrict__ loss_part, size_t nvox,
+                                                            const unsigned int* __restrict__ region_part, int n_part)
 {
-    const float inv_count = 1.0f / (float)max(1u, region[0]);
-    __shared__ float sg[4][17];
+    __shared__ float sg[4][33];
     __shared__ double sl[4];
+    __shared__ unsigned int sr[4];
+    const int wave = threadIdx.x >> 6;
+    unsigned int n_region = (int)threadIdx.x < n_part ? region_part[threadIdx.x] : 0u;
+    for (int o = 32; o > 0; o >>= 1) n_region += __shfl_xor(n_region, o);
+    if ((threadIdx.x & 63) == 0) sr[wave] = n_region;
+    __syncthreads();
+    const float inv_count = 1.0f / (float)max(1u, sr[0] + sr[1] + sr[2] + sr[3]);
     const float sc = fmaxf(scale[0], 1e-30f);
     const float isc = 1.0f / sc;
-    float wv[16], gw[16];
+    float wv[16], sums[33];   // gradients of w, then b, then the bias
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-        wv[c] = w[c];
-        gw[c] = 0.f;
-    }
-    float gb = 0.f;
+    for (int c = 0; c < 16; ++c) wv[c] = w[c];
+#pragma unroll
+    for (int c = 0; c < 33; ++c) sums[c] = 0.f;
     double l = 0.0;
-    for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < nvox; v += (size_t)gridDim.x * blockDim.x) {
-        const float e = (out[v] - target[v]) * isc;
-        l += (double)e * e;
-        const float g = 2.f * e * inv_count;
-        gb += g;
-        const uint4* src = reinterpret_cast<const uint4*>(d1 + v * 16);
-        uint4* dst = reinterpret_cast<uint4*>(dd1 + v * 16);
+    // two voxels at a time: eight loads in flight per lane
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t v0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v0 < nvox; v0 += 2 * stride) {
+        const bool two = v0 + stride < nvox;
+        float ov[2], tv[2];
+        uint4 src[2][2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint4 q = src[h];
-            const uint32_t in[4] = {q.x, q.y, q.z, q.w};
-            uint32_t o[4];
+        for (int k = 0; k < 2; ++k) {
+            const size_t v = k && two ? v0 + stride : v0;
+            ov[k] = out[v];
+            tv[k] = target[v];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int c = 8 * h + 2 * k;
-                gw[c] += g * __uint_as_float(in[k] << 16);
-                gw[c + 1] += g * __uint_as_float(in[k] & 0xFFFF0000u);
-                o[k] = (uint32_t)f2bf(g * wv[c]) | ((uint32_t)f2bf(g * wv[c + 1]) << 16);
+            for (int h = 0; h < 2; ++h) src[k][h] = reinterpret_cast<const uint4*>(d1 + v * 16)[h];
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (k && !two) break;
+            const float e = (ov[k] - tv[k]) * isc;
+            l += (double)e * e;
+            const float g = 2.f * e * inv_count;
+            sums[16] += g;
+            uint4* dst = reinterpret_cast<uint4*>(dd1 + (v0 + k * stride) * 16);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint4 q = src[k][h];
+                const uint32_t in[4] = {q.x, q.y, q.z, q.w};
+                uint32_t o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int c = 8 * h + 2 * i;
+                    const float lo = __uint_as_float(in[i] << 16), hi = __uint_as_float(in[i] & 0xFFFF0000u);
+                    sums[c] += g * lo;
+                    sums[c + 1] += g * hi;
+                    const uint32_t dlo = relu_grad(f2bf(g * wv[c]), lo > 0.f), dhi = relu_grad(f2bf(g * wv[c + 1]), hi > 0.f);
+                    sums[17 + c] += bf2f((uint16_t)dlo);
+                    sums[18 + c] += bf2f((uint16_t)dhi);
+                    o[i] = dlo | (dhi << 16);
+                }
+                dst[h] = make_uint4(o[0], o[1], o[2], o[3]);
             }
-            dst[h] = make_uint4(o[0], o[1], o[2], o[3]);
         }
     }
     for (int o = 32; o > 0; o >>= 1) {
-        gb += __shfl_xor(gb, o);
         l += __shfl_xor(l, o);
 #pragma unroll
-        for (int c = 0; c < 16; ++c) gw[c] += __shfl_xor(gw[c], o);
+        for (int c = 0; c < 33; ++c) sums[c] += __shfl_xor(sums[c], o);
     }
-    const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-        for (int c = 0; c < 16; ++c) sg[wave][c] = gw[c];
-        sg[wave][16] = gb;
+        for (int c = 0; c < 33; ++c) sg[wave][c] = sums[c];
         sl[wave] = l;
     }
     __syncthreads();
-    if (threadIdx.x < 17) {
-        const float t = sg[0][threadIdx.x] + sg[1][threadIdx.x] + sg[2][threadIdx.x] + sg[3][threadIdx.x];
-        atomicAdd(threadIdx.x < 16 ? &dw[threadIdx.x] : db, t);
-    } else if (threadIdx.x == 32) {
-        atomicAdd(loss, (sl[0] + sl[1] + sl[2] + sl[3]) * inv_count);
+    const int c = threadIdx.x;
+    if (c < 33) {
+        const float t = sg[0][c] + sg[1][c] + sg[2][c] + sg[3][c];
+        atomicAdd(c < 16 ? &dw[c] : (c == 16 ? db : &dbias[c - 17]), t);
+    } else if (c == 64) {
+        loss_part[blockIdx.x] = (sl[0] + sl[1] + sl[2] + sl[3]) * inv_count;
     }
 }
 
 // Adam on FP32 master parameters; refreshes the BF16 copies of the
 // convolution weights (p_bf == NULL for parameters kept in FP32)
-// sum of squares of a float vector into *out (FP64; one atomic per block)
-__global__ void __launch_bounds__(256) sqnorm_kernel(const float* __restrict__ g, size_t n, double* out)
+// part[b] = workgroup b's share of the sum of squares of a float vector, in
+// FP64 (host memory)
+__global__ void __launch_bounds__(256) sqnorm_kernel(const float* __restrict__ g, size_t n, double* __restrict__ parts)
 {
     __shared__ double part[4];
     double acc = 0.0;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const double v = (double)g[i];
-        acc += v * v;
-    }
+    each_of(n, g, [&](float v) { acc += (double)v * (double)v; });
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const double t = part[0] + part[1] + part[2] + part[3];
-        if (t != 0.0) unsafeAtomicAdd(out, t);
-    }
+    if (threadIdx.x == 0) parts[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
 // Adam on gradient gs * g (gs: the caller's clipping factor, 1 = plain)
@@ -980,9 +1035,16 @@ hipError_t nn_conv3d_fwd_cat_head(const uint16_t* in, const uint16_t* coarse, in
     return conv3d_fwd<kHead>({in, coarse, Cc, wt, bias, out, N, D, H, W, Cin, 16, Kp, 1}, after, s);
 }
 
-hipError_t nn_flip_weights(const uint16_t* w, uint16_t* wf, int Cin, int Cout, int Kp, int Kpf, hipStream_t s)
+hipError_t nn_flip_weights(const FlipLayer* layers, int n, hipStream_t s)
 {
-    hipLaunchKernelGGL(flip_weights_kernel, dim3(grid_for((size_t)Cin * Kpf)), dim3(256), 0, s, w, wf, Cin, Cout, Kp, Kpf);
+    if (n < 1 || n > 7) return hipErrorInvalidValue;
+    FlipLayers f{};
+    int most = 0;
+    for (int i = 0; i < n; ++i) {
+        f.l[i] = layers[i];
+        most = std::max(most, layers[i].Cin * layers[i].Kpf);
+    }
+    hipLaunchKernelGGL(flip_weights_kernel, dim3(grid_for(most), n), dim3(256), 0, s, f);
     return hipGetLastError();
 }
 
@@ -1023,21 +1085,17 @@ hipError_t nn_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float* dw, 
     return nn_conv3d_wgrad_cat(in, nullptr, 0, dout, dw, N, D, H, W, Cin, Cout, Kp, s);
 }
 
-hipError_t nn_relu_bias_bwd(uint16_t* dy, const uint16_t* y, float* db, size_t nvox, int C, hipStream_t s)
+// dpool NULL: no pooled output's gradient to add
+hipError_t nn_grad_relu(const uint16_t* src, const uint16_t* dpool, const uint16_t* y, uint16_t* dy, float* db, int N,
+                        int D, int H, int W, int C, hipStream_t s)
 {
-    if (C < 8 || C > 256 || C % 8 || 256 % (C / 8)) return hipErrorInvalidValue;
-    // a few hundred workgroups: each adds C partial sums to the same C addresses
-    hipLaunchKernelGGL(relu_bias_bwd_kernel, dim3(grid_for(nvox, 256 / (C / 8), 512)), dim3(256), 0, s, dy, y, db,
-                       nvox, C);
-    return hipGetLastError();
-}
-
-hipError_t nn_pool_bwd(const uint16_t* dout, const uint16_t* add, uint16_t* din, int N, int D, int H, int W, int C,
-                       hipStream_t s)
-{
-    if (C % 8) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pool_bwd_kernel, dim3(grid_for((size_t)N * D * H * W * (C / 8))), dim3(256), 0, s, dout, add,
-                       din, N, D, H, W, C);
+    if (C < 8 || C > 256 || C % 8 || 256 % (C / 8) || (dpool && (D % 2 || H % 2 || W % 2))) return hipErrorInvalidValue;
+    const unsigned rows = (unsigned)N * D * H;
+    const unsigned blocks = std::min(512u, std::max(1u, rows / 4));
+    if (dpool)
+        hipLaunchKernelGGL(grad_relu_kernel<true>, dim3(blocks), dim3(256), 0, s, src, dpool, y, dy, db, rows, D, H, W, C);
+    else
+        hipLaunchKernelGGL(grad_relu_kernel<false>, dim3(blocks), dim3(256), 0, s, src, dpool, y, dy, db, rows, D, H, W, C);
     return hipGetLastError();
 }
 
@@ -1053,15 +1111,17 @@ hipError_t nn_make_input(const float* dose, const float* rho, float* scale, uint
     return hipGetLastError();
 }
 
+// region_part: kParts counts (device); loss_part: the shares of the loss
+// (pinned host memory, up to 2 kParts), of which *n_loss are written
 hipError_t nn_loss_head_bwd(const float* out, const float* target, const float* dose, const float* scale,
-                            unsigned int* region, const uint16_t* d1, const float* w, uint16_t* dd1, float* dw,
-                            float* db, double* loss, size_t nvox, int C, hipStream_t s)
+                            unsigned int* region_part, const uint16_t* d1, const float* w, uint16_t* dd1, float* dw,
+                            float* db, float* dbias, double* loss_part, int* n_loss, size_t nvox, hipStream_t s)
 {
-    if (C != 16) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(region_count_kernel, dim3(grid_for(nvox, 256, 1024)), dim3(256), 0, s, dose, nvox, scale, 0.01f,
-                       region);
-    hipLaunchKernelGGL(loss_head_bwd_kernel, dim3(grid_for(nvox, 256, 1024)), dim3(256), 0, s, out, target, scale, d1, w,
-                       dd1, dw, db, loss, nvox, (const unsigned int*)region);
+    const unsigned blocks = grid_for(nvox, 256, kParts);
+    hipLaunchKernelGGL(region_count_kernel, dim3(blocks), dim3(256), 0, s, dose, nvox, scale, 0.01f, region_part);
+    *n_loss = (int)grid_for(nvox, 256, 2 * kParts);
+    hipLaunchKernelGGL(loss_head_bwd_kernel, dim3(*n_loss), dim3(256), 0, s, out, target, scale, d1, w, dd1, dw, db, dbias,
+                       loss_part, nvox, (const unsigned int*)region_part, (int)blocks);
     return hipGetLastError();
 }
 
@@ -1073,9 +1133,11 @@ hipError_t nn_adam(float* p, float* g, float* m1, float* m2, uint16_t* p_bf, siz
     return hipGetLastError();
 }
 
-hipError_t nn_sqnorm(const float* g, size_t n, double* out, hipStream_t s)
+// parts: kParts shares (pinned host memory), of which *n_parts are written
+hipError_t nn_sqnorm(const float* g, size_t n, double* parts, int* n_parts, hipStream_t s)
 {
-    hipLaunchKernelGGL(sqnorm_kernel, dim3(grid_for(n, 256, 1024)), dim3(256), 0, s, g, n, out);
+    *n_parts = (int)grid_for(n, 256, kParts);
+    hipLaunchKernelGGL(sqnorm_kernel, dim3(*n_parts), dim3(256), 0, s, g, n, parts);
     return hipGetLastError();
 }
 

@@ -312,6 +312,17 @@ def test_network_forward_backward(shape):
     net.close()
 
 
+@pytest.mark.parametrize("shape", [
+    (1, 8, 8, 8),        # coarsest level 1 x 1 x 1: every block mostly outside the grid
+    (1, 24, 8, 152),     # rows past one pass of a workgroup's lanes, a half-filled last x tile
+    (3, 8, 40, 24),      # several volumes, an odd number of rows per workgroup
+])
+def test_network_at_tile_edges(shape):
+    """Pooling, the head, the split gradient and the ReLU backward at grid
+    sizes that do not fill their blocks; same comparison and bounds."""
+    test_network_forward_backward(shape)
+
+
 def test_adam_step_and_bf16_refresh():
     """One Adam step against the oracle's Adam on the same (GPU) gradients,
     and the forward after the step equals the forward of a fresh network
