@@ -409,7 +409,7 @@ pmc_status pmc_moliere_table(float* out, int32_t n_floats);
  * deposit cache's sums, keys and LET numerators, the control words, the
  * staged arguments and a batch's per-plan ledgers and counters) and the
  * sizes of the device buffers the kernel indexes (tally planes, generation
- * and workgroup queues, claim counters, the primary work list). */
+ * and workgroup queues, the primary work list). */
 typedef struct {
     int32_t block_threads;      /* workgroup size, multiple of 64 in [64, 1024] */
     int32_t grid_blocks;        /* workgroups of the launch; 0 = not yet known
@@ -436,7 +436,7 @@ typedef struct {
     int32_t cache_slots, key_words, tally_planes, local_queue_cap, args_bytes, reserved;
     uint64_t queue_cap;         /* generation queue entries (12 u32 planes each) */
     uint64_t local_queue_words; /* all workgroup queues (12 u32 per entry) */
-    uint64_t claim_words;       /* per-generation claim counters (u64) */
+    uint64_t claim_words;       /* work claims (u64), one per workgroup and generation, each kept in LDS */
     uint64_t order_words;       /* primary work list (u64) */
 } pmc_launch_layout;
 

@@ -29,7 +29,8 @@ constexpr int kCtrIncSecondaries = 10;
 constexpr int kCtrIncCollisions = 11;
 // LDS control words of a workgroup (u32), after the deposit cache: own
 // secondary queue produced / claimed / published, alive lanes at the epoch
-// end, primaries exhausted, workgroup done
+// end, state (primaries exhausted, workgroup done), a recent place in the
+// primary work list, and as u64 the work-list entries claimed
 constexpr int kWgCtlWords = 8;
 // a workgroup's own secondary queue entry: 12 u32 (px py pz ux uy uz E w
 // uid_lo uid_hi group plan), 48 bytes
@@ -167,11 +168,10 @@ struct KernelArgs {
     int epoch_iters;
     int cache_probes;   // slots tried (linear probing) before a deposit goes to the tally
     // work claims: workgroup b of a launch of G workgroups takes its j-th
-    // index from its own counter wg_claims[gen * G + b] and maps it to
+    // index from its own counter (in LDS) and maps it to
     // ((j >> c) * G + b) << c | (j & (2^c - 1)), i.e. runs of 2^c consecutive
     // indices dealt round-robin; c is at most claim_log2 and small enough
     // that every workgroup gets about four runs of the generation's work
-    unsigned long long* wg_claims;
     int claim_log2;
     int args_off;   // LDS word offset (even) of the staged LdsArgs
     // secondaries a workgroup emits go first to its own queue (loc_cap AoS

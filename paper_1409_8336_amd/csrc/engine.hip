@@ -129,7 +129,7 @@ struct pmc_ctx {
     DevBuf<float> d_vav;       // Vavilov quantile table (PMC_VAVILOV)
     DevBuf<float> d_mol, d_molmat;  // Molière table and material constants (PMC_MOLIERE)
     DevBuf<uint32_t> d_q[2];
-    DevBuf<unsigned long long> d_gc, d_counters, d_order, d_wgc;
+    DevBuf<unsigned long long> d_gc, d_counters, d_order;
     DevBuf<uint32_t> d_qloc;   // per-workgroup secondary queues
     DevBuf<float> d_spots;
     DevBuf<PlanDesc> d_plans;
@@ -588,10 +588,6 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     why = plan_layout(lq, &lay);
     if (!why.empty()) return fail(c, PMC_ERR_ARG, "launch layout: " + why);
     if (lay.lds_bytes != lds) return fail(c, PMC_ERR_DEVICE, "internal: launch layout changed with the grid");
-    // per-workgroup claim counters of every generation
-    HIPCHK(c->d_wgc.ensure(lay.claim_words), "alloc claim counters");
-    HIPCHK(launch_zero(c->d_wgc.p, lay.claim_words * 8, st), "zero claim counters");
-    a.wg_claims = c->d_wgc.p;
     // per-workgroup secondary queues (48-byte entries); automatic: up to
     // 65536 entries per workgroup within 1 GiB for the whole grid (a
     // workgroup of the 16-plan batch emits about 40000 secondaries)

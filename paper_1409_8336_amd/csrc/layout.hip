@@ -59,8 +59,8 @@ std::string plan_layout(const LayoutQuery& q, LaunchLayout* out)
     L.cache_slots = slots;
     L.key_off = L.cache_off + 2 * slots;
     L.num_off = L.key_off + L.key_words * slots;
-    L.ctl_off = L.num_off + (q.score_let ? slots : 0);
-    L.args_off = (L.ctl_off + kWgCtlWords + 1) & ~1;
+    L.ctl_off = (L.num_off + (q.score_let ? slots : 0) + 1) & ~1;   // (the claim count is 64-bit)
+    L.args_off = L.ctl_off + kWgCtlWords;
     L.led_off = L.args_off + (int)(sizeof(LdsArgs) / 4);
     L.cnt_off = L.led_off + (q.multi ? 6 * np : 0);
     L.end_words = L.cnt_off + (q.multi ? 2 * kWgCounters * np : 0);
@@ -96,7 +96,7 @@ std::string check_layout(const LayoutQuery& q, const LaunchLayout& L)
         r.push_back({"cache keys", L.key_off, L.key_off + (long)L.key_words * s, 4 * L.key_words});
         if (q.score_let) r.push_back({"cache LET numerators", L.num_off, L.num_off + (long)s, 4});
     }
-    r.push_back({"control words", L.ctl_off, L.ctl_off + kWgCtlWords, 4});
+    r.push_back({"control words", L.ctl_off, L.ctl_off + kWgCtlWords, 8});
     r.push_back({"staged arguments", L.args_off, L.args_off + (long)(sizeof(LdsArgs) / 4), 8});
     if (q.multi) {
         r.push_back({"plan ledgers", L.led_off, L.led_off + 6L * np, 8});
@@ -117,8 +117,8 @@ std::string check_layout(const LayoutQuery& q, const LaunchLayout& L)
         prev_end = g.end;
         prev = g.name;
     }
-    // the kernel's control words: produced, claimed, published, busy, primaries done, done
-    static_assert(kWgCtlWords >= 6, "the transport kernel uses six control words");
+    // the kernel's control words: produced, claimed, published, busy, state, work place, work claimed (2)
+    static_assert(kWgCtlWords == 8, "the transport kernel uses eight control words");
     static_assert(sizeof(LdsArgs) % 8 == 0, "the per-plan ledgers after the staged arguments are doubles");
     // ---- deposit cache keys and slots
     if (s < 0 || s > 16384) return "cache slots outside [0, 16384]";

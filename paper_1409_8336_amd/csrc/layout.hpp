@@ -48,7 +48,7 @@ struct LaunchLayout {
     unsigned long long q_cap = 0;          // generation queue entries
     int loc_cap = 0;                       // per-workgroup queue entries
     unsigned long long qloc_words = 0;     // all workgroup queues
-    unsigned long long claim_words = 0;    // per-generation claim counters
+    unsigned long long claim_words = 0;    // work claims, one per workgroup and generation (each in its workgroup's LDS)
     unsigned long long order_words = 0;    // primary work list
 };
 
