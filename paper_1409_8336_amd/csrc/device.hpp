@@ -64,6 +64,17 @@ constexpr uint32_t kTrace = 1u << 9;
 // event list (IncEvent) for the cascade kernel, and the proton stops.
 constexpr uint32_t kInc = 64u;
 constexpr uint32_t kTraceNone = 0xFFFFFFFFu;
+// Run flag set by the engine when a plan's grid is past narrow_index.
+constexpr uint32_t kWideIndex = 1u << 10;
+// Whether the transport kernel can index a grid in 32 bits: the row z * ny + y
+// and nx within the 24-bit multiplier, the byte offset of a voxel record (8
+// bytes) and the tally index within 32 bits, below the cache's free-slot key.
+inline bool narrow_index(unsigned long long nx, unsigned long long ny, unsigned long long nz, unsigned long long planes)
+{
+    const unsigned long long k24 = 1ull << 24;
+    return nx < k24 && ny < k24 && nz < k24 && ny * nz < k24 && nx * ny * nz <= (1ull << 29) &&
+           nx * ny * nz * planes < 0xFFFFFFFFull;
+}
 
 // One plan: its geometry (voxel record = {density as float bits, material
 // bin}), its dose tally and its random-number key.  64 bytes.

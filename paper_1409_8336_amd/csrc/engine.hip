@@ -525,6 +525,8 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     a.molmat = c->d_molmat.p;
     a.k_batches = K;
     a.flags = c->p.flags | (let ? kScoreLet : 0u);
+    for (const PlanIn& q : plans)
+        if (!narrow_index(q.g->nx, q.g->ny, q.g->nz, planes)) a.flags |= kWideIndex;
     a.f_mcs = (float)c->p.f_mcs;
     a.s_min = (float)c->p.s_min_cm;
     a.spots = c->d_spots.p;

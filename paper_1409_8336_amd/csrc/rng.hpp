@@ -11,6 +11,16 @@
 
 namespace pmc {
 
+// a ^ b ^ c: one instruction on the device (the compiler makes two)
+__host__ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+    return a ^ b ^ c;
+#endif
+}
+
 // Philox4x32-10 (Salmon et al. 2011); key = run seed, counter = (uid, k, tag)
 template <bool kScalarKey = false>
 __host__ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1)
@@ -27,8 +37,8 @@ __host__ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint3
         }
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;
@@ -37,7 +47,13 @@ __host__ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint3
     return make_uint4(c0, c1, c2, c3);
 }
 
-// strictly inside (0,1), exactly representable in float
-__host__ __device__ __forceinline__ float u01(uint32_t x) { return ((float)(x >> 9) + 0.5f) * (1.0f / 8388608.0f); }
+// (n + 1/2) 2^-23 for n = x >> 9: strictly inside (0,1), exactly representable
+// in float.  Formed as (1 + n 2^-23) - (1 - 2^-24): the first from its bits,
+// and the difference is exact.
+__host__ __device__ __forceinline__ float u01(uint32_t x)
+{
+    const uint32_t bits = (x >> 9) | 0x3F800000u;
+    return __builtin_bit_cast(float, bits) - 0x1.fffffep-1f;
+}
 
 }  // namespace pmc

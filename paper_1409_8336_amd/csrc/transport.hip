@@ -103,6 +103,15 @@ DEV float inv_erf(float x)
     return p * x;
 }
 
+// a * b + c for a, b < 2^24 at full rate (the compiler falls back to a
+// quarter-rate 64-bit multiply-add where it does not see the bounds)
+DEV uint32_t mad24(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t d;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+
 DEV int mbcnt(unsigned long long m)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -139,7 +148,7 @@ DEV bool locate_axis(float p, float d, int n, int& v)
     int i = (int)f;
     if (p == f && d < 0.f) --i;
     v = i;
-    return i >= 0 && i < n;
+    return (uint32_t)i < (uint32_t)n;   // (n > 0)
 }
 
 // grid position of energy e: bin i in [0, 998] and fraction t
@@ -219,8 +228,17 @@ struct Plans<true> {
 
 // kOpt: the instantiation with the optional paths (LET_d scoring, Vavilov
 // straggling, Molière scattering; each still selected by its run flag); the
-// other one carries none of their code
-template <bool kMulti, bool kOpt>
+// other one carries none of their code.  kWide: 64-bit voxel and tally
+// indices, for grids past the limits of narrow_index (always with kOpt: the
+// instantiation serves every run).  The narrow index is two 24-bit multiply-adds
+// at full rate instead of seven 64-bit steps at a quarter of it.
+//
+// Bound by vector instructions: about 460 of them per step, of which 75
+// (transcendentals, Philox's 64-bit products) at a quarter of the rate; the SIMDs
+// issue one in nine cycles of ten.  With 490 per step (64-bit indices, register
+// copies, two instructions per xor of three) the launch of 1e7 histories of 2000
+// spots took 18.7 ms instead of 17.8.
+template <bool kMulti, bool kOpt, bool kWide>
 __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
 {
     // all LDS is the dynamic allocation (no static __shared__ variables, so
@@ -322,8 +340,20 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     auto claim_index = [&](unsigned long long j) {
         return ((((j >> cl2) * gridDim.x) + blockIdx.x) << cl2) | (j & cmask);
     };
-    const int K = a.k_batches;
+    const uint32_t K = (uint32_t)a.k_batches;
     const uint32_t flags = a.flags;
+    using Index = std::conditional_t<kWide, unsigned long long, uint32_t>;
+    auto voxel_index = [&](uint32_t pl, int x, int y, int z) -> Index {
+        if constexpr (kWide) return ((unsigned long long)z * P.ny(pl) + y) * P.nx(pl) + x;
+        else return mad24(mad24((uint32_t)z, (uint32_t)P.ny(pl), (uint32_t)y), (uint32_t)P.nx(pl), (uint32_t)x);
+    };
+    auto voxel_record = [&](uint32_t pl, Index vi) {
+        // (narrow: a 32-bit byte offset from the plan's base)
+        const GLOBAL unsigned char* base = gbl(reinterpret_cast<const unsigned char*>(P.vox(pl)));
+        const Index off = vi * 8u;
+        return *reinterpret_cast<const GLOBAL unsigned long long*>(base + off);
+    };
+    auto plan_voxels = [&](uint32_t pl) { return (Index)P.nx(pl) * (Index)P.ny(pl) * (Index)P.nz(pl); };
 
     // particle state
     float px = 0, py = 0, pz = 0, ux = 0, uy = 0, uz = 1, E = 0, mfp = 0, w = 0;
@@ -374,8 +404,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     // else straight to the FP64 tally.  With a LET_d numerator (a step's
     // deposit, idx = voxel * K + group) the numerator shares the dose's slot,
     // or goes to the numerator plane element num_idx beside it.
-    auto deposit = [&](unsigned long long idx, double v, bool with_num = false, double num = 0.0,
-                       unsigned long long num_idx = 0ull) {
+    auto deposit = [&](Index idx, double v, bool with_num = false, double num = 0.0, Index num_idx = 0) {
         ++n_dep;
         if (use_cache) {
             Key key = (Key)(uint32_t)idx;
@@ -403,12 +432,9 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     // a deposit that belongs to no proton step (Sec. III LET_d leaves out
     // such local deposits): into the dose, and with LET_d scoring also into
     // the plane that the LET denominator subtracts from the dose
-    auto deposit_local = [&](unsigned long long vi, double v) {
+    auto deposit_local = [&](Index vi, double v) {
         deposit(vi * K + batch, v);
-        if (kOpt && (flags & kScoreLet)) {
-            const unsigned long long nv = (unsigned long long)P.nx(plan) * P.ny(plan) * P.nz(plan);
-            deposit(nv * (K + 1) + vi, v);
-        }
+        if (kOpt && (flags & kScoreLet)) deposit(plan_voxels(plan) * (K + 1u) + vi, v);
     };
     bool exhausted = false;
     uint32_t epoch = 0;
@@ -503,7 +529,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         const int ns1 = nsp + 1;
                         const GLOBAL unsigned long long* ord = gbl(L->order);
                         auto search = [&](unsigned long long x) {
-                            int p0 = 0, p1 = K * ns1 - 1;   // the last part that starts at or before x
+                            int p0 = 0, p1 = (int)K * ns1 - 1;   // the last part that starts at or before x
                             while (p1 - p0 > 1) {
                                 const int mid = (p0 + p1) >> 1;
                                 if (ord[mid] <= x) p0 = mid;
@@ -532,7 +558,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         *work_at = (uint32_t)part;
                         const int bg = (int)((uint32_t)part / (uint32_t)ns1), lo = part - bg * ns1;
                         const GLOBAL float* sp = gbl(L->spots) + 8 * lo;
-                        const unsigned long long uid = ord[K * ns1 + bg * nsp + lo] + (idx - start);
+                        const unsigned long long uid = ord[(int)K * ns1 + bg * nsp + lo] + (idx - start);
                         if constexpr (kMulti) {
                             const uint32_t np = __float_as_uint(sp[6]);
                             if (np != plan) {
@@ -588,21 +614,20 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 }
             }
         }
-        const unsigned long long busy = __ballot(alive);
-        if (busy == 0) {
-            // nothing to run: with the work list exhausted and nothing
-            // published in the own queue, wait for the epoch end
-            if (exhausted) break;
-            continue;
-        }
+        // (one way through the iteration, without continue or break: with
+        // them the compiler keeps a second copy of the particle's registers,
+        // some 30 moves per iteration and 12 registers)
+        // nothing to run: with the work list exhausted and nothing published
+        // in the own queue, go to the epoch end
+        if (__ballot(alive) == 0ull && exhausted) it = a.epoch_iters;
 
         // ------------------------------------------------------------ step
         bool stepped = false, short_step = false;
         uint32_t tr_key = kTraceNone;   // measurement trace (flag kTrace)
         if (alive && !pend) {
-            const unsigned long long vi = ((unsigned long long)vz * P.ny(plan) + vy) * P.nx(plan) + vx;
+            const Index vi = voxel_index(plan, vx, vy, vz);
             if constexpr (kOpt && !kMulti) tr_key = (uint32_t)(vi * K + batch);
-            const unsigned long long rec = gbl(reinterpret_cast<const unsigned long long*>(P.vox(plan)))[vi];
+            const unsigned long long rec = voxel_record(plan, vi);
             // what does not depend on the voxel record is computed while its
             // gather is in flight: the step's random numbers, the energy's
             // grid position and the distance to the voxel boundary
@@ -699,8 +724,10 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 }
                 const float tt = (lr - lo_l) * frcp(hi_l - lo_l);
                 const float e_tab = fexp(kLnE0 + ((float)j + tt) * kH);
-                const float e_low = fexp(kLnE0 + (r1 > 0.f ? r1 : 0.f) * frcp(r_first) * kH);
-                e1 = r1 <= r_first ? e_low : e_tab;
+                e1 = e_tab;
+                // below the first range grid point: only the last steps above
+                // the cut-off (where the range ends the step e1 is not used)
+                if (r1 <= r_first && !stop_here) e1 = fexp(kLnE0 + (r1 > 0.f ? r1 : 0.f) * frcp(r_first) * kH);
             }
             float de_mean = E - e1;
             de_mean = de_mean > 0.f ? de_mean : 0.f;
@@ -835,32 +862,25 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 // power averaged over the step's mean loss (over the residual
                 // range when the range ends the step), MeV/cm
                 const float l = stop_here ? (E - kECut) * frcp(s_range) : de_mean * frcp(s);
-                const unsigned long long nv = (unsigned long long)P.nx(plan) * P.ny(plan) * P.nz(plan);
-                deposit(vi * K + batch, dep, true, dep * (double)l, nv * K + vi);
+                deposit(vi * K + batch, dep, true, dep * (double)l, plan_voxels(plan) * K + vi);
             } else {
                 deposit(vi * K + batch, dep);
             }
-            if (stop_here) {
-                alive = false;
-            } else {
-                mfp = nuc ? 0.f : fmaxf(mfp - sigma * s, 0.f);
-                E = e_new;
-                ++k;
-                stepped = true;
-                const bool inside = locate_axis(px, ux, P.nx(plan), vx) & locate_axis(py, uy, P.ny(plan), vy) &
-                                    locate_axis(pz, uz, P.nz(plan), vz);
-                if (E <= kECut || k >= kMaxSteps) {
-                    // below the cut-off (or past the step cap that guards
-                    // against non-terminating histories): deposit the rest
-                    deposit_local(vi, (double)w * (double)E);
-                    alive = false;
-                } else if (!inside) {
-                    acc_esc += (double)w * (double)E;
-                    alive = false;
-                } else if (nuc) {
-                    pend = true;
-                }
-            }
+            // (a proton that stopped takes the new values too; it is refilled
+            // before they are read)
+            mfp = nuc ? 0.f : fmaxf(mfp - sigma * s, 0.f);
+            E = e_new;
+            ++k;
+            stepped = !stop_here;
+            const bool inside = locate_axis(px, ux, P.nx(plan), vx) & locate_axis(py, uy, P.ny(plan), vy) &
+                                locate_axis(pz, uz, P.nz(plan), vz);
+            // below the cut-off (or past the step cap that guards against
+            // non-terminating histories): deposit the rest
+            const bool ends = stepped && (E <= kECut || k >= kMaxSteps);
+            if (ends) deposit_local(vi, (double)w * (double)E);
+            alive = stepped && !ends && inside;
+            if (stepped && !ends && !inside) acc_esc += (double)w * (double)E;
+            pend = alive && nuc;
         }
         n_steps += stepped;
         n_short += stepped && short_step;
@@ -874,16 +894,12 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         }
 
         // ------------------------------------------- batched nuclear events
-        const unsigned long long pm = __ballot(pend);
-        if (pm == 0) continue;
-        {
-            const int np = __popcll(pm);
-            const int occ = __popcll(__ballot(alive));
-            int need = occ >> 3;
-            need = need < 1 ? 1 : need;
-            need = need < a.batch_events ? need : a.batch_events;
-            if (np < need && np < occ) continue;
-        }
+        const int np = __popcll(__ballot(pend));
+        const int occ = __popcll(__ballot(alive));
+        int need = occ >> 3;
+        need = need < 1 ? 1 : need;
+        need = need < a.batch_events ? need : a.batch_events;
+        if (np >= need || (np > 0 && np >= occ)) {
         int n_out = 0;
         float ce0 = 0.f, ce1 = 0.f, ce2 = 0.f, ce3 = 0.f;   // emitted energies (0 = not emitted)
         float rdx = 0.f, rdy = 0.f, rdz = 0.f;              // recoil-proton direction
@@ -896,11 +912,11 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         bool inc_ev = false;
         int inc_el = 0;
         float inc_t = 0.f;
-        unsigned long long inc_vi = 0;
+        Index inc_vi = 0;
         if (pend) {
             pend = false;
-            const unsigned long long vi = ((unsigned long long)vz * P.ny(plan) + vy) * P.nx(plan) + vx;
-            const unsigned long long rec = gbl(reinterpret_cast<const unsigned long long*>(P.vox(plan)))[vi];
+            const Index vi = voxel_index(plan, vx, vy, vz);
+            const unsigned long long rec = voxel_record(plan, vi);
             const int m = (int)(uint32_t)(rec >> 32);
             const float T = E;
             int gi;
@@ -1077,7 +1093,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         e4[1] = u32x4{__float_as_uint(ody), __float_as_uint(odz), __float_as_uint(inc_t),
                                       __float_as_uint(w)};
                         e4[2] = u32x4{uid_lo, uid_hi, batch, plan};
-                        e4[3] = u32x4{ks, (uint32_t)inc_el, (uint32_t)inc_vi, (uint32_t)(inc_vi >> 32)};
+                        e4[3] = u32x4{ks, (uint32_t)inc_el, (uint32_t)inc_vi, (uint32_t)((unsigned long long)inc_vi >> 32)};
                     } else {
                         acc_ovf += (double)w * (double)inc_t;
                     }
@@ -1091,7 +1107,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             const unsigned long long b0 = __ballot(n_out & 1), b1 = __ballot(n_out & 2),
                                      b2 = __ballot(n_out & 4);
             const int total = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
-            if (total == 0) continue;
+            if (total != 0) {
             const int off = mbcnt(b0) + 2 * mbcnt(b1) + 4 * mbcnt(b2);
             const uint32_t lcap = (uint32_t)L->loc_cap;
             uint32_t lbase = 0;
@@ -1154,6 +1170,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         ++li;
                     }
                 }
+            }
+        }
             }
         }
     }   // iterations of one epoch
@@ -1423,37 +1441,30 @@ __global__ void zero_kernel(unsigned long long* __restrict__ p, unsigned long lo
 
 namespace {
 // the instantiation for a launch: batched or not, with the optional paths if
-// any of their flags is set
-const void* kernel_for(bool multi, bool opt)
+// any of their flags is set, with 64-bit indices where the grid needs them
+const void* kernel_for(bool multi, uint32_t flags)
 {
-    if (multi) return opt ? (const void*)transport_kernel<true, true> : (const void*)transport_kernel<true, false>;
-    return opt ? (const void*)transport_kernel<false, true> : (const void*)transport_kernel<false, false>;
+    const bool opt = (flags & (kScoreLet | kVavilov | kMoliere | kTrace | kInc)) != 0u;
+    const bool wide = (flags & kWideIndex) != 0u;
+    if (wide) return multi ? (const void*)transport_kernel<true, true, true> : (const void*)transport_kernel<false, true, true>;
+    if (multi)
+        return opt ? (const void*)transport_kernel<true, true, false> : (const void*)transport_kernel<true, false, false>;
+    return opt ? (const void*)transport_kernel<false, true, false> : (const void*)transport_kernel<false, false, false>;
 }
 }  // namespace
-
-bool transport_needs_options(uint32_t flags)
-{
-    return (flags & (kScoreLet | kVavilov | kMoliere | kTrace | kInc)) != 0u;
-}
 
 hipError_t launch_transport(const KernelArgs& a, bool multi, int grid, int block, size_t lds_bytes,
                             hipStream_t s)
 {
-    const bool opt = transport_needs_options(a.flags);
-    if (multi) {
-        if (opt) hipLaunchKernelGGL((transport_kernel<true, true>), dim3(grid), dim3(block), lds_bytes, s, a);
-        else hipLaunchKernelGGL((transport_kernel<true, false>), dim3(grid), dim3(block), lds_bytes, s, a);
-    } else {
-        if (opt) hipLaunchKernelGGL((transport_kernel<false, true>), dim3(grid), dim3(block), lds_bytes, s, a);
-        else hipLaunchKernelGGL((transport_kernel<false, false>), dim3(grid), dim3(block), lds_bytes, s, a);
-    }
-    return hipGetLastError();
+    KernelArgs args = a;
+    void* params[] = {&args};
+    return hipLaunchKernel(kernel_for(multi, a.flags), dim3(grid), dim3(block), params, lds_bytes, s);
 }
 
 hipError_t transport_max_block(bool multi, uint32_t flags, int* max_threads)
 {
     hipFuncAttributes attr;
-    const void* f = kernel_for(multi, transport_needs_options(flags));
+    const void* f = kernel_for(multi, flags);
     hipError_t e = hipFuncGetAttributes(&attr, f);
     if (e != hipSuccess) return e;
     // the LDS layout assumes the dynamic allocation starts at byte 0
@@ -1464,7 +1475,7 @@ hipError_t transport_max_block(bool multi, uint32_t flags, int* max_threads)
 
 hipError_t transport_occupancy(bool multi, uint32_t flags, int block, size_t lds_bytes, int* blocks_per_cu)
 {
-    const void* f = kernel_for(multi, transport_needs_options(flags));
+    const void* f = kernel_for(multi, flags);
     if (lds_bytes > 65536) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
