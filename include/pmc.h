@@ -103,10 +103,13 @@ typedef struct {
     int32_t batch_events;    /* a wave handles pending nuclear events once this many lanes wait; 0 = tuned */
     int32_t tally_cache;     /* LDS deposit cache per workgroup: slots, 512..16384; 0 = automatic
                                 (the tuner may turn it off, else sized from the LDS left by the
-                                tables); -1 = off (every deposit is a global FP64 atomic) */
+                                tables); -1 = off (every deposit is a global FP64 atomic).  The
+                                memory of a slot is a sum, a key and with LET_d a numerator; the
+                                kernel divides the slots' memory into lines of eight sums with
+                                one key */
     int32_t epoch_steps;     /* loop iterations between epoch ends (cache flush, own-queue
-                                publication); 0 = 32 */
-    int32_t cache_probes;    /* cache slots tried per deposit (linear probing), 1..16; 0 = 3 */
+                                publication); 0 = 24 */
+    int32_t cache_probes;    /* cache lines tried per deposit (linear probing), 1..16; 0 = 3 */
     int32_t claim_run_log2;  /* a workgroup claims primaries in runs of up to 2^claim_run_log2
                                 consecutive histories (a pencil's worth for the cache), 4..16;
                                 0 = 10 */
@@ -430,7 +433,8 @@ typedef struct {
 
 typedef struct {
     uint64_t lds_bytes;         /* dynamic LDS per workgroup */
-    /* LDS regions, 32-bit word offsets from the start of the allocation */
+    /* LDS regions, 32-bit word offsets from the start of the allocation (the
+     * deposit cache's, [cache_off, ctl_off), as cache_slots single slots) */
     int32_t blob_words, plan_desc_off, cache_off, key_off, num_off, ctl_off, args_off,
         ledger_off, counter_off, end_words;
     int32_t cache_slots, key_words, tally_planes, local_queue_cap, args_bytes, reserved;

@@ -28,16 +28,16 @@ hipError_t launch_transport(const KernelArgs& a, bool multi, int grid, int block
                             hipStream_t s);
 hipError_t transport_occupancy(bool multi, uint32_t flags, int block, size_t lds_bytes, int* blocks_per_cu);
 hipError_t transport_max_block(bool multi, uint32_t flags, int* max_threads);
-hipError_t launch_stats(const double* tally, const uint2* vox, unsigned long long nvox, int K,
+hipError_t launch_stats(const double* tally, const uint2* vox, int nx, int ny, int nz, int K, int planes, bool lines,
                         double conv0, double* dose, double* var, double* dep_sum, double* let,
                         hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
-hipError_t launch_density(const uint2* vox, unsigned long long nvox, float* rho, hipStream_t s);
+hipError_t launch_density(const uint2* vox, int nx, int ny, int nz, float* rho, hipStream_t s);
 hipError_t launch_atomic_probe(double* tally, int nx, int ny, int nz, int K, int grid,
                                unsigned long long per_lane, hipStream_t st);
 hipError_t launch_replay(int mode, const uint32_t* trace, unsigned long long trace_iters, unsigned long long lanes,
-                         const uint32_t* epochs, int epoch_iters, int K, const uint2* vox, double* tally,
-                         int n_slots, int probes, int grid, int block, unsigned long long* sink, hipStream_t st);
+                         const uint32_t* epochs, int epoch_iters, uint32_t plane, uint32_t planes, uint32_t columns, uint32_t nz, const uint2* vox, double* tally,
+                         int n_lines, int probes, int grid, int block, unsigned long long* sink, hipStream_t st);
 hipError_t launch_stream_read(const void* p, size_t bytes, unsigned long long* sink, int grid, hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, int grid, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, unsigned long long n, uint32_t v, hipStream_t st);
@@ -82,8 +82,9 @@ struct Geometry {
     int nx = 0, ny = 0, nz = 0;
     float vs[3] = {0, 0, 0};
     DevBuf<uint2> vox;
-    DevBuf<double> tally;        // [nvox][K] for runs on this geometry
+    DevBuf<double> tally;        // [planes][lines()][kLine] for runs on this geometry
     size_t nvox() const { return (size_t)nx * ny * nz; }
+    size_t lines() const { return (nvox() + kLine - 1) / kLine; }   // of a tally plane
 };
 
 // launch shape chosen by the autotuner (or fixed by the caller)
@@ -267,9 +268,10 @@ pmc_status build_geometry(pmc_ctx* c, Geometry& g, const int16_t* hu, int nx, in
     const size_t nv = (size_t)nx * ny * nz;
     std::vector<uint2> rec(nv);
     const int nb = (int)mats.size();
-    for (size_t v = 0; v < nv; ++v) {
-        int h = hu[v];
-        h = h < -1000 ? -1000 : (h > 3000 ? 3000 : h);
+    // the record of every HU number on the scale, then one lookup per voxel
+    constexpr int kHuMin = -1000, kHuMax = 3000;
+    std::vector<uint2> of_hu(kHuMax - kHuMin + 1);
+    for (int h = kHuMin; h <= kHuMax; ++h) {
         int b = 0;
         while (b + 1 < nb && mats[b + 1].hu_lo <= h) ++b;
         const Material& m = mats[b];
@@ -278,8 +280,20 @@ pmc_status build_geometry(pmc_ctx* c, Geometry& g, const int16_t* hu, int nx, in
         const float rf = (float)rho;
         uint32_t bits;
         std::memcpy(&bits, &rf, 4);
-        rec[v] = make_uint2(bits, (uint32_t)b);
+        of_hu[h - kHuMin] = make_uint2(bits, (uint32_t)b);
     }
+    // (records are z-fastest; in tiles, so that both sides stay in the caches)
+    constexpr int kTile = 16;
+    for (int y = 0; y < ny; ++y)
+        for (int x0 = 0; x0 < nx; x0 += kTile)
+            for (int z0 = 0; z0 < nz; z0 += kTile)
+                for (int x = x0; x < std::min(x0 + kTile, nx); ++x) {
+                    uint2* to = rec.data() + ((size_t)y * nx + x) * nz;
+                    for (int z = z0; z < std::min(z0 + kTile, nz); ++z) {
+                        const int h = hu[((size_t)z * ny + y) * nx + x];
+                        to[z] = of_hu[std::clamp(h, kHuMin, kHuMax) - kHuMin];
+                    }
+                }
     pmc_status s = upload(c, g.vox, rec, "upload voxel records");
     if (s != PMC_OK) return s;
     g.nx = nx; g.ny = ny; g.nz = nz;
@@ -397,7 +411,7 @@ struct RunResult {
 // in, the launch shape and trace extent out
 struct TraceReq {
     unsigned long long iters = 0;
-    int grid = 0, block = 0, slots = 0, epoch_iters = 0, probes = 0;
+    int grid = 0, block = 0, slots = 0, lines = 0, epoch_iters = 0, probes = 0;
     unsigned long long lanes = 0;
 };
 
@@ -478,10 +492,11 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     std::vector<PlanDesc> pd(np);
     for (int p = 0; p < np; ++p) {
         Geometry& g = *plans[p].g;
-        HIPCHK(g.tally.ensure(g.nvox() * planes), "alloc tally");
+        HIPCHK(g.tally.ensure(g.lines() * kLine * planes), "alloc tally");
         PlanDesc& d = pd[p];
         std::memset(&d, 0, sizeof(d));
         d.nx = g.nx; d.ny = g.ny; d.nz = g.nz;
+        d.lines = (uint32_t)g.lines();
         for (int i = 0; i < 3; ++i) { d.vs[i] = g.vs[i]; d.ivs[i] = 1.0f / g.vs[i]; }
         d.vox = g.vox.p;
         d.tally = g.tally.p;
@@ -501,7 +516,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     HIPCHK(hipMemcpyAsync(c->d_plans.p, pd.data(), np * sizeof(PlanDesc), hipMemcpyHostToDevice, st), "upload plans");
     HIPCHK(hipEventRecord(c->ev0, st), "event");
     for (int p = 0; p < np; ++p)
-        HIPCHK(launch_zero(pd[p].tally, plans[p].g->nvox() * planes * 8, st), "zero tally");
+        HIPCHK(launch_zero(pd[p].tally, plans[p].g->lines() * kLine * planes * 8, st), "zero tally");
     HIPCHK(launch_zero(c->d_gc.p, c->d_gc.n * 8, st), "zero counters");
     HIPCHK(launch_zero(c->d_counters.p, 8 * (size_t)kPlanCounters * np, st), "zero counters");
     HIPCHK(launch_zero(c->d_ledger.p, 32 * (size_t)np, st), "zero ledger");
@@ -567,15 +582,19 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
         lay.planes != planes || lay.order_words != order.size())
         return fail(c, PMC_ERR_DEVICE, "internal: launch layout disagrees with the run's buffers");
     const int slots = lay.cache_slots;
-    a.cache_slots = slots;
+    a.cache_lines = lay.cache_lines;
+    a.planes = planes;
     a.cache_off = lay.cache_off;
-    a.key_off = lay.key_off;
-    a.num_off = lay.num_off;
+    a.key_off = lay.line_key_off;
+    a.num_off = lay.line_num_off;
     a.ctl_off = lay.ctl_off;
     a.args_off = lay.args_off;
     a.led_off = lay.led_off;
     a.cnt_off = lay.cnt_off;
-    a.epoch_iters = c->p.epoch_steps ? c->p.epoch_steps : 32;
+    // (epochs of 24 iterations: the lines of a single spot's epoch fit the
+    // cache, launch 2.27 ms, of 32 they overflow, 2.77; the 2000-spot field takes
+    // 15.8 ms with 16, 15.4 with 24, 15.3 with 32)
+    a.epoch_iters = c->p.epoch_steps ? c->p.epoch_steps : 24;
     a.cache_probes = c->p.cache_probes ? c->p.cache_probes : 3;
     const size_t lds = lay.lds_bytes;
     int max_block = 0;
@@ -613,6 +632,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
         trace->grid = grid;
         trace->block = block;
         trace->slots = slots;
+        trace->lines = lay.cache_lines;
         trace->epoch_iters = a.epoch_iters;
         trace->probes = a.cache_probes;
         trace->lanes = lanes;
@@ -666,7 +686,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
                     IncLaunch il{c->d_inc_ev.p, c->d_inc_count.p + gidx, cap, c->d_inc_nuc.p, c->d_inc_tab.p,
                                  c->d_inc_count.p + kMaxGenerations + 8 * gidx, c->d_plans.p,
                                  np, K, let ? 1 : 0, a.q_out, cap, &c->d_gc.p[2 * (gidx + 1)],
-                                 c->d_ledger.p, c->d_counters.p};
+                                 c->d_ledger.p, c->d_counters.p, slots > 0 ? 0 : planes};
                     HIPCHK(hipEventRecord(c->ev_inc[2 * gidx], st), "event");
                     HIPCHK(launch_inc_transport(il, c->inc_grid, st), "cascade launch");
                     HIPCHK(hipEventRecord(c->ev_inc[2 * gidx + 1], st), "event");
@@ -694,7 +714,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
             const Geometry& g = *plans[p].g;
             const double vol = (double)g.vs[0] * g.vs[1] * g.vs[2];
             const double conv0 = wtot[p] > 0.0 ? 1.602176634e-10 / (vol * wtot[p]) : 0.0;
-            HIPCHK(launch_stats(g.tally.p, g.vox.p, g.nvox(), K, conv0, plans[p].d_dose, plans[p].d_var,
+            HIPCHK(launch_stats(g.tally.p, g.vox.p, g.nx, g.ny, g.nz, K, planes, slots > 0, conv0, plans[p].d_dose, plans[p].d_var,
                                 c->d_ledger.p + 4 * p + 3, plans[p].d_let, st), "stats launch");
         }
     }
@@ -785,16 +805,21 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
 pmc_status choose_shape(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, hipStream_t st, Shape* out)
 {
     Shape s;
-    s.block = c->p.block_threads ? c->p.block_threads : 256;
-    s.blocks_per_cu = c->p.blocks_per_cu;
-    s.refill = c->p.refill_lanes ? c->p.refill_lanes : 16;
-    s.batch = c->p.batch_events ? c->p.batch_events : 4;
-    const bool tune = c->p.block_threads == 0 || c->p.refill_lanes == 0 || c->p.batch_events == 0;
     unsigned long long total = 0, vox = 0;
     for (const PlanIn& p : plans) {
         total += p.n_hist;
         vox += p.g->nvox();
     }
+    // runs too small to tune: from 40000 histories the workgroup size whose
+    // deposit cache fits (launches of 5e4 histories took 0.33 to 0.74 ms so and
+    // 0.35 to 0.70 with 256 lanes, of 2e5 0.55 to 1.03 and 0.97 to 1.78), below it
+    // small workgroups, which leave the CU sooner (of 1e4 0.26 to 0.62 and 0.20 to
+    // 0.56)
+    s.block = c->p.block_threads ? c->p.block_threads : (total < 40000ull ? 256 : 1024);
+    s.blocks_per_cu = c->p.blocks_per_cu;
+    s.refill = c->p.refill_lanes ? c->p.refill_lanes : 16;
+    s.batch = c->p.batch_events ? c->p.batch_events : 4;
+    const bool tune = c->p.block_threads == 0 || c->p.refill_lanes == 0 || c->p.batch_events == 0;
     if (!tune || total < 200000ull) {
         *out = s;
         return PMC_OK;
@@ -1177,7 +1202,7 @@ pmc_status pmc_geometry_density(pmc_ctx* c, int32_t geometry_id, float* d_rho, v
         return fail(c, PMC_ERR_ARG, "density: bad geometry id or NULL output");
     HIPCHK(hipSetDevice(c->device), "set device");
     const Geometry& g = *c->geoms[geometry_id];
-    HIPCHK(launch_density((const uint2*)g.vox.p, g.nvox(), d_rho, (hipStream_t)stream), "density");
+    HIPCHK(launch_density((const uint2*)g.vox.p, g.nx, g.ny, g.nz, d_rho, (hipStream_t)stream), "density");
     return PMC_OK;
 }
 
@@ -1319,7 +1344,7 @@ pmc_status pmc_roofline_replay(pmc_ctx* c, const pmc_spot* spots, int n_spots, u
         for (int rep = 0; rep < 3; ++rep) {
             HIPCHK(hipEventRecord(c->ev0, st), "event");
             HIPCHK(launch_replay(mode, c->d_trace.p, tr.iters, tr.lanes, c->d_trace_epochs.p, tr.epoch_iters,
-                                 c->p.k_batches, g.vox.p, g.tally.p, tr.slots, tr.probes, tr.grid, tr.block,
+                                 (uint32_t)(g.lines() * kLine), (uint32_t)c->p.k_batches, (uint32_t)g.nx * (uint32_t)g.ny, (uint32_t)g.nz, g.vox.p, g.tally.p, tr.lines, tr.probes, tr.grid, tr.block,
                                  c->d_sink.p, st), "replay launch");
             HIPCHK(hipEventRecord(c->ev1, st), "event");
             HIPCHK(hipEventSynchronize(c->ev1), "replay");
@@ -1441,7 +1466,7 @@ pmc_status pmc_atomic_probe(pmc_ctx* c, uint64_t n_atomics, void* hip_stream, do
     hipStream_t st = (hipStream_t)hip_stream;
     const int K = c->p.k_batches;
     Geometry& g = *c->geoms[0];
-    HIPCHK(g.tally.ensure(g.nvox() * K), "alloc tally");
+    HIPCHK(g.tally.ensure(g.lines() * kLine * K), "alloc tally");
     const int grid = c->num_cu * 4;
     const unsigned long long lanes = (unsigned long long)grid * 256;
     const unsigned long long per_lane = (n_atomics + lanes - 1) / lanes;

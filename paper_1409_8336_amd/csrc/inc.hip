@@ -958,12 +958,14 @@ struct TransportSrc {
         if (s.r.attempts > 0) neutral += s.r.binding + s.r.e_star_fin;
         if (local != 0.0) {
             const int K = a.k_batches;
-            const unsigned long long vi = ((unsigned long long)ev.vi_hi << 32) | ev.vi_lo;
-            __hip_atomic_fetch_add(pd.tally + vi * K + ev.batch, w * local, __ATOMIC_RELAXED,
+            const unsigned long long at = ((unsigned long long)ev.ti_hi << 32) | ev.ti_lo;
+            // strides of a voxel and of a plane
+            const unsigned long long sv = a.row_planes ? (unsigned long long)a.row_planes : 1ull;
+            const unsigned long long plane = a.row_planes ? 1ull : (unsigned long long)pd.lines * kLine;
+            __hip_atomic_fetch_add(pd.tally + plane * ev.batch + at * sv, w * local, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             if (a.score_let) {
-                const unsigned long long nv = (unsigned long long)pd.nx * pd.ny * pd.nz;
-                __hip_atomic_fetch_add(pd.tally + nv * (K + 1) + vi, w * local, __ATOMIC_RELAXED,
+                __hip_atomic_fetch_add(pd.tally + plane * (K + 1) + at * sv, w * local, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
             }
         }

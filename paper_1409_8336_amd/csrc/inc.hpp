@@ -54,10 +54,10 @@ struct IncTab {
 // the proton at the interaction point (position in voxel units of its plan,
 // direction, kinetic energy, weight), its random stream (uid, the step index
 // of the event), statistical group, plan, the struck element (1..6) and the
-// voxel the local deposit goes to.
+// place in a tally plane that the local deposit goes to.
 struct IncEvent {
     float px, py, pz, ux, uy, uz, e, w;
-    uint32_t uid_lo, uid_hi, batch, plan, ks, element, vi_lo, vi_hi;
+    uint32_t uid_lo, uid_hi, batch, plan, ks, element, ti_lo, ti_hi;
 };
 static_assert(sizeof(IncEvent) == 64, "IncEvent is 64 bytes");
 
@@ -96,6 +96,7 @@ struct IncLaunch {
     unsigned long long* out_reserve;      // entries produced for the next generation
     double* ledger;                       // [plan][4]: escaped, neutral, overflow, deposited
     unsigned long long* counters;         // [plan][kPlanCounters]
+    int row_planes;                       // planes of a voxel's row (run without the deposit cache); 0: z-fastest planes
 };
 
 // Host: the six target nuclei (Woods-Saxon shells by Gauss-Legendre

@@ -38,7 +38,7 @@ std::string plan_layout(const LayoutQuery& q, LaunchLayout* out)
     L.planes = q.k_batches + (q.score_let ? 2 : 0);
     L.key_words = q.multi ? 2 : 1;
     const int slot_words = 2 + L.key_words + (q.score_let ? 1 : 0);
-    // the cache key is the tally index as u32 (0xFFFFFFFF marks a free slot)
+    // a line's index in the tally is a u32 key (0xFFFFFFFF marks a free line)
     const bool keys_fit = q.max_nvox * (unsigned long long)L.planes < 0xFFFFFFFFull;
     L.cache_off = (table_words + 1) & ~1;
     const long plan_block_bytes = q.multi ? (long)kPlanLdsBytes * np : 0L;
@@ -60,6 +60,9 @@ std::string plan_layout(const LayoutQuery& q, LaunchLayout* out)
     L.key_off = L.cache_off + 2 * slots;
     L.num_off = L.key_off + L.key_words * slots;
     L.ctl_off = (L.num_off + (q.score_let ? slots : 0) + 1) & ~1;   // (the claim count is 64-bit)
+    L.cache_lines = slots * slot_words / (2 * kLine + L.key_words + (q.score_let ? kLine : 0));
+    L.line_key_off = L.cache_off + 2 * kLine * L.cache_lines;
+    L.line_num_off = L.line_key_off + L.key_words * L.cache_lines;
     L.args_off = L.ctl_off + kWgCtlWords;
     L.led_off = L.args_off + (int)(sizeof(LdsArgs) / 4);
     L.cnt_off = L.led_off + (q.multi ? 6 * np : 0);
@@ -88,13 +91,14 @@ std::string check_layout(const LayoutQuery& q, const LaunchLayout& L)
         int align;         // bytes
     };
     std::vector<Region> r;
-    const int np = q.n_plans, s = L.cache_slots;
+    const int np = q.n_plans, s = L.cache_slots, n = L.cache_lines;
     r.push_back({"table blob", 0, L.blob_words, 4});
     if (q.multi) r.push_back({"plan descriptors", L.pd_off, L.pd_off + 16L * np, 16});
     if (s > 0) {
-        r.push_back({"cache sums", L.cache_off, L.cache_off + 2L * s, 8});
-        r.push_back({"cache keys", L.key_off, L.key_off + (long)L.key_words * s, 4 * L.key_words});
-        if (q.score_let) r.push_back({"cache LET numerators", L.num_off, L.num_off + (long)s, 4});
+        if (n < 1 || n >= 1 << 14) return "cache lines outside [1, 2^14)";
+        r.push_back({"cache sums", L.cache_off, L.cache_off + 2L * kLine * n, 8});
+        r.push_back({"cache keys", L.line_key_off, L.line_key_off + (long)L.key_words * n, 4 * L.key_words});
+        if (q.score_let) r.push_back({"cache LET numerators", L.line_num_off, L.line_num_off + (long)kLine * n, 4});
     }
     r.push_back({"control words", L.ctl_off, L.ctl_off + kWgCtlWords, 8});
     r.push_back({"staged arguments", L.args_off, L.args_off + (long)(sizeof(LdsArgs) / 4), 8});

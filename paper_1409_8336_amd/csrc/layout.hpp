@@ -43,6 +43,11 @@ struct LaunchLayout {
     size_t lds_bytes = 0;
     int cache_slots = 0;
     int key_words = 1;
+    // the cache's area (cache_slots single sums, keys and LET numerators) as
+    // the kernel divides it: lines of kLine sums, one key each
+    int cache_lines = 0;
+    int line_key_off = 0;
+    int line_num_off = 0;
     // device buffers
     int planes = 0;                        // tally doubles per voxel
     unsigned long long q_cap = 0;          // generation queue entries

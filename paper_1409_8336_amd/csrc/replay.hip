@@ -7,7 +7,7 @@
 // scales the HBM byte counters).
 //
 // The trace holds, per loop iteration and lane, the tally element the step
-// deposited into (voxel * K + group; 0xFFFFFFFF: no step), see kTrace.
+// deposited into (0xFFFFFFFF: no step), see kTrace.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -31,17 +31,17 @@ __global__ void __launch_bounds__(1024) replay_kernel(const uint32_t* __restrict
                                                       unsigned long long trace_iters,
                                                       unsigned long long lanes,
                                                       const uint32_t* __restrict__ epochs, int epoch_iters,
-                                                      uint32_t k_magic, uint32_t K,
+                                                      uint32_t plane, uint32_t planes, uint32_t columns, uint32_t nz,
                                                       const uint2* __restrict__ vox, double* tally,
-                                                      int n_slots, int probes, unsigned long long* sink)
+                                                      int n_lines, int probes, unsigned long long* sink)
 {
-    extern __shared__ double cval[];   // n_slots sums, then n_slots u32 keys
+    extern __shared__ double cval[];   // n_lines lines of kLine sums, then n_lines u32 keys
     constexpr bool kCache = (kMode & kReplayCache) != 0;
-    uint32_t* ckey = reinterpret_cast<uint32_t*>(cval + n_slots);
+    uint32_t* ckey = reinterpret_cast<uint32_t*>(cval + (size_t)kLine * n_lines);
     if constexpr (kCache) {
-        for (int i = threadIdx.x; i < n_slots; i += blockDim.x) {
+        for (int i = threadIdx.x; i < kLine * n_lines; i += blockDim.x) {
             cval[i] = 0.0;
-            ckey[i] = kTraceNone;
+            ckey[i / kLine] = kTraceNone;
         }
         __syncthreads();
     }
@@ -55,20 +55,17 @@ __global__ void __launch_bounds__(1024) replay_kernel(const uint32_t* __restrict
             acc += key;
             if (key == kTraceNone) continue;
             if constexpr ((kMode & kReplayGather) != 0) {
-                // voxel = key / K: a high-product estimate within one of the
-                // quotient, corrected (an estimate one too high could index
-                // past the grid)
-                uint32_t v = __umulhi(key, k_magic);
-                v -= (uint32_t)((unsigned long long)v * K > key);
-                v += (uint32_t)((unsigned long long)(v + 1u) * K <= key);
-                const uint2 r = vox[v];
+                // (a step's element is a voxel's: below a plane's padding)
+                const uint32_t row = key / planes;
+                const uint2 r = vox[n_lines > 0 ? key % plane : (row % columns) * nz + row / columns];
                 acc += r.x ^ r.y;
             }
             if constexpr ((kMode & kReplayAtomic) != 0) {
                 if constexpr (kCache) {
-                    const int slot = cache_slot(ckey, key, key * 0x9E3779B1u, (uint32_t)n_slots, probes);
-                    if (slot >= 0) {
-                        unsafeAtomicAdd(&cval[slot], 0.0);
+                    const uint32_t line = key / kLine;
+                    const int at = cache_line(ckey, line, line_hash(line), (uint32_t)n_lines, probes);
+                    if (at >= 0) {
+                        unsafeAtomicAdd(&cval[kLine * at + (int)(key % kLine)], 0.0);
                         continue;
                     }
                 }
@@ -77,12 +74,14 @@ __global__ void __launch_bounds__(1024) replay_kernel(const uint32_t* __restrict
         }
         if constexpr (kCache) {
             __syncthreads();
-            for (int i = threadIdx.x; i < n_slots; i += blockDim.x) {
-                const uint32_t key = ckey[i];
-                if (key != kTraceNone) {
-                    unsafeAtomicAdd(&tally[key], cval[i]);
-                    ckey[i] = kTraceNone;
+            // (eight lanes a line, as the transport flushes it: elements that
+            // took no deposit are left out there, here the sums are all zero)
+            for (int i = threadIdx.x; i < kLine * n_lines; i += blockDim.x) {
+                const uint32_t line = ckey[i / kLine];
+                if (line != kTraceNone) {
+                    unsafeAtomicAdd(&tally[(size_t)line * kLine + i % kLine], cval[i]);
                     cval[i] = 0.0;
+                    if (i % kLine == 0) ckey[i / kLine] = kTraceNone;
                 }
             }
             __syncthreads();
@@ -129,18 +128,17 @@ __global__ void count_steps_kernel(const uint32_t* __restrict__ trace, unsigned 
 
 template <int kMode>
 hipError_t launch_mode(const uint32_t* trace, unsigned long long trace_iters, unsigned long long lanes,
-                       const uint32_t* epochs, int epoch_iters, int K, const uint2* vox, double* tally,
-                       int n_slots, int probes, int grid, int block, unsigned long long* sink, hipStream_t st)
+                       const uint32_t* epochs, int epoch_iters, uint32_t plane, uint32_t planes, uint32_t columns, uint32_t nz, const uint2* vox, double* tally,
+                       int n_lines, int probes, int grid, int block, unsigned long long* sink, hipStream_t st)
 {
-    const size_t lds = (kMode & kReplayCache) ? (size_t)n_slots * 12 : 0;
+    const size_t lds = (kMode & kReplayCache) ? (size_t)n_lines * (8 * kLine + 4) : 0;
     if (lds > 65536) {
         const hipError_t e = hipFuncSetAttribute((const void*)replay_kernel<kMode>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    const uint32_t k_magic = (uint32_t)((0x100000000ull + (unsigned)K - 1) / (unsigned)K);
     hipLaunchKernelGGL(replay_kernel<kMode>, dim3(grid), dim3(block), lds, st, trace, trace_iters, lanes, epochs,
-                       epoch_iters, k_magic, (uint32_t)K, vox, tally, n_slots, probes, sink);
+                       epoch_iters, plane, planes, columns, nz, vox, tally, n_lines, probes, sink);
     return hipGetLastError();
 }
 
@@ -149,21 +147,21 @@ hipError_t launch_mode(const uint32_t* trace, unsigned long long trace_iters, un
 // mode: 0 trace only, 1 gathers, 2 direct atomics, 3 gathers + direct atomics, 6 cached atomics,
 // 7 gathers + cached atomics
 hipError_t launch_replay(int mode, const uint32_t* trace, unsigned long long trace_iters, unsigned long long lanes,
-                         const uint32_t* epochs, int epoch_iters, int K, const uint2* vox, double* tally,
-                         int n_slots, int probes, int grid, int block, unsigned long long* sink, hipStream_t st)
+                         const uint32_t* epochs, int epoch_iters, uint32_t plane, uint32_t planes, uint32_t columns, uint32_t nz, const uint2* vox, double* tally,
+                         int n_lines, int probes, int grid, int block, unsigned long long* sink, hipStream_t st)
 {
     switch (mode) {
-    case 0: return launch_mode<0>(trace, trace_iters, lanes, epochs, epoch_iters, K, vox, tally, n_slots, probes,
+    case 0: return launch_mode<0>(trace, trace_iters, lanes, epochs, epoch_iters, plane, planes, columns, nz, vox, tally, n_lines, probes,
                                   grid, block, sink, st);
-    case 1: return launch_mode<1>(trace, trace_iters, lanes, epochs, epoch_iters, K, vox, tally, n_slots, probes,
+    case 1: return launch_mode<1>(trace, trace_iters, lanes, epochs, epoch_iters, plane, planes, columns, nz, vox, tally, n_lines, probes,
                                   grid, block, sink, st);
-    case 2: return launch_mode<2>(trace, trace_iters, lanes, epochs, epoch_iters, K, vox, tally, n_slots, probes,
+    case 2: return launch_mode<2>(trace, trace_iters, lanes, epochs, epoch_iters, plane, planes, columns, nz, vox, tally, n_lines, probes,
                                   grid, block, sink, st);
-    case 3: return launch_mode<3>(trace, trace_iters, lanes, epochs, epoch_iters, K, vox, tally, n_slots, probes,
+    case 3: return launch_mode<3>(trace, trace_iters, lanes, epochs, epoch_iters, plane, planes, columns, nz, vox, tally, n_lines, probes,
                                   grid, block, sink, st);
-    case 6: return launch_mode<6>(trace, trace_iters, lanes, epochs, epoch_iters, K, vox, tally, n_slots, probes,
+    case 6: return launch_mode<6>(trace, trace_iters, lanes, epochs, epoch_iters, plane, planes, columns, nz, vox, tally, n_lines, probes,
                                   grid, block, sink, st);
-    case 7: return launch_mode<7>(trace, trace_iters, lanes, epochs, epoch_iters, K, vox, tally, n_slots, probes,
+    case 7: return launch_mode<7>(trace, trace_iters, lanes, epochs, epoch_iters, plane, planes, columns, nz, vox, tally, n_lines, probes,
                                   grid, block, sink, st);
     default: return hipErrorInvalidValue;
     }

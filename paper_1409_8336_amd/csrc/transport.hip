@@ -201,6 +201,7 @@ struct Plans<false> {
     DEV int nx(uint32_t) const { return a.single.nx; }
     DEV int ny(uint32_t) const { return a.single.ny; }
     DEV int nz(uint32_t) const { return a.single.nz; }
+    DEV uint32_t lines(uint32_t) const { return a.single.lines; }
     DEV float vs(uint32_t, int i) const { return a.single.vs[i]; }
     DEV float ivs(uint32_t, int i) const { return a.single.ivs[i]; }
     DEV const uint2* vox(uint32_t) const { return a.single.vox; }
@@ -216,6 +217,7 @@ struct Plans<true> {
     DEV int nx(uint32_t p) const { return pd[p].nx; }
     DEV int ny(uint32_t p) const { return pd[p].ny; }
     DEV int nz(uint32_t p) const { return pd[p].nz; }
+    DEV uint32_t lines(uint32_t p) const { return pd[p].lines; }
     DEV float vs(uint32_t p, int i) const { return pd[p].vs[i]; }
     DEV float ivs(uint32_t p, int i) const { return pd[p].ivs[i]; }
     DEV const uint2* vox(uint32_t p) const { return pd[p].vox; }
@@ -250,14 +252,14 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         const uint32_t* src = reinterpret_cast<const uint32_t*>(a.plans);
         for (int i = threadIdx.x; i < a.n_plans * 16; i += blockDim.x) dst[i] = src[i];
     }
-    // deposit cache at an even word offset: slot values (double), slot keys
-    // (tally index; in a batch of plans, plan << 32 | tally index), with
-    // LET_d scoring the slots' LET numerators (float partial sums, flushed to
-    // the FP64 numerator plane), then the workgroup's control words
+    // deposit cache at an even word offset: lines of kLine sums (double), line
+    // keys (the line's index in the tally; in a batch of plans, plan << 32 |
+    // index), with LET_d scoring the sums' LET numerators (float partial sums,
+    // flushed to the FP64 numerator plane), then the workgroup's control words
     using Key = std::conditional_t<kMulti, unsigned long long, uint32_t>;
-    constexpr Key kEmptySlot = ~Key(0);
-    const int n_slots = a.cache_slots;
-    const bool use_cache = n_slots > 0;
+    constexpr Key kEmptyLine = ~Key(0);
+    const int n_lines = a.cache_lines;
+    const bool use_cache = n_lines > 0;
     const bool score_let = kOpt && (a.flags & kScoreLet) != 0u;
     double* const cval = reinterpret_cast<double*>(lds + a.cache_off);
     Key* const ckey = reinterpret_cast<Key*>(lds + a.key_off);
@@ -271,9 +273,9 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     uint32_t* const work_at = ctl + 5;        // a recent place in the primary work list (a hint)
     // work-list entries claimed by the workgroup's waves
     unsigned long long* const wg_claim = reinterpret_cast<unsigned long long*>(ctl + 6);
-    for (int i = threadIdx.x; i < n_slots; i += blockDim.x) {
+    for (int i = threadIdx.x; i < kLine * n_lines; i += blockDim.x) {
         cval[i] = 0.0;
-        ckey[i] = kEmptySlot;
+        ckey[i / kLine] = kEmptyLine;
         if (score_let) cnum[i] = 0.f;
     }
     if (threadIdx.x < kWgCtlWords) ctl[threadIdx.x] = 0u;
@@ -344,8 +346,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     const uint32_t flags = a.flags;
     using Index = std::conditional_t<kWide, unsigned long long, uint32_t>;
     auto voxel_index = [&](uint32_t pl, int x, int y, int z) -> Index {
-        if constexpr (kWide) return ((unsigned long long)z * P.ny(pl) + y) * P.nx(pl) + x;
-        else return mad24(mad24((uint32_t)z, (uint32_t)P.ny(pl), (uint32_t)y), (uint32_t)P.nx(pl), (uint32_t)x);
+        if constexpr (kWide) return ((unsigned long long)y * P.nx(pl) + x) * P.nz(pl) + z;
+        else return mad24(mad24((uint32_t)y, (uint32_t)P.nx(pl), (uint32_t)x), (uint32_t)P.nz(pl), (uint32_t)z);
     };
     auto voxel_record = [&](uint32_t pl, Index vi) {
         // (narrow: a 32-bit byte offset from the plan's base)
@@ -353,7 +355,16 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         const Index off = vi * 8u;
         return *reinterpret_cast<const GLOBAL unsigned long long*>(base + off);
     };
-    auto plan_voxels = [&](uint32_t pl) { return (Index)P.nx(pl) * (Index)P.ny(pl) * (Index)P.nz(pl); };
+    // a voxel's place in a plane of the tally (see PlanDesc), and its element in
+    // plane b (a dose group, or K and K + 1 for the LET planes)
+    auto tally_place = [&](uint32_t pl, int x, int y, int z, Index vi) -> Index {
+        if (use_cache) return vi;
+        if constexpr (kWide) return ((unsigned long long)z * P.ny(pl) + y) * P.nx(pl) + x;
+        else return mad24((uint32_t)z, (uint32_t)(P.nx(pl) * P.ny(pl)), mad24((uint32_t)y, (uint32_t)P.nx(pl), (uint32_t)x));
+    };
+    auto element = [&](uint32_t pl, uint32_t b, Index at) -> Index {
+        return use_cache ? (Index)P.lines(pl) * kLine * b + at : at * (Index)a.planes + b;
+    };
 
     // particle state
     float px = 0, py = 0, pz = 0, ux = 0, uy = 0, uz = 1, E = 0, mfp = 0, w = 0;
@@ -400,25 +411,21 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         n_steps = n_el = n_ne = n_short = n_dep = n_glob = n_flush = n_locq = 0;
     };
     // one deposit into tally element idx of the current plan: through the
-    // workgroup's LDS cache when the slot is free or already holds idx,
-    // else straight to the FP64 tally.  With a LET_d numerator (a step's
-    // deposit, idx = voxel * K + group) the numerator shares the dose's slot,
-    // or goes to the numerator plane element num_idx beside it.
+    // workgroup's LDS cache when the line is there or finds a free place, else
+    // straight to the FP64 tally.  With a LET_d numerator (a step's deposit)
+    // the numerator shares the dose's place in the line, or goes to the
+    // numerator plane's element num_idx beside it.
     auto deposit = [&](Index idx, double v, bool with_num = false, double num = 0.0, Index num_idx = 0) {
         ++n_dep;
         if (use_cache) {
-            Key key = (Key)(uint32_t)idx;
-            uint32_t h = (uint32_t)idx * 0x9E3779B1u;
-            if constexpr (kMulti) {
-                key |= (Key)plan << 32;
-                h ^= plan * 0x85EBCA6Bu;
-            }
-            // multiplicative hash; a slot is ours if it holds the key or we
-            // claim it empty
-            const int slot = cache_slot(ckey, key, h, (uint32_t)n_slots, a.cache_probes);
-            if (slot >= 0) {
-                unsafeAtomicAdd(&cval[slot], v);
-                if (with_num) atomicAdd(&cnum[slot], (float)num);
+            const uint32_t line = (uint32_t)(idx / kLine);
+            Key key = (Key)line;
+            if constexpr (kMulti) key |= (Key)plan << 32;
+            const int at = cache_line(ckey, key, line_hash(line, kMulti ? plan : 0u), (uint32_t)n_lines, a.cache_probes);
+            if (at >= 0) {
+                const uint32_t e = (uint32_t)at * kLine + (uint32_t)(idx % kLine);
+                unsafeAtomicAdd(&cval[e], v);
+                if (with_num) atomicAdd(&cnum[e], (float)num);
                 return;
             }
         }
@@ -432,9 +439,9 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     // a deposit that belongs to no proton step (Sec. III LET_d leaves out
     // such local deposits): into the dose, and with LET_d scoring also into
     // the plane that the LET denominator subtracts from the dose
-    auto deposit_local = [&](Index vi, double v) {
-        deposit(vi * K + batch, v);
-        if (kOpt && (flags & kScoreLet)) deposit(plan_voxels(plan) * (K + 1u) + vi, v);
+    auto deposit_local = [&](Index ti, double v) {
+        deposit(element(plan, batch, ti), v);
+        if (kOpt && (flags & kScoreLet)) deposit(element(plan, K + 1u, ti), v);
     };
     bool exhausted = false;
     uint32_t epoch = 0;
@@ -626,7 +633,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         uint32_t tr_key = kTraceNone;   // measurement trace (flag kTrace)
         if (alive && !pend) {
             const Index vi = voxel_index(plan, vx, vy, vz);
-            if constexpr (kOpt && !kMulti) tr_key = (uint32_t)(vi * K + batch);
+            const Index ti = tally_place(plan, vx, vy, vz, vi);
+            if constexpr (kOpt && !kMulti) tr_key = (uint32_t)element(plan, batch, ti);
             const unsigned long long rec = voxel_record(plan, vi);
             // what does not depend on the voxel record is computed while its
             // gather is in flight: the step's random numbers, the energy's
@@ -862,9 +870,9 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 // power averaged over the step's mean loss (over the residual
                 // range when the range ends the step), MeV/cm
                 const float l = stop_here ? (E - kECut) * frcp(s_range) : de_mean * frcp(s);
-                deposit(vi * K + batch, dep, true, dep * (double)l, plan_voxels(plan) * K + vi);
+                deposit(element(plan, batch, ti), dep, true, dep * (double)l, element(plan, K, ti));
             } else {
-                deposit(vi * K + batch, dep);
+                deposit(element(plan, batch, ti), dep);
             }
             // (a proton that stopped takes the new values too; it is refilled
             // before they are read)
@@ -877,7 +885,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             // below the cut-off (or past the step cap that guards against
             // non-terminating histories): deposit the rest
             const bool ends = stepped && (E <= kECut || k >= kMaxSteps);
-            if (ends) deposit_local(vi, (double)w * (double)E);
+            if (ends) deposit_local(ti, (double)w * (double)E);
             alive = stepped && !ends && inside;
             if (stepped && !ends && !inside) acc_esc += (double)w * (double)E;
             pend = alive && nuc;
@@ -912,10 +920,11 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         bool inc_ev = false;
         int inc_el = 0;
         float inc_t = 0.f;
-        Index inc_vi = 0;
+        Index inc_ti = 0;
         if (pend) {
             pend = false;
             const Index vi = voxel_index(plan, vx, vy, vz);
+            const Index ti = tally_place(plan, vx, vy, vz, vi);
             const unsigned long long rec = voxel_record(plan, vi);
             const int m = (int)(uint32_t)(rec >> 32);
             const float T = E;
@@ -1003,15 +1012,15 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         rotate(rdx, rdy, rdz, cr, sr, phi + 0.5f);
                         const double resid = (double)T - (double)tn_f - (double)tr_f;
                         if (resid != 0.0) {
-                            deposit_local(vi, (double)w * resid);
+                            deposit_local(ti, (double)w * resid);
                         }
                     } else {
-                        deposit_local(vi, (double)w * ((double)T - (double)tn_f));
+                        deposit_local(ti, (double)w * ((double)T - (double)tn_f));
                     }
                     rotate(ux, uy, uz, ct, st, phi);
                     E = tn_f;
                     if (E <= kECut) {
-                        deposit_local(vi, (double)w * (double)E);
+                        deposit_local(ti, (double)w * (double)E);
                         alive = false;
                     } else {
                         mfp = -fln(u01(r3.w));
@@ -1022,7 +1031,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                     inc_ev = true;
                     inc_el = el;
                     inc_t = T;
-                    inc_vi = vi;
+                    inc_ti = ti;
                     alive = false;
                 } else {
                     // non-elastic: secondary protons from the per-nucleus table
@@ -1067,7 +1076,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                     if (n > 2 && ce2 <= kECut) { local += ce2; ce2 = 0.f; }
                     if (n > 3 && ce3 <= kECut) { local += ce3; ce3 = 0.f; }
                     n_out = (ce0 > 0.f) + (ce1 > 0.f) + (ce2 > 0.f) + (ce3 > 0.f);
-                    deposit_local(vi, (double)w * local);
+                    deposit_local(ti, (double)w * local);
                     acc_neu += (double)w * ((double)T - loc - carried);
                     alive = false;
                 }
@@ -1093,7 +1102,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         e4[1] = u32x4{__float_as_uint(ody), __float_as_uint(odz), __float_as_uint(inc_t),
                                       __float_as_uint(w)};
                         e4[2] = u32x4{uid_lo, uid_hi, batch, plan};
-                        e4[3] = u32x4{ks, (uint32_t)inc_el, (uint32_t)inc_vi, (uint32_t)((unsigned long long)inc_vi >> 32)};
+                        e4[3] = u32x4{ks, (uint32_t)inc_el, (uint32_t)inc_ti, (uint32_t)((unsigned long long)inc_ti >> 32)};
                     } else {
                         acc_ovf += (double)w * (double)inc_t;
                     }
@@ -1186,33 +1195,36 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     }
     ++epoch;
     __syncthreads();
-    // write the epoch's cached sums to the tally and clear the cache
-    for (int i = threadIdx.x; i < n_slots; i += blockDim.x) {
-        const Key key = ckey[i];
-        if (key != kEmptySlot) {
-            if constexpr (kMulti)
-                __hip_atomic_fetch_add(gbl(P.tally((uint32_t)(key >> 32))) + (uint32_t)key, cval[i], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            else unsafeAtomicAdd(&a.single.tally[key], cval[i]);
-            ++n_glob;
-            ++n_flush;
+    // write the epoch's cached sums to the tally and clear the cache: eight
+    // neighbouring lanes a line, so that its sums leave as one 64-byte request
+    // (an element without a deposit has a zero sum)
+    for (int i = threadIdx.x; i < kLine * n_lines; i += blockDim.x) {
+        const Key key = ckey[i / kLine];
+        if (key != kEmptyLine) {
+            const uint32_t line = (uint32_t)key, in = (uint32_t)i % kLine;
+            const uint32_t pk = kMulti ? (uint32_t)((unsigned long long)key >> 32) : 0u;
+            GLOBAL double* const to = gbl(P.tally(pk)) + in;
+            const double v = cval[i];
+            if (v != 0.0) {
+                __hip_atomic_fetch_add(to + (unsigned long long)line * kLine, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ++n_glob;
+                ++n_flush;
+            }
+            cval[i] = 0.0;
             if (score_let) {
-                // the slot's LET numerator, if it held step deposits (key =
-                // voxel * K + group), to element voxel of the numerator plane
+                // the LET numerator, if the element took step deposits, to the
+                // same line of the numerator plane
                 const float nm = cnum[i];
                 if (nm != 0.f) {
-                    const uint32_t pk = kMulti ? (uint32_t)(key >> 32) : 0u;
-                    const uint32_t t = (uint32_t)key;
-                    const unsigned long long nv = (unsigned long long)P.nx(pk) * P.ny(pk) * P.nz(pk);
-                    __hip_atomic_fetch_add(gbl(P.tally(pk)) + nv * K + t / (uint32_t)K, (double)nm,
+                    const uint32_t pl = P.lines(pk);
+                    __hip_atomic_fetch_add(to + ((unsigned long long)pl * K + line % pl) * kLine, (double)nm,
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     ++n_glob;
                     ++n_flush;
                 }
                 cnum[i] = 0.f;
             }
-            ckey[i] = kEmptySlot;
-            cval[i] = 0.0;
+            if (in == 0u) ckey[i / kLine] = kEmptyLine;   // (its eight lanes have read it)
         }
     }
     // publish what the lanes queued this epoch (written before the barrier
@@ -1287,7 +1299,7 @@ __global__ void __launch_bounds__(256) atomic_probe_kernel(double* tally, int nx
             y = y0 + (int)((s >> 8) % (uint32_t)wy);
             z = 0;
         }
-        const unsigned long long v = ((unsigned long long)z * ny + y) * nx + x;
+        const unsigned long long v = ((unsigned long long)y * nx + x) * nz + z;
         unsafeAtomicAdd(&tally[v * K + b], 0.0);
         ++z;
     }
@@ -1303,131 +1315,140 @@ hipError_t launch_atomic_probe(double* tally, int nx, int ny, int nz, int K, int
 // dose statistics over the K groups: total, variance of the total, and the
 // deposited-energy sum (Sec. II.B.2); with LET_d scoring also the LET_d of
 // every voxel from the two planes after the groups
-// A block takes kStatsVox consecutive voxels at a time: their [voxel][K]
-// tally rows form one contiguous run, read with 16-byte unit-stride loads
-// into LDS rows padded to an odd number of doubles (fewer bank conflicts),
-// then each lane reduces its voxel's K groups from LDS.  With kPre (K <= 16:
-// a run is at most kStatsPre 16-byte loads per lane) the next run's loads are
-// issued into registers before the current run is reduced, so that they are
-// in flight during the reduction.
-constexpr int kStatsVox = 128;
-constexpr int kStatsPre = 8;
+// The tally is z-fastest, one plane per group; dose, variance and LET are
+// x-fastest.  A workgroup takes tiles of 16 columns (x) by 16 voxels in z: its
+// lanes read the K planes 16 consecutive doubles a column, and the tile's
+// results turn through LDS into rows of 16 consecutive x.  (Of a run without the
+// deposit cache the tally is one row of groups per voxel, x-fastest: the lanes
+// then read the tile as they write it.)  Bound by the tally's bytes.  With kPre (K <= 16) a voxel's groups are read at once into registers,
+// else twice (the second time from the caches).
+constexpr int kStatsTile = 16;
+constexpr int kStatsPre = 16;
+
+// tile t of a grid -> its y and the corner x0, z0 (z tiles innermost: the
+// tiles that share the lines at a tile's edge follow each other)
+struct TileGrid {
+    int nx, ny, nz, tx, tz;
+    DEV void at(unsigned long long t, int& x0, int& y, int& z0) const
+    {
+        z0 = (int)(t % (unsigned)tz) * kStatsTile;
+        t /= (unsigned)tz;
+        x0 = (int)(t % (unsigned)tx) * kStatsTile;
+        y = (int)(t / (unsigned)tx);
+    }
+};
+
 template <bool kPre>
-__global__ void __launch_bounds__(kStatsVox) stats_kernel(const double* __restrict__ tally,
+__global__ void __launch_bounds__(kStatsTile* kStatsTile) stats_kernel(const double* __restrict__ tally,
                                                           const uint2* __restrict__ vox,
-                                                          unsigned long long nvox, int K, uint32_t k_magic,
+                                                          TileGrid tg, unsigned long long n_tiles,
+                                                          unsigned rows, unsigned long long plane, int K,
                                                           double inv_k, double k_ratio, double conv0,
                                                           double* __restrict__ dose,
                                                           double* __restrict__ var, double* dep_sum,
-                                                          const double* __restrict__ let_nd,
                                                           double* __restrict__ let)
 {
-    extern __shared__ double rows[];   // kStatsVox * (K | 1)
-    const int pitch = K | 1;
-    const unsigned long long stride = (unsigned long long)gridDim.x * kStatsVox;
+    __shared__ double turn[3][kStatsTile][kStatsTile + 1];   // [dose, variance, LET][z][x]
+    __shared__ double sums[kStatsTile * kStatsTile / 64];
+    const int a = (int)threadIdx.x % kStatsTile, b = (int)threadIdx.x / kStatsTile;
     double part = 0.0;
-    // element e of a run lies in row e / K, computed as a high product with
-    // k_magic = ceil(2^32 / K) (exact for e < 2^32 / K^2, here e < 8192)
-    auto put = [&](int i, const double2& q) {
-        const uint32_t e0 = 2u * (uint32_t)i, e1 = e0 + 1u;
-        const uint32_t r0 = __umulhi(e0, k_magic), r1 = __umulhi(e1, k_magic);
-        rows[r0 * pitch + (e0 - r0 * K)] = q.x;
-        rows[r1 * pitch + (e1 - r1 * K)] = q.y;
-    };
-    // pairs of doubles of the run that starts at voxel w (16-byte aligned:
-    // it starts at w * K doubles, w a multiple of kStatsVox)
-    auto pairs = [&](unsigned long long w) {
-        const unsigned long long left = nvox - w;
-        return ((left < (unsigned long long)kStatsVox ? (int)left : kStatsVox) * K) >> 1;
-    };
-    double2 pre[kPre ? kStatsPre : 1];
-    if (kPre && blockIdx.x * (unsigned long long)kStatsVox < nvox) {
-        const unsigned long long w = blockIdx.x * (unsigned long long)kStatsVox;
-        const double2* src2 = reinterpret_cast<const double2*>(tally + w * K);
-        const int np = pairs(w);
+    for (unsigned long long t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+        int x0, y, z0;
+        tg.at(t, x0, y, z0);
+        {
+            // lane (a, b): voxel z0 + a of column x0 + b (of rows the reverse)
+            const int ta = rows ? b : a, tb = rows ? a : b;   // place in z, in x
+            const int x = x0 + tb, z = z0 + ta;
+            const bool in = x < tg.nx && z < tg.nz;
+            const unsigned long long v = in ? ((unsigned long long)y * tg.nx + x) * tg.nz + z : 0ull;
+            const double* tv = tally + (rows ? (((unsigned long long)z * tg.ny + y) * tg.nx + x) * rows : v);
+            double tot = 0.0, ss = 0.0;
+            float rho = 1.f;
+            if (in) {
+                rho = __uint_as_float(vox[v].x);
+                if constexpr (kPre) {
+                    double g[kStatsPre];
 #pragma unroll
-        for (int j = 0; j < (kPre ? kStatsPre : 1); ++j) {
-            const int i = (int)threadIdx.x + j * kStatsVox;
-            if (i < np) pre[j] = src2[i];
-        }
-    }
-    for (unsigned long long v0 = blockIdx.x * (unsigned long long)kStatsVox; v0 < nvox; v0 += stride) {
-        const unsigned long long left = nvox - v0;
-        const int nv = left < (unsigned long long)kStatsVox ? (int)left : kStatsVox;
-        const int n = nv * K;                      // doubles in this run
-        // the voxel's record is read before the barrier, off the dependent path
-        const unsigned long long v = v0 + threadIdx.x;
-        const float rho = (int)threadIdx.x < nv ? __uint_as_float(vox[v].x) : 1.f;
-        __syncthreads();
-        if (kPre) {
+                    for (int k = 0; k < kStatsPre; ++k)
+                        if (k < K) g[k] = tv[plane * (unsigned)k];
 #pragma unroll
-            for (int j = 0; j < (kPre ? kStatsPre : 1); ++j) {
-                const int i = (int)threadIdx.x + j * kStatsVox;
-                if (i < (n >> 1)) put(i, pre[j]);
+                    for (int k = 0; k < kStatsPre; ++k)
+                        if (k < K) tot += g[k];
+                    const double mean = tot * inv_k;
+#pragma unroll
+                    for (int k = 0; k < kStatsPre; ++k)
+                        if (k < K) {
+                            const double dd = g[k] - mean;
+                            ss += dd * dd;
+                        }
+                } else {
+                    for (int k = 0; k < K; ++k) tot += tv[plane * (unsigned)k];
+                    const double mean = tot * inv_k;
+                    for (int k = 0; k < K; ++k) {
+                        const double dd = tv[plane * (unsigned)k] - mean;
+                        ss += dd * dd;
+                    }
+                }
             }
-        } else {
-            const double2* src2 = reinterpret_cast<const double2*>(tally + v0 * K);
-            for (int i = threadIdx.x; i < (n >> 1); i += kStatsVox) put(i, src2[i]);
-        }
-        if ((n & 1) && threadIdx.x == 0) rows[((n - 1) / K) * pitch + (n - 1) % K] = tally[v0 * K + n - 1];
-        __syncthreads();
-        if (kPre && v0 + stride < nvox) {
-            // the next run's loads, in flight while this run is reduced
-            const unsigned long long w = v0 + stride;
-            const double2* src2 = reinterpret_cast<const double2*>(tally + w * K);
-            const int np = pairs(w);
-#pragma unroll
-            for (int j = 0; j < (kPre ? kStatsPre : 1); ++j) {
-                const int i = (int)threadIdx.x + j * kStatsVox;
-                if (i < np) pre[j] = src2[i];
+            // conv0 / rho: an FP32 reciprocal refined by two Newton steps in FP64
+            const double rd = (double)rho;
+            double ir = (double)frcp(rho);
+            ir = ir * (2.0 - rd * ir);
+            ir = ir * (2.0 - rd * ir);
+            const double conv = conv0 * ir;
+            turn[0][ta][tb] = tot * conv;
+            if (var) turn[1][ta][tb] = k_ratio * ss * conv * conv;
+            part += tot;
+            if (let && in) {
+                // LET_d (keV/um; 1 MeV/cm = 0.1 keV/um): numerator over the
+                // energy of the proton steps, i.e. the dose minus what was
+                // deposited outside any step
+                const double num = tv[plane * (unsigned)K], den = tot - tv[plane * (unsigned)(K + 1)];
+                turn[2][ta][tb] = (num > 0.0 && den > 0.0) ? 0.1 * num / den : 0.0;
             }
         }
-        if ((int)threadIdx.x >= nv) continue;
-        const double* t = rows + threadIdx.x * pitch;
-        double tot = 0.0;
-        for (int b = 0; b < K; ++b) tot += t[b];
-        const double mean = tot * inv_k;
-        double ss = 0.0;
-        for (int b = 0; b < K; ++b) {
-            const double dd = t[b] - mean;
-            ss += dd * dd;
+        __syncthreads();
+        {
+            // lane (a, b): voxel x0 + a of row z0 + b
+            const int x = x0 + a, z = z0 + b;
+            if (x < tg.nx && z < tg.nz) {
+                const unsigned long long o = ((unsigned long long)z * tg.ny + y) * tg.nx + x;
+                dose[o] = turn[0][b][a];
+                if (var) var[o] = turn[1][b][a];
+                if (let) let[o] = turn[2][b][a];
+            }
         }
-        // conv0 / rho: an FP32 reciprocal refined by two Newton steps in FP64
-        const double rd = (double)rho;
-        double ir = (double)frcp(rho);
-        ir = ir * (2.0 - rd * ir);
-        ir = ir * (2.0 - rd * ir);
-        const double conv = conv0 * ir;
-        dose[v] = tot * conv;
-        if (var) var[v] = k_ratio * ss * conv * conv;
-        part += tot;
-        if (let) {
-            // LET_d (keV/um; 1 MeV/cm = 0.1 keV/um): numerator over the
-            // energy of the proton steps, i.e. the dose minus what was
-            // deposited outside any step
-            const double num = let_nd[v], den = tot - let_nd[nvox + v];
-            let[v] = (num > 0.0 && den > 0.0) ? 0.1 * num / den : 0.0;
-        }
+        __syncthreads();
     }
     // one atomic per workgroup: the workgroups' partial sums all go to one
-    // address, where memory-side atomics serialise (one per wave of 65536
-    // workgroups took most of the kernel's time)
+    // address, where memory-side atomics serialise
     for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) rows[threadIdx.x >> 6] = part;
+    if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = part;
     __syncthreads();
     if (threadIdx.x == 0) {
         double sum = 0.0;
-        for (int w = 0; w < kStatsVox / 64; ++w) sum += rows[w];
+        for (double w : sums) sum += w;
         if (sum != 0.0) unsafeAtomicAdd(dep_sum, sum);
     }
 }
 
-__global__ void density_kernel(const uint2* __restrict__ vox, unsigned long long nvox, float* __restrict__ rho)
+// densities of the z-fastest records, x-fastest (in the same tiles)
+__global__ void __launch_bounds__(kStatsTile* kStatsTile) density_kernel(const uint2* __restrict__ vox, TileGrid tg,
+                                                                         unsigned long long n_tiles,
+                                                                         float* __restrict__ rho)
 {
-    for (unsigned long long v = blockIdx.x * (unsigned long long)blockDim.x + threadIdx.x; v < nvox;
-         v += (unsigned long long)gridDim.x * blockDim.x)
-        rho[v] = __uint_as_float(vox[v].x);
+    __shared__ float turn[kStatsTile][kStatsTile + 1];
+    const int a = (int)threadIdx.x % kStatsTile, b = (int)threadIdx.x / kStatsTile;
+    for (unsigned long long t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+        int x0, y, z0;
+        tg.at(t, x0, y, z0);
+        if (x0 + b < tg.nx && z0 + a < tg.nz)
+            turn[a][b] = __uint_as_float(vox[((unsigned long long)y * tg.nx + x0 + b) * tg.nz + z0 + a].x);
+        __syncthreads();
+        if (x0 + a < tg.nx && z0 + b < tg.nz)
+            rho[((unsigned long long)(z0 + b) * tg.ny + y) * tg.nx + x0 + a] = turn[b][a];
+        __syncthreads();
+    }
 }
 
 __global__ void zero_kernel(unsigned long long* __restrict__ p, unsigned long long n)
@@ -1483,48 +1504,53 @@ hipError_t transport_occupancy(bool multi, uint32_t flags, int block, size_t lds
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, block, lds_bytes);
 }
 
-hipError_t launch_stats(const double* tally, const uint2* vox, unsigned long long nvox, int K,
+namespace {
+TileGrid tile_grid(int nx, int ny, int nz, unsigned long long* n_tiles)
+{
+    TileGrid tg{nx, ny, nz, (nx + kStatsTile - 1) / kStatsTile, (nz + kStatsTile - 1) / kStatsTile};
+    *n_tiles = (unsigned long long)tg.tx * (unsigned long long)tg.tz * (unsigned long long)ny;
+    return tg;
+}
+}  // namespace
+
+hipError_t launch_stats(const double* tally, const uint2* vox, int nx, int ny, int nz, int K, int planes, bool lines,
                         double conv0, double* dose, double* var, double* dep_sum, double* let,
                         hipStream_t s)
 {
     if (K < 2 || K > 64) return hipErrorInvalidValue;
-    const size_t bytes = (size_t)kStatsVox * (K | 1) * sizeof(double);
-    // registers hold a whole run when it is at most kStatsPre loads per lane
-    const bool pre = (size_t)kStatsVox * K / 2 <= (size_t)kStatsPre * kStatsVox;
-    if (bytes > 65536) {
-        const hipError_t ea = hipFuncSetAttribute(pre ? (const void*)stats_kernel<true> : (const void*)stats_kernel<false>,
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (ea != hipSuccess) return ea;
-    }
+    const bool pre = K <= kStatsPre;
     // as many workgroups as are resident at once (a second, partial wave of
-    // workgroups would run after the first), each looping over runs of voxels
+    // workgroups would run after the first), each looping over tiles
     const void* kfn = pre ? (const void*)stats_kernel<true> : (const void*)stats_kernel<false>;
+    constexpr int kThreads = kStatsTile * kStatsTile;
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, kStatsVox, bytes);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, kThreads, 0);
     if (e != hipSuccess) return e;
     const unsigned long long resident = (unsigned long long)std::max(1, cus) * (unsigned long long)std::max(1, per_cu);
-    unsigned long long blocks = (nvox + kStatsVox - 1) / kStatsVox;
-    if (blocks > resident) blocks = resident;
-    if (blocks == 0) blocks = 1;
-    const uint32_t k_magic = (uint32_t)((0x100000000ull + (unsigned)K - 1) / (unsigned)K);
-    const double* let_nd = let ? tally + nvox * (unsigned long long)K : nullptr;
+    unsigned long long n_tiles;
+    const TileGrid tg = tile_grid(nx, ny, nz, &n_tiles);
+    const unsigned blocks = (unsigned)std::max(1ull, std::min(n_tiles, resident));
+    // doubles of a voxel's row (0: z-fastest planes), and from plane to plane
+    const unsigned rows = lines ? 0u : (unsigned)planes;
+    const unsigned long long plane = lines ? ((unsigned long long)nx * ny * nz + kLine - 1) / kLine * kLine : 1ull;
     if (pre)
-        hipLaunchKernelGGL(stats_kernel<true>, dim3((unsigned)blocks), dim3(kStatsVox), bytes, s, tally, vox, nvox, K,
-                           k_magic, 1.0 / K, (double)K / (K - 1), conv0, dose, var, dep_sum, let_nd, let);
+        hipLaunchKernelGGL(stats_kernel<true>, dim3(blocks), dim3(kThreads), 0, s, tally, vox, tg, n_tiles, rows, plane, K,
+                           1.0 / K, (double)K / (K - 1), conv0, dose, var, dep_sum, let);
     else
-        hipLaunchKernelGGL(stats_kernel<false>, dim3((unsigned)blocks), dim3(kStatsVox), bytes, s, tally, vox, nvox, K,
-                           k_magic, 1.0 / K, (double)K / (K - 1), conv0, dose, var, dep_sum, let_nd, let);
+        hipLaunchKernelGGL(stats_kernel<false>, dim3(blocks), dim3(kThreads), 0, s, tally, vox, tg, n_tiles, rows, plane, K,
+                           1.0 / K, (double)K / (K - 1), conv0, dose, var, dep_sum, let);
     return hipGetLastError();
 }
 
-hipError_t launch_density(const uint2* vox, unsigned long long nvox, float* rho, hipStream_t s)
+hipError_t launch_density(const uint2* vox, int nx, int ny, int nz, float* rho, hipStream_t s)
 {
-    unsigned long long blocks = (nvox + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
+    unsigned long long n_tiles;
+    const TileGrid tg = tile_grid(nx, ny, nz, &n_tiles);
+    const unsigned blocks = (unsigned)std::min(n_tiles, 16384ull);
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(density_kernel, dim3((unsigned)blocks), dim3(256), 0, s, vox, nvox, rho);
+    hipLaunchKernelGGL(density_kernel, dim3(blocks), dim3(kStatsTile * kStatsTile), 0, s, vox, tg, n_tiles, rho);
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""Grids past the 24-bit row limit take the transport's 64-bit indices: the
+"""Grids past the 24-bit column limit take the transport's 64-bit indices: the
 histories of a beam near the low corner of a very long grid are those of the
 same beam in a short one (same voxel size, so the same coordinates), and no
 proton of 60 MeV reaches the short grid's far side.  Doses then agree to the
@@ -11,8 +11,8 @@ from paper_1409_8336_amd import pmc, synth
 
 pytestmark = pytest.mark.gpu
 
-NY, NZ = 64, 64
-VOXEL = (20.0, 0.2, 0.2)
+NY, NZ = 64, 8
+VOXEL = (20.0, 0.2, 1.6)
 
 
 def _run(mode, ny):
@@ -46,7 +46,7 @@ def _run(mode, ny):
 def test_long_grid_equals_short_grid(mode):
     print("case:", mode, flush=True)
     short, short_x, _, ss = _run(mode, NY)
-    wide, wide_x, beyond, sw = _run(mode, (1 << 18) + 1)
+    wide, wide_x, beyond, sw = _run(mode, (1 << 24) + 1)
     assert beyond == 0.0 and short.max() > 0.0
     np.testing.assert_allclose(wide, short, rtol=0, atol=1e-11 * short.max())
     tol = 1e-5 if mode == "let" else 1e-11
