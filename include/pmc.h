@@ -100,7 +100,8 @@ typedef struct {
     int32_t block_threads;   /* transport workgroup size (64..1024, multiple of 64); 0 = tuned */
     int32_t blocks_per_cu;   /* resident workgroups per CU for the persistent grid; 0 = occupancy */
     int32_t refill_lanes;    /* a wave refills when at least this many of its 64 lanes are idle; 0 = tuned */
-    int32_t batch_events;    /* a wave handles pending nuclear events once this many lanes wait; 0 = tuned */
+    int32_t batch_events;    /* a wave handles pending nuclear events (in larger runs: lists them for
+                                a full wave) once this many lanes wait; 0 = tuned */
     int32_t tally_cache;     /* LDS deposit cache per workgroup: slots, 512..16384; 0 = automatic
                                 (the tuner may turn it off, else sized from the LDS left by the
                                 tables); -1 = off (every deposit is a global FP64 atomic).  The
@@ -108,7 +109,7 @@ typedef struct {
                                 kernel divides the slots' memory into lines of eight sums with
                                 one key */
     int32_t epoch_steps;     /* loop iterations between epoch ends (cache flush, own-queue
-                                publication); 0 = 24 */
+                                publication); 0 = 16 */
     int32_t cache_probes;    /* cache lines tried per deposit (linear probing), 1..16; 0 = 3 */
     int32_t claim_run_log2;  /* a workgroup claims primaries in runs of up to 2^claim_run_log2
                                 consecutive histories (a pencil's worth for the cache), 4..16;

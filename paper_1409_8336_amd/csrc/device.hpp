@@ -28,9 +28,9 @@ constexpr int kCtrIncEvents = 9;
 constexpr int kCtrIncSecondaries = 10;
 constexpr int kCtrIncCollisions = 11;
 // LDS control words of a workgroup (u32), after the deposit cache: own
-// secondary queue produced / claimed / published, alive lanes at the epoch
-// end, state (primaries exhausted, workgroup done), a recent place in the
-// primary work list, and as u64 the work-list entries claimed
+// secondary queue produced / claimed, continuing protons produced, alive lanes
+// at the epoch end, state (primaries exhausted, workgroup done), a recent place
+// in the primary work list, and as u64 the work-list entries claimed
 constexpr int kWgCtlWords = 8;
 // a workgroup's own secondary queue entry: 12 u32 (px py pz ux uy uz E w
 // uid_lo uid_hi group plan), 48 bytes
@@ -123,7 +123,8 @@ struct alignas(8) LdsArgs {
     uint32_t* q_loc;   // this launch's per-workgroup queues (loc_cap entries each)
     void* inc_ev;      // flag PMC_INC: this generation's event list (IncEvent entries)
     unsigned long long* inc_count;   // events recorded in it
-    unsigned long long inc_cap;
+    uint32_t ev_pushed;      // protons with a nuclear event pushed by the workgroup (counting, not staged)
+    uint32_t cont_claimed;   // continuing protons taken by its lanes (counting)
     int n_spots;
     int loc_cap;
 };
@@ -213,7 +214,26 @@ struct KernelArgs {
     // each), its counter and capacity
     void* inc_ev;
     unsigned long long* inc_count;
-    unsigned long long inc_cap;
+    // nuclear events by full waves (NULL: each wave its own lanes' in place):
+    // EvQueue::entries(block) protons of 64 bytes per workgroup
+    uint32_t* q_ev;
+};
+
+// A workgroup's part of q_ev, in entries of one proton: two event lists of a
+// block each (pushed in one epoch, worked in the next), the parking places of the
+// block's lanes while they work an event, and the ring of protons that continue
+// after theirs.  The ring never fills: new protons are taken only by lanes that
+// found it empty, so what it holds beyond the idle lanes is at most the two
+// lists' survivors.
+struct EvQueue {
+    static constexpr int kEntryWords = 16;
+    static __host__ __device__ uint32_t ring(uint32_t block)
+    {
+        uint32_t r = 64;
+        while (r < 3u * block) r *= 2u;
+        return r;
+    }
+    static __host__ __device__ uint32_t entries(uint32_t block) { return 3u * block + ring(block); }
 };
 
 }  // namespace pmc

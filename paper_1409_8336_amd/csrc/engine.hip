@@ -132,6 +132,7 @@ struct pmc_ctx {
     DevBuf<uint32_t> d_q[2];
     DevBuf<unsigned long long> d_gc, d_counters, d_order;
     DevBuf<uint32_t> d_qloc;   // per-workgroup secondary queues
+    DevBuf<uint32_t> d_qev;    // per-workgroup event queues (EvQueue)
     DevBuf<float> d_spots;
     DevBuf<PlanDesc> d_plans;
     DevBuf<uint32_t> d_trace, d_trace_epochs;   // roofline replay: address trace (kTrace)
@@ -591,10 +592,10 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     a.args_off = lay.args_off;
     a.led_off = lay.led_off;
     a.cnt_off = lay.cnt_off;
-    // (epochs of 24 iterations: the lines of a single spot's epoch fit the
-    // cache, launch 2.27 ms, of 32 they overflow, 2.77; the 2000-spot field takes
-    // 15.8 ms with 16, 15.4 with 24, 15.3 with 32)
-    a.epoch_iters = c->p.epoch_steps ? c->p.epoch_steps : 24;
+    // (epochs of 16 iterations: the lines of a single spot's epoch mostly fit
+    // the cache, launch 2.1 ms, of 24 they begin to overflow, 2.4, of 32 more, 2.8;
+    // the 2000-spot field takes 14.4 ms with 16, 14.3 with 24)
+    a.epoch_iters = c->p.epoch_steps ? c->p.epoch_steps : 16;
     a.cache_probes = c->p.cache_probes ? c->p.cache_probes : 3;
     const size_t lds = lay.lds_bytes;
     int max_block = 0;
@@ -616,6 +617,13 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     if (a.loc_cap > 0) {
         HIPCHK(c->d_qloc.ensure(lay.qloc_words), "alloc workgroup queues");
         a.q_loc = c->d_qloc.p;
+    }
+    // events by full waves where lanes get several histories each: at about four
+    // (1e6 histories, one spot) the gain is gone in the drain, which works them in
+    // place
+    if (total >= 2ull * (unsigned long long)grid * (unsigned long long)block) {
+        if (c->d_qev.ensure((size_t)grid * EvQueue::entries(block) * EvQueue::kEntryWords) == hipSuccess) a.q_ev = c->d_qev.p;
+        else (void)hipGetLastError();   // (no room: events in place)
     }
     if (trace) {
         // the address trace of generation 0: trace->iters loop iterations of
@@ -649,7 +657,6 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
         HIPCHK(c->d_inc_count.ensure(9 * kMaxGenerations), "alloc event counters");
         HIPCHK(launch_zero(c->d_inc_count.p, 9 * kMaxGenerations * 8, st), "zero event counters");
         a.inc_ev = c->d_inc_ev.p;
-        a.inc_cap = cap;
     }
     const uint32_t run_flags = a.flags;
     int gens = 0;

@@ -121,7 +121,7 @@ std::string check_layout(const LayoutQuery& q, const LaunchLayout& L)
         prev_end = g.end;
         prev = g.name;
     }
-    // the kernel's control words: produced, claimed, published, busy, state, work place, work claimed (2)
+    // the kernel's control words: produced, claimed, continuing, busy, state, work place, work claimed (2)
     static_assert(kWgCtlWords == 8, "the transport kernel uses eight control words");
     static_assert(sizeof(LdsArgs) % 8 == 0, "the per-plan ledgers after the staged arguments are doubles");
     // ---- deposit cache keys and slots

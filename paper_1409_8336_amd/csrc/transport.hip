@@ -226,6 +226,11 @@ struct Plans<true> {
     DEV uint32_t key_hi(uint32_t p) const { return pd[p].key_hi; }
 };
 
+// iterations a wave leaves out of an epoch in which it worked a full wave's
+// events, so that it reaches the epoch end with the others (left in: one spot
+// 2.41 ms instead of 2.27, the 2000-spot field even)
+constexpr int kEventIters = 3;
+
 // -------------------------------------------------------------- the kernel
 
 // kOpt: the instantiation with the optional paths (LET_d scoring, Vavilov
@@ -267,7 +272,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     uint32_t* const ctl = reinterpret_cast<uint32_t*>(lds + a.ctl_off);
     uint32_t* const loc_produced = ctl + 0;   // entries reserved in the own queue
     uint32_t* const loc_claimed = ctl + 1;    // entries taken by lanes
-    uint32_t* const loc_avail = ctl + 2;      // entries published (written before the last epoch end)
+    uint32_t* const cont_produced = ctl + 2;  // protons that continue after their event
     uint32_t* const wg_busy = ctl + 3;        // alive lanes counted at the epoch end
     uint32_t* const wg_state = ctl + 4;       // 1: some wave found the work list exhausted; 2: the workgroup is done
     uint32_t* const work_at = ctl + 5;        // a recent place in the primary work list (a hint)
@@ -314,7 +319,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         L->q_loc = a.q_loc + (size_t)blockIdx.x * (size_t)a.loc_cap * kLocEntryWords;
         L->inc_ev = a.inc_ev;
         L->inc_count = a.inc_count;
-        L->inc_cap = a.inc_cap;
+        L->ev_pushed = 0u;
+        L->cont_claimed = 0u;
     }
     __syncthreads();
     const PlanDesc* pds = reinterpret_cast<const PlanDesc*>(lds + a.pd_offset);
@@ -443,6 +449,60 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         deposit(element(plan, batch, ti), v);
         if (kOpt && (flags & kScoreLet)) deposit(element(plan, K + 1u, ti), v);
     };
+    // a proton's state in 64 bytes (its voxel too: after an event at a voxel
+    // face the direction alone would not give it back)
+    auto save_state = [&](GLOBAL u32x4* q) {
+        q[0] = u32x4{__float_as_uint(px), __float_as_uint(py), __float_as_uint(pz), __float_as_uint(ux)};
+        q[1] = u32x4{__float_as_uint(uy), __float_as_uint(uz), __float_as_uint(E), __float_as_uint(mfp)};
+        q[2] = u32x4{__float_as_uint(w), uid_lo, uid_hi, k};
+        q[3] = u32x4{batch | plan << 8 | (uint32_t)alive << 16 | (uint32_t)pend << 17, (uint32_t)vx, (uint32_t)vy,
+                     (uint32_t)vz};
+    };
+    auto load_state = [&](const GLOBAL u32x4* q) {
+        const u32x4 e0 = q[0], e1 = q[1], e2 = q[2], e3 = q[3];
+        px = __uint_as_float(e0.x);
+        py = __uint_as_float(e0.y);
+        pz = __uint_as_float(e0.z);
+        ux = __uint_as_float(e0.w);
+        uy = __uint_as_float(e1.x);
+        uz = __uint_as_float(e1.y);
+        E = __uint_as_float(e1.z);
+        mfp = __uint_as_float(e1.w);
+        w = __uint_as_float(e2.x);
+        uid_lo = e2.y;
+        uid_hi = e2.z;
+        k = e2.w;
+        batch = e3.x & 255u;
+        if constexpr (kMulti) {
+            const uint32_t np = (e3.x >> 8) & 255u;
+            if (np != plan) {
+                flush(plan);
+                plan = np;
+            }
+        }
+        alive = (e3.x >> 16 & 1u) != 0u;
+        pend = (e3.x >> 17 & 1u) != 0u;
+        vx = (int)e3.y;
+        vy = (int)e3.z;
+        vz = (int)e3.w;
+    };
+    // Nuclear events by full waves.  A wave's few protons at an event (four to
+    // eight of its 64 lanes) would run the event code, many times a step's
+    // length, with the other lanes idle; while there is new work for their
+    // lanes they go to the workgroup's event list instead.  At the start of the
+    // next epoch wave v parks its own lanes and works entries 64 v ...; protons
+    // that survive go to the ring, which idle lanes read from the epoch after.
+    // Once the work list is exhausted a wave runs its events in place: the lanes
+    // would idle, and the tail would wait for epochs.  Launch of 1e7 histories of
+    // 2000 spots 15.5 ms with events in place, 14.2 so; 2e6 of 444 spots 3.1 and
+    // 2.9.
+    const bool ev_queue = a.q_ev != nullptr;
+    GLOBAL u32x4* const evq = reinterpret_cast<GLOBAL u32x4*>(
+        gbl(a.q_ev) + (size_t)blockIdx.x * EvQueue::entries(blockDim.x) * EvQueue::kEntryWords);
+    auto ev_entry = [&](uint32_t i) { return evq + (size_t)i * (EvQueue::kEntryWords / 4); };
+    uint32_t ev_base = 0, ev_ready = 0;     // pushes before this epoch; entries to work in it
+    uint32_t loc_av = 0, cont_av = 0;       // entries published at the last epoch end (own queue, ring)
+
     bool exhausted = false;
     uint32_t epoch = 0;
 
@@ -451,33 +511,39 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     // it is done
     for (;;) {
     for (int it = 0; it < a.epoch_iters; ++it) {
+        const bool chunk = it == 0 && threadIdx.x - (uint32_t)lane < ev_ready;   // (wave-uniform) events to work
         // ---------------------------------------------------------- refill
         // idle lanes take first the published entries of the workgroup's own
         // queue, then indices of the generation's work list
         const unsigned long long idle = __ballot(!alive);
         const int n_idle = __popcll(idle);
         if (n_idle > 0 && (n_idle == kWave || n_idle >= a.refill_lanes || exhausted)) {
-            const int rank = mbcnt(idle);
-            uint32_t n_sec = 0, sec_base = 0;
-            if (lane == 0 && L->loc_cap > 0) {
+            const int idle_rank = mbcnt(idle);
+            uint32_t n_cont = 0, cont_base = 0, n_sec = 0, sec_base = 0;
+            if (lane == 0) {
                 // claim up to n_idle published entries: compare-and-swap on the
                 // LDS counter (a failed swap means another wave claimed)
-                const uint32_t av = *loc_avail;
-                uint32_t c = *loc_claimed;
-                while (c < av) {
-                    const uint32_t take = min(av - c, (uint32_t)n_idle);
-                    const uint32_t prev = atomicCAS(loc_claimed, c, c + take);
-                    if (prev == c) {
-                        sec_base = c;
-                        n_sec = take;
-                        break;
+                auto claim = [&](uint32_t* claimed, uint32_t av, uint32_t want, uint32_t& base) {
+                    uint32_t c = *claimed;
+                    while ((int32_t)(av - c) > 0 && want > 0u) {
+                        const uint32_t take = min(av - c, want);
+                        const uint32_t prev = atomicCAS(claimed, c, c + take);
+                        if (prev == c) {
+                            base = c;
+                            return take;
+                        }
+                        c = prev;
                     }
-                    c = prev;
-                }
+                    return 0u;
+                };
+                if (ev_queue) n_cont = claim(&L->cont_claimed, cont_av, (uint32_t)n_idle, cont_base);
+                n_sec = claim(loc_claimed, loc_av, (uint32_t)n_idle - n_cont, sec_base);
             }
+            n_cont = __builtin_amdgcn_readfirstlane(n_cont);
+            cont_base = __builtin_amdgcn_readfirstlane(cont_base);
             n_sec = __builtin_amdgcn_readfirstlane(n_sec);
             sec_base = __builtin_amdgcn_readfirstlane(sec_base);
-            const int n_rest = n_idle - (int)n_sec;
+            const int n_rest = n_idle - (int)n_cont - (int)n_sec;
             const bool take_prim = !exhausted && n_rest > 0;
             unsigned long long base = 0;
             if (take_prim) {
@@ -485,7 +551,12 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 base = bcast0(base);
                 if (claim_index(base + (unsigned long long)n_rest) >= limit) exhausted = true;
             }
-            if (!alive) {
+            if (!alive && idle_rank < (int)n_cont) {
+                // a proton that continues after its event
+                const uint32_t ring = EvQueue::ring(blockDim.x);
+                load_state(ev_entry(3u * blockDim.x + ((cont_base + (uint32_t)idle_rank) & (ring - 1u))));
+            } else if (!alive) {
+                const int rank = idle_rank - (int)n_cont;
                 bool got = false;
                 if (rank < (int)n_sec) {
                     // a secondary of this workgroup (48-byte entry)
@@ -907,7 +978,25 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         int need = occ >> 3;
         need = need < 1 ? 1 : need;
         need = need < a.batch_events ? need : a.batch_events;
-        if (np >= need || (np > 0 && np >= occ)) {
+        const bool ripe = np >= need || (np > 0 && np >= occ);
+        if (ripe && ev_queue && !exhausted && !chunk) {
+            // to the event list (a full one takes them in the next epoch)
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&L->ev_pushed, (uint32_t)np);
+            base = __builtin_amdgcn_readfirstlane(base) - ev_base;
+            const uint32_t i = base + (uint32_t)mbcnt(__ballot(pend));
+            if (pend && i < blockDim.x) {
+                save_state(ev_entry((epoch & 1u) * blockDim.x + i));
+                alive = false;
+                pend = false;
+            }
+        } else if (ripe || chunk) {
+        if (chunk) {
+            save_state(ev_entry(2u * blockDim.x + threadIdx.x));
+            alive = false;
+            pend = false;
+            if (threadIdx.x < ev_ready) load_state(ev_entry((~epoch & 1u) * blockDim.x + threadIdx.x));
+        }
         int n_out = 0;
         float ce0 = 0.f, ce1 = 0.f, ce2 = 0.f, ce3 = 0.f;   // emitted energies (0 = not emitted)
         float rdx = 0.f, rdy = 0.f, rdz = 0.f;              // recoil-proton direction
@@ -1094,7 +1183,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 base = bcast0(base);
                 if (inc_ev) {
                     const unsigned long long idx = base + (unsigned long long)mbcnt(bm);
-                    if (idx < L->inc_cap) {
+                    if (idx < L->q_cap) {   // (the event list's capacity too)
                         GLOBAL u32x4* e4 = reinterpret_cast<GLOBAL u32x4*>(
                             reinterpret_cast<GLOBAL unsigned char*>(gbl(L->inc_ev)) + idx * 64ull);
                         e4[0] = u32x4{__float_as_uint(ox), __float_as_uint(oy), __float_as_uint(oz),
@@ -1182,6 +1271,19 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             }
         }
             }
+        if (chunk) {
+            // the protons that go on to the ring, the wave's own lanes back
+            const unsigned long long m = __ballot(alive);
+            if (m != 0ull) {
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(cont_produced, (uint32_t)__popcll(m));
+                base = __builtin_amdgcn_readfirstlane(base) + (uint32_t)mbcnt(m);
+                const uint32_t ring = EvQueue::ring(blockDim.x);
+                if (alive) save_state(ev_entry(3u * blockDim.x + (base & (ring - 1u))));
+            }
+            load_state(ev_entry(2u * blockDim.x + threadIdx.x));
+            it += kEventIters;
+        }
         }
     }   // iterations of one epoch
     // epoch end: every wave reports its alive lanes (pending events
@@ -1228,13 +1330,17 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         }
     }
     // publish what the lanes queued this epoch (written before the barrier
-    // above); the workgroup is done when the work list is exhausted, no lane
-    // is alive and every published entry has been taken
+    // above; the counts change again only after the next one); the workgroup is
+    // done when the work list is exhausted, no lane is alive and every published
+    // entry has been taken
+    loc_av = min(*loc_produced, (uint32_t)L->loc_cap);
+    cont_av = *cont_produced;
+    ev_ready = L->ev_pushed - ev_base;
+    ev_base += ev_ready;
+    ev_ready = min(ev_ready, blockDim.x);
     if (threadIdx.x == 0) {
-        const uint32_t lcap = (uint32_t)L->loc_cap;
-        const uint32_t prod = min(*loc_produced, lcap);
-        *loc_avail = prod;
-        const bool done = *wg_state != 0u && *wg_busy == 0u && *loc_claimed >= prod;
+        const bool done = *wg_state != 0u && *wg_busy == 0u && *loc_claimed >= loc_av &&
+                          L->cont_claimed == cont_av && ev_ready == 0u;
         const bool stop = !done && epoch >= kMaxEpochs;
         if (stop) atomicAdd(&L->counters[kCtrAborted], 1ull);
         if (done || stop) *wg_state = 2u;
