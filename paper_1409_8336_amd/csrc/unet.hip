@@ -125,7 +125,7 @@ struct pmc_unet {
     // gradients
     Act g_d1, g_d2, g_e1s, g_d3, g_e2s, g_e4, g_e3s, g_p3, g_p2, g_p1;
     float* out = nullptr;     // FP32 network output (denoised dose)
-    float* scale = nullptr;
+    float* scale = nullptr;          // the maximum dose, then the shares it came from (kParts)
     unsigned int* region = nullptr;   // kParts counts of voxels in the dose region (loss normalisation)
     // pinned host memory the kernels write to: the workgroups' shares of the
     // loss (2 kParts) and of the squared gradient norm (kParts)
@@ -225,7 +225,6 @@ hipError_t forward(pmc_unet* u, const float* dose, const float* rho, float* out,
 {
     hipError_t e;
     const size_t nv = u->x.nvox;
-    if ((e = hipMemsetAsync(u->scale, 0, sizeof(float), s)) != hipSuccess) return e;
     if ((e = nn_make_input(dose, rho, u->scale, u->x.p, nv, u->N, u->D, u->H, u->W, d, h, w, s)) != hipSuccess)
         return e;
     if ((e = enc_fwd(u, u->conv[0], u->x, u->e1, &u->p1, 0, s)) != hipSuccess) return e;
@@ -363,7 +362,7 @@ pmc_status pmc_unet_create(pmc_unet** out, int device, int n, int d, int h, int 
     A(act(u, u->g_p2, 2, 32));
     A(act(u, u->g_p1, 1, 16));
     A(ualloc(u, &u->out, u->x.nvox));
-    A(ualloc(u, &u->scale, 1));
+    A(ualloc(u, &u->scale, 1 + kParts));
     A(ualloc(u, &u->region, kParts));
     A(hipHostMalloc((void**)&u->loss, 3 * kParts * sizeof(double), hipHostMallocDefault));
     u->gnorm2 = u->loss + 2 * kParts;

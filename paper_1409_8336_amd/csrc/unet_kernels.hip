@@ -697,39 +697,6 @@ __global__ void __launch_bounds__(256) grad_relu_kernel(const uint16_t* src, con
     add_bias_grad(acc, G, C, db);
 }
 
-// network input: x[v] = (dose[v] * inv_scale, density[v] * 0.5, 0 x 6), zero
-// outside the caller's grid
-__global__ void make_input_kernel(const float* __restrict__ dose, const float* __restrict__ rho,
-                                  const float* __restrict__ scale, uint16_t* __restrict__ x, size_t nvox, Region rg)
-{
-    const float inv = 1.0f / fmaxf(scale[0], 1e-30f);
-    for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < nvox; v += (size_t)gridDim.x * blockDim.x) {
-        const long long vc = rg.compact(v);
-        uint16_t* o = x + 8 * v;
-        o[0] = vc >= 0 ? f2bf(dose[vc] * inv) : (uint16_t)0;
-        o[1] = vc >= 0 ? f2bf(rho[vc] * 0.5f) : (uint16_t)0;
-#pragma unroll
-        for (int c = 2; c < 8; ++c) o[c] = 0;
-    }
-}
-
-// scale[0] = max_v dose[v]  (non-negative input; scale must start at 0);
-// one atomic per block
-__global__ void __launch_bounds__(256) max_kernel(const float* __restrict__ a, size_t n, float* __restrict__ scale)
-{
-    __shared__ float part[4];
-    float m = 0.f;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        m = fmaxf(m, a[i]);
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
-        atomicMax(reinterpret_cast<unsigned int*>(scale), __float_as_uint(m));
-    }
-}
-
 // Workgroups of the reductions below; each leaves its value in an array that
 // the next kernel (or the host) adds up, since atomics of all workgroups on
 // one address serialise at about 12 ns each (counting the dose region with
@@ -750,6 +717,43 @@ DEV void each_of(size_t n, const float* __restrict__ a, F f)
         for (int k = 0; k < 8; ++k) f(v[k]);
     }
     for (; i < n; i += stride) f(a[i]);
+}
+
+// parts[b] = max of workgroup b's voxels of a (non-negative input), 0 for none
+__global__ void __launch_bounds__(256) max_kernel(const float* __restrict__ a, size_t n, float* __restrict__ parts)
+{
+    __shared__ float part[4];
+    float m = 0.f;
+    each_of(n, a, [&](float v) { m = fmaxf(m, v); });
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) parts[blockIdx.x] = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+}
+
+// network input: x[v] = (dose[v] * inv_scale, density[v] * 0.5, 0 x 6), zero
+// outside the caller's grid; scale[0] = the maximum dose, from the n_parts <= 256
+// shares after it, which every workgroup reads again (one kernel for the maximum
+// with an atomic per workgroup, behind a clear of its target, took 16.5 us on
+// 160 x 128 x 128 voxels where the shares take 5).  Bound by its bytes: 24 per
+// voxel, 13 us.
+__global__ void __launch_bounds__(256) make_input_kernel(const float* __restrict__ dose, const float* __restrict__ rho,
+                                                         float* __restrict__ scale, int n_parts,
+                                                         uint4* __restrict__ x, size_t nvox, Region rg)
+{
+    __shared__ float part[4];
+    float m = (int)threadIdx.x < n_parts ? scale[1 + threadIdx.x] : 0.f;
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+    if (blockIdx.x == 0 && threadIdx.x == 0) scale[0] = m;
+    const float inv = 1.0f / fmaxf(m, 1e-30f);
+    for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < nvox; v += (size_t)gridDim.x * blockDim.x) {
+        const long long vc = rg.compact(v);
+        const uint32_t both = vc >= 0 ? (uint32_t)f2bf(dose[vc] * inv) | (uint32_t)f2bf(rho[vc] * 0.5f) << 16 : 0u;
+        x[v] = make_uint4(both, 0u, 0u, 0u);
+    }
 }
 
 // part[b] = workgroup b's number of voxels with dose >= frac * scale (the dose
@@ -1099,15 +1103,18 @@ hipError_t nn_grad_relu(const uint16_t* src, const uint16_t* dpool, const uint16
     return hipGetLastError();
 }
 
-// nvox: voxels of the network grid; the region gives the caller's (compact)
+// scale: 1 + kParts floats, the first the maximum dose; nvox: voxels of the
+// network grid; the region gives the caller's (compact)
 // grid inside it, whose ncomp = n d h w voxels hold dose and density
 hipError_t nn_make_input(const float* dose, const float* rho, float* scale, uint16_t* x, size_t nvox, int N, int D,
                          int H, int W, int d, int h, int w, hipStream_t s)
 {
     const Region rg{D, H, W, d, h, w};
     const size_t ncomp = (size_t)N * d * h * w;
-    hipLaunchKernelGGL(max_kernel, dim3(grid_for(ncomp, 256, 1024)), dim3(256), 0, s, dose, ncomp, scale);
-    hipLaunchKernelGGL(make_input_kernel, dim3(grid_for(nvox)), dim3(256), 0, s, dose, rho, scale, x, nvox, rg);
+    const unsigned parts = grid_for(ncomp, 256, kParts);
+    hipLaunchKernelGGL(max_kernel, dim3(parts), dim3(256), 0, s, dose, ncomp, scale + 1);
+    hipLaunchKernelGGL(make_input_kernel, dim3(grid_for(nvox, 256, 2048)), dim3(256), 0, s, dose, rho, scale, (int)parts,
+                       reinterpret_cast<uint4*>(x), nvox, rg);
     return hipGetLastError();
 }
 
