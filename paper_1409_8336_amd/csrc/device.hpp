@@ -219,6 +219,19 @@ struct KernelArgs {
     uint32_t* q_ev;
 };
 
+// Ranges of 8-byte words that one launch clears.
+struct ZeroRanges {
+    unsigned long long* p[kMaxPlans + 1];
+    unsigned long long n[kMaxPlans + 1];
+    int count = 0;
+    ZeroRanges& add(void* at, size_t words)
+    {
+        p[count] = static_cast<unsigned long long*>(at);
+        n[count++] = words;
+        return *this;
+    }
+};
+
 // A workgroup's part of q_ev, in entries of one proton: two event lists of a
 // block each (pushed in one epoch, worked in the next), the parking places of the
 // block's lanes while they work an event, and the ring of protons that continue

@@ -31,7 +31,7 @@ hipError_t transport_max_block(bool multi, uint32_t flags, int* max_threads);
 hipError_t launch_stats(const double* tally, const uint2* vox, int nx, int ny, int nz, int K, int planes, bool lines,
                         double conv0, double* dose, double* var, double* dep_sum, double* let,
                         hipStream_t s);
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
+hipError_t launch_zero(const ZeroRanges& z, hipStream_t s);
 hipError_t launch_density(const uint2* vox, int nx, int ny, int nz, float* rho, hipStream_t s);
 hipError_t launch_atomic_probe(double* tally, int nx, int ny, int nz, int K, int grid,
                                unsigned long long per_lane, hipStream_t st);
@@ -126,22 +126,21 @@ struct pmc_ctx {
     // device tables
     DevBuf<float> d_blob, d_el_sig, d_npg, d_elem, d_mult, d_floc, d_xcdf, d_mucdf;
     // run buffers
-    DevBuf<double> d_dose, d_var, d_let, d_ledger;
+    DevBuf<double> d_dose, d_var, d_let;
     DevBuf<float> d_vav;       // Vavilov quantile table (PMC_VAVILOV)
     DevBuf<float> d_mol, d_molmat;  // Molière table and material constants (PMC_MOLIERE)
     DevBuf<uint32_t> d_q[2];
-    DevBuf<unsigned long long> d_gc, d_counters, d_order;
+    // a run's ledgers, counters, generation and event counts (cleared by one
+    // launch, read back in one copy), and its plans, work list and spots (one upload)
+    DevBuf<unsigned long long> d_ctl, d_up;
     DevBuf<uint32_t> d_qloc;   // per-workgroup secondary queues
     DevBuf<uint32_t> d_qev;    // per-workgroup event queues (EvQueue)
-    DevBuf<float> d_spots;
-    DevBuf<PlanDesc> d_plans;
     DevBuf<uint32_t> d_trace, d_trace_epochs;   // roofline replay: address trace (kTrace)
     // intranuclear cascade (PMC_INC): the six target nuclei, the event list
     // of a generation (IncEvent) and each generation's event count
     DevBuf<IncNucleus> d_inc_nuc;
     DevBuf<IncTab> d_inc_tab;
     DevBuf<IncEvent> d_inc_ev;
-    DevBuf<unsigned long long> d_inc_count;
     int inc_grid = 0;
     hipEvent_t ev_inc[2 * kMaxGenerations] = {};
     DevBuf<unsigned long long> d_sink;
@@ -470,15 +469,22 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     // one group (one tally column) while it moves across neighbouring spots.
     // The history index (random-number stream) and the group of every
     // primary are those of the spot-major numbering.
+    // The upload: plan descriptors, work list, spots.
     const size_t ns1 = (size_t)n_spots + 1;
-    std::vector<unsigned long long> order((size_t)K * ns1 + (size_t)K * n_spots + 1, 0ull);
+    const size_t plan_words = (size_t)np * (sizeof(PlanDesc) / 8);
+    const size_t order_words = (size_t)K * ns1 + (size_t)K * n_spots + 1;
+    std::vector<unsigned long long> up(plan_words + order_words + (sp.size() + 1) / 2, 0ull);
+    unsigned long long* const order = up.data() + plan_words;
+    std::memcpy(order + order_words, sp.data(), sp.size() * 4);
     {
         unsigned long long at = 0;
+        std::vector<unsigned long long> from(n_spots, 0ull);   // ceil(b n / K)
         for (int b = 0; b < K; ++b) {
             for (int s2 = 0; s2 < n_spots; ++s2) {
                 const unsigned long long n = start[s2 + 1] - start[s2];
-                const unsigned long long p0 = ((unsigned long long)b * n + K - 1) / K;
+                const unsigned long long p0 = from[s2];
                 const unsigned long long p1 = ((unsigned long long)(b + 1) * n + K - 1) / K;
+                from[s2] = p1;
                 order[b * ns1 + s2] = at;
                 order[(size_t)K * ns1 + (size_t)b * n_spots + s2] = first[s2] + p0;
                 at += p1 - p0;
@@ -506,25 +512,33 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     }
     HIPCHK(c->d_q[0].ensure(cap * kQueuePlanes), "alloc queue");
     HIPCHK(c->d_q[1].ensure(cap * kQueuePlanes), "alloc queue");
-    HIPCHK(c->d_gc.ensure(2 * (kMaxGenerations + 2)), "alloc counters");
-    HIPCHK(c->d_counters.ensure((size_t)kPlanCounters * np), "alloc counters");
-    HIPCHK(c->d_ledger.ensure(4 * np), "alloc ledger");
-    HIPCHK(c->d_spots.ensure(sp.size()), "alloc spots");
-    HIPCHK(c->d_order.ensure(order.size()), "alloc spots");
-    HIPCHK(c->d_plans.ensure(np), "alloc plans");
-    HIPCHK(hipMemcpyAsync(c->d_spots.p, sp.data(), sp.size() * 4, hipMemcpyHostToDevice, st), "upload spots");
-    HIPCHK(hipMemcpyAsync(c->d_order.p, order.data(), order.size() * 8, hipMemcpyHostToDevice, st), "upload spots");
-    HIPCHK(hipMemcpyAsync(c->d_plans.p, pd.data(), np * sizeof(PlanDesc), hipMemcpyHostToDevice, st), "upload plans");
+    const bool inc = (c->p.flags & kInc) != 0u;
+    // control words: ledgers [np][4] (double), counters [np][kPlanCounters],
+    // generation counts, and with the cascade per generation the events recorded
+    // and then the eight claim counters of its kernel's waves
+    const size_t led_words = 4 * (size_t)np, cnt_words = (size_t)kPlanCounters * np;
+    constexpr size_t kGenWords = 2 * (kMaxGenerations + 2);
+    const size_t read_words = led_words + cnt_words + kGenWords;
+    const size_t ctl_words = read_words + (inc ? 9 * (size_t)kMaxGenerations : 0);
+    if (read_words * 8 > kPinnedBytes) return fail(c, PMC_ERR_ARG, "too many plans");
+    HIPCHK(c->d_ctl.ensure(ctl_words), "alloc counters");
+    HIPCHK(c->d_up.ensure(up.size()), "alloc spots");
+    double* const d_ledger = reinterpret_cast<double*>(c->d_ctl.p);
+    unsigned long long* const d_counters = c->d_ctl.p + led_words;
+    unsigned long long* const d_gc = d_counters + cnt_words;
+    unsigned long long* const d_inc_count = c->d_ctl.p + read_words;
+    const PlanDesc* const d_plans = reinterpret_cast<const PlanDesc*>(c->d_up.p);
+    std::memcpy(up.data(), pd.data(), np * sizeof(PlanDesc));
+    HIPCHK(hipMemcpyAsync(c->d_up.p, up.data(), up.size() * 8, hipMemcpyHostToDevice, st), "upload spots");
     HIPCHK(hipEventRecord(c->ev0, st), "event");
-    for (int p = 0; p < np; ++p)
-        HIPCHK(launch_zero(pd[p].tally, plans[p].g->lines() * kLine * planes * 8, st), "zero tally");
-    HIPCHK(launch_zero(c->d_gc.p, c->d_gc.n * 8, st), "zero counters");
-    HIPCHK(launch_zero(c->d_counters.p, 8 * (size_t)kPlanCounters * np, st), "zero counters");
-    HIPCHK(launch_zero(c->d_ledger.p, 32 * (size_t)np, st), "zero ledger");
+    ZeroRanges zero;
+    for (int p = 0; p < np; ++p) zero.add(pd[p].tally, plans[p].g->lines() * kLine * planes);
+    zero.add(c->d_ctl.p, ctl_words);
+    HIPCHK(launch_zero(zero, st), "zero tally");
 
     KernelArgs a{};
     a.single = pd[0];
-    a.plans = c->d_plans.p;
+    a.plans = d_plans;
     a.n_plans = np;
     a.blob = c->d_blob.p;
     a.blob_words = (int)c->blob.size();
@@ -545,14 +559,14 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
         if (!narrow_index(q.g->nx, q.g->ny, q.g->nz, planes)) a.flags |= kWideIndex;
     a.f_mcs = (float)c->p.f_mcs;
     a.s_min = (float)c->p.s_min_cm;
-    a.spots = c->d_spots.p;
-    a.order = c->d_order.p;
+    a.order = c->d_up.p + plan_words;
+    a.spots = reinterpret_cast<const float*>(a.order + order_words);
     a.n_spots = n_spots;
     a.n_primary = total;
     a.q_cap = cap;
-    a.gen_counters = c->d_gc.p;
-    a.ledger = c->d_ledger.p;
-    a.counters = c->d_counters.p;
+    a.gen_counters = d_gc;
+    a.ledger = d_ledger;
+    a.counters = d_counters;
     a.refill_lanes = shape.refill;
     a.batch_events = shape.batch;
 
@@ -580,7 +594,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     std::string why = plan_layout(lq, &lay);
     if (!why.empty()) return fail(c, PMC_ERR_ARG, "launch layout: " + why);
     if (lay.blob_words != a.blob_words || lay.pd_off != a.pd_offset || lay.q_cap != cap ||
-        lay.planes != planes || lay.order_words != order.size())
+        lay.planes != planes || lay.order_words != order_words)
         return fail(c, PMC_ERR_DEVICE, "internal: launch layout disagrees with the run's buffers");
     const int slots = lay.cache_slots;
     a.cache_lines = lay.cache_lines;
@@ -647,15 +661,10 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     }
     // non-elastic events by the intranuclear cascade: one event list per
     // generation, worked by the cascade kernel right after the transport
-    const bool inc = (a.flags & kInc) != 0u;
     if (inc) {
         pmc_status si = ensure_inc(c);
         if (si != PMC_OK) return si;
         HIPCHK(c->d_inc_ev.ensure(cap), "alloc event list");
-        // per generation: events recorded; then per generation the eight
-        // claim counters of the cascade kernel's waves
-        HIPCHK(c->d_inc_count.ensure(9 * kMaxGenerations), "alloc event counters");
-        HIPCHK(launch_zero(c->d_inc_count.p, 9 * kMaxGenerations * 8, st), "zero event counters");
         a.inc_ev = c->d_inc_ev.p;
     }
     const uint32_t run_flags = a.flags;
@@ -669,6 +678,25 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     // overflowed them, almost always nothing: launch one at a time, so that a
     // run is one launch unless its workgroup queues overflowed
     const int group = a.loc_cap > 0 ? 1 : kGenGroup;
+    // the run's outputs and the read-back of its counts
+    auto finish = [&]() -> pmc_status {
+        for (int p = 0; p < np && !tuning; ++p) {
+            const Geometry& g = *plans[p].g;
+            const double vol = (double)g.vs[0] * g.vs[1] * g.vs[2];
+            const double conv0 = wtot[p] > 0.0 ? 1.602176634e-10 / (vol * wtot[p]) : 0.0;
+            HIPCHK(launch_stats(g.tally.p, g.vox.p, g.nx, g.ny, g.nz, K, planes, slots > 0, conv0, plans[p].d_dose,
+                                plans[p].d_var, d_ledger + 4 * p + 3, plans[p].d_let, st), "stats launch");
+        }
+        HIPCHK(hipEventRecord(c->ev1, st), "event");
+        HIPCHK(hipMemcpyAsync(c->h_pinned, c->d_ctl.p, read_words * 8, hipMemcpyDeviceToHost, st), "read counters");
+        HIPCHK(hipStreamSynchronize(st), "run");
+        return PMC_OK;
+    };
+    // with a launch per generation the first one is almost always the only one:
+    // its outputs follow it without waiting for its count, and are made again
+    // after the later ones where there are any (the wait took 25 to 45 us)
+    const bool at_once = group == 1 && !inc;
+    bool finished = false;
     if (total > 0) {
         bool done = false;
         while (!done) {
@@ -683,17 +711,17 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
                 a.q_in = c->d_q[gidx & 1].p;
                 a.q_out = c->d_q[(gidx + 1) & 1].p;
                 a.flags = run_flags | (trace && gidx == 0 ? kTrace : 0u);
-                a.inc_count = inc ? c->d_inc_count.p + gidx : nullptr;
+                a.inc_count = inc ? d_inc_count + gidx : nullptr;
                 HIPCHK(hipEventRecord(c->ev_gen[2 * gidx], st), "event");
                 HIPCHK(launch_transport(a, multi, grid, block, lds, st), "transport launch");
                 HIPCHK(hipEventRecord(c->ev_gen[2 * gidx + 1], st), "event");
                 if (inc) {
                     // this generation's events; their protons join the next
                     // generation's queue
-                    IncLaunch il{c->d_inc_ev.p, c->d_inc_count.p + gidx, cap, c->d_inc_nuc.p, c->d_inc_tab.p,
-                                 c->d_inc_count.p + kMaxGenerations + 8 * gidx, c->d_plans.p,
-                                 np, K, let ? 1 : 0, a.q_out, cap, &c->d_gc.p[2 * (gidx + 1)],
-                                 c->d_ledger.p, c->d_counters.p, slots > 0 ? 0 : planes};
+                    IncLaunch il{c->d_inc_ev.p, d_inc_count + gidx, cap, c->d_inc_nuc.p, c->d_inc_tab.p,
+                                 d_inc_count + kMaxGenerations + 8 * gidx, d_plans,
+                                 np, K, let ? 1 : 0, a.q_out, cap, &d_gc[2 * (gidx + 1)],
+                                 d_ledger, d_counters, slots > 0 ? 0 : planes};
                     HIPCHK(hipEventRecord(c->ev_inc[2 * gidx], st), "event");
                     HIPCHK(launch_inc_transport(il, c->inc_grid, st), "cascade launch");
                     HIPCHK(hipEventRecord(c->ev_inc[2 * gidx + 1], st), "event");
@@ -701,11 +729,19 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
             }
             launched = g1;
             // produced counts of generations g0+1 .. g1: words 2(g0+1) .. 2 g1
-            HIPCHK(hipMemcpyAsync(c->h_pinned, c->d_gc.p + 2 * (g0 + 1), 8 * (2 * (g1 - g0) - 1),
-                                  hipMemcpyDeviceToHost, st), "read counters");
-            HIPCHK(hipStreamSynchronize(st), "transport");
+            const unsigned long long* produced = c->h_pinned;
+            if (at_once && g0 == 0) {
+                const pmc_status sf = finish();
+                if (sf != PMC_OK) return sf;
+                finished = true;
+                produced = c->h_pinned + led_words + cnt_words + 2;
+            } else {
+                HIPCHK(hipMemcpyAsync(c->h_pinned, d_gc + 2 * (g0 + 1), 8 * (2 * (g1 - g0) - 1), hipMemcpyDeviceToHost, st),
+                       "read counters");
+                HIPCHK(hipStreamSynchronize(st), "transport");
+            }
             for (int gidx = g0; gidx < g1; ++gidx) {
-                const unsigned long long prod = c->h_pinned[2 * (gidx - g0)];
+                const unsigned long long prod = produced[2 * (gidx - g0)];
                 ++gens;
                 produced_total += prod;
                 if (prod > cap) overflow_n += prod - cap;
@@ -716,21 +752,15 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
             }
         }
     }
-    if (!tuning) {
-        for (int p = 0; p < np; ++p) {
-            const Geometry& g = *plans[p].g;
-            const double vol = (double)g.vs[0] * g.vs[1] * g.vs[2];
-            const double conv0 = wtot[p] > 0.0 ? 1.602176634e-10 / (vol * wtot[p]) : 0.0;
-            HIPCHK(launch_stats(g.tally.p, g.vox.p, g.nx, g.ny, g.nz, K, planes, slots > 0, conv0, plans[p].d_dose, plans[p].d_var,
-                                c->d_ledger.p + 4 * p + 3, plans[p].d_let, st), "stats launch");
+    if (!finished || launched > 1) {
+        if (finished && !tuning) {
+            ZeroRanges sums;   // the deposited energies, added up again
+            for (int p = 0; p < np; ++p) sums.add(d_ledger + 4 * p + 3, 1);
+            HIPCHK(launch_zero(sums, st), "zero ledger");
         }
+        const pmc_status sf = finish();
+        if (sf != PMC_OK) return sf;
     }
-    HIPCHK(hipEventRecord(c->ev1, st), "event");
-    const size_t led_words = 4 * (size_t)np, cnt_words = (size_t)kPlanCounters * np;
-    if ((led_words + cnt_words) * 8 > kPinnedBytes) return fail(c, PMC_ERR_ARG, "too many plans");
-    HIPCHK(hipMemcpyAsync(c->h_pinned, c->d_ledger.p, led_words * 8, hipMemcpyDeviceToHost, st), "read ledger");
-    HIPCHK(hipMemcpyAsync(c->h_pinned + led_words, c->d_counters.p, cnt_words * 8, hipMemcpyDeviceToHost, st), "read counters");
-    HIPCHK(hipStreamSynchronize(st), "run");
     float ms = 0.f;
     HIPCHK(hipEventElapsedTime(&ms, c->ev0, c->ev1), "event time");
     double transport_ms = 0.0, first_ms = 0.0, inc_ms = 0.0;
@@ -747,7 +777,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     if (inc && launched > 0) {
         // events beyond the list's capacity were counted as overflow
         std::vector<unsigned long long> ec(launched);
-        HIPCHK(hipMemcpy(ec.data(), c->d_inc_count.p, 8 * (size_t)launched, hipMemcpyDeviceToHost), "read events");
+        HIPCHK(hipMemcpy(ec.data(), d_inc_count, 8 * (size_t)launched, hipMemcpyDeviceToHost), "read events");
         for (int gidx = 0; gidx < launched; ++gidx)
             if (ec[gidx] > cap) overflow_n += ec[gidx] - cap;
     }
@@ -1341,7 +1371,7 @@ pmc_status pmc_roofline_replay(pmc_ctx* c, const pmc_spot* spots, int n_spots, u
         tr.iters = need + 4096;
     }
     HIPCHK(c->d_sink.ensure(2), "alloc sink");
-    HIPCHK(launch_zero(c->d_sink.p, 16, st), "zero sink");
+    HIPCHK(launch_zero(ZeroRanges().add(c->d_sink.p, 2), st), "zero sink");
     HIPCHK(launch_count_steps(c->d_trace.p, tr.iters * tr.lanes, c->d_sink.p + 1, st), "count trace");
     unsigned long long traced = 0;
     HIPCHK(hipMemcpyAsync(&traced, c->d_sink.p + 1, 8, hipMemcpyDeviceToHost, st), "read count");
@@ -1445,7 +1475,7 @@ pmc_status pmc_stream_probe(pmc_ctx* c, uint64_t bytes, void* hip_stream, double
     HIPCHK(a.ensure(bytes / 16), "alloc probe");
     HIPCHK(b.ensure(bytes / 16), "alloc probe");
     HIPCHK(c->d_sink.ensure(2), "alloc sink");
-    HIPCHK(launch_zero(a.p, bytes, st), "fill probe");
+    HIPCHK(launch_zero(ZeroRanges().add(a.p, bytes / 8), st), "fill probe");
     const int grid = 8 * c->num_cu;
     for (int which = 0; which < 2; ++which) {
         double best = 1e300;

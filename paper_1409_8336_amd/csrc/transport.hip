@@ -1557,8 +1557,11 @@ __global__ void __launch_bounds__(kStatsTile* kStatsTile) density_kernel(const u
     }
 }
 
-__global__ void zero_kernel(unsigned long long* __restrict__ p, unsigned long long n)
+// clears 8-byte words of up to kMaxPlans + 1 ranges (blockIdx.y) in one launch
+__global__ void __launch_bounds__(256) zero_kernel(ZeroRanges z)
 {
+    unsigned long long* const p = z.p[blockIdx.y];
+    const unsigned long long n = z.n[blockIdx.y];
     for (unsigned long long i = blockIdx.x * (unsigned long long)blockDim.x + threadIdx.x; i < n;
          i += (unsigned long long)gridDim.x * blockDim.x)
         p[i] = 0ull;
@@ -1660,14 +1663,13 @@ hipError_t launch_density(const uint2* vox, int nx, int ny, int nz, float* rho, 
     return hipGetLastError();
 }
 
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t s)
+hipError_t launch_zero(const ZeroRanges& z, hipStream_t s)
 {
-    const unsigned long long n = bytes / 8;
-    if (n == 0) return hipSuccess;
-    unsigned long long blocks = (n + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks), dim3(256), 0, s,
-                       (unsigned long long*)p, n);
+    unsigned long long most = 0;
+    for (int r = 0; r < z.count; ++r) most = std::max(most, z.n[r]);
+    if (most == 0) return hipSuccess;
+    const unsigned long long blocks = std::min((most + 255) / 256, 16384ull / (unsigned)z.count);
+    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks, (unsigned)z.count), dim3(256), 0, s, z);
     return hipGetLastError();
 }
 
