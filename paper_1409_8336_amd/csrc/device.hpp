@@ -50,6 +50,14 @@ constexpr int kOffInvOwn = 2512;
 constexpr int kOffSigma = 3024;      // n_mat x 1000 total cross section per gram
 // then n_mat x 4 words: f (Eq. 1; 1 for own-table bins), X0 (g/cm^2), Z/A, own flag
 
+// secondary-proton tables in one array, by nucleus and energy row: multiplicity
+// CDF [6][25][5], local fraction [6][25], energy CDF [6][25][33], angle CDF [6][25][33]
+constexpr int kSecMultAt = 0;
+constexpr int kSecFlocAt = kSecMultAt + 6 * 25 * 5;
+constexpr int kSecXAt = kSecFlocAt + 6 * 25;
+constexpr int kSecMuAt = kSecXAt + 6 * 25 * 33;
+constexpr int kSecWords = kSecMuAt + 6 * 25 * 33;
+
 // Run flag set by the engine (beside the public PMC_NO_* switches, bits 0-2)
 // when LET_d is scored: the tally of a plan then holds, after the planes of
 // its k_batches dose groups, two more: the LET
@@ -103,14 +111,11 @@ static_assert(sizeof(PlanDesc) == 64, "PlanDesc is 16 words");
 // start of the transport kernel and read there at their use sites, so that
 // they do not hold scalar registers across the loop.
 struct alignas(8) LdsArgs {
+    float range_c[2][4]; // water, own: range at grid point 1, ln of it, coarse-index cells per unit ln(range)
     const float* el_sig;
     const float* mat_npg;
     const float* elem;
-    const float* sec_mult;
-    const float* sec_floc;
-    const float* sec_x;
-    const float* sec_mu;
-    const float* spots;
+    const float* sec;    // secondary-proton tables (kSec...At)
     const unsigned long long* order;
     const float* vav;  // Vavilov straggling quantile table (flag PMC_VAVILOV), or NULL
     const float* mol;     // Molière sampling table (flag PMC_MOLIERE), or NULL
@@ -145,10 +150,7 @@ struct KernelArgs {
     const float* el_sig;    // [2][7][1000] barn, process 0 elastic, 1 non-elastic
     const float* mat_npg;   // [n_mat][7] nuclei per gram per barn
     const float* elem;      // [7][8]: target mass MeV, a1, b1, a2, b2 (Eq. 3)
-    const float* sec_mult;  // [6][25][5]
-    const float* sec_floc;  // [6][25]
-    const float* sec_x;     // [6][25][33]
-    const float* sec_mu;    // [6][25][33]
+    const float* sec;       // secondary-proton tables (kSec...At)
     const float* vav;       // [5][31][97] Vavilov quantiles (flag PMC_VAVILOV), or NULL
     const float* mol;       // [13][161] Molière ln R (flag PMC_MOLIERE), or NULL
     const float* molmat;    // [n_mat][16] Molière material constants
@@ -163,8 +165,7 @@ struct KernelArgs {
     // group b of spot s starts (entry n_spots: where group b ends), and
     // order[K * (n_spots + 1) + b * n_spots + s] the history index within its
     // plan (the random-number stream) of that part's first history
-    const float* spots;
-    const unsigned long long* order;
+    const unsigned long long* order;   // followed by the spots
     int n_spots;
     unsigned long long n_primary;
     // secondary queues: plane p of entry i at q[p * q_cap + i]

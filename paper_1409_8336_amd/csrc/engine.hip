@@ -124,7 +124,7 @@ struct pmc_ctx {
     // geometries: slot 0 is pmc_load_geometry's, slots >= 1 from pmc_load_geometry_slot
     std::vector<std::unique_ptr<Geometry>> geoms;
     // device tables
-    DevBuf<float> d_blob, d_el_sig, d_npg, d_elem, d_mult, d_floc, d_xcdf, d_mucdf;
+    DevBuf<float> d_blob, d_el_sig, d_npg, d_elem, d_sec;
     // run buffers
     DevBuf<double> d_dose, d_var, d_let;
     DevBuf<float> d_vav;       // Vavilov quantile table (PMC_VAVILOV)
@@ -549,7 +549,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     a.ln_r1[0] = (float)c->water.ln_r1; a.ln_r1[1] = (float)own.ln_r1;
     a.inv_step[0] = (float)c->water.inv_step; a.inv_step[1] = (float)own.inv_step;
     a.el_sig = c->d_el_sig.p; a.mat_npg = c->d_npg.p; a.elem = c->d_elem.p;
-    a.sec_mult = c->d_mult.p; a.sec_floc = c->d_floc.p; a.sec_x = c->d_xcdf.p; a.sec_mu = c->d_mucdf.p;
+    a.sec = c->d_sec.p;
     a.vav = c->d_vav.p;
     a.mol = c->d_mol.p;
     a.molmat = c->d_molmat.p;
@@ -560,7 +560,6 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     a.f_mcs = (float)c->p.f_mcs;
     a.s_min = (float)c->p.s_min_cm;
     a.order = c->d_up.p + plan_words;
-    a.spots = reinterpret_cast<const float*>(a.order + order_words);
     a.n_spots = n_spots;
     a.n_primary = total;
     a.q_cap = cap;
@@ -1167,10 +1166,10 @@ pmc_status pmc_load_physics(pmc_ctx* c, const pmc_nuclear_data* nd)
     pmc_status s;
     if ((s = upload(c, c->d_el_sig, el, "upload cross sections")) != PMC_OK) return s;
     if ((s = upload(c, c->d_elem, elem, "upload element constants")) != PMC_OK) return s;
-    if ((s = upload(c, c->d_mult, c->mult, "upload multiplicities")) != PMC_OK) return s;
-    if ((s = upload(c, c->d_floc, c->floc, "upload local fractions")) != PMC_OK) return s;
-    if ((s = upload(c, c->d_xcdf, c->xcdf, "upload energy CDFs")) != PMC_OK) return s;
-    if ((s = upload(c, c->d_mucdf, c->mucdf, "upload angle CDFs")) != PMC_OK) return s;
+    std::vector<float> sec;
+    for (const std::vector<float>* v : {&c->mult, &c->floc, &c->xcdf, &c->mucdf}) sec.insert(sec.end(), v->begin(), v->end());
+    if (sec.size() != (size_t)kSecWords) return fail(c, PMC_ERR_DEVICE, "internal: secondary tables have another size");
+    if ((s = upload(c, c->d_sec, sec, "upload secondary tables")) != PMC_OK) return s;
     if (c->water.lnr.empty()) c->water = build_range_table(water_z_over_a(), kWaterIeV);
     c->have_phys = true;
     return upload_tables(c);

@@ -300,14 +300,15 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         L->el_sig = a.el_sig;
         L->mat_npg = a.mat_npg;
         L->elem = a.elem;
-        L->sec_mult = a.sec_mult;
-        L->sec_floc = a.sec_floc;
-        L->sec_x = a.sec_x;
-        L->sec_mu = a.sec_mu;
+        L->sec = a.sec;
+        for (int o = 0; o < 2; ++o) {
+            L->range_c[o][0] = a.r_first[o];
+            L->range_c[o][1] = a.ln_r1[o];
+            L->range_c[o][2] = a.inv_step[o];
+        }
         L->vav = a.vav;
         L->mol = a.mol;
         L->molmat = a.molmat;
-        L->spots = a.spots;
         L->order = a.order;
         L->q_in = a.q_in;
         L->q_out = a.q_out;
@@ -635,7 +636,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         }
                         *work_at = (uint32_t)part;
                         const int bg = (int)((uint32_t)part / (uint32_t)ns1), lo = part - bg * ns1;
-                        const GLOBAL float* sp = gbl(L->spots) + 8 * lo;
+                        // (the spots follow the list: K (2 n_spots + 1) + 1 words)
+                        const GLOBAL float* sp = reinterpret_cast<const GLOBAL float*>(ord + (int)K * (2 * nsp + 1) + 1) + 8 * lo;
                         const unsigned long long uid = ord[(int)K * ns1 + bg * nsp + lo] + (idx - start);
                         if constexpr (kMulti) {
                             const uint32_t np = __float_as_uint(sp[6]);
@@ -700,6 +702,10 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         if (__ballot(alive) == 0ull && exhausted) it = a.epoch_iters;
 
         // ------------------------------------------------------------ step
+        // (tested where they are used: hoisted out of the loop, the tests are
+        // 64-bit masks that spill to vector lanes)
+        uint32_t step_flags = flags;
+        asm volatile("" : "+s"(step_flags));
         bool stepped = false, short_step = false;
         uint32_t tr_key = kTraceNone;   // measurement trace (flag kTrace)
         if (alive && !pend) {
@@ -751,16 +757,18 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             // (table offsets selected, not pointers: the addresses stay LDS ones)
             const float* lnr = lds + (own ? kOffLnrOwn : kOffLnrWater);
             const uint16_t* inv = lds16 + 2 * (own ? kOffInvOwn : kOffInvWater);
-            const float r_first = own ? a.r_first[1] : a.r_first[0];
-            const float ln_r1 = own ? a.ln_r1[1] : a.ln_r1[0];
-            const float inv_step = own ? a.inv_step[1] : a.inv_step[0];
+            // (from LDS by the lane's table: as scalars the six constants, the
+            // selects and the spilled flag tests took 20 vector instructions of
+            // 620, the launch of 1e7 histories of 2000 spots 14.9 ms, not 14.2)
+            const float* rc = L->range_c[own ? 1 : 0];
+            const float r_first = rc[0], ln_r1 = rc[1], inv_step = rc[2];
 
             const float l_a = own ? lo0 : lw0, l_b = own ? lo1 : lw1;
             const float range_tab = fexp(l_a + gt * (l_b - l_a));
             const float range = gi == 0 ? gt * r_first : range_tab;
             const float s_range = range * frcp(scale);
             float sigma = 0.f;
-            if (!(flags & kNoNuclear)) {
+            if (!(step_flags & kNoNuclear)) {
                 const float* sm = sig + 1000 * m;
                 sigma = rho * (sm[gi] + gt * (sm[gi + 1] - sm[gi]));
             }
@@ -816,11 +824,11 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             const float pv = emid * (emid + 2.f * kMp) * ie_tot;      // p beta c
             const float b2 = pv * ie_tot;
             float de = de_mean;
-            if (!(flags & kNoStraggle)) {
+            if (!(step_flags & kNoStraggle)) {
                 const float g = e_tot * (1.0f / kMp);
                 const float var = kStraggleK * rho * mza * s * g * g * (1.f - 0.5f * b2);
                 float z = 1.414213562f * inv_erf(2.f * u01(r.w) - 1.f);
-                if (kOpt && (flags & kVavilov)) {
+                if (kOpt && (step_flags & kVavilov)) {
                     // Vavilov-Gaussian (Sec. II.A.2): the normal score through
                     // the Vavilov quantile function of the step's kappa =
                     // xi / T_max and beta^2, tabulated at log10 kappa = -2 +
@@ -852,9 +860,9 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 de = de < 0.f ? 0.f : (de > E ? E : de);
             }
             float theta = 0.f;
-            if (!(flags & kNoMcs)) {
+            if (!(step_flags & kNoMcs)) {
                 bool moliere = false;
-                if (kOpt && (flags & kMoliere)) {
+                if (kOpt && (step_flags & kMoliere)) {
                     // Molière (Sec. II.A.2 option), Bethe's form: chi_c^2 =
                     // K m_e c^2 sum w Z(Z+1)/A rho s / (p beta)^2; the
                     // screening angle from the Z(Z+1)/A-weighted logs of the
@@ -936,7 +944,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             const float e_new = E - de;
             // range-limited: the proton stops in this voxel with all of E
             const double dep = stop_here ? (double)w * (double)E : (double)w * ((double)E - (double)e_new);
-            if (kOpt && (flags & kScoreLet)) {
+            if (kOpt && (step_flags & kScoreLet)) {
                 // LET_d numerator: the deposit times the medium's stopping
                 // power averaged over the step's mean loss (over the residual
                 // range when the range ends the step), MeV/cm
@@ -1129,12 +1137,12 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                     j = j > 24 ? 24 : j;
                     const int row = nu * 25 + j;
                     sec_row = row;
-                    const GLOBAL float* mc5 = gbl(L->sec_mult) + 5 * row;
+                    const GLOBAL float* mc5 = gbl(L->sec) + kSecMultAt + 5 * row;
                     const float um = u01(r4.x);
                     int n = 0;
                     while (n < 4 && !(um < mc5[n])) ++n;
-                    const float fl = gbl(L->sec_floc)[row];
-                    const GLOBAL float* xr = gbl(L->sec_x) + 33 * row;
+                    const float fl = gbl(L->sec)[kSecFlocAt + row];
+                    const GLOBAL float* xr = gbl(L->sec) + kSecXAt + 33 * row;
                     float sum = 0.f;
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
@@ -1230,7 +1238,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         const uint32_t jj = recoil ? 0u : (uint32_t)(c + 1);
                         if (!recoil) {
                             const uint4 rc = philox<!kMulti>(uid_lo, uid_hi, ks, 16u + jj, P.key_lo(plan), P.key_hi(plan));
-                            const float mu = inv_cdf33(gbl(L->sec_mu) + 33 * sec_row, u01(rc.y), -1.f, 1.f);
+                            const float mu = inv_cdf33(gbl(L->sec) + kSecMuAt + 33 * sec_row, u01(rc.y), -1.f, 1.f);
                             dx = odx;
                             dy = ody;
                             dz = odz;
