@@ -111,7 +111,9 @@ static_assert(sizeof(PlanDesc) == 64, "PlanDesc is 16 words");
 // start of the transport kernel and read there at their use sites, so that
 // they do not hold scalar registers across the loop.
 struct alignas(8) LdsArgs {
-    float range_c[2][4]; // water, own: range at grid point 1, ln of it, coarse-index cells per unit ln(range)
+    // range at grid point 1, ln of it, coarse-index cells per unit ln(range): 0..2
+    // water, 4..6 own; of a single plan 3, 7, 8 the voxel size, 9..11 its inverse
+    float c[12];
     const float* el_sig;
     const float* mat_npg;
     const float* elem;
@@ -120,11 +122,9 @@ struct alignas(8) LdsArgs {
     const float* vav;  // Vavilov straggling quantile table (flag PMC_VAVILOV), or NULL
     const float* mol;     // Molière sampling table (flag PMC_MOLIERE), or NULL
     const float* molmat;  // [n_mat][16] Molière material constants, or NULL
-    const uint32_t* q_in;
     uint32_t* q_out;
     unsigned long long q_cap;
     double* ledger;
-    unsigned long long* counters;
     uint32_t* q_loc;   // this launch's per-workgroup queues (loc_cap entries each)
     void* inc_ev;      // flag PMC_INC: this generation's event list (IncEvent entries)
     unsigned long long* inc_count;   // events recorded in it

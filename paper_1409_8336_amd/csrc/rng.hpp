@@ -52,7 +52,11 @@ __host__ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint3
 // and the difference is exact.
 __host__ __device__ __forceinline__ float u01(uint32_t x)
 {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint32_t bits = __builtin_amdgcn_alignbit(127u, x, 9u);   // {127, x} >> 9
+#else
     const uint32_t bits = (x >> 9) | 0x3F800000u;
+#endif
     return __builtin_bit_cast(float, bits) - 0x1.fffffep-1f;
 }
 

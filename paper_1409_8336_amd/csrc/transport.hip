@@ -104,11 +104,14 @@ DEV float inv_erf(float x)
 }
 
 // a * b + c for a, b < 2^24 at full rate (the compiler falls back to a
-// quarter-rate 64-bit multiply-add where it does not see the bounds)
+// 64-bit multiply-add and its moves where it does not see the bounds); kScalar:
+// b is the same for the wave
+template <bool kScalar>
 DEV uint32_t mad24(uint32_t a, uint32_t b, uint32_t c)
 {
     uint32_t d;
-    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    if constexpr (kScalar) asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(b), "v"(c));
+    else asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
     return d;
 }
 
@@ -157,10 +160,9 @@ DEV void grid_pos(float e, int& i, float& t)
     const float x = (fln(e) - kLnE0) * kInvH;
     int j = (int)x;
     j = j < 0 ? 0 : (j > 998 ? 998 : j);
-    float f = x - (float)j;
-    f = f < 0.f ? 0.f : (f > 1.f ? 1.f : f);
+    const float f = x - (float)j;
     i = j;
-    t = f;
+    t = __builtin_amdgcn_fmed3f(f, 0.f, 1.f);
 }
 
 // x at CDF value u of a 33-point table (CDF at lo + (hi - lo) i / 32, linear
@@ -198,12 +200,13 @@ template <>
 struct Plans<false> {
     const KernelArgs& a;
     const PlanDesc* pd;
+    const float* c;   // LdsArgs::c
     DEV int nx(uint32_t) const { return a.single.nx; }
     DEV int ny(uint32_t) const { return a.single.ny; }
     DEV int nz(uint32_t) const { return a.single.nz; }
     DEV uint32_t lines(uint32_t) const { return a.single.lines; }
-    DEV float vs(uint32_t, int i) const { return a.single.vs[i]; }
-    DEV float ivs(uint32_t, int i) const { return a.single.ivs[i]; }
+    DEV float vs(uint32_t, int i) const { return c[i == 0 ? 3 : 6 + i]; }
+    DEV float ivs(uint32_t, int i) const { return c[9 + i]; }
     DEV const uint2* vox(uint32_t) const { return a.single.vox; }
     DEV double* tally(uint32_t) const { return a.single.tally; }
     DEV uint32_t key_lo(uint32_t) const { return a.single.key_lo; }
@@ -214,6 +217,7 @@ template <>
 struct Plans<true> {
     const KernelArgs& a;
     const PlanDesc* pd;
+    const float* c;
     DEV int nx(uint32_t p) const { return pd[p].nx; }
     DEV int ny(uint32_t p) const { return pd[p].ny; }
     DEV int nz(uint32_t p) const { return pd[p].nz; }
@@ -238,13 +242,14 @@ constexpr int kEventIters = 3;
 // other one carries none of their code.  kWide: 64-bit voxel and tally
 // indices, for grids past the limits of narrow_index (always with kOpt: the
 // instantiation serves every run).  The narrow index is two 24-bit multiply-adds
-// at full rate instead of seven 64-bit steps at a quarter of it.
+// instead of seven 64-bit steps.
 //
-// Bound by vector instructions: about 460 of them per step, of which 75
-// (transcendentals, Philox's 64-bit products) at a quarter of the rate; the SIMDs
-// issue one in nine cycles of ten.  With 490 per step (64-bit indices, register
-// copies, two instructions per xor of three) the launch of 1e7 histories of 2000
-// spots took 18.7 ms instead of 17.8.
+// Bound by vector instructions: 377 to a step (single plan), every one of them
+// issued for the wave's 64 lanes of which 52 work; the SIMDs issue nine cycles of
+// ten.  1e7 histories of 2000 spots: with 490 a step (64-bit indices, register
+// copies, two instructions per xor of three, selects and spills of scalars) the
+// launch took 18.7 ms, with 460 17.8.  Lines of deposits (cache.hpp) and events in
+// full waves then brought it to 14.9 with 432 a step, 14.2 with 412, 13.8 with 377.
 template <bool kMulti, bool kOpt, bool kWide>
 __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
 {
@@ -302,19 +307,21 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         L->elem = a.elem;
         L->sec = a.sec;
         for (int o = 0; o < 2; ++o) {
-            L->range_c[o][0] = a.r_first[o];
-            L->range_c[o][1] = a.ln_r1[o];
-            L->range_c[o][2] = a.inv_step[o];
+            L->c[4 * o + 0] = a.r_first[o];
+            L->c[4 * o + 1] = a.ln_r1[o];
+            L->c[4 * o + 2] = a.inv_step[o];
         }
+        L->c[3] = a.single.vs[0];
+        L->c[7] = a.single.vs[1];
+        L->c[8] = a.single.vs[2];
+        for (int o = 0; o < 3; ++o) L->c[9 + o] = a.single.ivs[o];
         L->vav = a.vav;
         L->mol = a.mol;
         L->molmat = a.molmat;
         L->order = a.order;
-        L->q_in = a.q_in;
         L->q_out = a.q_out;
         L->q_cap = a.q_cap;
         L->ledger = a.ledger;
-        L->counters = a.counters;
         L->n_spots = a.n_spots;
         L->loc_cap = a.loc_cap;
         L->q_loc = a.q_loc + (size_t)blockIdx.x * (size_t)a.loc_cap * kLocEntryWords;
@@ -325,7 +332,10 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     }
     __syncthreads();
     const PlanDesc* pds = reinterpret_cast<const PlanDesc*>(lds + a.pd_offset);
-    const Plans<kMulti> P{a, pds};
+    auto counters_of = [&](uint32_t pl) {   // (the counters follow the plans' ledgers)
+        return reinterpret_cast<unsigned long long*>(L->ledger) + 4 * (kMulti ? a.n_plans : 1) + kPlanCounters * pl;
+    };
+    const Plans<kMulti> P{a, pds, L->c};
 
     const uint16_t* lds16 = reinterpret_cast<const uint16_t*>(lds);
     const float* sig = lds + kOffSigma;
@@ -354,7 +364,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     using Index = std::conditional_t<kWide, unsigned long long, uint32_t>;
     auto voxel_index = [&](uint32_t pl, int x, int y, int z) -> Index {
         if constexpr (kWide) return ((unsigned long long)y * P.nx(pl) + x) * P.nz(pl) + z;
-        else return mad24(mad24((uint32_t)y, (uint32_t)P.nx(pl), (uint32_t)x), (uint32_t)P.nz(pl), (uint32_t)z);
+        else return mad24<!kMulti>(mad24<!kMulti>((uint32_t)y, (uint32_t)P.nx(pl), (uint32_t)x), (uint32_t)P.nz(pl), (uint32_t)z);
     };
     auto voxel_record = [&](uint32_t pl, Index vi) {
         // (narrow: a 32-bit byte offset from the plan's base)
@@ -367,7 +377,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     auto tally_place = [&](uint32_t pl, int x, int y, int z, Index vi) -> Index {
         if (use_cache) return vi;
         if constexpr (kWide) return ((unsigned long long)z * P.ny(pl) + y) * P.nx(pl) + x;
-        else return mad24((uint32_t)z, (uint32_t)(P.nx(pl) * P.ny(pl)), mad24((uint32_t)y, (uint32_t)P.nx(pl), (uint32_t)x));
+        else return mad24<!kMulti>((uint32_t)z, (uint32_t)(P.nx(pl) * P.ny(pl)), mad24<!kMulti>((uint32_t)y, (uint32_t)P.nx(pl), (uint32_t)x));
     };
     auto element = [&](uint32_t pl, uint32_t b, Index at) -> Index {
         return use_cache ? (Index)P.lines(pl) * kLine * b + at : at * (Index)a.planes + b;
@@ -377,11 +387,13 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     float px = 0, py = 0, pz = 0, ux = 0, uy = 0, uz = 1, E = 0, mfp = 0, w = 0;
     uint32_t uid_lo = 0, uid_hi = 0, k = 0, batch = 0, plan = 0;
     int vx = 0, vy = 0, vz = 0;
-    bool alive = false, pend = false;
+    uint32_t life = 0u;   // 0 no proton, 1 in flight, 2 at a nuclear event
 
     // per-lane ledger and counters of the lane's current plan
     double acc_esc = 0.0, acc_neu = 0.0, acc_ovf = 0.0;
     uint32_t n_steps = 0, n_el = 0, n_ne = 0, n_short = 0, n_dep = 0, n_glob = 0, n_flush = 0, n_locq = 0;
+    // (of a single plan the wave's steps, short steps and their deposits: scalar)
+    unsigned long long wave_steps = 0, wave_short = 0, wave_dep = 0;
     auto flush = [&](uint32_t pl) {
         if constexpr (kMulti) {
             double* LG = wg_led + 3 * pl;
@@ -402,15 +414,15 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             return;
         }
         double* LG = L->ledger + 4 * pl;
-        unsigned long long* C = L->counters + kPlanCounters * pl;
+        unsigned long long* C = counters_of(pl);
         if (acc_esc != 0.0) unsafeAtomicAdd(&LG[0], acc_esc);
         if (acc_neu != 0.0) unsafeAtomicAdd(&LG[1], acc_neu);
         if (acc_ovf != 0.0) unsafeAtomicAdd(&LG[2], acc_ovf);
-        if (n_steps) atomicAdd(&C[0], (unsigned long long)n_steps);
+        if (wave_steps) atomicAdd(&C[0], wave_steps);
         if (n_el) atomicAdd(&C[1], (unsigned long long)n_el);
         if (n_ne) atomicAdd(&C[2], (unsigned long long)n_ne);
-        if (n_short) atomicAdd(&C[3], (unsigned long long)n_short);
-        if (n_dep) atomicAdd(&C[4], (unsigned long long)n_dep);
+        if (wave_short) atomicAdd(&C[3], wave_short);
+        if (wave_dep + n_dep) atomicAdd(&C[4], wave_dep + n_dep);
         if (n_glob) atomicAdd(&C[5], (unsigned long long)n_glob);
         if (n_flush) atomicAdd(&C[6], (unsigned long long)n_flush);
         if (n_locq) atomicAdd(&C[7], (unsigned long long)n_locq);
@@ -422,8 +434,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     // straight to the FP64 tally.  With a LET_d numerator (a step's deposit)
     // the numerator shares the dose's place in the line, or goes to the
     // numerator plane's element num_idx beside it.
-    auto deposit = [&](Index idx, double v, bool with_num = false, double num = 0.0, Index num_idx = 0) {
-        ++n_dep;
+    auto deposit = [&](Index idx, double v, bool step = false, bool with_num = false, double num = 0.0, Index num_idx = 0) {
+        if (kMulti || !step) ++n_dep;   // (a single plan's steps are counted by the wave)
         if (use_cache) {
             const uint32_t line = (uint32_t)(idx / kLine);
             Key key = (Key)line;
@@ -456,7 +468,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         q[0] = u32x4{__float_as_uint(px), __float_as_uint(py), __float_as_uint(pz), __float_as_uint(ux)};
         q[1] = u32x4{__float_as_uint(uy), __float_as_uint(uz), __float_as_uint(E), __float_as_uint(mfp)};
         q[2] = u32x4{__float_as_uint(w), uid_lo, uid_hi, k};
-        q[3] = u32x4{batch | plan << 8 | (uint32_t)alive << 16 | (uint32_t)pend << 17, (uint32_t)vx, (uint32_t)vy,
+        q[3] = u32x4{batch | plan << 8 | life << 16, (uint32_t)vx, (uint32_t)vy,
                      (uint32_t)vz};
     };
     auto load_state = [&](const GLOBAL u32x4* q) {
@@ -481,8 +493,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 plan = np;
             }
         }
-        alive = (e3.x >> 16 & 1u) != 0u;
-        pend = (e3.x >> 17 & 1u) != 0u;
+        life = e3.x >> 16;
         vx = (int)e3.y;
         vy = (int)e3.z;
         vz = (int)e3.w;
@@ -516,7 +527,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         // ---------------------------------------------------------- refill
         // idle lanes take first the published entries of the workgroup's own
         // queue, then indices of the generation's work list
-        const unsigned long long idle = __ballot(!alive);
+        const unsigned long long idle = __ballot(life == 0u);
         const int n_idle = __popcll(idle);
         if (n_idle > 0 && (n_idle == kWave || n_idle >= a.refill_lanes || exhausted)) {
             const int idle_rank = mbcnt(idle);
@@ -552,11 +563,11 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 base = bcast0(base);
                 if (claim_index(base + (unsigned long long)n_rest) >= limit) exhausted = true;
             }
-            if (!alive && idle_rank < (int)n_cont) {
+            if (life == 0u && idle_rank < (int)n_cont) {
                 // a proton that continues after its event
                 const uint32_t ring = EvQueue::ring(blockDim.x);
                 load_state(ev_entry(3u * blockDim.x + ((cont_base + (uint32_t)idle_rank) & (ring - 1u))));
-            } else if (!alive) {
+            } else if (life == 0u) {
                 const int rank = idle_rank - (int)n_cont;
                 bool got = false;
                 if (rank < (int)n_sec) {
@@ -662,7 +673,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                         mfp = -fln(u01(r.z));
                         batch = (uint32_t)bg;
                     } else {
-                        const GLOBAL uint32_t* q = gbl(L->q_in) + idx;
+                        const GLOBAL uint32_t* q = gbl(a.q_in) + idx;
                         const unsigned long long c = L->q_cap;
                         px = __uint_as_float(q[0]);
                         py = __uint_as_float(q[c]);
@@ -688,9 +699,10 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                 }
                 if (got) {
                     k = 0;
-                    alive = locate_axis(px, ux, P.nx(plan), vx) && locate_axis(py, uy, P.ny(plan), vy) &&
-                            locate_axis(pz, uz, P.nz(plan), vz);
-                    if (!alive) acc_esc += (double)w * (double)E;
+                    const bool inside = locate_axis(px, ux, P.nx(plan), vx) && locate_axis(py, uy, P.ny(plan), vy) &&
+                                        locate_axis(pz, uz, P.nz(plan), vz);
+                    life = inside ? 1u : 0u;
+                    if (!inside) acc_esc += (double)w * (double)E;
                 }
             }
         }
@@ -699,7 +711,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         // some 30 moves per iteration and 12 registers)
         // nothing to run: with the work list exhausted and nothing published
         // in the own queue, go to the epoch end
-        if (__ballot(alive) == 0ull && exhausted) it = a.epoch_iters;
+        if (__ballot(life != 0u) == 0ull && exhausted) it = a.epoch_iters;
 
         // ------------------------------------------------------------ step
         // (tested where they are used: hoisted out of the loop, the tests are
@@ -708,7 +720,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         asm volatile("" : "+s"(step_flags));
         bool stepped = false, short_step = false;
         uint32_t tr_key = kTraceNone;   // measurement trace (flag kTrace)
-        if (alive && !pend) {
+        const unsigned long long flying = __ballot(life == 1u);
+        if (life == 1u) {
             const Index vi = voxel_index(plan, vx, vy, vz);
             const Index ti = tally_place(plan, vx, vy, vz, vi);
             if constexpr (kOpt && !kMulti) tr_key = (uint32_t)element(plan, batch, ti);
@@ -757,10 +770,9 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             // (table offsets selected, not pointers: the addresses stay LDS ones)
             const float* lnr = lds + (own ? kOffLnrOwn : kOffLnrWater);
             const uint16_t* inv = lds16 + 2 * (own ? kOffInvOwn : kOffInvWater);
-            // (from LDS by the lane's table: as scalars the six constants, the
-            // selects and the spilled flag tests took 20 vector instructions of
-            // 620, the launch of 1e7 histories of 2000 spots 14.9 ms, not 14.2)
-            const float* rc = L->range_c[own ? 1 : 0];
+            // (from LDS by the lane's table: as scalars the six constants take
+            // twelve more instructions for moves and selects)
+            const float* rc = L->c + (own ? 4 : 0);
             const float r_first = rc[0], ln_r1 = rc[1], inv_step = rc[2];
 
             const float l_a = own ? lo0 : lw0, l_b = own ? lo1 : lw1;
@@ -857,7 +869,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                     }
                 }
                 de = de_mean + fsqrt(var) * z;
-                de = de < 0.f ? 0.f : (de > E ? E : de);
+                de = __builtin_amdgcn_fmed3f(de, 0.f, E);
             }
             float theta = 0.f;
             if (!(step_flags & kNoMcs)) {
@@ -943,15 +955,15 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             pz = on_face && axis == 2 ? face : pz;
             const float e_new = E - de;
             // range-limited: the proton stops in this voxel with all of E
-            const double dep = stop_here ? (double)w * (double)E : (double)w * ((double)E - (double)e_new);
+            const double dep = (double)w * ((double)E - (double)(stop_here ? 0.f : e_new));
             if (kOpt && (step_flags & kScoreLet)) {
                 // LET_d numerator: the deposit times the medium's stopping
                 // power averaged over the step's mean loss (over the residual
                 // range when the range ends the step), MeV/cm
                 const float l = stop_here ? (E - kECut) * frcp(s_range) : de_mean * frcp(s);
-                deposit(element(plan, batch, ti), dep, true, dep * (double)l, element(plan, K, ti));
+                deposit(element(plan, batch, ti), dep, true, true, dep * (double)l, element(plan, K, ti));
             } else {
-                deposit(element(plan, batch, ti), dep);
+                deposit(element(plan, batch, ti), dep, true);
             }
             // (a proton that stopped takes the new values too; it is refilled
             // before they are read)
@@ -965,12 +977,18 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             // non-terminating histories): deposit the rest
             const bool ends = stepped && (E <= kECut || k >= kMaxSteps);
             if (ends) deposit_local(ti, (double)w * (double)E);
-            alive = stepped && !ends && inside;
+            const bool goes_on = stepped && !ends && inside;
             if (stepped && !ends && !inside) acc_esc += (double)w * (double)E;
-            pend = alive && nuc;
+            life = goes_on ? (nuc ? 2u : 1u) : 0u;
         }
-        n_steps += stepped;
-        n_short += stepped && short_step;
+        if constexpr (kMulti) {
+            n_steps += stepped;
+            n_short += stepped && short_step;
+        } else {
+            wave_dep += (unsigned)__popcll(flying);
+            wave_steps += (unsigned)__popcll(__ballot(stepped));
+            wave_short += (unsigned)__popcll(__ballot(stepped && short_step));
+        }
         if constexpr (kOpt && !kMulti) {
             if (flags & kTrace) {
                 const unsigned long long n = (unsigned long long)epoch * (unsigned)a.epoch_iters + (unsigned)it;
@@ -981,8 +999,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         }
 
         // ------------------------------------------- batched nuclear events
-        const int np = __popcll(__ballot(pend));
-        const int occ = __popcll(__ballot(alive));
+        const int np = __popcll(__ballot(life == 2u));
+        const int occ = __popcll(__ballot(life != 0u));
         int need = occ >> 3;
         need = need < 1 ? 1 : need;
         need = need < a.batch_events ? need : a.batch_events;
@@ -992,17 +1010,15 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             uint32_t base = 0;
             if (lane == 0) base = atomicAdd(&L->ev_pushed, (uint32_t)np);
             base = __builtin_amdgcn_readfirstlane(base) - ev_base;
-            const uint32_t i = base + (uint32_t)mbcnt(__ballot(pend));
-            if (pend && i < blockDim.x) {
+            const uint32_t i = base + (uint32_t)mbcnt(__ballot(life == 2u));
+            if (life == 2u && i < blockDim.x) {
                 save_state(ev_entry((epoch & 1u) * blockDim.x + i));
-                alive = false;
-                pend = false;
+                life = 0u;
             }
         } else if (ripe || chunk) {
         if (chunk) {
             save_state(ev_entry(2u * blockDim.x + threadIdx.x));
-            alive = false;
-            pend = false;
+            life = 0u;
             if (threadIdx.x < ev_ready) load_state(ev_entry((~epoch & 1u) * blockDim.x + threadIdx.x));
         }
         int n_out = 0;
@@ -1018,8 +1034,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         int inc_el = 0;
         float inc_t = 0.f;
         Index inc_ti = 0;
-        if (pend) {
-            pend = false;
+        if (life == 2u) {
+            life = 1u;
             const Index vi = voxel_index(plan, vx, vy, vz);
             const Index ti = tally_place(plan, vx, vy, vz, vi);
             const unsigned long long rec = voxel_record(plan, vi);
@@ -1118,7 +1134,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                     E = tn_f;
                     if (E <= kECut) {
                         deposit_local(ti, (double)w * (double)E);
-                        alive = false;
+                        life = 0u;
                     } else {
                         mfp = -fln(u01(r3.w));
                     }
@@ -1129,7 +1145,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                     inc_el = el;
                     inc_t = T;
                     inc_ti = ti;
-                    alive = false;
+                    life = 0u;
                 } else {
                     // non-elastic: secondary protons from the per-nucleus table
                     const int nu = el - 1;
@@ -1175,7 +1191,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
                     n_out = (ce0 > 0.f) + (ce1 > 0.f) + (ce2 > 0.f) + (ce3 > 0.f);
                     deposit_local(ti, (double)w * local);
                     acc_neu += (double)w * ((double)T - loc - carried);
-                    alive = false;
+                    life = 0u;
                 }
             }
         }
@@ -1281,13 +1297,13 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             }
         if (chunk) {
             // the protons that go on to the ring, the wave's own lanes back
-            const unsigned long long m = __ballot(alive);
+            const unsigned long long m = __ballot(life != 0u);
             if (m != 0ull) {
                 uint32_t base = 0;
                 if (lane == 0) base = atomicAdd(cont_produced, (uint32_t)__popcll(m));
                 base = __builtin_amdgcn_readfirstlane(base) + (uint32_t)mbcnt(m);
                 const uint32_t ring = EvQueue::ring(blockDim.x);
-                if (alive) save_state(ev_entry(3u * blockDim.x + (base & (ring - 1u))));
+                if (life != 0u) save_state(ev_entry(3u * blockDim.x + (base & (ring - 1u))));
             }
             load_state(ev_entry(2u * blockDim.x + threadIdx.x));
             it += kEventIters;
@@ -1297,7 +1313,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     // epoch end: every wave reports its alive lanes (pending events
     // included) and whether it found the work list exhausted
     {
-        const int n_alive = __popcll(__ballot(alive));
+        const int n_alive = __popcll(__ballot(life != 0u));
         if (lane == 0) {
             if (n_alive > 0) atomicAdd(wg_busy, (uint32_t)n_alive);
             if (exhausted) *wg_state = 1u;
@@ -1350,7 +1366,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         const bool done = *wg_state != 0u && *wg_busy == 0u && *loc_claimed >= loc_av &&
                           L->cont_claimed == cont_av && ev_ready == 0u;
         const bool stop = !done && epoch >= kMaxEpochs;
-        if (stop) atomicAdd(&L->counters[kCtrAborted], 1ull);
+        if (stop) atomicAdd(&counters_of(0)[kCtrAborted], 1ull);
         if (done || stop) *wg_state = 2u;
         *wg_busy = 0u;
     }
@@ -1371,17 +1387,15 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         }
         for (int i = threadIdx.x; i < kWgCounters * a.n_plans; i += blockDim.x) {
             const int pl = i / kWgCounters, f = i - kWgCounters * pl;
-            if (wg_cnt[i] != 0ull) atomicAdd(&L->counters[kPlanCounters * pl + f], wg_cnt[i]);
+            if (wg_cnt[i] != 0ull) atomicAdd(&counters_of(pl)[f], wg_cnt[i]);
         }
     } else {
         for (int o = 32; o > 0; o >>= 1) {
             acc_esc += __shfl_xor(acc_esc, o);
             acc_neu += __shfl_xor(acc_neu, o);
             acc_ovf += __shfl_xor(acc_ovf, o);
-            n_steps += __shfl_xor(n_steps, o);
             n_el += __shfl_xor(n_el, o);
             n_ne += __shfl_xor(n_ne, o);
-            n_short += __shfl_xor(n_short, o);
             n_dep += __shfl_xor(n_dep, o);
             n_glob += __shfl_xor(n_glob, o);
             n_flush += __shfl_xor(n_flush, o);
