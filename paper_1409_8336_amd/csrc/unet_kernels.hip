@@ -735,7 +735,7 @@ __global__ void __launch_bounds__(256) max_kernel(const float* __restrict__ a, s
 // outside the caller's grid; scale[0] = the maximum dose, from the n_parts <= 256
 // shares after it, which every workgroup reads again (one kernel for the maximum
 // with an atomic per workgroup, behind a clear of its target, took 16.5 us on
-// 160 x 128 x 128 voxels where the shares take 5).  Bound by its bytes: 24 per
+// 160 x 128 x 128 voxels where the shares take 7).  Bound by its bytes: 24 per
 // voxel, 13 us.
 __global__ void __launch_bounds__(256) make_input_kernel(const float* __restrict__ dose, const float* __restrict__ rho,
                                                          float* __restrict__ scale, int n_parts,
