@@ -691,10 +691,13 @@ __device__ __forceinline__ void stage_words(void* dst, const void* src, int byte
 // iteration, and gives an idle lane a new event as soon as six are idle,
 // so lanes are not held by the longest event of a batch.  The expensive
 // steps wait for company: a collision runs once kCollBatch lanes have one
-// pending (or too few lanes are still flying for that to happen), an
-// evaporation step once kEvapBatch lanes are evaporating, an entry attempt
-// once kEntryBatch lanes are entering; meanwhile the other lanes keep
-// flying.
+// pending (or, with few lanes still flying, half as many as those), an
+// evaporation step once kEvapBatch lanes are evaporating or nothing else is
+// left, an entry attempt once kEntryBatch lanes are entering; meanwhile the
+// other lanes keep flying.  A launch ends with its longest events, whose flights
+// wait for whatever else their wave runs: with collisions and evaporation steps
+// of single lanes run at once in the tail, the launches of 1e6 histories' events
+// took 7.5 ms instead of 7.0, of 4e6 10.9 instead of 10.0.
 constexpr int kCollBatch = 24, kEvapBatch = 12, kEntryBatch = 8, kRefillIdle = 6;
 constexpr int kClaimRanges = 8;   // the event list in 8 ranges, each with its own claim counter
 
@@ -752,11 +755,11 @@ __device__ void run_events(Src& src, const IncNucleus* nuc, const IncTab& tab, P
         const int n_run = __popcll(__ballot(s.phase == kPhEntry || s.phase == kPhFlight ||
                                             s.phase == kPhAttemptEnd));
         const int n_col = __popcll(__ballot(s.phase == kPhCollide));
-        if (n_col >= kCollBatch || (n_col > 0 && n_run < kCollBatch)) {
+        if (n_col >= kCollBatch || (n_col > 0 && n_run < kCollBatch && 2 * n_col >= n_run)) {
             if (s.phase == kPhCollide) ev_collide(s, nuc[s.element - 1], stack);
         }
         const int n_ev = __popcll(__ballot(s.phase == kPhEvap));
-        if (n_ev >= kEvapBatch || (n_ev > 0 && n_run + n_col < kEvapBatch)) {
+        if (n_ev >= kEvapBatch || (n_ev > 0 && n_run + n_col == 0)) {
             if (s.phase == kPhEvap) ev_evaporate(s, tab, emit);
         }
         if (s.phase == kPhDone) {
