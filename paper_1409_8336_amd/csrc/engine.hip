@@ -720,7 +720,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
                     IncLaunch il{c->d_inc_ev.p, d_inc_count + gidx, cap, c->d_inc_nuc.p, c->d_inc_tab.p,
                                  d_inc_count + kMaxGenerations + 8 * gidx, d_plans,
                                  np, K, let ? 1 : 0, a.q_out, cap, &d_gc[2 * (gidx + 1)],
-                                 d_ledger, d_counters, slots > 0 ? 0 : planes};
+                                 d_ledger, d_counters, slots > 0 ? 0 : planes, c->num_cu};
                     HIPCHK(hipEventRecord(c->ev_inc[2 * gidx], st), "event");
                     HIPCHK(launch_inc_transport(il, c->inc_grid, st), "cascade launch");
                     HIPCHK(hipEventRecord(c->ev_inc[2 * gidx + 1], st), "event");

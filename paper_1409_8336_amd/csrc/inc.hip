@@ -698,6 +698,13 @@ __device__ __forceinline__ void stage_words(void* dst, const void* src, int byte
 // wait for whatever else their wave runs: with collisions and evaporation steps
 // of single lanes run at once in the tail, the launches of 1e6 histories' events
 // took 7.5 ms instead of 7.0, of 4e6 10.9 instead of 10.0.
+//   For the same reason a wave holds no more events than an even share of the
+// list (with more than 64 events per wave the share is all its lanes), and once
+// the list is used up and fewer lanes than a collision batch are left, these
+// fly kTailFlights times between two looks at the other steps: two flights
+// are 1% to 7% slower than four, eight or sixteen no faster.  Shares and tail flights together: launches of 2e5 histories'
+// events 4.7 -> 3.5 ms, 1e6 7.2 -> 6.0, 4e6 10.2 -> 9.1.
+constexpr int kTailFlights = 4;
 constexpr int kCollBatch = 24, kEvapBatch = 12, kEntryBatch = 8, kRefillIdle = 6;
 constexpr int kClaimRanges = 8;   // the event list in 8 ranges, each with its own claim counter
 
@@ -707,7 +714,7 @@ __device__ __forceinline__ int wave_mbcnt(unsigned long long m)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Src: n (events), claim(count) -> first index or >= n; begin(i, s);
+// Src: n (events), waves (that work on them), claim(count) -> first index or >= n; begin(i, s);
 // emit(i, s, kind, stage, id, t, d, j); finish(i, s); flush(force)
 template <class Src>
 __device__ void run_events(Src& src, const IncNucleus* nuc, const IncTab& tab, Part* stack)
@@ -719,13 +726,17 @@ __device__ void run_events(Src& src, const IncNucleus* nuc, const IncTab& tab, P
     // asked near the end of a range of the list, none once every range is
     // used up, and only that ends the wave's claims
     bool more = src.n > 0;
+    // lanes of this wave that take events
+    const unsigned long long share = (src.n + src.waves - 1) / src.waves;
+    const int lanes = __builtin_amdgcn_readfirstlane((int)(share < 64 ? share : 64));
+    const int refill = min(lanes, kRefillIdle);
     for (;;) {
         // refill: idle lanes take new events, one claim for the wave
         const unsigned long long idle = __ballot(s.phase == kPhIdle);
-        const int n_idle = __popcll(idle);
-        if (more && (n_idle >= kRefillIdle || n_idle == 64)) {
+        const int n_busy = 64 - __popcll(idle);
+        if (more && lanes - n_busy >= refill) {
             int got = 0;
-            const unsigned long long base = src.claim(n_idle, &got);
+            const unsigned long long base = src.claim(lanes - n_busy, &got);
             if (got == 0) more = false;
             if (s.phase == kPhIdle) {
                 const int rank = wave_mbcnt(idle);
@@ -735,7 +746,8 @@ __device__ void run_events(Src& src, const IncNucleus* nuc, const IncTab& tab, P
                 }
             }
         }
-        if (__ballot(s.phase != kPhIdle) == 0ull) {
+        const unsigned long long act = __ballot(s.phase != kPhIdle);
+        if (act == 0ull) {
             if (!more) break;
             continue;
         }
@@ -750,7 +762,8 @@ __device__ void run_events(Src& src, const IncNucleus* nuc, const IncTab& tab, P
                 if (s.phase == kPhEntry) ev_entry(s, nuc[s.element - 1]);
             }
         }
-        if (s.phase == kPhFlight) ev_flight(s, nuc[s.element - 1], stack, emit);
+        for (int rep = more || __popcll(act) >= kCollBatch ? 1 : kTailFlights; rep > 0; --rep)
+            if (s.phase == kPhFlight) ev_flight(s, nuc[s.element - 1], stack, emit);
         if (s.phase == kPhAttemptEnd) ev_attempt_end(s, nuc[s.element - 1]);
         const int n_run = __popcll(__ballot(s.phase == kPhEntry || s.phase == kPhFlight ||
                                             s.phase == kPhAttemptEnd));
@@ -808,7 +821,7 @@ struct RangeClaim {
 // Scheduled as in the transport (ctr: kClaimRanges zeroed counters).
 struct InspectSrc {
     RangeClaim rc;
-    unsigned long long n;
+    unsigned long long n, waves;
     const int32_t* element;
     const double* t;
     const unsigned long long* uid;
@@ -857,8 +870,8 @@ __global__ void __launch_bounds__(256) inc_inspect_kernel(const IncNucleus* __re
     stage_words(&tb, tab, (int)sizeof(IncTab));
     __syncthreads();
     Part stack[kIncMaxParticles];
-    InspectSrc src{{ctr, (unsigned long long)n, (int)(blockIdx.x % kClaimRanges)}, (unsigned long long)n, element,
-                   t, uid, ks, k0, k1, evap != 0, res, out};
+    InspectSrc src{{ctr, (unsigned long long)n, (int)(blockIdx.x % kClaimRanges)}, (unsigned long long)n,
+                   (unsigned long long)gridDim.x * (256 / 64), element, t, uid, ks, k0, k1, evap != 0, res, out};
     run_events(src, nuc, tb, stack);
 }
 
@@ -870,7 +883,7 @@ namespace {
 constexpr int kIncBlock = 256;
 constexpr int kIncWaves = kIncBlock / 64;
 constexpr int kStageW = 512;      // children a wave stages in LDS before writing them out
-constexpr int kStageFlush = 384;  // write out at this fill (an iteration adds at most 128)
+constexpr int kStageFlush = 384;  // write out at this fill (an iteration adds at most 128, or a child reserves its own slot)
 constexpr int kStageWords = 6;    // event index, child id, energy (FP32), direction (3 x FP32)
 
 // One child proton of event ev into slot of the next generation's queue
@@ -914,7 +927,7 @@ __device__ __noinline__ bool write_child(const IncLaunch& a, const PlanDesc* pds
 struct TransportSrc {
     const IncLaunch& a;
     RangeClaim rc;
-    unsigned long long n;
+    unsigned long long n, waves;
     uint32_t* stg;                 // this wave's stage
     uint32_t* n_staged;            // its fill
     double (*led)[2];
@@ -1025,7 +1038,10 @@ struct TransportSrc {
     }
 };
 
-__global__ void __launch_bounds__(kIncBlock) inc_transport_kernel(IncLaunch a)
+// Two waves per SIMD are asked for: left to itself the compiler takes 14
+// registers more for the tail's flights and one wave per SIMD fits, 10.3 instead
+// of 9.2 ms for 4e6 histories' events; held to 256 it spills 11.
+__global__ void __launch_bounds__(kIncBlock, 2) inc_transport_kernel(IncLaunch a)
 {
     __shared__ IncNucleus nuc[kIncTargets];
     __shared__ IncTab tb;
@@ -1045,9 +1061,17 @@ __global__ void __launch_bounds__(kIncBlock) inc_transport_kernel(IncLaunch a)
     __syncthreads();
     const int wave = threadIdx.x >> 6;
     const unsigned long long rec = *a.ev_count;
-    const unsigned long long n = rec < a.ev_cap ? rec : a.ev_cap;
+    const unsigned long long listed = rec < a.ev_cap ? rec : a.ev_cap;
+    // A list that a workgroup per CU holds at once is left to one workgroup per
+    // CU: two share its SIMDs, and each of the chains that the launch waits
+    // for gets half of the issue (2e5 histories' events 4.7 -> 4.4 ms, 1e6 7.2 ->
+    // 6.8).  A longer list needs both to cover each other's latency.
+    const unsigned groups = min((unsigned)a.num_cu, gridDim.x);
+    const bool single = listed <= (unsigned long long)groups * kIncBlock;
+    const unsigned long long n = single && blockIdx.x >= groups ? 0ull : listed;
+    const unsigned long long waves = (unsigned long long)(single ? groups : gridDim.x) * kIncWaves;
     Part stack[kIncMaxParticles];
-    TransportSrc src{a, {a.claim, n, (int)(blockIdx.x % kClaimRanges)}, n, stage[wave], &n_staged[wave], led, cnt,
+    TransportSrc src{a, {a.claim, n, (int)(blockIdx.x % kClaimRanges)}, n, waves, stage[wave], &n_staged[wave], led, cnt,
                      pds, 0.0, 0.0, 0.0, 0ull};
     run_events(src, nuc, tb, stack);
     __syncthreads();

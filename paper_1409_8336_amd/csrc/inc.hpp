@@ -97,6 +97,7 @@ struct IncLaunch {
     double* ledger;                       // [plan][4]: escaped, neutral, overflow, deposited
     unsigned long long* counters;         // [plan][kPlanCounters]
     int row_planes;                       // planes of a voxel's row (run without the deposit cache); 0: z-fastest planes
+    int num_cu;                           // compute units: workgroups that a short event list is left to
 };
 
 // Host: the six target nuclei (Woods-Saxon shells by Gauss-Legendre
