@@ -32,8 +32,8 @@ HBM_PEAK = 8.0e12
 # HBM bytes per transport launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs,
 # scaled by a plain-copy calibration, valid only for the kernel source whose
 # sha256 is recorded (see profiles/); None once the kernel has changed.
-TRAFFIC = {"transport_sha256": "929dca0a10ffe80db56ce8eef760f9a7d66f54df3270313b7a27c5e499a954d1",
-           "bytes_per_launch": 6.46965e9, "let_bytes_per_launch": 1.45400e10}
+TRAFFIC = {"transport_sha256": "5d23a0242eacaea870bf17889dda95ea1ec135146ea158434223546ec9f6a0ea",
+           "bytes_per_launch": 6.32396e9, "let_bytes_per_launch": 1.59498e10}
 
 
 def _kernel_sha():

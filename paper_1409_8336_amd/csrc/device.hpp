@@ -37,7 +37,7 @@ constexpr int kWgCtlWords = 8;
 constexpr int kLocEntryWords = 12;
 // epochs after which a workgroup stops (a guard against a non-terminating
 // launch; reported as an error)
-constexpr uint32_t kMaxEpochs = 1u << 22;
+constexpr uint32_t kMaxEpochs = 1u << 23;
 
 // tally elements of a cache line (consecutive in z, 64 bytes)
 constexpr int kLine = 8;

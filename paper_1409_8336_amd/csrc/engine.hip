@@ -607,8 +607,10 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     a.cnt_off = lay.cnt_off;
     // (epochs of 16 iterations: the lines of a single spot's epoch mostly fit
     // the cache, launch 2.1 ms, of 24 they begin to overflow, 2.4, of 32 more, 2.8;
-    // the 2000-spot field takes 14.4 ms with 16, 14.3 with 24)
-    a.epoch_iters = c->p.epoch_steps ? c->p.epoch_steps : 16;
+    // the 2000-spot field takes 14.4 ms with 16, 14.3 with 24; with LET_d half as
+    // many lines fit: 2e6 histories of 444 spots 3.5 ms with 8, 4.0 with 16, 3.9
+    // with 6, 1e6 of four spots 2.9, 4.1 and 2.9)
+    a.epoch_iters = c->p.epoch_steps ? c->p.epoch_steps : (let ? 8 : 16);
     a.cache_probes = c->p.cache_probes ? c->p.cache_probes : 3;
     const size_t lds = lay.lds_bytes;
     int max_block = 0;

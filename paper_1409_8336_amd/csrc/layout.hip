@@ -60,9 +60,10 @@ std::string plan_layout(const LayoutQuery& q, LaunchLayout* out)
     L.key_off = L.cache_off + 2 * slots;
     L.num_off = L.key_off + L.key_words * slots;
     L.ctl_off = (L.num_off + (q.score_let ? slots : 0) + 1) & ~1;   // (the claim count is 64-bit)
-    L.cache_lines = slots * slot_words / (2 * kLine + L.key_words + (q.score_let ? kLine : 0));
-    L.line_key_off = L.cache_off + 2 * kLine * L.cache_lines;
-    L.line_num_off = L.line_key_off + L.key_words * L.cache_lines;
+    const int sum_words = 2 * kLine * (q.score_let ? 2 : 1);   // a line's sums, its LET numerators
+    L.cache_lines = slots * slot_words / (sum_words + L.key_words);
+    L.line_num_off = L.cache_off + 2 * kLine * L.cache_lines;
+    L.line_key_off = L.cache_off + sum_words * L.cache_lines;
     L.args_off = L.ctl_off + kWgCtlWords;
     L.led_off = L.args_off + (int)(sizeof(LdsArgs) / 4);
     L.cnt_off = L.led_off + (q.multi ? 6 * np : 0);
@@ -98,7 +99,7 @@ std::string check_layout(const LayoutQuery& q, const LaunchLayout& L)
         if (n < 1 || n >= 1 << 14) return "cache lines outside [1, 2^14)";
         r.push_back({"cache sums", L.cache_off, L.cache_off + 2L * kLine * n, 8});
         r.push_back({"cache keys", L.line_key_off, L.line_key_off + (long)L.key_words * n, 4 * L.key_words});
-        if (q.score_let) r.push_back({"cache LET numerators", L.line_num_off, L.line_num_off + (long)kLine * n, 4});
+        if (q.score_let) r.push_back({"cache LET numerators", L.line_num_off, L.line_num_off + 2L * kLine * n, 8});
     }
     r.push_back({"control words", L.ctl_off, L.ctl_off + kWgCtlWords, 8});
     r.push_back({"staged arguments", L.args_off, L.args_off + (long)(sizeof(LdsArgs) / 4), 8});

@@ -44,7 +44,8 @@ struct LaunchLayout {
     int cache_slots = 0;
     int key_words = 1;
     // the cache's area (cache_slots single sums, keys and LET numerators) as
-    // the kernel divides it: lines of kLine sums, one key each
+    // the kernel divides it: lines of kLine sums and kLine LET numerators (both
+    // double), one key each
     int cache_lines = 0;
     int line_key_off = 0;
     int line_num_off = 0;

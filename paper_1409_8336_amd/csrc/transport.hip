@@ -262,10 +262,11 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
         const uint32_t* src = reinterpret_cast<const uint32_t*>(a.plans);
         for (int i = threadIdx.x; i < a.n_plans * 16; i += blockDim.x) dst[i] = src[i];
     }
-    // deposit cache at an even word offset: lines of kLine sums (double), line
-    // keys (the line's index in the tally; in a batch of plans, plan << 32 |
-    // index), with LET_d scoring the sums' LET numerators (float partial sums,
-    // flushed to the FP64 numerator plane), then the workgroup's control words
+    // deposit cache at an even word offset: lines of kLine sums (double), with
+    // LET_d scoring as many sums of LET numerators (double too: a line collects
+    // thousands of deposits in an epoch, and of 2e5 histories of four spots LET_d
+    // was 2e-8 off with float sums), line keys (the line's index in the tally;
+    // in a batch of plans, plan << 32 | index), then the workgroup's control words
     using Key = std::conditional_t<kMulti, unsigned long long, uint32_t>;
     constexpr Key kEmptyLine = ~Key(0);
     const int n_lines = a.cache_lines;
@@ -273,7 +274,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     const bool score_let = kOpt && (a.flags & kScoreLet) != 0u;
     double* const cval = reinterpret_cast<double*>(lds + a.cache_off);
     Key* const ckey = reinterpret_cast<Key*>(lds + a.key_off);
-    float* const cnum = reinterpret_cast<float*>(lds + a.num_off);
+    double* const cnum = reinterpret_cast<double*>(lds + a.num_off);
     uint32_t* const ctl = reinterpret_cast<uint32_t*>(lds + a.ctl_off);
     uint32_t* const loc_produced = ctl + 0;   // entries reserved in the own queue
     uint32_t* const loc_claimed = ctl + 1;    // entries taken by lanes
@@ -286,7 +287,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
     for (int i = threadIdx.x; i < kLine * n_lines; i += blockDim.x) {
         cval[i] = 0.0;
         ckey[i / kLine] = kEmptyLine;
-        if (score_let) cnum[i] = 0.f;
+        if (score_let) cnum[i] = 0.0;
     }
     if (threadIdx.x < kWgCtlWords) ctl[threadIdx.x] = 0u;
     LdsArgs* const L = reinterpret_cast<LdsArgs*>(lds + a.args_off);
@@ -444,7 +445,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             if (at >= 0) {
                 const uint32_t e = (uint32_t)at * kLine + (uint32_t)(idx % kLine);
                 unsafeAtomicAdd(&cval[e], v);
-                if (with_num) atomicAdd(&cnum[e], (float)num);
+                if (with_num) unsafeAtomicAdd(&cnum[e], num);
                 return;
             }
         }
@@ -1340,15 +1341,15 @@ __global__ void __launch_bounds__(1024) transport_kernel(KernelArgs a)
             if (score_let) {
                 // the LET numerator, if the element took step deposits, to the
                 // same line of the numerator plane
-                const float nm = cnum[i];
-                if (nm != 0.f) {
+                const double nm = cnum[i];
+                if (nm != 0.0) {
                     const uint32_t pl = P.lines(pk);
-                    __hip_atomic_fetch_add(to + ((unsigned long long)pl * K + line % pl) * kLine, (double)nm,
+                    __hip_atomic_fetch_add(to + ((unsigned long long)pl * K + line % pl) * kLine, nm,
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     ++n_glob;
                     ++n_flush;
                 }
-                cnum[i] = 0.f;
+                cnum[i] = 0.0;
             }
             if (in == 0u) ckey[i / kLine] = kEmptyLine;   // (its eight lanes have read it)
         }
