@@ -12,6 +12,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 namespace pmc {
 
@@ -423,7 +424,10 @@ __global__ void flip_weights_kernel(FlipLayers f)
 // first copies and the final sums, which every workgroup pays once (192 -> 64
 // on 40 x 32 x 32: 59 us, before 243; 64 -> 128 on 20 x 16 x 16: 31, before
 // 124).
+// kWide: z planes whose byte offsets do not fit the buffer loads' 32 bits: the
+// copies take 64-bit addresses, lanes outside the grid those of a page of zeros.
 constexpr int kWgWaves = 12;
+__device__ const u32x4 kZeros[1] = {};
 
 // 64 lanes x 16 bytes at the lanes' byte offsets of a buffer to LDS address
 // `to` + 16 * lane; lanes past the buffer's end write zeros.  As an
@@ -445,7 +449,7 @@ struct WgTile {
     static constexpr int PER = (NIN + NDO + kWgWaves - 1) / kWgWaves;
 };
 
-template <int NCI, int NCO>
+template <int NCI, int NCO, bool kWide>
 __global__ void __launch_bounds__(64 * kWgWaves, 3)
     conv3d_wgrad_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ coarse, int Cc,
                         const uint16_t* __restrict__ dout, float* __restrict__ dw, int D, int H, int W, int Cin, int Cout, int Kp, int n_xt, int n_yt, unsigned long long n_planes,
@@ -494,8 +498,9 @@ __global__ void __launch_bounds__(64 * kWgWaves, 3)
     const int x0 = 32 * xt, y0 = TY * yt;
     // byte offsets, within a z plane, of the entries this lane copies: blocks
     // of 64 dealt to the waves in turn, the input's tiles first
-    constexpr uint32_t kOutside = 0xFFFFFFF0u;
-    uint32_t off[T::PER];
+    using Offset = std::conditional_t<kWide, size_t, uint32_t>;
+    constexpr Offset kOutside = kWide ? ~(Offset)0 : (Offset)0xFFFFFFF0u;
+    Offset off[T::PER];
 #pragma unroll
     for (int q = 0; q < T::PER; ++q) {
         const int blk = wave + kWgWaves * q;
@@ -505,32 +510,43 @@ __global__ void __launch_bounds__(64 * kWgWaves, 3)
             const int row = e / 68, r2 = e % 68;
             const int x = x0 + (r2 >> 1) - 1, y = y0 + row, c = ci0 + 16 * (blk / T::IBLK) + 8 * (r2 & 1);
             if (row < TY && x >= 0 && x < W && y < H && c < Cin)
-                off[q] = c < Cc ? (((uint32_t)(y >> 1) * (W >> 1) + (x >> 1)) * Cc + c) * 2u
-                                : (((uint32_t)y * W + x) * (Cin - Cc) + (c - Cc)) * 2u;
+                off[q] = c < Cc ? (((Offset)(y >> 1) * (W >> 1) + (x >> 1)) * Cc + c) * 2u
+                                : (((Offset)y * W + x) * (Cin - Cc) + (c - Cc)) * 2u;
         } else if (blk < T::NIN + T::NDO) {
             const int d = blk - T::NIN;
             const int x = x0 + (lane >> 1), y = y0 + d % (TY + 2) - 1, c = co0 + 16 * (d / (TY + 2)) + 8 * (lane & 1);
-            if (x < W && y >= 0 && y < H && c < Cout) off[q] = (((uint32_t)y * W + x) * Cout + c) * 2u;
+            if (x < W && y >= 0 && y < H && c < Cout) off[q] = (((Offset)y * W + x) * Cout + c) * 2u;
         }
     }
-    // z plane -> buffer descriptor (empty outside the grid: every lane reads zero)
-    auto plane_rsrc = [&](const uint16_t* t, int z, int planes, size_t bytes) {
+    // z plane -> buffer descriptor (empty outside the grid: every lane reads
+    // zero); wide: its address (NULL outside)
+    auto plane_at = [&](const uint16_t* t, int z, int planes, size_t bytes) {
         const bool ok = z >= 0 && z < planes;
         const uint64_t at = (uint64_t)(uintptr_t)t + (n * planes + (ok ? z : 0)) * bytes;
-        return (i32x4){(int)(uint32_t)at, (int)(uint32_t)(at >> 32), ok ? (int)(uint32_t)bytes : 0, 0x00020000};
+        if constexpr (kWide) return ok ? at : (uint64_t)0;
+        else return (i32x4){(int)(uint32_t)at, (int)(uint32_t)(at >> 32), ok ? (int)(uint32_t)bytes : 0, 0x00020000};
+    };
+    auto copy = [&](auto from, Offset o, uint32_t to) __attribute__((always_inline)) {
+        if constexpr (kWide) {
+            const GLOBAL char* src = from != 0 && o != kOutside ? (const GLOBAL char*)(uintptr_t)(from + o)
+                                                                : (const GLOBAL char*)&kZeros[0];
+            __builtin_amdgcn_global_load_lds((const GLOBAL void*)src, (LOCAL void*)(uintptr_t)to, 16, 0, 0);
+        } else {
+            copy_to_lds(from, o, to);
+        }
     };
     // input plane z (its own buffer) and output-gradient plane zd to LDS
     auto load = [&](int z, bool with_in, int zd) __attribute__((always_inline)) {
-        const i32x4 ri = plane_rsrc(in, z, D, plane * (Cin - Cc) * 2), rd = plane_rsrc(dout, zd, D, plane * Cout * 2);
-        const i32x4 rc = plane_rsrc(coarse, z >> 1, D >> 1, (plane >> 2) * Cc * 2);
+        const auto ri = plane_at(in, z, D, plane * (Cin - Cc) * 2), rd = plane_at(dout, zd, D, plane * Cout * 2);
+        const auto rc = plane_at(coarse, z >> 1, D >> 1, (plane >> 2) * Cc * 2);
         const uint32_t ti = lds0 + (z & 1) * kInBytes, td = lds0 + 2 * kInBytes + (zd & 3) * kDoBytes;
 #pragma unroll
         for (int q = 0; q < T::PER; ++q) {
             const int blk = wave + kWgWaves * q;
             if (blk < T::NIN) {
-                if (with_in) copy_to_lds(ci0 + 16 * (blk / T::IBLK) < Cc ? rc : ri, off[q], ti + 1024 * blk);
+                if (with_in) copy(ci0 + 16 * (blk / T::IBLK) < Cc ? rc : ri, off[q], ti + 1024 * blk);
             } else if (blk < T::NIN + T::NDO) {
-                copy_to_lds(rd, off[q], td + 1024 * (blk - T::NIN));
+                copy(rd, off[q], td + 1024 * (blk - T::NIN));
             }
         }
     };
@@ -1052,7 +1068,7 @@ hipError_t nn_flip_weights(const FlipLayer* layers, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int NCI, int NCO>
+template <int NCI, int NCO, bool kWide = false>
 static hipError_t launch_wgrad(const uint16_t* in, const uint16_t* coarse, int Cc, const uint16_t* dout, float* dw, int N,
                                int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s)
 {
@@ -1063,7 +1079,7 @@ static hipError_t launch_wgrad(const uint16_t* in, const uint16_t* coarse, int C
     // dealt to its workgroups in equal runs
     const unsigned long long n_planes = (unsigned long long)N * n_yt * n_xt * D;
     const int per_block = (int)std::min<unsigned long long>(n_planes, (unsigned long long)std::max(1, 256 / blocks));
-    hipLaunchKernelGGL((conv3d_wgrad_kernel<NCI, NCO>), dim3((unsigned)(blocks * per_block)), dim3(64 * kWgWaves), 0, s, in,
+    hipLaunchKernelGGL((conv3d_wgrad_kernel<NCI, NCO, kWide>), dim3((unsigned)(blocks * per_block)), dim3(64 * kWgWaves), 0, s, in,
                        coarse, Cc, dout, dw, D, H, W, Cin, Cout, Kp, n_xt, n_yt, n_planes, per_block);
     return hipGetLastError();
 }
@@ -1072,9 +1088,10 @@ hipError_t nn_conv3d_wgrad_cat(const uint16_t* in, const uint16_t* coarse, int C
                                int D, int H, int W, int Cin, int Cout, int Kp, hipStream_t s)
 {
     if (Cc < 0 || Cc % 16 || Cc >= Cin || (Cc && !coarse) || (Cc && (D % 2 || H % 2 || W % 2))) return hipErrorInvalidValue;
-    // (the kernel keeps byte offsets within a z plane in 32 bits)
-    if ((size_t)H * W * (size_t)std::max(Cin, Cout) >= (size_t)0x7FFFFFFF) return hipErrorInvalidValue;
-#define PMC_WG(NCI, NCO) launch_wgrad<NCI, NCO>(in, coarse, Cc, dout, dw, N, D, H, W, Cin, Cout, Kp, s)
+#define PMC_WG(NCI, ...) launch_wgrad<NCI, __VA_ARGS__>(in, coarse, Cc, dout, dw, N, D, H, W, Cin, Cout, Kp, s)
+    // z planes of 4 GiB and more (2^28 voxels of 8 channels): past the 32-bit
+    // byte offsets; one tiling serves them, bound by the planes' bytes
+    if ((size_t)H * W * (size_t)std::max(Cin, Cout) >= (size_t)0x7FFFFFFF) return PMC_WG(2, 2, true);
     // input tiles: three of 16 channels where they divide the channels, else two, or one
     const int ti = (Cin + 15) / 16, to = (Cout + 15) / 16;
     const int nci = ti % 3 == 0 ? 3 : (ti == 1 ? 1 : 2);
