@@ -415,6 +415,29 @@ struct TraceReq {
     unsigned long long lanes = 0;
 };
 
+// The layout query of a run with workgroups of `block` lanes; cache: the
+// deposit cache asked for where the caller leaves it open.
+LayoutQuery layout_query(const pmc_ctx* c, const std::vector<PlanIn>& plans, bool multi, bool let, int block, int cache)
+{
+    LayoutQuery lq;
+    lq.block = block;
+    lq.n_plans = (int)plans.size();
+    lq.multi = multi;
+    lq.score_let = let;
+    lq.k_batches = c->p.k_batches;
+    lq.n_mat = (int)c->mats.size();
+    lq.cache_request = c->p.tally_cache != 0 ? c->p.tally_cache : cache;
+    lq.local_queue = c->p.local_queue;
+    lq.queue_capacity = c->p.queue_capacity;
+    for (const PlanIn& q : plans) {
+        lq.n_histories += q.n_hist;
+        lq.n_spots += q.n_hist > 0 ? q.n_spots : 0;
+        lq.max_nvox = std::max<unsigned long long>(lq.max_nvox, q.g->nvox());
+        lq.max_plan_histories = std::max<unsigned long long>(lq.max_plan_histories, q.n_hist);
+    }
+    return lq;
+}
+
 // The driver.  tuning = a calibration run: no statistics, no outputs.
 pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const Shape& shape,
                       hipStream_t st, bool tuning, RunResult* rr, TraceReq* trace = nullptr)
@@ -573,22 +596,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     // launch layout (LDS regions, buffer sizes): computed and checked by
     // plan_layout, which the kernel's offsets come from; the grid-dependent
     // parts once the occupancy has fixed the grid
-    LayoutQuery lq;
-    lq.block = block;
-    lq.n_plans = np;
-    lq.multi = multi;
-    lq.score_let = let;
-    lq.k_batches = K;
-    lq.n_mat = a.n_mat;
-    lq.cache_request = c->p.tally_cache != 0 ? c->p.tally_cache : shape.cache;
-    lq.local_queue = c->p.local_queue;
-    lq.queue_capacity = c->p.queue_capacity;
-    lq.n_histories = total;
-    lq.n_spots = n_spots;
-    for (const PlanIn& q : plans) {
-        lq.max_nvox = std::max<unsigned long long>(lq.max_nvox, q.g->nvox());
-        lq.max_plan_histories = std::max<unsigned long long>(lq.max_plan_histories, q.n_hist);
-    }
+    LayoutQuery lq = layout_query(c, plans, multi, let, block, shape.cache);
     LaunchLayout lay;
     std::string why = plan_layout(lq, &lay);
     if (!why.empty()) return fail(c, PMC_ERR_ARG, "launch layout: " + why);
@@ -848,12 +856,25 @@ pmc_status choose_shape(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, hipS
         total += p.n_hist;
         vox += p.g->nvox();
     }
-    // runs too small to tune: from 40000 histories the workgroup size whose
-    // deposit cache fits (launches of 5e4 histories took 0.33 to 0.74 ms so and
-    // 0.35 to 0.70 with 256 lanes, of 2e5 0.55 to 1.03 and 0.97 to 1.78), below it
-    // small workgroups, which leave the CU sooner (of 1e4 0.26 to 0.62 and 0.20 to
-    // 0.56)
-    s.block = c->p.block_threads ? c->p.block_threads : (total < 40000ull ? 256 : 1024);
+    bool let = false;
+    for (const PlanIn& p : plans) let = let || p.d_let != nullptr;
+    // runs too small to tune: from 40000 histories the largest workgroups if
+    // their deposit cache holds enough lines (launches of 5e4 histories took
+    // 0.33 to 0.74 ms so and 0.35 to 0.70 with 256 lanes, of 2e5 0.55 to 1.03 and
+    // 0.97 to 1.78), below it small workgroups, which leave the CU sooner (of 1e4
+    // 0.26 to 0.62 and 0.20 to 0.56).  Without a cache, or with one the caller
+    // made small, the lanes of large workgroups only wait for each other: with
+    // none 4e4 to 2e5 histories took 0.91 to 1.09 times as long as with 256
+    // lanes, with 62 or 90 lines 0.88 to 1.44, with 248 or 361 0.90 to 1.38, with
+    // 496 or 722 0.61 to 1.05.
+    constexpr int kFewLines = 400;
+    s.block = c->p.block_threads;
+    if (s.block == 0) {
+        LaunchLayout lay;
+        s.block = total >= 40000ull &&
+                  plan_layout(layout_query(c, plans, multi, let, 1024, 0), &lay).empty() &&
+                  lay.cache_lines >= kFewLines ? 1024 : 256;
+    }
     s.blocks_per_cu = c->p.blocks_per_cu;
     s.refill = c->p.refill_lanes ? c->p.refill_lanes : 16;
     s.batch = c->p.batch_events ? c->p.batch_events : 4;
@@ -863,8 +884,6 @@ pmc_status choose_shape(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, hipS
         return PMC_OK;
     }
     auto log2i = [](unsigned long long v) { int l = 0; while (v >>= 1) ++l; return l; };
-    bool let = false;
-    for (const PlanIn& p : plans) let = let || p.d_let != nullptr;
     const auto key = std::make_tuple((int)multi + 2 * (int)let, (int)plans.size(), log2i(total), log2i(vox));
     auto it = c->tuned.find(key);
     if (it != c->tuned.end()) {
