@@ -1447,12 +1447,15 @@ hipError_t launch_atomic_probe(double* tally, int nx, int ny, int nz, int K, int
 // The tally is z-fastest, one plane per group; dose, variance and LET are
 // x-fastest.  A workgroup takes tiles of 16 columns (x) by 16 voxels in z: its
 // lanes read the K planes 16 consecutive doubles a column, and the tile's
-// results turn through LDS into rows of 16 consecutive x.  (Of a run without the
+// results turn through LDS into rows of 16 consecutive x.  Of a run without the
 // deposit cache the tally is one row of groups per voxel, x-fastest: the lanes
-// then read the tile as they write it.)  Bound by the tally's bytes.  With kPre (K <= 16) a voxel's groups are read at once into registers,
-// else twice (the second time from the caches).
+// then read the tile as they write it, each its own voxel's row, or with kTurn 16
+// lanes the rows of their 16 voxels, 16 groups (128 bytes) at a time, turned
+// through LDS.  A voxel's K <= kGroups groups pass through registers once.  Bound
+// by the tally's bytes: 128 x 128 x 160 voxels and 32 groups take 0.32 ms in planes
+// (read twice 0.37) and in rows (each lane its own 0.45, that twice 3.1).
 constexpr int kStatsTile = 16;
-constexpr int kStatsPre = 16;
+constexpr int kStatsOwnRow = 12;   // groups up to which lanes read their own rows (8: 0.07 and 0.08 ms, 16: 0.21 and 0.15)
 
 // tile t of a grid -> its y and the corner x0, z0 (z tiles innermost: the
 // tiles that share the lines at a tile's edge follow each other)
@@ -1467,7 +1470,7 @@ struct TileGrid {
     }
 };
 
-template <bool kPre>
+template <int kGroups, bool kTurn>
 __global__ void __launch_bounds__(kStatsTile* kStatsTile) stats_kernel(const double* __restrict__ tally,
                                                           const uint2* __restrict__ vox,
                                                           TileGrid tg, unsigned long long n_tiles,
@@ -1479,6 +1482,8 @@ __global__ void __launch_bounds__(kStatsTile* kStatsTile) stats_kernel(const dou
 {
     __shared__ double turn[3][kStatsTile][kStatsTile + 1];   // [dose, variance, LET][z][x]
     __shared__ double sums[kStatsTile * kStatsTile / 64];
+    // [z][x][group]: the 16 lanes of a z row use their own part
+    __shared__ double rows_turn[kTurn ? kStatsTile : 1][kStatsTile][kStatsTile + 1];
     const int a = (int)threadIdx.x % kStatsTile, b = (int)threadIdx.x / kStatsTile;
     double part = 0.0;
     for (unsigned long long t = blockIdx.x; t < n_tiles; t += gridDim.x) {
@@ -1490,34 +1495,50 @@ __global__ void __launch_bounds__(kStatsTile* kStatsTile) stats_kernel(const dou
             const int x = x0 + tb, z = z0 + ta;
             const bool in = x < tg.nx && z < tg.nz;
             const unsigned long long v = in ? ((unsigned long long)y * tg.nx + x) * tg.nz + z : 0ull;
-            const double* tv = tally + (rows ? (((unsigned long long)z * tg.ny + y) * tg.nx + x) * rows : v);
+            const unsigned long long row0 = (((unsigned long long)z * tg.ny + y) * tg.nx + x0) * rows;
+            const double* tv = tally + (rows ? row0 + (unsigned long long)a * rows : v);
             double tot = 0.0, ss = 0.0;
             float rho = 1.f;
+            double g[kGroups];
+            if constexpr (kTurn) {
+                const int n_x = z < tg.nz ? min(kStatsTile, tg.nx - x0) : 0;
+#pragma unroll
+                for (int c = 0; c < kGroups; c += kStatsTile) {
+                    if (c >= K) break;
+                    double q[kStatsTile];
+#pragma unroll
+                    for (int i = 0; i < kStatsTile; ++i)
+                        if (i < n_x && c + a < K) q[i] = tally[row0 + (unsigned long long)i * rows + (unsigned)(c + a)];
+#pragma unroll
+                    for (int i = 0; i < kStatsTile; ++i)
+                        if (i < n_x && c + a < K) rows_turn[b][i][a] = q[i];
+                    // (a wave's own LDS: in order)
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int k = 0; k < kStatsTile; ++k)
+                        if (in && c + k < K) g[c + k] = rows_turn[b][a][k];
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
             if (in) {
                 rho = __uint_as_float(vox[v].x);
-                if constexpr (kPre) {
-                    double g[kStatsPre];
+                if constexpr (!kTurn) {
 #pragma unroll
-                    for (int k = 0; k < kStatsPre; ++k)
+                    for (int k = 0; k < kGroups; ++k)
                         if (k < K) g[k] = tv[plane * (unsigned)k];
+                }
 #pragma unroll
-                    for (int k = 0; k < kStatsPre; ++k)
-                        if (k < K) tot += g[k];
-                    const double mean = tot * inv_k;
+                for (int k = 0; k < kGroups; ++k)
+                    if (k < K) tot += g[k];
+                const double mean = tot * inv_k;
 #pragma unroll
-                    for (int k = 0; k < kStatsPre; ++k)
-                        if (k < K) {
-                            const double dd = g[k] - mean;
-                            ss += dd * dd;
-                        }
-                } else {
-                    for (int k = 0; k < K; ++k) tot += tv[plane * (unsigned)k];
-                    const double mean = tot * inv_k;
-                    for (int k = 0; k < K; ++k) {
-                        const double dd = tv[plane * (unsigned)k] - mean;
+                for (int k = 0; k < kGroups; ++k)
+                    if (k < K) {
+                        const double dd = g[k] - mean;
                         ss += dd * dd;
                     }
-                }
             }
             // conv0 / rho: an FP32 reciprocal refined by two Newton steps in FP64
             const double rd = (double)rho;
@@ -1650,15 +1671,16 @@ hipError_t launch_stats(const double* tally, const uint2* vox, int nx, int ny, i
                         hipStream_t s)
 {
     if (K < 2 || K > 64) return hipErrorInvalidValue;
-    const bool pre = K <= kStatsPre;
     // as many workgroups as are resident at once (a second, partial wave of
     // workgroups would run after the first), each looping over tiles
-    const void* kfn = pre ? (const void*)stats_kernel<true> : (const void*)stats_kernel<false>;
+    const bool turn = !lines && K > kStatsOwnRow;
+    const auto kfn = turn ? (K <= 16 ? stats_kernel<16, true> : stats_kernel<64, true>)
+                          : (K <= 16 ? stats_kernel<16, false> : stats_kernel<64, false>);
     constexpr int kThreads = kStatsTile * kStatsTile;
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, kThreads, 0);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kfn, kThreads, 0);
     if (e != hipSuccess) return e;
     const unsigned long long resident = (unsigned long long)std::max(1, cus) * (unsigned long long)std::max(1, per_cu);
     unsigned long long n_tiles;
@@ -1667,12 +1689,8 @@ hipError_t launch_stats(const double* tally, const uint2* vox, int nx, int ny, i
     // doubles of a voxel's row (0: z-fastest planes), and from plane to plane
     const unsigned rows = lines ? 0u : (unsigned)planes;
     const unsigned long long plane = lines ? ((unsigned long long)nx * ny * nz + kLine - 1) / kLine * kLine : 1ull;
-    if (pre)
-        hipLaunchKernelGGL(stats_kernel<true>, dim3(blocks), dim3(kThreads), 0, s, tally, vox, tg, n_tiles, rows, plane, K,
-                           1.0 / K, (double)K / (K - 1), conv0, dose, var, dep_sum, let);
-    else
-        hipLaunchKernelGGL(stats_kernel<false>, dim3(blocks), dim3(kThreads), 0, s, tally, vox, tg, n_tiles, rows, plane, K,
-                           1.0 / K, (double)K / (K - 1), conv0, dose, var, dep_sum, let);
+    hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kThreads), 0, s, tally, vox, tg, n_tiles, rows, plane, K, 1.0 / K,
+                       (double)K / (K - 1), conv0, dose, var, dep_sum, let);
     return hipGetLastError();
 }
 
