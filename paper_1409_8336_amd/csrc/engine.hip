@@ -30,7 +30,7 @@ hipError_t transport_occupancy(bool multi, uint32_t flags, int block, size_t lds
 hipError_t transport_max_block(bool multi, uint32_t flags, int* max_threads);
 hipError_t launch_stats(const double* tally, const uint2* vox, int nx, int ny, int nz, int K, int planes, bool lines,
                         double conv0, double* dose, double* var, double* dep_sum, double* let,
-                        hipStream_t s);
+                        const unsigned long long* more, hipStream_t s);
 hipError_t launch_zero(const ZeroRanges& z, hipStream_t s);
 hipError_t launch_density(const uint2* vox, int nx, int ny, int nz, float* rho, hipStream_t s);
 hipError_t launch_atomic_probe(double* tally, int nx, int ny, int nz, int K, int grid,
@@ -687,14 +687,15 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
     // overflowed them, almost always nothing: launch one at a time, so that a
     // run is one launch unless its workgroup queues overflowed
     const int group = a.loc_cap > 0 ? 1 : kGenGroup;
-    // the run's outputs and the read-back of its counts
-    auto finish = [&]() -> pmc_status {
+    // the run's outputs (unless *more secondaries are left) and the read-back of
+    // its counts
+    auto finish = [&](const unsigned long long* more) -> pmc_status {
         for (int p = 0; p < np && !tuning; ++p) {
             const Geometry& g = *plans[p].g;
             const double vol = (double)g.vs[0] * g.vs[1] * g.vs[2];
             const double conv0 = wtot[p] > 0.0 ? 1.602176634e-10 / (vol * wtot[p]) : 0.0;
             HIPCHK(launch_stats(g.tally.p, g.vox.p, g.nx, g.ny, g.nz, K, planes, slots > 0, conv0, plans[p].d_dose,
-                                plans[p].d_var, d_ledger + 4 * p + 3, plans[p].d_let, st), "stats launch");
+                                plans[p].d_var, d_ledger + 4 * p + 3, plans[p].d_let, more, st), "stats launch");
         }
         HIPCHK(hipEventRecord(c->ev1, st), "event");
         HIPCHK(hipMemcpyAsync(c->h_pinned, c->d_ctl.p, read_words * 8, hipMemcpyDeviceToHost, st), "read counters");
@@ -702,10 +703,9 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
         return PMC_OK;
     };
     // with a launch per generation the first one is almost always the only one:
-    // its outputs follow it without waiting for its count, and are made again
-    // after the later ones where there are any (the wait took 25 to 45 us)
+    // its outputs follow it without waiting for its count (the wait took 25 to 45
+    // us), which the device reads: where there are later ones they follow these
     const bool at_once = group == 1 && !inc;
-    bool finished = false;
     if (total > 0) {
         bool done = false;
         while (!done) {
@@ -740,9 +740,8 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
             // produced counts of generations g0+1 .. g1: words 2(g0+1) .. 2 g1
             const unsigned long long* produced = c->h_pinned;
             if (at_once && g0 == 0) {
-                const pmc_status sf = finish();
+                const pmc_status sf = finish(d_gc + 2);
                 if (sf != PMC_OK) return sf;
-                finished = true;
                 produced = c->h_pinned + led_words + cnt_words + 2;
             } else {
                 HIPCHK(hipMemcpyAsync(c->h_pinned, d_gc + 2 * (g0 + 1), 8 * (2 * (g1 - g0) - 1), hipMemcpyDeviceToHost, st),
@@ -761,13 +760,8 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
             }
         }
     }
-    if (!finished || launched > 1) {
-        if (finished && !tuning) {
-            ZeroRanges sums;   // the deposited energies, added up again
-            for (int p = 0; p < np; ++p) sums.add(d_ledger + 4 * p + 3, 1);
-            HIPCHK(launch_zero(sums, st), "zero ledger");
-        }
-        const pmc_status sf = finish();
+    if (!at_once || launched != 1) {
+        const pmc_status sf = finish(nullptr);
         if (sf != PMC_OK) return sf;
     }
     float ms = 0.f;

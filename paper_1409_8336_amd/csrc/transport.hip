@@ -1454,6 +1454,7 @@ hipError_t launch_atomic_probe(double* tally, int nx, int ny, int nz, int K, int
 // through LDS.  A voxel's K <= kGroups groups pass through registers once.  Bound
 // by the tally's bytes: 128 x 128 x 160 voxels and 32 groups take 0.32 ms in planes
 // (read twice 0.37) and in rows (each lane its own 0.45, that twice 3.1).
+// more: NULL, or a count that has to be 0 for there to be anything to do.
 constexpr int kStatsTile = 16;
 constexpr int kStatsOwnRow = 12;   // groups up to which lanes read their own rows (8: 0.07 and 0.08 ms, 16: 0.21 and 0.15)
 
@@ -1478,8 +1479,9 @@ __global__ void __launch_bounds__(kStatsTile* kStatsTile) stats_kernel(const dou
                                                           double inv_k, double k_ratio, double conv0,
                                                           double* __restrict__ dose,
                                                           double* __restrict__ var, double* dep_sum,
-                                                          double* __restrict__ let)
+                                                          double* __restrict__ let, const unsigned long long* more)
 {
+    if (more && *more != 0ull) return;   // (the same for every lane)
     __shared__ double turn[3][kStatsTile][kStatsTile + 1];   // [dose, variance, LET][z][x]
     __shared__ double sums[kStatsTile * kStatsTile / 64];
     // [z][x][group]: the 16 lanes of a z row use their own part
@@ -1668,7 +1670,7 @@ TileGrid tile_grid(int nx, int ny, int nz, unsigned long long* n_tiles)
 
 hipError_t launch_stats(const double* tally, const uint2* vox, int nx, int ny, int nz, int K, int planes, bool lines,
                         double conv0, double* dose, double* var, double* dep_sum, double* let,
-                        hipStream_t s)
+                        const unsigned long long* more, hipStream_t s)
 {
     if (K < 2 || K > 64) return hipErrorInvalidValue;
     // as many workgroups as are resident at once (a second, partial wave of
@@ -1690,7 +1692,7 @@ hipError_t launch_stats(const double* tally, const uint2* vox, int nx, int ny, i
     const unsigned rows = lines ? 0u : (unsigned)planes;
     const unsigned long long plane = lines ? ((unsigned long long)nx * ny * nz + kLine - 1) / kLine * kLine : 1ull;
     hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kThreads), 0, s, tally, vox, tg, n_tiles, rows, plane, K, 1.0 / K,
-                       (double)K / (K - 1), conv0, dose, var, dep_sum, let);
+                       (double)K / (K - 1), conv0, dose, var, dep_sum, let, more);
     return hipGetLastError();
 }
 
