@@ -433,11 +433,15 @@ __device__ const u32x4 kZeros[1] = {};
 // `to` + 16 * lane; lanes past the buffer's end write zeros.  As an
 // instruction the compiler does not see as a load, so that it does not wait
 // for the copy before unrelated LDS reads: the caller waits for vmcnt(0)
-// before the barrier that hands the data over.
+// before the barrier that hands the data over.  m0 is left as it was (the
+// compiler takes it for its own register and may count on its value); the wait
+// states are for m0 and, should the descriptor have come from vector registers
+// just before, for it.
 DEV void copy_to_lds(i32x4 rsrc, uint32_t off, uint32_t to)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 4\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0)
                  : "s"(to), "v"(off), "s"(rsrc)
                  : "memory");
 }
