@@ -434,14 +434,18 @@ typedef struct {
 
 typedef struct {
     uint64_t lds_bytes;         /* dynamic LDS per workgroup */
-    /* LDS regions, 32-bit word offsets from the start of the allocation (the
-     * deposit cache's, [cache_off, ctl_off), as cache_slots single slots) */
+    /* LDS regions, 32-bit word offsets from the start of the allocation.  The
+     * deposit cache has [cache_off, ctl_off), the memory of cache_slots slots
+     * of a sum (8 bytes), a key (key_words) and with LET_d a word: key_off and
+     * num_off count these and are no offsets the kernel uses, see
+     * pmc_plan_cache */
     int32_t blob_words, plan_desc_off, cache_off, key_off, num_off, ctl_off, args_off,
         ledger_off, counter_off, end_words;
     int32_t cache_slots, key_words, tally_planes, local_queue_cap, args_bytes, reserved;
     uint64_t queue_cap;         /* generation queue entries (12 u32 planes each) */
     uint64_t local_queue_words; /* all workgroup queues (12 u32 per entry) */
-    uint64_t claim_words;       /* work claims (u64), one per workgroup and generation, each kept in LDS */
+    uint64_t claim_words;       /* work claims (u64), one per workgroup and generation; no buffer: each
+                                   is two of its workgroup's control words */
     uint64_t order_words;       /* primary work list (u64) */
 } pmc_launch_layout;
 
@@ -452,6 +456,21 @@ typedef struct {
  * (why_len bytes, NUL-terminated; may be NULL) and *out as far as computed.
  * Errors: PMC_ERR_ARG (NULL q/out, or the launch does not fit). */
 pmc_status pmc_plan_launch(const pmc_launch_query* q, pmc_launch_layout* out, char* why, int32_t why_len);
+
+/* How the kernel divides the deposit cache's memory (host only): lines of
+ * line_sums consecutive tally elements, each with one key. */
+typedef struct {
+    int32_t lines;       /* 0: no cache */
+    int32_t line_sums;   /* sums (double) of a line */
+    int32_t sums_off;    /* LDS word offsets: the lines' sums, */
+    int32_t num_off;     /* with LET_d as many numerators (double; else an empty region), */
+    int32_t key_off;     /* and a key of key_words 32-bit words per line */
+    int32_t key_words;
+} pmc_cache_layout;
+
+/* Fills *out for a query that pmc_plan_launch accepts.  Errors: PMC_ERR_ARG
+ * (NULL q/out, or the launch does not fit). */
+pmc_status pmc_plan_cache(const pmc_launch_query* q, pmc_cache_layout* out);
 
 /* ---- Intranuclear cascade and evaporation (Sec. II.A.4; flag PMC_INC) ----
  * Targets: element 1..6 = C-12, N-14, O-16, P-31, Ca-40, Ti-48 (the

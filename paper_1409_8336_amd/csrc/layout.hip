@@ -149,10 +149,8 @@ std::string check_layout(const LayoutQuery& q, const LaunchLayout& L)
 
 }  // namespace pmc
 
-extern "C" pmc_status pmc_plan_launch(const pmc_launch_query* q, pmc_launch_layout* out, char* why, int32_t why_len)
+static pmc::LayoutQuery layout_query(const pmc_launch_query* q)
 {
-    if (why && why_len > 0) why[0] = 0;
-    if (!q || !out) return PMC_ERR_ARG;
     pmc::LayoutQuery lq;
     lq.block = q->block_threads;
     lq.grid = q->grid_blocks;
@@ -168,8 +166,15 @@ extern "C" pmc_status pmc_plan_launch(const pmc_launch_query* q, pmc_launch_layo
     lq.max_plan_histories = q->max_plan_histories;
     lq.n_spots = q->n_spots;
     lq.max_nvox = q->max_nvox;
+    return lq;
+}
+
+extern "C" pmc_status pmc_plan_launch(const pmc_launch_query* q, pmc_launch_layout* out, char* why, int32_t why_len)
+{
+    if (why && why_len > 0) why[0] = 0;
+    if (!q || !out) return PMC_ERR_ARG;
     pmc::LaunchLayout L;
-    const std::string e = pmc::plan_layout(lq, &L);
+    const std::string e = pmc::plan_layout(layout_query(q), &L);
     std::memset(out, 0, sizeof(*out));
     out->lds_bytes = L.lds_bytes;
     out->blob_words = L.blob_words;
@@ -198,5 +203,14 @@ extern "C" pmc_status pmc_plan_launch(const pmc_launch_query* q, pmc_launch_layo
         }
         return PMC_ERR_ARG;
     }
+    return PMC_OK;
+}
+
+extern "C" pmc_status pmc_plan_cache(const pmc_launch_query* q, pmc_cache_layout* out)
+{
+    if (!q || !out) return PMC_ERR_ARG;
+    pmc::LaunchLayout L;
+    if (!pmc::plan_layout(layout_query(q), &L).empty()) return PMC_ERR_ARG;
+    *out = {L.cache_lines, pmc::kLine, L.cache_off, L.line_num_off, L.line_key_off, L.key_words};
     return PMC_OK;
 }

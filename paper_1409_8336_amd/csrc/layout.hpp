@@ -32,9 +32,9 @@ struct LaunchLayout {
     // LDS, in 32-bit words from the start of the dynamic allocation
     int blob_words = 0;
     int pd_off = 0;       // plan descriptors (batched launch)
-    int cache_off = 0;    // slot sums (double)
-    int key_off = 0;      // slot keys (u32; u64 in a batched launch)
-    int num_off = 0;      // slot LET numerators (float)
+    int cache_off = 0;    // the deposit cache's memory (its lines' sums first)
+    int key_off = 0;      // the memory's extent in slots: sums, keys, a word of
+    int num_off = 0;      // LET_d (the kernel has lines there, below)
     int ctl_off = 0;      // control words
     int args_off = 0;     // staged arguments
     int led_off = 0;      // per-plan ledgers (batched)
@@ -43,9 +43,9 @@ struct LaunchLayout {
     size_t lds_bytes = 0;
     int cache_slots = 0;
     int key_words = 1;
-    // the cache's area (cache_slots single sums, keys and LET numerators) as
-    // the kernel divides it: lines of kLine sums and kLine LET numerators (both
-    // double), one key each
+    // the cache's memory as the kernel divides it: lines of kLine sums and, with
+    // LET_d, kLine numerators (both double), one key each (u32; u64 in a batched
+    // launch)
     int cache_lines = 0;
     int line_key_off = 0;
     int line_num_off = 0;

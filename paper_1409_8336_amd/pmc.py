@@ -28,7 +28,7 @@ EXPORTS = ("pmc_default_params", "pmc_create", "pmc_destroy", "pmc_last_error",
            "pmc_inspect_tables", "pmc_atomic_probe", "pmc_load_geometry_slot", "pmc_run_plans",
            "pmc_geometry_density", "pmc_version", "pmc_run_spots_let", "pmc_run_spots_let_dev",
            "pmc_vavilov_table", "pmc_moliere_table", "pmc_plan_launch", "pmc_roofline_replay",
-           "pmc_stream_probe", "pmc_inc_events", "pmc_inc_nucleus", "pmc_inc_width")
+           "pmc_stream_probe", "pmc_inc_events", "pmc_inc_nucleus", "pmc_inc_width", "pmc_plan_cache")
 
 
 class PMCError(RuntimeError):
@@ -109,6 +109,10 @@ class pmc_launch_layout(C.Structure):
         ("order_words", C.c_uint64)]
 
 
+class pmc_cache_layout(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("lines", "line_sums", "sums_off", "num_off", "key_off", "key_words")]
+
+
 class pmc_replay_result(C.Structure):
     _fields_ = [(n, C.c_double) for n in ("transport_ms", "trace_only_ms", "gather_ms", "atomic_ms",
                                           "cached_atomic_ms", "combined_ms")] + [
@@ -173,6 +177,7 @@ def lib():
         L.pmc_moliere_table.argtypes = [vp, C.c_int32]
         L.pmc_plan_launch.argtypes = [C.POINTER(pmc_launch_query), C.POINTER(pmc_launch_layout), C.c_char_p,
                                       C.c_int32]
+        L.pmc_plan_cache.argtypes = [C.POINTER(pmc_launch_query), C.POINTER(pmc_cache_layout)]
         L.pmc_roofline_replay.argtypes = [vp, vp, i32, u64, u64, vp, C.POINTER(pmc_replay_result)]
         L.pmc_stream_probe.argtypes = [vp, u64, vp, C.POINTER(C.c_double), C.POINTER(C.c_double)]
         L.pmc_inc_events.argtypes = [vp, vp, vp, vp, vp, C.c_int32, u64, C.c_int32, vp, vp]
@@ -429,6 +434,15 @@ def pmc_plan_launch(**query):
     why = C.create_string_buffer(256)
     rc = lib().pmc_plan_launch(C.byref(q), C.byref(out), why, 256)
     return rc, {f[0]: getattr(out, f[0]) for f in pmc_launch_layout._fields_}, why.value.decode()
+
+
+def pmc_plan_cache(**query):
+    """The deposit cache's lines in the launch layout for the query fields
+    (pmc_launch_query); host only.  Returns (status, fields as a dict)."""
+    q = pmc_launch_query(**query)
+    out = pmc_cache_layout()
+    rc = lib().pmc_plan_cache(C.byref(q), C.byref(out))
+    return rc, {f[0]: getattr(out, f[0]) for f in pmc_cache_layout._fields_}
 
 
 def _stream_handle(stream):
