@@ -89,9 +89,10 @@ struct Region {
 // kPipe: two buffers, the copies of stage c+1 overlap the arithmetic of stage
 // c; else one, and the workgroups on a CU (three with NB = 1, two with NB = 2)
 // overlap each other.
-template <int NB, int QC>
+// kFlat: one z plane, 64 x 8 x 1 voxels.
+template <int NB, int QC, bool kFlat>
 struct FwdTile {
-    static constexpr int TX = 16, TY = 8, TZ = 4, WAVES = 8;
+    static constexpr int TX = kFlat ? 64 : 16, TY = 8, TZ = kFlat ? 1 : 4, WAVES = 8;
     static constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
     static constexpr int NHALO = HX * HY * HZ;                  // voxels
     static constexpr int HBLK = (NHALO * QC + 63) / 64;         // 64-entry copies of the halo
@@ -122,13 +123,13 @@ struct FwdAfter {
     Region rg;
 };
 
-template <int NB, int QC, bool kPipe, int kMinWaves, int kAfter>
+template <int NB, int QC, bool kPipe, int kMinWaves, int kAfter, bool kFlat>
 __global__ void __launch_bounds__(512, kMinWaves)
     conv3d_fwd_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ coarse, int Cc,
                       const uint16_t* __restrict__ wt, const float* __restrict__ bias, uint16_t* __restrict__ out,
                       int N, int D, int H, int W, int Cin, int Cout, int Kp, int relu, FwdAfter after)
 {
-    using T = FwdTile<NB, QC>;
+    using T = FwdTile<NB, QC, kFlat>;
     constexpr int WAVES = T::WAVES;
     // two distinct LDS objects, so that the compiler's wait for the copies
     // into one is not placed before reads of the other
@@ -208,10 +209,10 @@ __global__ void __launch_bounds__(512, kMinWaves)
     for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int j = 0; j < NB; ++j) acc[t][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    // this wave's voxels: y0 + yw + t, z0 + zw; its lane's first halo entry
-    // and first weight entry
-    const int yw = 4 * (wave & 1), zw = wave >> 1;
-    const int vox0 = (zw * T::HY + yw) * T::HX + m;
+    // this wave's voxels: x0 + xw + m, y0 + yw + t, z0 + zw; its lane's first halo
+    // entry and first weight entry
+    const int xw = kFlat ? 16 * (wave >> 1) : 0, yw = 4 * (wave & 1), zw = kFlat ? 0 : wave >> 1;
+    const int vox0 = (zw * T::HY + yw) * T::HX + xw + m;
     const int wt0 = g * 16 * NB + m;
     auto compute = [&](const u32x4* bf, int q) __attribute__((always_inline)) {
 #pragma unroll
@@ -264,7 +265,7 @@ __global__ void __launch_bounds__(512, kMinWaves)
         }
     }
     // lane (m, g) holds output channels co0 + 16 j + 4 g .. + 3 of voxel m
-    const int x = x0 + m, z = z0 + zw;
+    const int x = x0 + xw + m, z = z0 + zw;
     const bool in_xz = x < W && z < D;
     // the block's channels go to a coarse gradient (kSplit): nothing to store per voxel
     const bool to_half = kAfter == kSplit && co0 < after.Cc;
@@ -956,13 +957,13 @@ struct FwdArgs {
     int N, D, H, W, Cin, Cout, Kp, relu;
 };
 
-template <int NB, int QC, bool kPipe, int kMinWaves, int kAfter>
+template <int NB, int QC, bool kPipe, int kMinWaves, int kAfter, bool kFlat = false>
 static hipError_t launch_fwd(const FwdArgs& a, const FwdAfter& after, hipStream_t s)
 {
-    using T = FwdTile<NB, QC>;
+    using T = FwdTile<NB, QC, kFlat>;
     const int cgroups = (a.Cout + 16 * NB - 1) / (16 * NB);
     dim3 grid((a.W + T::TX - 1) / T::TX, ((a.H + T::TY - 1) / T::TY) * cgroups, a.N * ((a.D + T::TZ - 1) / T::TZ));
-    hipLaunchKernelGGL((conv3d_fwd_kernel<NB, QC, kPipe, kMinWaves, kAfter>), grid, dim3(64 * T::WAVES), 0, s, a.in,
+    hipLaunchKernelGGL((conv3d_fwd_kernel<NB, QC, kPipe, kMinWaves, kAfter, kFlat>), grid, dim3(64 * T::WAVES), 0, s, a.in,
                        a.coarse, a.Cc, a.wt, a.bias, a.out, a.N, a.D, a.H, a.W, a.Cin, a.Cout, a.Kp, a.relu, after);
     return hipGetLastError();
 }
@@ -994,6 +995,15 @@ static hipError_t conv3d_fwd(const FwdArgs& a, const FwdAfter& after, hipStream_
     //   63 against 72 with 16; 48 -> 32 on 2 x 41 x 53 x 75: 45 and 53).
     const size_t tiles = (size_t)N * ((D + 3) / 4) * ((H + 7) / 8) * ((W + 15) / 16);
     const int n16 = (Cout + 15) / 16;
+    // - One z plane wider than 16 voxels, more than one workgroup per CU: flat
+    //   blocks, of which a quarter as many voxels lie outside: 48 -> 16 on 1024 x
+    //   1024: 149 and 69; 32 -> 32 on 512 x 512: 53 and 23, on 2 x 100000: 123 and
+    //   44; 64 -> 64 on 200 planes of 16 x 16: 44 and 52, so not there.  Two planes:
+    //   48 -> 16 on 1024 x 1024: 170 and 346.
+    if constexpr (kAfter == kPlain) {
+        if (D == 1 && W > 16 && tiles * n16 > 256)
+            return Cout <= 16 ? launch_fwd<1, 1, false, 8, kPlain, true>(a, after, s) : launch_fwd<2, 1, false, 6, kPlain, true>(a, after, s);
+    }
     // (a stage of two chunks has one source and never runs past the last
     // channel; the network's head has 48 input channels, its other epilogues
     // 32 or more output channels where there are more than 24 input channels)
