@@ -407,6 +407,11 @@ struct RunResult {
     int generations = 0;
 };
 
+// Histories per lane from which a run lists its nuclear events for full waves: at
+// about four (1e6 histories, one spot) the gain is gone in the drain, which works
+// them in place.
+constexpr unsigned long long kListedPerLane = 2;
+
 // a traced run (kTrace, first generation only): iterations to hold per lane
 // in, the launch shape and trace extent out
 struct TraceReq {
@@ -641,10 +646,8 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
         HIPCHK(c->d_qloc.ensure(lay.qloc_words), "alloc workgroup queues");
         a.q_loc = c->d_qloc.p;
     }
-    // events by full waves where lanes get several histories each: at about four
-    // (1e6 histories, one spot) the gain is gone in the drain, which works them in
-    // place
-    if (total >= 2ull * (unsigned long long)grid * (unsigned long long)block) {
+    // events by full waves
+    if (total >= kListedPerLane * (unsigned long long)grid * (unsigned long long)block) {
         if (c->d_qev.ensure((size_t)grid * EvQueue::entries(block) * EvQueue::kEntryWords) == hipSuccess) a.q_ev = c->d_qev.p;
         else (void)hipGetLastError();   // (no room: events in place)
     }
@@ -841,7 +844,7 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
 
 // Launch shape of a run: the caller's fixed values, and for the fields left
 // at 0 the fastest of a few candidates timed on a scaled-down copy of the
-// workload (2e5 histories), remembered per workload signature.
+// workload, remembered per workload signature.
 pmc_status choose_shape(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, hipStream_t st, Shape* out)
 {
     Shape s;
@@ -917,16 +920,22 @@ pmc_status choose_shape(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, hipS
         }
     };
     // calibration work: a fifth of the run, 2e5 to 2e6 histories, enough to
-    // reach the steady state of a full grid of 1024-lane workgroups
-    const double cal_hist = std::min(2.0e6, std::max(2.0e5, 0.2 * (double)total));
+    // reach the steady state of a full grid of 1024-lane workgroups; of a run
+    // that lists its nuclear events (two histories a lane of such a grid) as
+    // many as make the candidates list them too (not with the cascade, whose
+    // launches are most of a calibration run: 1e6 histories' first run took 283 ms
+    // so, 227 before)
+    double cal_hist = std::min(2.0e6, std::max(2.0e5, 0.2 * (double)total));
+    const double listed = kListedPerLane * 1024.0 * c->num_cu;
+    if ((double)total >= listed && !(c->p.flags & kInc)) cal_hist = std::min((double)total, std::max(cal_hist, 1.05 * listed));
     std::vector<PlanIn> cal;
     std::vector<std::vector<pmc_spot>> cal_spots;
     sample(cal_hist / (double)total, cal, cal_spots);
     std::vector<Shape> cands;
-    for (int b : {256, 512, 1024})
-        for (int r : {8, 16})
-            for (int e : {4, 8})
-                for (int ch : {0, -1}) {
+    for (int b : {1024, 512, 256})
+        for (int ch : {0, -1})
+            for (int r : {8, 16})
+                for (int e : {4, 8}) {
                     Shape x;
                     x.block = c->p.block_threads ? c->p.block_threads : b;
                     x.blocks_per_cu = c->p.blocks_per_cu;
@@ -943,13 +952,22 @@ pmc_status choose_shape(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, hipS
     // every candidate once, then the three fastest twice more: a shape is
     // rated by the best of its three times, which keeps one noisy
     // calibration launch from deciding (neighbouring shapes differ by a few
-    // per cent)
+    // per cent).  The thresholds move a shape by a tenth: of a workgroup size and
+    // cache whose first pair is far behind the others are left out (without the
+    // cache one spot's LET_d takes five times as long, and such launches were
+    // most of a first run: of 4e6 histories 949 ms, 258 so)
+    constexpr double kFarBehind = 1.5;
     std::vector<std::pair<double, int>> times;
+    double best_t1 = 1e300, first_t = 0.0;   // the best so far; the first of this size and cache
     for (size_t i = 0; i < cands.size(); ++i) {
+        const bool first = i == 0 || cands[i].block != cands[i - 1].block || cands[i].cache != cands[i - 1].cache;
+        if (!first && first_t > kFarBehind * best_t1) continue;
         RunResult r;
         pmc_status st2 = run_driver(c, cal, multi, cands[i], st, true, &r);
         if (st2 != PMC_OK) return st2;
         times.push_back({r.transport_ms, (int)i});
+        if (first) first_t = r.transport_ms;
+        best_t1 = std::min(best_t1, r.transport_ms);
     }
     std::sort(times.begin(), times.end());
     const size_t n_final = std::min<size_t>(3, times.size());
@@ -962,15 +980,15 @@ pmc_status choose_shape(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, hipS
         }
     std::sort(times.begin(), times.end());
     int best_i = times[0].second;
-    // the best shape of each workgroup size once more on a sample as large
-    // as the run (up to 2e7 histories, best of two each): the workgroup size
-    // sets the occupancy and the cache size, and shapes that come out within
-    // a few per cent on the calibration sample can differ by more on the
-    // whole field
+    // the best shape of each workgroup size that is not far behind once more on
+    // a sample as large as the run (up to 2e7 histories, best of two each): the
+    // workgroup size sets the occupancy and the cache size, and shapes that come
+    // out within a few per cent on the calibration sample can differ by more on
+    // the whole field
     if (total > (unsigned long long)cal_hist) {
         std::vector<int> finalists;
         for (const auto& t : times) {
-            bool seen = false;
+            bool seen = t.first > kFarBehind * times[0].first;
             for (int f : finalists) seen |= cands[f].block == cands[t.second].block;
             if (!seen) finalists.push_back(t.second);
         }
