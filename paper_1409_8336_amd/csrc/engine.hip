@@ -646,11 +646,6 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
         HIPCHK(c->d_qloc.ensure(lay.qloc_words), "alloc workgroup queues");
         a.q_loc = c->d_qloc.p;
     }
-    // events by full waves
-    if (total >= kListedPerLane * (unsigned long long)grid * (unsigned long long)block) {
-        if (c->d_qev.ensure((size_t)grid * EvQueue::entries(block) * EvQueue::kEntryWords) == hipSuccess) a.q_ev = c->d_qev.p;
-        else (void)hipGetLastError();   // (no room: events in place)
-    }
     if (trace) {
         // the address trace of generation 0: trace->iters loop iterations of
         // every lane, pre-filled with "no step"
@@ -678,6 +673,11 @@ pmc_status run_driver(pmc_ctx* c, std::vector<PlanIn>& plans, bool multi, const 
         if (si != PMC_OK) return si;
         HIPCHK(c->d_inc_ev.ensure(cap), "alloc event list");
         a.inc_ev = c->d_inc_ev.p;
+    }
+    // events by full waves (last: what the run cannot do without comes first)
+    if (total >= kListedPerLane * (unsigned long long)grid * (unsigned long long)block) {
+        if (c->d_qev.ensure((size_t)grid * EvQueue::entries(block) * EvQueue::kEntryWords) == hipSuccess) a.q_ev = c->d_qev.p;
+        else (void)hipGetLastError();   // (no room: events in place)
     }
     const uint32_t run_flags = a.flags;
     int gens = 0;
