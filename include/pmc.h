@@ -105,11 +105,13 @@ typedef struct {
     int32_t tally_cache;     /* LDS deposit cache per workgroup: slots, 512..16384; 0 = automatic
                                 (the tuner may turn it off, else sized from the LDS left by the
                                 tables); -1 = off (every deposit is a global FP64 atomic).  The
-                                memory of a slot is a sum, a key and with LET_d a numerator; the
-                                kernel divides the slots' memory into lines of eight sums with
-                                one key */
+                                memory of a slot is a sum, a key and with LET_d a word; the kernel
+                                divides the slots' memory into lines of eight sums (and with LET_d
+                                eight numerators) with one key (pmc_plan_cache) */
     int32_t epoch_steps;     /* loop iterations between epoch ends (cache flush, own-queue
-                                publication); 0 = 16 */
+                                publication); 0 = 16, with LET_d 8.  Longer epochs overflow the
+                                cache's lines where many lanes deposit near each other (1e6
+                                histories of one spot: 64 take twice as long as 16) */
     int32_t cache_probes;    /* cache lines tried per deposit (linear probing), 1..16; 0 = 3 */
     int32_t claim_run_log2;  /* a workgroup claims primaries in runs of up to 2^claim_run_log2
                                 consecutive histories (a pencil's worth for the cache), 4..16;
@@ -121,12 +123,19 @@ typedef struct {
 } pmc_params;
 /* Autotuning: when any of block_threads, refill_lanes, batch_events is 0 and
  * a run has at least 2e5 histories, the first run of each workload signature
- * (single/batched, plan count, log2 of histories and voxels) times the
- * candidate launch shapes (workgroup size, refill and event thresholds, LDS
- * deposit cache on or off) on the first spots of every plan, a fifth of the
- * run (2e5 to 2e6 histories), times the three fastest twice more, and keeps
- * the one with the best of its times for that signature.  Results do not
- * depend on the shape. */
+ * (single/batched, with LET_d or not, plan count, log2 of histories and voxels)
+ * times the candidate launch shapes (workgroup size, refill and event thresholds,
+ * LDS deposit cache on or off; of a size and cache far behind the best one pair
+ * of thresholds) on some spots of every plan, a fifth of the run (2e5 to 2e6
+ * histories, and two per lane of a full grid where the run has that many), times
+ * the three fastest twice more and the best of each workgroup size on a sample as
+ * large as the run (up to 2e7), and keeps the fastest for that signature.
+ * Results do not depend on the shape.
+ * Device memory a context keeps beside its tallies: the queues (queue_capacity,
+ * local_queue) and, from the first run with at least two histories per lane of its
+ * grid on, the workgroups' lists of nuclear events (28 to 460 KB per workgroup,
+ * 117 MB for one 1024-lane workgroup on each of 256 CUs); a run that finds no
+ * room for these lists goes without. */
 
 /* Fill *p with the defaults above.  Never fails for a non-NULL p. */
 pmc_status pmc_default_params(pmc_params* p);

@@ -4,14 +4,18 @@
 //
 // Design (CDNA4):
 //   - one history per lane, state in registers for its whole residency;
-//   - persistent waves refill idle lanes from a global claim counter (primary
-//     uids in generation 0, the previous generation's secondary queue later)
-//     with one atomic per wave, so lanes stay busy without any host loop;
-//   - nuclear events are rare and long: lanes that reach one wait, and the
-//     wave processes several of them together, then appends the emitted
-//     protons to the next generation's queue with one atomic per wave;
+//   - persistent waves refill idle lanes from their workgroup's own queue of
+//     secondaries, then from its share of the work list (primaries in generation
+//     0, what overflowed the workgroups' queues later), claimed through an LDS
+//     counter with one atomic per wave: no host loop, no global counter;
+//   - nuclear events are rare and long: lanes that reach one wait for a few
+//     others of the wave, whose states then go to the workgroup's event list for
+//     full waves (at the end of the work list the wave works them in place); the
+//     protons emitted are queued with one LDS atomic per wave;
 //   - range/cross-section tables live in LDS; the voxel record is one 8-byte
-//     gather; the dose is one FP64 atomic add per step into [voxel][group].
+//     gather; the dose is one FP64 add per step, through lines of eight sums in
+//     LDS into z-fastest planes of the statistical groups (cache.hpp), or without
+//     that cache an atomic into a voxel's row of groups.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
