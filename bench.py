@@ -32,8 +32,8 @@ HBM_PEAK = 8.0e12
 # HBM bytes per transport launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs,
 # scaled by a plain-copy calibration, valid only for the kernel source whose
 # sha256 is recorded (see profiles/); None once the kernel has changed.
-TRAFFIC = {"transport_sha256": "5d23a0242eacaea870bf17889dda95ea1ec135146ea158434223546ec9f6a0ea",
-           "bytes_per_launch": 6.32396e9, "let_bytes_per_launch": 1.59498e10}
+TRAFFIC = {"transport_sha256": "5376f9e4bb65963c411d73cd63abb06685e5de2d68d5e839b281725af79419f5",
+           "bytes_per_launch": 6.30986e9, "let_bytes_per_launch": 1.59376e10}
 
 
 def _kernel_sha():
