@@ -161,11 +161,17 @@ static_assert(kOffsetsHost.upto[kNear * kNear] == kNearCount, "offsets within th
 // neighbouring voxels fall into the same lines, where those of one voxel's
 // offsets scatter.  160 x 128 x 128 voxels, all above the cutoff, 2%/2 mm, the
 // evaluated dose 30% off everywhere (every voxel searches the whole sphere):
-// 15.5 ms with groups and waves, 8.5 so, with a search of 6 mm 351 and 68.
+// 15.5 ms with groups and waves, 8.5 so, with a search of 6 mm 351 and 66 (80 x
+// 64 x 64 voxels 61 and 8.4, 9.8 with the whole near sphere in LDS and four
+// workgroups a CU).
 constexpr int kGammaRun = 512;
 constexpr int kGroup = 8;
 constexpr int kFirst = 65;   // the zero offset and eight rounds of a group
 constexpr int kDense = kGammaRun / 2;
+constexpr int kDenseBlocks = 5 * 256;   // as many as are resident
+// the near sphere's radius in steps: of a dense run smaller, so that its offsets
+// leave LDS for five workgroups a CU
+constexpr int near_steps(bool dense) { return dense ? 7 : kNear; }
 constexpr unsigned long long kDenseUnit = 1ull << 40;   // a dense run in the count of voxels evaluated
 template <bool kDenseRuns>
 __global__ void __launch_bounds__(256) gamma_kernel(const double* __restrict__ ref, const double* __restrict__ ev,
@@ -175,14 +181,16 @@ __global__ void __launch_bounds__(256) gamma_kernel(const double* __restrict__ r
                                                     float step, int n_near, float* __restrict__ gamma,
                                                     unsigned long long* __restrict__ counts)
 {
+    constexpr int kSteps = near_steps(kDenseRuns);
     __shared__ double sh[4];
     __shared__ unsigned long long shc[4][2];
     extern __shared__ float4 near[];   // n_near entries: offset in voxels, distance term (negative: not in the sphere)
     __shared__ unsigned short list[kGammaRun], late[kGammaRun];
     __shared__ double late_best[kGammaRun];
     __shared__ int n_list, n_late, n_other;
+    __shared__ float far_x[kDenseRuns ? 2 * 64 + 1 : 1];   // offsets along x in voxels (search / step <= 64)
     const int nsteps = (int)floorf(search / step + 1e-4f);
-    const bool far = search > step * (kNear + 0.01f);   // the next shell lies at sqrt(65) steps
+    const bool far = search > step * (kSteps + 0.01f);   // the next shell lies at sqrt(kSteps^2 + 1) steps
     auto dist_term = [&](int i, int j, int k, float& d2) {
         const float ox = i * step, oy = j * step, oz = k * step;
         d2 = ox * ox + oy * oy + oz * oz;
@@ -196,8 +204,14 @@ __global__ void __launch_bounds__(256) gamma_kernel(const double* __restrict__ r
                         !(d2 > search * search * (1.0f + 1e-6f));
         near[e] = make_float4(i * step / dx, j * step / dy, k * step / dz, in ? dist : -1.f);
     }
-    const double dmax = max_of_partials(partial, n_partial, sh);
+    if (kDenseRuns && far)
+        for (int i = threadIdx.x; i <= 2 * nsteps; i += blockDim.x) far_x[i] = (i - nsteps) * step / dx;
+    const double dmax = max_of_partials(partial, n_partial, sh);   // (with its barriers)
     const double crit = dose_frac * dmax;
+    // a value that cannot be the smallest needs no division (a bound with a margin
+    // far above its roundings, unless crit^2 leaves the range of doubles)
+    const double crit2 = crit * crit * (1.0 + 1e-9);
+    const bool screen = crit2 > 1e-280 && crit2 < 1e280;
     const size_t nv = (size_t)nx * ny * nz;
     const int lane = threadIdx.x & 63;
     unsigned long long n_eval = 0, n_pass = 0;
@@ -206,7 +220,9 @@ __global__ void __launch_bounds__(256) gamma_kernel(const double* __restrict__ r
         const float px = x + fx, py = y + fy, pz = z + fz;
         // points outside the grid carry no evaluated dose: skipped
         if (px < 0.f || py < 0.f || pz < 0.f || px > nx - 1 || py > ny - 1 || pz > nz - 1) return;
-        const double dd = (trilinear(ev, nx, ny, nz, px, py, pz) - r) / crit;
+        const double diff = trilinear(ev, nx, ny, nz, px, py, pz) - r;
+        if (kDenseRuns && screen && diff * diff > (best - dist) * crit2) return;
+        const double dd = diff / crit;
         const double g2 = dist + dd * dd;
         if (g2 < best) best = g2;
     };
@@ -250,8 +266,8 @@ __global__ void __launch_bounds__(256) gamma_kernel(const double* __restrict__ r
                 if (__ballot(!shut(dist_term(0, j, k, d2))) == 0ull || d2 > search * search * (1.0f + 1e-5f)) continue;
                 for (int i = -nsteps; i <= nsteps; ++i) {
                     const double dist = dist_term(i, j, k, d2);
-                    if (i * i + j * j + k * k <= kNear * kNear || d2 > search * search * (1.0f + 1e-6f)) continue;
-                    if (!(dist >= best)) offer(x, y, z, r, i * step / dx, j * step / dy, k * step / dz, dist, best);
+                    if (i * i + j * j + k * k <= kSteps * kSteps || d2 > search * search * (1.0f + 1e-6f)) continue;
+                    if (!(dist >= best)) offer(x, y, z, r, far_x[i + nsteps], j * step / dy, k * step / dz, dist, best);
                 }
             }
     };
@@ -366,7 +382,7 @@ __global__ void __launch_bounds__(256) gamma_kernel(const double* __restrict__ r
                     for (int j = lane / side - nsteps, i = lane % side - nsteps; j <= nsteps;) {
                         float d2;
                         const double dist = dist_term(i, j, k, d2);
-                        if (i * i + j * j + k * k > kNear * kNear && !(d2 > search * search * (1.0f + 1e-6f)) && !(dist >= best))
+                        if (i * i + j * j + k * k > kSteps * kSteps && !(d2 > search * search * (1.0f + 1e-6f)) && !(dist >= best))
                             offer(x, y, z, r, i * step / dx, j * step / dy, k * step / dz, dist, best);
                         j += 64 / side;
                         i += 64 % side;
@@ -499,8 +515,7 @@ extern "C" pmc_status pmc_gamma_index(const double* ref, const double* ev, int n
     const size_t nv = (size_t)nx * ny * nz;
     const unsigned max_blocks = pmc::red_blocks(nv, 256, pmc::kMaxBlocks);
     // the near offsets that can lie in the search sphere
-    const double r2 = std::min((double)pmc::kNear * pmc::kNear, (double)search / step * ((double)search / step) * 1.001 + 1.0);
-    const int n_near = pmc::kOffsetsHost.upto[(int)r2];
+    const double r2 = (double)search / step * ((double)search / step) * 1.001 + 1.0;
     hipLaunchKernelGGL(pmc::max_partials_kernel, dim3(max_blocks), dim3(256), 0, s, ref, nv, red.partial);
     hipError_t e = hipGetLastError();
     unsigned long long evaluated = 0, passed = 0;
@@ -509,7 +524,10 @@ extern "C" pmc_status pmc_gamma_index(const double* ref, const double* ev, int n
     for (bool dense : {false, true}) {
         if (dense && evaluated < pmc::kDenseUnit) break;
         evaluated %= pmc::kDenseUnit;
-        const unsigned blocks = pmc::red_blocks(nv, dense ? pmc::kGammaRun / 2 : pmc::kGammaRun, pmc::kRedBlocks);
+        const int steps = pmc::near_steps(dense);
+        const int n_near = pmc::kOffsetsHost.upto[(int)std::min((double)(steps * steps), r2)];
+        const unsigned blocks = dense ? pmc::red_blocks(nv, pmc::kGammaRun / 2, pmc::kDenseBlocks)
+                                      : pmc::red_blocks(nv, pmc::kGammaRun, pmc::kRedBlocks);
         unsigned long long c0 = 0, c1 = 0;
         if (e == hipSuccess) {
             hipLaunchKernelGGL(dense ? pmc::gamma_kernel<true> : pmc::gamma_kernel<false>, dim3(blocks), dim3(256),

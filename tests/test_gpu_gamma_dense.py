@@ -28,6 +28,7 @@ VOX = (0.23, 0.27, 0.31)   # no multiple of the step: no search point on a face
 ])
 @pytest.mark.parametrize("off,search", [
     ("near", 0.3), ("far", 0.3), ("far", 0.55), ("mixed", 0.3), ("mixed", 0.55), ("mixed", 0.0),
+    ("far", 0.35), ("far", 0.357), ("mixed", 0.4),   # seven steps, the next shell, eight
 ])
 def test_dense_runs_match_oracle(shape, above, off, search):
     import torch
